@@ -11,7 +11,8 @@ Kinds of pass (``case["kind"]``):
 * ``kalman`` -- the Kalman filter over a batch of sequences.
 
 ``listed`` gives fixed cases, ``draw`` one more case of the same ranges.  Inputs are drawn on the GPU
-from the seed alone, with the distributions of ``workloads.py``.
+from the seed alone, with the distributions of ``workloads.py``.  ``exact`` gives the same outputs as torch
+computes them in 64 bits.
 """
 import math
 
@@ -215,6 +216,118 @@ def run(s):
         return la.sgp_criterion(s["Kuu"], s["Kuf"], s["Kff_diag"], s["y"], 0.1)
     nll, f, F = la.kalman_filter(*s["par"], s["v"], want_states=case["states"])
     return {"nll": nll, "f": f, "F": F} if case["states"] else {"nll": nll}
+
+
+# -----------------------------------------------------------------------------------------------
+# the same outputs in 64 bits, with torch alone
+# -----------------------------------------------------------------------------------------------
+def _solve(L, X, trans=False, left=True):
+    """t(L)^-1 X, or X t(L)^-1, for a lower L."""
+    M = L.mT if trans else L
+    return torch.linalg.solve_triangular(M, X, upper=trans, left=left)
+
+
+def _factor_gradient(L, Lbar):
+    """1/2 L^-T copyltu(L^T Lbar) L^-1 of lower-triangular L, Lbar."""
+    P = torch.matmul(L.mT.contiguous(), Lbar).tril()
+    P = P + P.tril(-1).mT
+    W = _solve(L, _solve(L, P, trans=True), left=False)
+    return 0.25 * (W + W.mT)
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    s = prepare(case, seed)
+    if kind == "kalman":
+        return _exact_kalman(case, [x.double() for x in s["par"]], s["v"].double())
+    s = {k: (x.double() if torch.is_tensor(x) else x) for k, x in s.items()}
+    mul = torch.matmul
+    if kind == "step":
+        L = torch.linalg.cholesky(s["A"])
+        t = (lambda x: x) if case["lower"] else (lambda x: x.mT.contiguous())
+        out = {"L": t(L)}
+        if case["m"]:  # an upper factor R = L^T solves R X = rhs
+            out["X"] = _solve(L, s["rhs"], trans=not case["lower"])
+            if case["trmm"]:
+                out["Y"] = mul(L.mT.contiguous() if case["lower"] else L, s["rhs"])
+        if case["logdet"]:
+            out["logdet"] = L.diagonal(dim1=-2, dim2=-1).log().sum(-1)
+        out["Abar"] = _factor_gradient(L, t(s["Lbar"]))
+        return out
+    if kind == "ops":
+        L = torch.linalg.cholesky(s["A"])
+        Lt, Bbar, P, Q = L.mT.contiguous(), s["Bbar"], s["P"], s["Q"]
+        X = _solve(L, s["X"])
+        Linv = _solve(L, torch.eye(case["n"], device=L.device, dtype=L.dtype).expand_as(L))
+        Ainv, sym = mul(Linv.mT.contiguous(), Linv), Bbar + Bbar.mT
+        Y = _solve(L, s["Xbar"], trans=True)
+        return {
+            "L": L, "trsm": X, "trmm": mul(L, s["X"]), "syrk": mul(P, P.mT.contiguous()),
+            "logdet": L.diagonal(dim1=-2, dim2=-1).log().sum(-1), "gemm2": mul(P, Q), "potri": Ainv,
+            "potrf_b": _factor_gradient(L, s["Lbar"]), "trsm_b": (Y, -mul(Y, X.mT.contiguous()).tril()),
+            "trmm_b": (mul(Lt, s["Xbar"]), mul(s["Xbar"], s["X"].mT.contiguous()).tril()), "syrk_b": mul(sym, P),
+            "gemm2_b": (mul(Bbar, Q.mT.contiguous()), mul(P.mT.contiguous(), Bbar)),
+            "potri_b": -mul(mul(Ainv, sym), Linv.mT.contiguous()).tril(),
+        }
+    if kind == "gp":  # 1/2 y^T A^-1 y + 1/2 log det A; its gradient is 1/2 (A^-1 - a a^T), a = A^-1 y
+        L, y = torch.linalg.cholesky(s["A"]), s["y"][..., None]
+        Linv = _solve(L, torch.eye(case["n"], device=L.device, dtype=L.dtype).expand_as(L))
+        z = _solve(L, y)
+        a = _solve(L, z, trans=True)
+        logdet = L.diagonal(dim1=-2, dim2=-1).log().sum(-1)
+        loss = 0.5 * (z * z).sum((-2, -1)) + logdet
+        return {"loss": loss, "Abar": 0.5 * (mul(Linv.mT.contiguous(), Linv) - a * a.mT)}
+    n, lam = case["n"], torch.tensor(0.1, device="cuda", dtype=torch.float64)
+    x = [v.clone().requires_grad_() for v in (s["Kuu"], s["Kuf"], s["Kff_diag"], s["y"], lam)]
+    Kuu, Kuf, Kff, y, lam = x
+    B = _solve(torch.linalg.cholesky(Kuu), Kuf)
+    La = torch.linalg.cholesky(mul(B, B.mT) / lam + torch.eye(case["U"], device="cuda", dtype=torch.float64))
+    w = _solve(La, mul(B, y)[:, None])
+    phi = (0.5 * n * torch.log(2 * math.pi * lam) + La.diagonal().log().sum() + 0.5 * ((y * y).sum() - (w * w).sum() / lam) / lam
+           + 0.5 * (Kff.sum() - (B * B).sum()) / lam)
+    g = torch.autograd.grad(phi, x)
+    return {"phi": phi.detach().reshape(1), "Kuu_bar": 0.5 * (g[0] + g[0].mT), "Kuf_bar": g[1], "Kff_diag_bar": g[2],
+            "y_bar": g[3], "noise_bar": g[4].reshape(1)}
+
+
+def _small_cholesky(S):
+    """Column by column over a batch of small matrices."""
+    n, S, L = S.shape[-1], S.clone(), torch.zeros_like(S)
+    for k in range(n):
+        L[..., k:, k] = S[..., k:, k] / S[..., k, k].sqrt()[..., None]
+        S[..., k + 1:, k + 1:] -= L[..., k + 1:, k, None] * L[..., None, k + 1:, k]
+    return L
+
+
+def _exact_kalman(case, par, v):
+    A, B, Sh, Sv, f, F = par
+    b, T, dv = v.shape
+    A, B, Sh, Sv, F = (x.expand(b, *x.shape[-2:]).contiguous() for x in (A, B, Sh, Sv, F))
+    At, Bt, I = A.mT.contiguous(), B.mT.contiguous(), torch.eye(F.shape[-1], device=v.device, dtype=v.dtype)
+    f, nll, fs, Fs = f.expand(b, F.shape[-1]), 0.5 * T * dv * math.log(2 * math.pi), [], []
+    for t in range(T):
+        if t:
+            f, F = torch.matmul(A, f[..., None])[..., 0], torch.matmul(torch.matmul(A, F), At) + Sh
+        M = torch.matmul(F, Bt)
+        L = _small_cholesky(torch.matmul(B, M) + Sv)
+        d = (v[:, t] - torch.matmul(B, f[..., None])[..., 0])[..., None]
+        z, X = d.clone(), M.mT.contiguous()
+        for k in range(dv):  # L^-1 of the innovation and of M^T
+            for R in (z, X):
+                R[:, k] /= L[:, k, k, None]
+                R[:, k + 1:] -= L[:, k + 1:, k, None] * R[:, None, k]
+        nll = nll + 0.5 * (z * z).sum((-2, -1)) + L.diagonal(dim1=-2, dim2=-1).log().sum(-1)
+        for k in reversed(range(dv)):  # L^-T: X is then the transposed gain
+            X[:, k] /= L[:, k, k, None]
+            X[:, :k] -= L[:, k, :k, None] * X[:, None, k]
+        K = X.mT.contiguous()
+        J = I - torch.matmul(K, B)
+        f = f + torch.matmul(K, d)[..., 0]
+        F = torch.matmul(torch.matmul(J, F), J.mT.contiguous()) + torch.matmul(torch.matmul(K, Sv), X)
+        if case["states"]:
+            fs.append(f)
+            Fs.append(F)
+    return {"nll": nll, "f": torch.stack(fs, 1), "F": torch.stack(Fs, 1)} if case["states"] else {"nll": nll}
 
 
 # -----------------------------------------------------------------------------------------------
