@@ -403,6 +403,18 @@ struct Mfma<float> {
     static __device__ __forceinline__ int row(int l, int v) { return 4 * (l >> 4) + v; }
 };
 
+// a 16-byte chunk that starts anywhere an element may start (global loads need dword alignment only)
+template <typename T>
+struct LooseVec;
+template <>
+struct LooseVec<float> {
+    typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <>
+struct LooseVec<double> {
+    typedef double type __attribute__((ext_vector_type(2), aligned(8)));
+};
+
 // Reciprocal square root and reciprocal accurate to a few ulp of T.
 __device__ __forceinline__ float rsqrt_acc(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double rsqrt_acc(double x)

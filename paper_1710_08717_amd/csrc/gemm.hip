@@ -9,26 +9,23 @@
 // upper/lower variants never copy.  Triangular operands are masked while they are staged
 // in LDS and their structurally-zero K range is skipped.
 //
-// Two kernels:
-//  * k_gemm_fast: 16-byte vector loads, register prefetch of the next K slab while the
-//    current one is multiplied out of LDS, 128x128 (K slabs of 16, double-buffered LDS, one
-//    barrier per slab), 64x64 or 32x32 workgroup tiles (K slabs of 64 for the small,
-//    latency-bound grids of the recursion's lower levels; 32x32 when 64x64 tiles would leave
-//    most compute units idle), four wavefronts in a 2 x 2 arrangement, 16x16x4
-//    MFMA (v_mfma_f64_16x16x4_f64 / v_mfma_f32_16x16x4_f32).  Needs 16-byte aligned operands
-//    and K a multiple of 16.
-//  * k_gemm: element-wise staged fallback for everything else (ragged / unaligned shapes).
+// k_gemm: 16-byte vector loads, register prefetch of the next K slab while the current one is
+// multiplied out of LDS, 128x128 (K slabs of 16, double-buffered LDS, one barrier per slab),
+// 64x64 or 32x32 workgroup tiles (K slabs of 64 for the small, latency-bound grids of the
+// recursion's lower levels; 32x32 when 64x64 tiles would leave most compute units idle), four
+// wavefronts in a 2 x 2 arrangement, 16x16x4 MFMA (v_mfma_f64_16x16x4_f64 /
+// v_mfma_f32_16x16x4_f32).  Two forms: with 16-byte aligned operands and K a multiple of 16 every
+// chunk is one aligned load; otherwise (odd sizes and leading dimensions) the chunks are loaded
+// with the alignment of one element and the ones that cross the end of the operand element by
+// element, zeros behind it.  The second form keeps the pipeline of the first and issues the same
+// number of loads; a chunk then spans two cache lines more often.  (Staging such operands element by element without prefetch, as an earlier kernel
+// did, was bound by its load instructions and address arithmetic: factor + gradient of one
+// fp64 matrix of n = 3001 8.83 ms, now 2.77; 24 fp32 matrices of n = 333 0.70 ms, now 0.23.)
 #include <algorithm>
 
 #include "common.hpp"
 
 namespace la {
-
-__device__ __forceinline__ bool tri_keep(int tri, int o, int k)
-{
-    // tri 1 keeps o >= k, tri 2 keeps o <= k
-    return tri == 0 || (tri == 1 ? (o >= k) : (o <= k));
-}
 
 // ---------------------------------------------------------------------------------------
 // Workgroup -> work slot mapping.  Consecutive workgroups are dealt round-robin to the 8 XCDs
@@ -129,41 +126,6 @@ static inline int64_t tile_count(int order, int tiles_m, int tiles_n)
     return (int64_t)tiles_m * tiles_n;
 }
 
-// ---------------------------------------------------------------------------------------
-// Fallback kernel: element-wise staging, any strides / sizes.
-// ---------------------------------------------------------------------------------------
-template <int BM, int BN, int BK>
-struct GemmCfg {
-    static constexpr int PAD = 16;
-    static constexpr int A_ELEMS = (BK * (BM + PAD) > BM * (BK + 1)) ? BK * (BM + PAD) : BM * (BK + 1);
-    static constexpr int B_ELEMS = (BK * (BN + PAD) > BN * (BK + 1)) ? BK * (BN + PAD) : BN * (BK + 1);
-};
-
-template <typename T, int OUT, int BK, int PAD>
-__device__ __forceinline__ void stage_slab(T *s, const T *src, int64_t so, int64_t sk, int o0, int no, int k0,
-                                           int kmax, int tri, bool kfast)
-{
-    const int tid = threadIdx.x;
-    constexpr int N = OUT * BK;
-#pragma unroll
-    for (int t = 0; t < N / 256; ++t) {
-        const int idx = t * 256 + tid;
-        int o, k;
-        if (kfast) {
-            o = idx / BK;
-            k = idx % BK;
-        } else {
-            k = idx / OUT;
-            o = idx % OUT;
-        }
-        const int og = o0 + o, kg = k0 + k;
-        T v = T(0);
-        if ((og < no) && (kg < kmax) && tri_keep(tri, og, kg))
-            v = src[(int64_t)og * so + (int64_t)kg * sk];
-        s[kfast ? (o * (BK + 1) + k) : (k * (OUT + PAD) + o)] = v;
-    }
-}
-
 __device__ __forceinline__ void k_range(const GemmOpts &o, int i0, int j0, int BM, int BN, int K, int &kbeg, int &kend)
 {
     kbeg = 0;
@@ -203,101 +165,8 @@ __device__ __forceinline__ void store_c(T *Cp, int64_t rs, int64_t cs, int i, in
     }
 }
 
-template <typename T, int BM, int BN, int BK>
-__global__ __launch_bounds__(256) void k_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N,
-                                              int K, T alpha, T beta, GemmOpts o, int tiles_m, int tiles_n)
-{
-    using Cfg = GemmCfg<BM, BN, BK>;
-    using MF = Mfma<T>;
-    using acc_t = typename MF::acc_t;
-    constexpr int PAD = Cfg::PAD;
-    constexpr int WM = BM / 2, WN = BN / 2;
-    constexpr int TM = WM / 16, TN = WN / 16;
-    __shared__ T sA[Cfg::A_ELEMS];
-    __shared__ T sB[Cfg::B_ELEMS];
-
-    const int64_t bid = blockIdx.x;
-    const int64_t per = tile_count_dev(o.order, tiles_m, tiles_n);
-    const int64_t b = bid / per;
-    int tile = (int)(bid % per);
-    if (o.reverse && o.order != 5)
-        tile = (int)per - 1 - tile;
-    int tm, tn;
-    decode_tile(o.order, tile, tiles_m, tiles_n, tm, tn);
-    const int i0 = tm * BM, j0 = tn * BN;
-    if ((o.maskC == 1 && j0 > i0 + BM - 1) || (o.maskC == 2 && i0 > j0 + BN - 1))
-        return;  // tile entirely on the masked side of the diagonal
-
-    int kbeg, kend;
-    k_range(o, i0, j0, BM, BN, K, kbeg, kend);
-    kbeg = (kbeg / BK) * BK;
-
-    const T *Ap = A.item(b);
-    const T *Bp = B.item(b);
-    T *Cp = C.item(b);
-    const bool a_kfast = (A.cs == 1);
-    const bool b_kfast = (B.rs == 1);
-
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int wm = (w >> 1) * WM, wn = (w & 1) * WN;
-    const int l16 = lane & 15, lk = lane >> 4;
-
-    acc_t acc[TM][TN];
-#pragma unroll
-    for (int x = 0; x < TM; ++x)
-#pragma unroll
-        for (int y = 0; y < TN; ++y)
-            acc[x][y] = acc_t{0, 0, 0, 0};
-
-    const int a_si = a_kfast ? (BK + 1) : 1, a_sk = a_kfast ? 1 : (BM + PAD);
-    const int b_sj = b_kfast ? (BK + 1) : 1, b_sk = b_kfast ? 1 : (BN + PAD);
-    const int triB_o = o.triB == 1 ? 2 : (o.triB == 2 ? 1 : 0);  // in (j, k) order
-
-    for (int pass = 0; pass <= o.symsum; ++pass) {
-    if (pass == 1) {  // second half of A B + B^T A^T: same strides, the base pointers change places
-        const T *t = Ap;
-        Ap = Bp;
-        Bp = t;
-    }
-    for (int k0 = kbeg; k0 < kend; k0 += BK) {
-        stage_slab<T, BM, BK, PAD>(sA, Ap, A.rs, A.cs, i0, M, k0, kend, o.triA, a_kfast);
-        stage_slab<T, BN, BK, PAD>(sB, Bp, B.cs, B.rs, j0, N, k0, kend, triB_o, b_kfast);
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 4) {
-            T af[TM], bf[TN];
-#pragma unroll
-            for (int x = 0; x < TM; ++x)
-                af[x] = sA[(wm + x * 16 + l16) * a_si + (kk + lk) * a_sk];
-#pragma unroll
-            for (int y = 0; y < TN; ++y)
-                bf[y] = sB[(wn + y * 16 + l16) * b_sj + (kk + lk) * b_sk];
-#pragma unroll
-            for (int x = 0; x < TM; ++x)
-#pragma unroll
-                for (int y = 0; y < TN; ++y)
-                    acc[x][y] = MF::run(af[x], bf[y], acc[x][y]);
-        }
-        __syncthreads();
-    }
-    }
-
-#pragma unroll
-    for (int x = 0; x < TM; ++x)
-#pragma unroll
-        for (int y = 0; y < TN; ++y)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = i0 + wm + x * 16 + MF::row(lane, v), j = j0 + wn + y * 16 + l16;
-                if (o.symsum)
-                    store_c_sym<T>(Cp, C.rs, C.cs, i, j, M, acc[x][y][v], alpha);
-                else
-                    store_c<T>(Cp, C.rs, C.cs, i, j, M, N, acc[x][y][v], alpha, beta, o);
-            }
-}
-
 // ---------------------------------------------------------------------------------------
-// Fast kernel.  AKF: A(i,k) has k contiguous (A.cs == 1), else i contiguous (A.rs == 1).
+// Tile kernel.  AKF: A(i,k) has k contiguous (A.cs == 1), else i contiguous (A.rs == 1).
 // BKF: B(k,j) has k contiguous (B.rs == 1), else j contiguous (B.cs == 1).
 // LDS slab layouts (chosen so that global->LDS stores are 16-byte vectors and the MFMA
 // fragment reads are bank-conflict free):
@@ -329,11 +198,24 @@ struct Slab {
     }
 };
 
-template <typename T, int OUT, int BK, bool KF, typename RV>
-__device__ __forceinline__ void slab_fetch(RV &r, const T *src, int64_t so, int64_t sk, int o0, int no, int k0)
+// One slab of an operand into registers: outer rows o0 .. o0 + OUT - 1 of `no`, k from k0 on, of `nk`.
+// RAG = false: whole aligned chunks only (nk a multiple of BK; `no` a multiple of VW when !KF).
+template <typename T, int OUT, int BK, bool KF, bool RAG, typename RV>
+__device__ __forceinline__ void slab_fetch(RV &r, const T *src, int64_t so, int64_t sk, int o0, int no, int k0, int nk)
 {
     using S = Slab<T, OUT, BK, KF>;
     using V = typename Mfma<T>::vec_t;
+    using L = typename LooseVec<T>::type;
+    if (RAG && o0 + OUT <= no && k0 + BK <= nk) {  // (uniform) nothing crosses an end
+#pragma unroll
+        for (int c = 0; c < S::NCH; ++c) {
+            int o, k;
+            S::coords(c, o, k);
+            const L v = *reinterpret_cast<const L *>(src + (int64_t)(o0 + o) * so + (int64_t)(k0 + k) * sk);
+            r[c] = __builtin_bit_cast(V, v);
+        }
+        return;
+    }
 #pragma unroll
     for (int c = 0; c < S::NCH; ++c) {
         int o, k;
@@ -343,8 +225,24 @@ __device__ __forceinline__ void slab_fetch(RV &r, const T *src, int64_t so, int6
             v = V{0, 0};
         else
             v = V{0, 0, 0, 0};
-        if (o0 + o < no)  // whole chunk in range: K is a multiple of BK, `no` a multiple of VW when !KF
-            v = *reinterpret_cast<const V *>(src + (int64_t)(o0 + o) * so + (int64_t)(k0 + k) * sk);
+        const T *e = src + (int64_t)(o0 + o) * so + (int64_t)(k0 + k) * sk;
+        if constexpr (RAG) {
+            // elements of the chunk that exist
+            const int left = KF ? (o0 + o < no ? nk - (k0 + k) : 0) : (k0 + k < nk ? no - (o0 + o) : 0);
+            if (left >= S::VW) {
+                const L x = *reinterpret_cast<const L *>(e);
+                v = __builtin_bit_cast(V, x);
+            } else {
+                T *q = reinterpret_cast<T *>(&v);
+#pragma unroll
+                for (int u = 0; u < S::VW - 1; ++u)
+                    if (u < left)
+                        q[u] = e[u];
+            }
+        } else {
+            if (o0 + o < no)
+                v = *reinterpret_cast<const V *>(e);
+        }
         r[c] = v;
     }
 }
@@ -388,9 +286,9 @@ __device__ __forceinline__ void slab_commit(T *s, RV &r, int o0, int k0, int tri
     }
 }
 
-template <typename T, int BM, int BN, int BK, int NBUF, bool AKF, bool BKF, bool SYM = false>
-__global__ __launch_bounds__(256, 2) void k_gemm_fast(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M,
-                                                   int N, int K, T alpha, T beta, GemmOpts o, int tiles_m, int tiles_n)
+template <typename T, int BM, int BN, int BK, int NBUF, bool AKF, bool BKF, bool RAG, bool SYM>
+__global__ __launch_bounds__(256, 2) void k_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M,
+                                                 int N, int K, T alpha, T beta, GemmOpts o, int tiles_m, int tiles_n)
 {
     using MF = Mfma<T>;
     using acc_t = typename MF::acc_t;
@@ -436,7 +334,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_fast(View<const T> A, View<cons
     int kbeg, kend;
     k_range(o, i0, j0, BM, BN, Kl, kbeg, kend);
     kbeg = (kbeg / BK) * BK;
-    kend = ((kend + BK - 1) / BK) * BK;  // K is a multiple of BK, so this stays <= K
+    // (whole slabs: the triangular masks clear what lies past kend, the fetch what lies past K)
 
     const T *Ap = A.item(b);
     const T *Bp = B.item(b);
@@ -488,13 +386,13 @@ __global__ __launch_bounds__(256, 2) void k_gemm_fast(View<const T> A, View<cons
     }
     if constexpr (NBUF == 2) {
         if (kbeg < kend) {
-            slab_fetch<T, BM, BK, AKF>(ra, Ap, A.rs, A.cs, i0, M, kbeg);
-            slab_fetch<T, BN, BK, BKF>(rb, Bp, B.cs, B.rs, j0, N, kbeg);
+            slab_fetch<T, BM, BK, AKF, RAG>(ra, Ap, A.rs, A.cs, i0, M, kbeg, Kl);
+            slab_fetch<T, BN, BK, BKF, RAG>(rb, Bp, B.cs, B.rs, j0, N, kbeg, Kl);
             slab_commit<T, BM, BK, AKF>(sA[0], ra, i0, kbeg, o.triA);
             slab_commit<T, BN, BK, BKF>(sB[0], rb, j0, kbeg, triB_o);
             if (kbeg + BK < kend) {
-                slab_fetch<T, BM, BK, AKF>(ra, Ap, A.rs, A.cs, i0, M, kbeg + BK);
-                slab_fetch<T, BN, BK, BKF>(rb, Bp, B.cs, B.rs, j0, N, kbeg + BK);
+                slab_fetch<T, BM, BK, AKF, RAG>(ra, Ap, A.rs, A.cs, i0, M, kbeg + BK, Kl);
+                slab_fetch<T, BN, BK, BKF, RAG>(rb, Bp, B.cs, B.rs, j0, N, kbeg + BK, Kl);
             }
             __syncthreads();
         }
@@ -505,8 +403,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_fast(View<const T> A, View<cons
                 slab_commit<T, BN, BK, BKF>(sB[buf ^ 1], rb, j0, k0 + BK, triB_o);
             }
             if (k0 + 2 * BK < kend) {
-                slab_fetch<T, BM, BK, AKF>(ra, Ap, A.rs, A.cs, i0, M, k0 + 2 * BK);
-                slab_fetch<T, BN, BK, BKF>(rb, Bp, B.cs, B.rs, j0, N, k0 + 2 * BK);
+                slab_fetch<T, BM, BK, AKF, RAG>(ra, Ap, A.rs, A.cs, i0, M, k0 + 2 * BK, Kl);
+                slab_fetch<T, BN, BK, BKF, RAG>(rb, Bp, B.cs, B.rs, j0, N, k0 + 2 * BK, Kl);
             }
             multiply(sA[buf], sB[buf]);
             __syncthreads();
@@ -514,16 +412,16 @@ __global__ __launch_bounds__(256, 2) void k_gemm_fast(View<const T> A, View<cons
         }
     } else {
         if (kbeg < kend) {
-            slab_fetch<T, BM, BK, AKF>(ra, Ap, A.rs, A.cs, i0, M, kbeg);
-            slab_fetch<T, BN, BK, BKF>(rb, Bp, B.cs, B.rs, j0, N, kbeg);
+            slab_fetch<T, BM, BK, AKF, RAG>(ra, Ap, A.rs, A.cs, i0, M, kbeg, Kl);
+            slab_fetch<T, BN, BK, BKF, RAG>(rb, Bp, B.cs, B.rs, j0, N, kbeg, Kl);
         }
         for (int k0 = kbeg; k0 < kend; k0 += BK) {
             slab_commit<T, BM, BK, AKF>(sA[0], ra, i0, k0, o.triA);
             slab_commit<T, BN, BK, BKF>(sB[0], rb, j0, k0, triB_o);
             __syncthreads();
             if (k0 + BK < kend) {
-                slab_fetch<T, BM, BK, AKF>(ra, Ap, A.rs, A.cs, i0, M, k0 + BK);
-                slab_fetch<T, BN, BK, BKF>(rb, Bp, B.cs, B.rs, j0, N, k0 + BK);
+                slab_fetch<T, BM, BK, AKF, RAG>(ra, Ap, A.rs, A.cs, i0, M, k0 + BK, Kl);
+                slab_fetch<T, BN, BK, BKF, RAG>(rb, Bp, B.cs, B.rs, j0, N, k0 + BK, Kl);
             }
             multiply(sA[0], sB[0]);
             __syncthreads();
@@ -695,8 +593,8 @@ static inline int pick_order(const GemmOpts &o, int tiles_m, int tiles_n)
     return o.shells ? 3 : 0;
 }
 
-template <typename T, int BM, int BN, int BK, int NBUF>
-static void launch_fast(bool akf, bool bkf, View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N,
+template <typename T, int BM, int BN, int BK, int NBUF, bool RAG>
+static void launch_form(bool akf, bool bkf, View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N,
                         int K, T alpha, T beta, GemmOpts o, hipStream_t st)
 {
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -705,29 +603,42 @@ static void launch_fast(bool akf, bool bkf, View<const T> A, View<const T> B, Vi
     o.xcd_batch = (batch >= 8 && per > 1) ? 1 : 0;
     const int64_t wgs = o.xcd_batch ? 8 * ((batch + 7) / 8) * per : per * batch;
     const dim3 grid((unsigned)wgs), block(256);
-#define LA_GO(AK, BKF_)                                                                                              \
-    LA_LAUNCH((k_gemm_fast<T, BM, BN, BK, NBUF, AK, BKF_>), grid, block, 0, st, A, B, C, batch, M, N, K,    \
-                       alpha, beta, o, tiles_m, tiles_n)
+#define LA_GO(AK, BKF_, SYM_)                                                                                          \
+    LA_LAUNCH((k_gemm<T, BM, BN, BK, NBUF, AK, BKF_, RAG, SYM_>), grid, block, 0, st, A, B, C, batch, M, N, K, alpha,  \
+              beta, o, tiles_m, tiles_n)
     if constexpr (BM <= 64) {  // the symmetric sum exists for the small tiles only (launch_gemm picks them)
         if (o.symsum) {         // and its operands have mirrored strides, so akf == bkf
             if (akf)
-                LA_LAUNCH((k_gemm_fast<T, BM, BN, BK, NBUF, true, true, true>), grid, block, 0, st, A, B, C, batch, M, N,
-                          K, alpha, beta, o, tiles_m, tiles_n);
+                LA_GO(true, true, true);
             else
-                LA_LAUNCH((k_gemm_fast<T, BM, BN, BK, NBUF, false, false, true>), grid, block, 0, st, A, B, C, batch, M,
-                          N, K, alpha, beta, o, tiles_m, tiles_n);
+                LA_GO(false, false, true);
             return;
         }
     }
     if (akf && bkf)
-        LA_GO(true, true);
+        LA_GO(true, true, false);
     else if (akf && !bkf)
-        LA_GO(true, false);
+        LA_GO(true, false, false);
     else if (!akf && bkf)
-        LA_GO(false, true);
+        LA_GO(false, true, false);
     else
-        LA_GO(false, false);
+        LA_GO(false, false, false);
 #undef LA_GO
+}
+
+struct GemmForm {
+    bool akf, bkf;  // k is the contiguous index of A, of B
+    bool rag;       // some chunk is unaligned or incomplete
+};
+
+template <typename T, int BM, int BN, int BK, int NBUF>
+static void launch_tiles(GemmForm f, View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N, int K,
+                         T alpha, T beta, GemmOpts o, hipStream_t st)
+{
+    if (f.rag)
+        launch_form<T, BM, BN, BK, NBUF, true>(f.akf, f.bkf, A, B, C, batch, M, N, K, alpha, beta, o, st);
+    else
+        launch_form<T, BM, BN, BK, NBUF, false>(f.akf, f.bkf, A, B, C, batch, M, N, K, alpha, beta, o, st);
 }
 
 static inline int flip_tri(int t) { return t == 1 ? 2 : (t == 2 ? 1 : 0); }
@@ -767,10 +678,15 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
         return launch_gemm<T>(B.t(), A.t(), C.t(), batch, N, M, K, alpha, beta, t, st);
     }
     constexpr int VW = Mfma<T>::VW;
-    const bool akf = (A.cs == 1), bkf = (B.rs == 1);
-    const bool a_ok = akf ? aligned16<T>(A, A.rs) : (A.rs == 1 && aligned16<T>(A, A.cs) && M % VW == 0);
-    const bool b_ok = bkf ? aligned16<T>(B, B.cs) : (B.cs == 1 && aligned16<T>(B, B.rs) && N % VW == 0);
-    if (K > 0 && K % 16 == 0 && a_ok && b_ok) {
+    GemmForm f;
+    f.akf = (A.cs == 1);
+    f.bkf = (B.rs == 1);
+    if ((!f.akf && A.rs != 1) || (!f.bkf && B.cs != 1))
+        return LA_ERR_UNSUPPORTED;  // (no operator of the library builds such a view)
+    const bool a_ok = f.akf ? aligned16<T>(A, A.rs) : (aligned16<T>(A, A.cs) && M % VW == 0);
+    const bool b_ok = f.bkf ? aligned16<T>(B, B.cs) : (aligned16<T>(B, B.rs) && N % VW == 0);
+    f.rag = !(K % 16 == 0 && a_ok && b_ok);
+    {
         const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch;
         if (t64 > 0x1fffffffll)  // (quarter tiles and the batched mapping round the grid up)
             return LA_ERR_UNSUPPORTED;
@@ -781,11 +697,12 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             return tile_count(pick_order(o, tm, tn), tm, tn) * batch;
         };
         const int64_t wg128 = wgs(128), wg64 = wgs(64);
-        const bool k64 = (K % 64 == 0);
+        // K slabs of 64: the whole range in such slabs, or (ragged) little of the last one empty
+        const bool k64 = f.rag ? (K >= 128 || (K & 63) == 0 || (K & 63) > 32) : K % 64 == 0;
         if (!o.triA && !o.triB && !o.min_tile64 && !o.ksplit && wg64 <= 128 && K >= 2048 && A.nb2 == 1 && B.nb2 == 1 &&
             C.nb2 == 1) {
             int splits = (int)std::min<int64_t>(512 / wg64, K / 256);
-            const int Kc = ((K / 16 + splits - 1) / splits) * 16;
+            const int Kc = (((K + 15) / 16 + splits - 1) / splits) * 16;
             splits = (K + Kc - 1) / Kc;
             const size_t bytes = (size_t)batch * splits * M * N * sizeof(T);
             if (splits >= 2 && bytes <= SPLITK_MAX_BYTES) {
@@ -799,7 +716,7 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
                 ps.maskC = o.maskC;  // tiles beyond the kept triangle are not computed (nor read back)
                 ps.ksplit = splits;
                 ps.ktotal = K;
-                launch_fast<T, 64, 64, 16, 2>(akf, bkf, As, Bs, Ps, batch * splits, M, N, Kc, T(1), T(0), ps, st);
+                launch_tiles<T, 64, 64, 16, 2>(f, As, Bs, Ps, batch * splits, M, N, Kc, T(1), T(0), ps, st);
                 LA_TRY(launch_check("gemm_splitk"));
                 const int64_t total = batch * mn;
                 LA_LAUNCH((k_splitk_reduce<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
@@ -839,35 +756,26 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
                 View<const T> A1 = A.sub(e, 0);
                 View<T> C1 = C.sub(e, 0);
                 if (e == 128)
-                    launch_fast<T, 128, 128, 16, 2>(akf, bkf, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
+                    launch_tiles<T, 128, 128, 16, 2>(f, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
                 else if (k64)
-                    launch_fast<T, 64, 64, 64, 1>(akf, bkf, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
+                    launch_tiles<T, 64, 64, 64, 1>(f, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
                 else
-                    launch_fast<T, 64, 64, 16, 2>(akf, bkf, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
-                LA_TRY(launch_check("gemm_fast"));
+                    launch_tiles<T, 64, 64, 16, 2>(f, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
+                LA_TRY(launch_check("gemm"));
                 return launch_gemm<T>(A.level2((int64_t)e * A.rs, (int)Tt), B.level2((int64_t)e * B.cs, (int)Tt),
                                       C.level2((int64_t)e * (C.rs + C.cs), (int)Tt), batch * Tt, e, e, K, alpha, beta, o, st);
             }
         }
         if (e == 128)
-            launch_fast<T, 128, 128, 16, 2>(akf, bkf, A, B, C, batch, M, N, K, alpha, beta, o, st);
+            launch_tiles<T, 128, 128, 16, 2>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
         else if (e == 32)
-            launch_fast<T, 32, 32, 64, 1>(akf, bkf, A, B, C, batch, M, N, K, alpha, beta, o, st);
+            launch_tiles<T, 32, 32, 64, 1>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
         else if (k64)  // small grids are latency bound: fewer, fatter K slabs
-            launch_fast<T, 64, 64, 64, 1>(akf, bkf, A, B, C, batch, M, N, K, alpha, beta, o, st);
+            launch_tiles<T, 64, 64, 64, 1>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
         else
-            launch_fast<T, 64, 64, 16, 2>(akf, bkf, A, B, C, batch, M, N, K, alpha, beta, o, st);
-        return launch_check("gemm_fast");
+            launch_tiles<T, 64, 64, 16, 2>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
+        return launch_check("gemm");
     }
-    constexpr int BM = 64, BN = 64, BK = 16;
-    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    o.order = pick_order(o, tiles_m, tiles_n);
-    const int64_t blocks = tile_count(o.order, tiles_m, tiles_n) * batch;
-    if (blocks > 0x7fffffffll)
-        return LA_ERR_UNSUPPORTED;
-    LA_LAUNCH((k_gemm<T, BM, BN, BK>), dim3((unsigned)blocks), dim3(256), 0, st, A, B, C, batch, M, N, K,
-                       alpha, beta, o, tiles_m, tiles_n);
-    return launch_check("gemm");
 }
 
 template la_status launch_gemm<float>(View<const float>, View<const float>, View<float>, int64_t, int, int, int, float,
