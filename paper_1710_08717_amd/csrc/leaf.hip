@@ -46,59 +46,6 @@ struct Leaf16 {
 
 __device__ __forceinline__ int tri_off(int i, int j) { return i * (i - 1) / 2 + j; }  // i > j
 
-// Factor and invert one 16 x 16 tile held one row per lane.  All four 16-lane rows of the
-// wavefront factor copies of the same tile; the inverse is shared out between them: in lane row
-// g register x[j] is column 4 j + g of the inverse.
-// In: a[c] = A(r, c) for c <= r (what lies above the diagonal is never looked at).
-// Out: a[c] = L(r, c) for c <= r, x[j] = L^-1(r, 4 j + g) (entries above the diagonal hold
-// leftovers, respectively zero) and the return value is the 1-based index of the first pivot that
-// is not > 0, or 0.
-//
-// The pivots run on the unscaled matrix,   a_rc -= a_rk a_ck / a_kk,   x_rc -= a_rk x_kc / a_kk,
-// which needs only a reciprocal on the critical path (started as soon as the next pivot is final);
-// the square roots are taken for all 16 pivots at once afterwards:
-// L = A_raw diag(d)^-1/2,  L^-1 = diag(d)^-1/2 X_raw.
-template <typename T>
-__device__ __forceinline__ int diag_factor_invert(T (&a)[LT], T (&x)[4], int r, int g)
-{
-    T d = T(1);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        x[j] = (4 * j + g == r) ? T(1) : T(0);
-    T rinv = rcp_newton(a[0]);  // meaningful in the pivot's lane only
-    static_for<0, LT>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        const T am = (r > k) ? a[k] : T(0);
-        d = (r == k) ? a[k] : d;
-        settle(rinv);
-        const T t = mul_row<k>(rinv, am);  // a_rk / a_kk below the pivot, zero elsewhere
-        if constexpr (k + 1 < LT) {
-            fnmac_row<k + 1>(a[k + 1], a[k], t);
-            rinv = rcp_newton(a[k + 1]);  // overlaps the rest of this pivot's updates
-        }
-        static_for<k + 2, LT>([&](auto cc) {
-            constexpr int c = decltype(cc)::value;
-            fnmac_row<c>(a[c], a[k], t);  // a_rc -= a_ck t_r
-        });
-        static_for<0, k / 4 + 1>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            fnmac_row_self<k>(x[j], t);  // x_rc -= x_kc t_r (a no-op where column c > k)
-        });
-    });
-    const unsigned long long bad = __ballot(!(d > T(0)));
-    T rs = rsqrt_acc(d);
-    settle(rs);
-    static_for<0, LT>([&](auto cc) {
-        constexpr int c = decltype(cc)::value;
-        a[c] = mul_row<c>(rs, a[c]);  // column c times d_c^-1/2
-    });
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        x[j] *= rs;  // row r times d_r^-1/2
-    const unsigned first = (unsigned)(bad & 0xffffu);
-    return first ? __builtin_ctz(first) + 1 : 0;
-}
-
 // ---------------------------------------------------------------------------------------
 // Tiles in LDS.  Diagonal tiles are stored with padded rows (stride PS) for the row-per-lane
 // accesses of the factorisation.  Off-diagonal tiles are 16 x 16 without padding, with the

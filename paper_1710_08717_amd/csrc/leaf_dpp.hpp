@@ -98,4 +98,73 @@ __device__ __forceinline__ void diag_invert(const T (&a)[LT], T dr, T (&x)[4], i
         x[j] *= rinv;
 }
 
+// Factor and invert one 16 x 16 tile held one row per lane.  All four 16-lane rows of the
+// wavefront factor copies of the same tile; the inverse is shared out between them: in lane row
+// g register x[j] is column 4 j + g of the inverse.
+// In: a[c] = A(r, c) for c <= r (what lies above the diagonal is never looked at).
+// Out: a[c] = L(r, c) for c <= r, x[j] = L^-1(r, 4 j + g) (entries above the diagonal hold
+// leftovers, respectively zero) and the return value is the 1-based index of the first pivot that
+// is not > 0, or 0.
+//
+// The pivots run on the unscaled matrix,   a_rc -= a_rk a_ck / a_kk,   x_rc -= a_rk x_kc / a_kk,
+// which needs only a reciprocal on the critical path (started as soon as the next pivot is final);
+// the square roots are taken for all 16 pivots at once afterwards:
+// L = A_raw diag(d)^-1/2,  L^-1 = diag(d)^-1/2 X_raw.
+// SKIP: rows and columns from nk on are those of the identity; their pivots are left out, four at a time.
+template <typename T, bool SKIP = false>
+__device__ __forceinline__ int diag_factor_invert(T (&a)[LT], T (&x)[4], int r, int g, int nk = LT)
+{
+    T d = T(1);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        x[j] = (4 * j + g == r) ? T(1) : T(0);
+    T rinv = rcp_newton(a[0]);  // meaningful in the pivot's lane only
+    static_for<0, LT / 4>([&](auto bc) {
+        constexpr int k0 = 4 * decltype(bc)::value;
+        if constexpr (SKIP) {
+            if (k0 >= nk)
+                return;
+            // a branch can leave copies of the operands right here: two wait states behind them
+#pragma unroll
+            for (int c = 0; c < LT; ++c)
+                asm volatile("" : "+v"(a[c]));
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                asm volatile("" : "+v"(x[j]));
+            asm volatile("s_nop 1");
+        }
+        static_for<k0, k0 + 4>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            const T am = (r > k) ? a[k] : T(0);
+            d = (r == k) ? a[k] : d;
+            settle(rinv);
+            const T t = mul_row<k>(rinv, am);  // a_rk / a_kk below the pivot, zero elsewhere
+            if constexpr (k + 1 < LT) {
+                fnmac_row<k + 1>(a[k + 1], a[k], t);
+                rinv = rcp_newton(a[k + 1]);  // overlaps the rest of this pivot's updates
+            }
+            static_for<k + 2, LT>([&](auto cc) {
+                constexpr int c = decltype(cc)::value;
+                fnmac_row<c>(a[c], a[k], t);  // a_rc -= a_ck t_r
+            });
+            static_for<0, k / 4 + 1>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                fnmac_row_self<k>(x[j], t);  // x_rc -= x_kc t_r (a no-op where column c > k)
+        });
+    });
+    });
+    const unsigned long long bad = __ballot(!(d > T(0)));
+    T rs = rsqrt_acc(d);
+    settle(rs);
+    static_for<0, LT>([&](auto cc) {
+        constexpr int c = decltype(cc)::value;
+        a[c] = mul_row<c>(rs, a[c]);  // column c times d_c^-1/2
+    });
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        x[j] *= rs;  // row r times d_r^-1/2
+    const unsigned first = (unsigned)(bad & 0xffffu);
+    return first ? __builtin_ctz(first) + 1 : 0;
+}
+
 }  // namespace la

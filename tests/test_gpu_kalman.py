@@ -119,3 +119,34 @@ def test_kalman_argument_errors(la):
     assert lib.la_kalman_filter(*args(2, 2, z)) == 1
     assert lib.la_kalman_filter(7, 1, 1, 2, 2, 1, p, p, p, p, p, p, p, z, z, p, z, z) == 1
     assert lib.la_kalman_filter(0, 0, 1, 2, 2, 1, z, z, z, z, z, z, z, z, z, z, z, z) == 0  # empty batch
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("batch,T,dh,dv", [(31, 4, 16, 16), (33, 3, 15, 9), (65, 3, 11, 12), (17, 5, 12, 1), (40, 2, 4, 13),
+                                           (32768 + 37, 2, 9, 3), (32768 + 33, 3, 3, 8), (1, 9, 1, 16)])
+@pytest.mark.parametrize("want_states", [True, False])
+def test_kalman_one_model_equals_repeated_model(la, dtype, batch, T, dh, dv, want_states):
+    """The kernel that shares the covariance recursion against the per-sequence one on the same model, repeated:
+    covariances that are not symmetric (read as they are), ends of the 16-sequence tiles, F items of odd size."""
+    w = workloads.make_kalman(batch, T, dh, dv, dtype=dtype, shared=True, seed=batch + 3 * T)
+    g = np.random.default_rng(batch)
+    for k in ("Sh", "S0"):
+        w[k] = (w[k] + 0.01 * g.standard_normal(w[k].shape)).astype(w[k].dtype)
+    rep = dict(w)
+    for k in ("A", "B", "Sh", "Sv", "mu0", "S0"):
+        rep[k] = np.repeat(w[k][None], batch, axis=0)
+    a, b = run(la, w, want_states), run(la, rep, want_states)
+    assert np.array_equal(a[3], b[3])
+    assert np.all(np.abs(a[0] - b[0]) <= TOL[dtype] * np.maximum(1.0, np.abs(b[0])))
+    if want_states:
+        assert rel(a[1], b[1]) <= TOL[dtype] and rel(a[2], b[2]) <= TOL[dtype]
+
+
+def test_kalman_one_model_bad_pivot(la):
+    """info and the step a pivot fails at, shared against repeated parameters."""
+    w = workloads.make_kalman(20, 4, 5, 3, dtype="f64", shared=True, seed=3)
+    w["Sv"] = -50.0 * np.eye(3)
+    rep = dict(w)
+    for k in ("A", "B", "Sh", "Sv", "mu0", "S0"):
+        rep[k] = np.repeat(w[k][None], 20, axis=0)
+    assert np.array_equal(run(la, w)[3], run(la, rep)[3])
