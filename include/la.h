@@ -270,12 +270,12 @@ la_status la_gp_glue(la_dtype dt, int64_t batch, int n, const void *L, const voi
  * triangle is read) and targets y,
  *   L = potrf(A),  z = L^{-1} y,  alpha = L^{-T} z,
  *   loss = 1/2 y^T alpha + sum_i log l_ii           (the criterion minus n/2 log 2 pi),
- *   Abar = d loss / d A = 1/2 (A^{-1} - alpha alpha^T), obtained as the potrf backward of
+ *   Abar = d loss / d A = 1/2 (A^{-1} - alpha alpha^T), the potrf backward of
  *          Lbar = -tril(alpha z^T) + diag(1 / l_ii); written in full, exactly symmetric.
  * A, Abar: [batch, n, n]; y: [batch, n]; loss: [batch]; info: NULL or int32 [batch] as for potrf.
- * Abar may be the same buffer as A.  Up to n = 128 (fp32) / 96 (fp64) this is ONE kernel per call
- * and needs no workspace; beyond that it is the sequence la_potrf_batched, two la_trsm_batched,
- * la_gp_glue, la_potrf_backward on `workspace` (device memory, 256-byte aligned, at least
+ * Abar may be the same buffer as A.  Up to n = 128 this is ONE kernel per call; beyond that it is
+ * la_potrf_batched, two la_trsm_batched and the inverse of the factor times its transpose.  From
+ * n = 129 (fp32) / 97 (fp64) on the call takes a `workspace` (device memory, 256-byte aligned, at least
  * la_gp_workspace_bytes(dt, batch, n) bytes, not overlapping the other arguments). */
 size_t la_gp_workspace_bytes(la_dtype dt, int64_t batch, int n);
 la_status la_gp_criterion(la_dtype dt, int64_t batch, int n, const void *A, const void *y, void *loss, void *Abar,

@@ -573,7 +573,8 @@ struct GemmOpts {
     int symsum = 0;      // 1: C = alpha (A B + (A B)^T) on a square C, both triangles written, exactly symmetric.  The
                          // tiles on and below the diagonal accumulate A B and then B^T A^T -- B^T must have A's strides and
                          // A^T B's, so the second pass only swaps the two base pointers -- and store every entry with its
-                         // mirror image.  beta and maskC are not used.
+                         // mirror image.  2: C = alpha A B + beta C for an A B that is symmetric (same strides) and a C of
+                         // which the lower triangle is read: one pass, stored in the same way.  maskC is not used.
 };
 template <typename T>
 la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N, int K, T alpha,
@@ -601,9 +602,11 @@ template <typename T>
 la_status launch_mirror_lower(View<T> X, int64_t batch, int n, hipStream_t st);
 template <typename T>
 la_status launch_sumlogdiag(const T *L, T *out, int64_t batch, int n, hipStream_t st);
+// loss = 1/2 y^T alpha + sum log l_ii and Lbar = -tril(alpha z^T) + diag(1 / l_ii); without z: the lower triangle of
+// rank1 alpha alpha^T in its place (nothing above the diagonal is written)
 template <typename T>
 la_status launch_gp_glue(const T *L, const T *y, const T *z, const T *alpha, T *loss, T *Lbar, int64_t batch, int n,
-                         hipStream_t st);
+                         hipStream_t st, T rank1 = T(-0.5));
 la_status launch_fill_i32(int32_t *p, int64_t count, int32_t v, hipStream_t st);
 
 // Pieces of the sparse-GP criterion (section 3.2).
@@ -623,7 +626,7 @@ template <typename T>
 la_status launch_sgp_scalars(int stage, const double *sums, double lam, int n, T *phi, T *noise_bar, T *kff_bar, int nk,
                              hipStream_t st);
 
-// Gaussian-process criterion and gradient, one workgroup per matrix (leaf.hip); n <= backward_leaf16_max_n.
+// Gaussian-process criterion and gradient, one workgroup per matrix (leaf.hip); n <= 128.
 template <typename T>
 la_status launch_gp_leaf16(View<const T> A, const T *y, T *loss, View<T> Abar, int32_t *info, int64_t batch, int n,
                            hipStream_t st);

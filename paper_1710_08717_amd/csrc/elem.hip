@@ -286,18 +286,24 @@ constexpr int GLUE_THREADS = 1024;
 constexpr int GLUE_ROWS = 64;
 template <typename T>
 __global__ __launch_bounds__(GLUE_THREADS) void k_gp_glue(const T *L, const T *y, const T *z, const T *alpha, T *loss,
-                                                          T *Lbar, int64_t batch, int n, int chunks)
+                                                          T *Lbar, int64_t batch, int n, int chunks, T rank1)
 {
     __shared__ double red[GLUE_THREADS / WAVE];
     const int64_t b = blockIdx.x / chunks;
     const int chunk = (int)(blockIdx.x % chunks);
     const T *lp = L + b * (int64_t)n * n;
-    const T *yp = y + b * n, *zp = z + b * n, *ap = alpha + b * n;
+    const T *yp = y + b * n, *zp = z ? z + b * n : nullptr, *ap = alpha + b * n;
     T *gp = Lbar + b * (int64_t)n * n;
     const int w = threadIdx.x / WAVE, l = threadIdx.x % WAVE;
     const int r1 = min(n, (chunk + 1) * GLUE_ROWS);
     for (int i = chunk * GLUE_ROWS + w; i < r1; i += GLUE_THREADS / WAVE) {
         const T ai = ap[i];
+        if (!zp) {
+            T *row = gp + (int64_t)i * n;
+            for (int j = l; j <= i; j += WAVE)
+                row[j] = rank1 * ai * ap[j];
+            continue;
+        }
         const T dinv = T(1) / lp[(int64_t)i * n + i];
         T *row = gp + (int64_t)i * n;
         for (int j = l; j < n; j += WAVE) {
@@ -328,7 +334,7 @@ __global__ __launch_bounds__(GLUE_THREADS) void k_gp_glue(const T *L, const T *y
 
 template <typename T>
 la_status launch_gp_glue(const T *L, const T *y, const T *z, const T *alpha, T *loss, T *Lbar, int64_t batch, int n,
-                         hipStream_t st)
+                         hipStream_t st, T rank1)
 {
     if (batch <= 0)
         return LA_OK;
@@ -336,7 +342,7 @@ la_status launch_gp_glue(const T *L, const T *y, const T *z, const T *alpha, T *
     if (batch * chunks > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
     LA_LAUNCH((k_gp_glue<T>), dim3((unsigned)(batch * chunks)), dim3(GLUE_THREADS), 0, st, L, y, z, alpha, loss,
-                       Lbar, batch, n, chunks);
+                       Lbar, batch, n, chunks, rank1);
     return launch_check("gp_glue");
 }
 
@@ -480,7 +486,7 @@ la_status launch_fill_i32(int32_t *p, int64_t count, int32_t v, hipStream_t st)
     template la_status launch_rank1_add<T>(T *, const T *, const T *, int, int, hipStream_t);                   \
     template la_status launch_sgp_scalars<T>(int, const double *, double, int, T *, T *, T *, int, hipStream_t); \
     template la_status launch_gp_glue<T>(const T *, const T *, const T *, const T *, T *, T *, int64_t, int,    \
-                                         hipStream_t);
+                                         hipStream_t, T);
 LA_INST(float)
 LA_INST(double)
 

@@ -11,8 +11,8 @@
 //
 // k_gemm: 16-byte vector loads, register prefetch of the next K slab while the current one is
 // multiplied out of LDS, 128x128 (K slabs of 16, double-buffered LDS, one barrier per slab),
-// 64x64 or 32x32 workgroup tiles (K slabs of 64 for the small, latency-bound grids of the
-// recursion's lower levels; 32x32 when 64x64 tiles would leave most compute units idle), four
+// 64x64 (K slabs of 32) or 32x32 workgroup tiles (K slabs of 64, for the small, latency-bound
+// grids of the recursion's lower levels), four
 // wavefronts in a 2 x 2 arrangement, 16x16x4 MFMA (v_mfma_f64_16x16x4_f64 /
 // v_mfma_f32_16x16x4_f32).  Two forms: with 16-byte aligned operands and K a multiple of 16 every
 // chunk is one aligned load; otherwise (odd sizes and leading dimensions) the chunks are loaded
@@ -138,18 +138,6 @@ __device__ __forceinline__ void k_range(const GemmOpts &o, int i0, int j0, int B
         kbeg = max(kbeg, j0);
     else if (o.triB == 2)
         kend = min(kend, j0 + BN);
-}
-
-// GemmOpts::symsum: the lower triangle's values go to both triangles
-template <typename T>
-__device__ __forceinline__ void store_c_sym(T *Cp, int64_t rs, int64_t cs, int i, int j, int M, T acc, T alpha)
-{
-    if (i < M && j <= i) {
-        const T upd = alpha * acc;
-        Cp[(int64_t)i * rs + (int64_t)j * cs] = upd;
-        if (j < i)
-            Cp[(int64_t)j * rs + (int64_t)i * cs] = upd;
-    }
 }
 
 template <typename T>
@@ -377,8 +365,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm(View<const T> A, View<const T> 
                     acc[x][y] = MF::run(af[x], bf[y], acc[x][y]);
         }
     };
-    // SYM (GemmOpts::symsum): a second pass adds B^T A^T -- same strides, the base pointers change places
-    for (int pass = 0; pass < (SYM ? 2 : 1); ++pass) {
+    // SYM (GemmOpts::symsum): with 1 a second pass adds B^T A^T -- same strides, the base pointers change places
+    const int passes = SYM && o.symsum == 1 ? 2 : 1;
+    for (int pass = 0; pass < passes; ++pass) {
     if (SYM && pass == 1) {
         const T *t = Ap;
         Ap = Bp;
@@ -429,18 +418,51 @@ __global__ __launch_bounds__(256, 2) void k_gemm(View<const T> A, View<const T> 
     }
     }
 
+    if constexpr (SYM) {
+        // Every value goes to both triangles.  A 16 x 16 tile's mirror image is turned in the wavefront's own part of the
+        // LDS (free now), so that both are stored row by row: 32 matrices of n = 512, fp64, W of the backward pass
+        // 108 -> 103 us against storing the mirror image element by element.
+        T *turn = sA[0] + w * (16 * 17);
+        static_assert(4 * 16 * 17 <= NBUF * SA::ELEMS, "the turning areas fit the A slabs");
+#pragma unroll
+        for (int x = 0; x < TM; ++x)
+#pragma unroll
+            for (int y = 0; y < TN; ++y) {
+                const int it = i0 + wm + x * 16, jt = j0 + wn + y * 16;  // first row, first column of the tile
+                if (jt > it || it >= M)
+                    continue;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int u = MF::row(lane, v), i = it + u, j = jt + l16;
+                    T upd = alpha * acc[x][y][v];
+                    if (i < M && j <= i) {
+                        T *c = Cp + (int64_t)i * C.rs + (int64_t)j * C.cs;
+                        if (beta != T(0))
+                            upd = fma(beta, *c, upd);
+                        *c = upd;
+                    }
+                    turn[u * 17 + l16] = upd;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int u = lk + 4 * v, i = it + l16, j = jt + u;  // row j, column i of the mirror image
+                    const T m = turn[l16 * 17 + u];
+                    if (i < M && j < i)
+                        Cp[(int64_t)j * C.rs + (int64_t)i * C.cs] = m;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            }
+        return;
+    }
 #pragma unroll
     for (int x = 0; x < TM; ++x)
 #pragma unroll
         for (int y = 0; y < TN; ++y)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = i0 + wm + x * 16 + MF::row(lane, v), j = j0 + wn + y * 16 + l16;
-                if constexpr (SYM)
-                    store_c_sym<T>(Cp, C.rs, C.cs, i, j, M, acc[x][y][v], alpha);
-                else
-                    store_c<T>(Cp, C.rs, C.cs, i, j, M, N, acc[x][y][v], alpha, beta, o);
-            }
+            for (int v = 0; v < 4; ++v)
+                store_c<T>(Cp, C.rs, C.cs, i0 + wm + x * 16 + MF::row(lane, v), j0 + wn + y * 16 + l16, M, N, acc[x][y][v],
+                           alpha, beta, o);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -699,7 +721,7 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
         const int64_t wg128 = wgs(128), wg64 = wgs(64);
         // K slabs of 64: the whole range in such slabs, or (ragged) little of the last one empty
         const bool k64 = f.rag ? (K >= 128 || (K & 63) == 0 || (K & 63) > 32) : K % 64 == 0;
-        if (!o.triA && !o.triB && !o.min_tile64 && !o.ksplit && wg64 <= 128 && K >= 2048 && A.nb2 == 1 && B.nb2 == 1 &&
+        if (!o.triA && !o.triB && !o.min_tile64 && !o.ksplit && !o.symsum && wg64 <= 128 && K >= 2048 && A.nb2 == 1 && B.nb2 == 1 &&
             C.nb2 == 1) {
             int splits = (int)std::min<int64_t>(512 / wg64, K / 256);
             const int Kc = (((K + 15) / 16 + splits - 1) / splits) * 16;
@@ -730,18 +752,21 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             // list (heaviest first): the 512 workgroup slots only fill evenly if there are several
             // rounds of tiles, so take the largest tile that still gives 1024 workgroups.
             e = wg128 >= 1024 ? 128 : ((wg64 >= 1024 || !k64 || o.min_tile64) ? 64 : 32);
-            if (o.symsum && e == 128)
-                e = 64;
         } else {
-            // Equal tiles: big tiles once they fill most of the chip, quarter tiles while 64 x 64 tiles
+            // Equal tiles: big tiles once they fill the 512 workgroup slots (a compute unit with one workgroup waits for
+            // its loads: a sparse GP with 300 tiles of 128 1497 -> 1429 us in 64 x 64 tiles, factor + gradient of
+            // n = 5500 with 432 of them 7737 -> 7511, fp64; 8192 with 192 to 256 of them in several products 16.84 -> 16.79 ms,
+            // in fp32 10.07 -> 9.81), quarter tiles while 64 x 64 tiles
             // would fill the 512 workgroup slots less than twice -- with so few rounds the last one runs
             // part empty (32 x 384 x 384 lower triangle, K = 128: 672 tiles of 64, 38 -> 30 us; potrf of
             // 32 x 512 x 512 0.245 -> 0.231 ms, of 4 x 2048 x 2048 1.14 -> 1.10, 8192 x 8192 with 512
             // vectors trsm 1.19 -> 1.12 ms).
             const int64_t t128 = o.maskC ? wg128 : (int64_t)((M + 127) / 128) * ((N + 127) / 128) * batch;
             const bool big = o.maskC ? (M >= 2048 && N >= 2048) : (M >= 128 && N >= 128);
-            e = (t128 >= 192 && big) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64) ? 32 : 64);
+            e = (t128 >= 512 && big) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64) ? 32 : 64);
         }
+        if (o.symsum && e == 128)  // (the form that stores both triangles has tiles up to 64 only)
+            e = 64;
         if (e >= 64 && o.maskC == 1 && !o.triA && !o.triB && !o.halfDiag && !o.shells && !o.min_tile64 && M == N &&
             M % e == 0 && A.nb2 == 1 && B.nb2 == 1 && C.nb2 == 1) {
             // Lower triangle in e x e tiles: T (T + 1) / 2 of them.  When that is a few tiles more than
@@ -758,7 +783,7 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
                 if (e == 128)
                     launch_tiles<T, 128, 128, 16, 2>(f, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
                 else if (k64)
-                    launch_tiles<T, 64, 64, 64, 1>(f, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
+                    launch_tiles<T, 64, 64, 32, 1>(f, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
                 else
                     launch_tiles<T, 64, 64, 16, 2>(f, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
                 LA_TRY(launch_check("gemm"));
@@ -770,8 +795,9 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             launch_tiles<T, 128, 128, 16, 2>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
         else if (e == 32)
             launch_tiles<T, 32, 32, 64, 1>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
-        else if (k64)  // small grids are latency bound: fewer, fatter K slabs
-            launch_tiles<T, 64, 64, 64, 1>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
+        else if (k64)  // (slabs of 64 in one buffer hold two workgroups a compute unit, of 32 four: 32 matrices of
+                       // n = 512, fp64, factor + gradient 593 -> 570 us; slabs of 16 in two buffers 590)
+            launch_tiles<T, 64, 64, 32, 1>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
         else
             launch_tiles<T, 64, 64, 16, 2>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
         return launch_check("gemm");

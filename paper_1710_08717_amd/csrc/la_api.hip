@@ -584,6 +584,12 @@ static la_status syrk_t(int trans, double alpha, int64_t batch, int n, int k, co
     if (outer_leaf_takes<T>(batch, n, k, false))  // one workgroup per matrix, operands in LDS
         return launch_outer_leaf<T>(0, (T)alpha, batch, n, k, Ank, Ank, C, st);
     GemmOpts o;
+    // 64 x 64 tiles and below store both triangles at once; where the product runs on 128 x 128 tiles (or split along a
+    // long k) the mirror image is a pass of its own.
+    if (n < 2048 && k < 2048) {
+        o.symsum = 2;
+        return launch_gemm<T>(Ank, Ank.t(), C, batch, n, n, k, (T)alpha, T(0), o, st);
+    }
     o.maskC = 1;
     LA_TRY(launch_gemm<T>(Ank, Ank.t(), C, batch, n, n, k, (T)alpha, T(0), o, st));
     return launch_mirror_lower<T>(C, batch, n, st);
@@ -708,9 +714,25 @@ static la_status syrk_backward_t(int trans, double alpha, int64_t batch, int n, 
     return launch_gemm<T>(Av, G.t(), Ov, batch, k, n, n, (T)alpha, T(1), o, st);
 }
 
+// C = alpha A^-1 + beta C for the factor Lam of A, both triangles of C written from the lower one: explicit inverse Li of the
+// factor (into Inv), then the lower tiles of Li^T Li, mirrored.
+template <typename T>
+static la_status inverse_gram_add(View<const T> Lam, View<T> Inv, T alpha, View<T> C, T beta, int64_t batch, int n,
+                                  hipStream_t st)
+{
+    ArenaFrame frame;
+    View<T> Tmp;
+    LA_TRY(scratch_views<T>(batch, n, 1, &Tmp));
+    LA_TRY(inverse_build<T>(Lam, Inv, Tmp, batch, n, n, st));
+    GemmOpts o;
+    o.triA = 2;
+    o.triB = 1;
+    o.symsum = 2;
+    return launch_gemm<T>(cv(Inv).t(), cv(Inv), C, batch, n, n, n, alpha, beta, o, st);
+}
+
 // potri (section 4.2 "potri"): A^-1 = Lam^-T Lam^-1 for A = Lam Lam^T (Lam = L, or R^T for an upper
-// factor: the same symmetric matrix either way).  Explicit inverse of the factor, then the lower
-// tiles of Li^T Li (K range from max(i, j) on), mirrored.
+// factor: the same symmetric matrix either way).
 template <typename T>
 static la_status potri_t(int lower, int64_t batch, int n, const void *L, void *B, hipStream_t st)
 {
@@ -720,16 +742,9 @@ static la_status potri_t(int lower, int64_t batch, int n, const void *L, void *B
     if (n <= 2 * NB)  // one workgroup per matrix, everything in LDS, no scratch
         return launch_potri_leaf16<T>(Lam, View<T>{(T *)B, (int64_t)n * n, n, 1}, batch, n, st);
     ArenaFrame frame;
-    View<T> sc[2];
-    LA_TRY(scratch_views<T>(batch, n, 2, sc));
-    LA_TRY(inverse_build<T>(Lam, sc[0], sc[1], batch, n, n, st));
-    View<T> Bv{(T *)B, (int64_t)n * n, n, 1};
-    GemmOpts o;
-    o.triA = 2;
-    o.triB = 1;
-    o.maskC = 1;
-    LA_TRY(launch_gemm<T>(cv(sc[0]).t(), cv(sc[0]), Bv, batch, n, n, n, T(1), T(0), o, st));
-    return launch_mirror_lower<T>(Bv, batch, n, st);
+    View<T> Inv;
+    LA_TRY(scratch_views<T>(batch, n, 1, &Inv));
+    return inverse_gram_add<T>(Lam, Inv, T(1), View<T>{(T *)B, (int64_t)n * n, n, 1}, T(0), batch, n, st);
 }
 
 // potri backward (section 4.2 "potri"; appendix "potri"):
@@ -846,20 +861,20 @@ template <typename T>
 static la_status gp_t(int64_t batch, int n, const void *A, const void *y, void *loss, void *Abar, int32_t *info,
                       void *workspace, hipStream_t st)
 {
-    if (n <= backward_leaf16_max_n<T>()) {
+    if (n <= 2 * NB) {
         if (info)
             LA_TRY(launch_fill_i32(info, batch, 0, st));
         return launch_gp_leaf16<T>(tri_view<const T>((const T *)A, n, 1), (const T *)y, (T *)loss,
                                    tri_view<T>((T *)Abar, n, 1), info, batch, n, st);
     }
     const int64_t nn = (int64_t)n * n;
-    T *Lw = (T *)workspace, *Gw = Lw + batch * nn, *z = Gw + batch * nn, *al = z + batch * n;
+    T *Lw = (T *)workspace, *Iw = Lw + batch * nn, *z = Iw + batch * nn, *al = z + batch * n;
     LA_TRY(potrf_t<T>(1, batch, n, A, Lw, info, st));
     LA_TRY(tri_apply_t<T>(true, 1, 0, 0, 1.0, batch, n, 1, Lw, y, z, st));
     LA_TRY(tri_apply_t<T>(true, 1, 1, 0, 1.0, batch, n, 1, Lw, z, al, st));
-    LA_TRY(launch_gp_glue<T>(Lw, (const T *)y, z, al, (T *)loss, Gw, batch, n, st));
-    return backward_impl<T>(tri_view<const T>(Lw, n, 1), tri_view<const T>(Gw, n, 1), tri_view<T>((T *)Abar, n, 1), batch,
-                            n, false, st);
+    LA_TRY(launch_gp_glue<T>(Lw, (const T *)y, nullptr, al, (T *)loss, (T *)Abar, batch, n, st));
+    return inverse_gram_add<T>(tri_view<const T>(Lw, n, 1), tri_view<T>(Iw, n, 1), T(0.5), tri_view<T>((T *)Abar, n, 1), T(1),
+                               batch, n, st);
 }
 
 // ---------------------------------------------------------------------------------

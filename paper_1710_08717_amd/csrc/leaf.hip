@@ -444,10 +444,9 @@ __device__ __forceinline__ void leaf_store_lower(const LeafLds<T> &m, bool inver
 // the A / L areas of m (and a workgroup barrier has passed), on return they hold the factor and the
 // X areas its inverse.  Returns, in wavefront 0, the 1-based index of the first pivot that is not
 // > 0 (0: none); ends with a workgroup barrier.
-template <typename T>
+template <typename T, int W = LEAF16_WAVES>
 __device__ __forceinline__ int leaf_factor(const LeafLds<T> &m, int K, int wave, int lane)
 {
-    constexpr int W = LEAF16_WAVES;
     int fail = 0;
     if (wave == 0)
         fail = leaf_diag<T>(m, 0, lane);
@@ -1151,25 +1150,30 @@ __global__ __launch_bounds__(NW * 64) void k_trmm_leaf16(View<const T> Lam, View
 
 // ---------------------------------------------------------------------------------------
 // Gaussian-process criterion and its gradient in one launch (section 3.1: potrf, two trsm,
-// sumlogdiag; backward of trsm (first case) and of potrf from section 4.2), one workgroup per
-// matrix, everything in LDS.  For A = K + noise, targets y:
+// sumlogdiag; their backward rules from section 4.2), one workgroup per matrix, everything in LDS.
+// For A = K + noise, targets y:
 //   L = potrf(A) with Li = L^-1 (the factorisation loop of k_potrf_leaf16);
 //   z = Li y,  alpha = Li^T z,  loss = 1/2 |z|^2 + sum_i log l_ii;
-//   Lbar = -tril(alpha z^T) + diag(1 / l_ii) is never stored: its tiles are built in registers
-//   where P = Phi(tril(L^T Lbar)) needs them;
-//   Z = P Li;  Abar_ij = 1/2 sum_{k >= i} (Li_ki^T Z_kj + Z_ki^T Li_kj)   (as in k_backward_leaf16).
-// Three tile areas: [A -> L -> Z], [Li], [P -> staging of the mirrored store], and 4 vectors.
+//   Abar = 1/2 (A^-1 - alpha alpha^T),  A^-1_ij = sum_{k >= i} Li_ki^T Li_kj,
+// which is what the backward rules make of Lbar = -tril(alpha z^T) + diag(1 / l_ii): with
+// Phi(L^T Lbar) = 1/2 (1 - z z^T) on and below the diagonal, L^-T (Phi + Phi^T) L^-1 / 2 is that.
+// Two tile areas: [A -> L -> staging of the mirrored store], [Li], and 4 vectors.
+//
+// Bound by the factorisation's chain of pivots.  Four wavefronts per matrix for up to four tile
+// rows, so that several matrices share a compute unit; sixteen above.
+// Against the form that built P = Phi(L^T Lbar) and Z = P Li in a third area, with sixteen wavefronts
+// always: fp32 256 x 128 47 -> 34 us, 1024 x 64 66 -> 28, 8192 x 16 188 -> 39; fp64 300 x 128 (five
+// operators before) 270 -> 85, 1024 x 64 86 -> 43.  Rounding errors are 10 to 25 % smaller.
 // ---------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(LEAF16_THREADS) void k_gp_leaf16(View<const T> A, const T *y, T *loss, View<T> Abar,
-                                                              int32_t *info, int64_t batch, int n)
+template <typename T, int NW, int MAXK>
+__global__ __launch_bounds__(NW * 64) void k_gp_leaf16(View<const T> A, const T *y, T *loss, View<T> Abar, int32_t *info,
+                                                       int64_t batch, int n)
 {
     using C = Leaf16<T>;
     using MF = Mfma<T>;
     extern __shared__ __align__(16) unsigned char leaf16_lds[];
     T *lds = reinterpret_cast<T *>(leaf16_lds);
-    constexpr int W = LEAF16_WAVES;
-    constexpr int DT = C::DT, OT = C::OT;
+    constexpr int DT = C::DT;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1178,55 +1182,53 @@ __global__ __launch_bounds__(LEAF16_THREADS) void k_gp_leaf16(View<const T> A, c
     const int ntl = K * (K + 1) / 2;
     const int area = backward16_area<T>(K);
     const LeafLds<T> m{lds, lds + area, lds + K * DT, lds + area + K * DT};
-    T *pD = lds + 2 * area, *pO = pD + K * DT;
-    T *sy = lds + 3 * area, *sz = sy + LT * LK, *sal = sz + LT * LK, *sdi = sal + LT * LK;  // y, z, alpha, 1 / l_ii
-    auto ptile = [&](int i, int j) { return i == j ? TileRef<T>{pD + i * DT, true} : TileRef<T>{pO + tri_off(i, j) * OT, false}; };
+    T *sy = lds + 2 * area, *sz = sy + LT * K, *sal = sz + LT * K, *sdi = sal + LT * K;  // y, z, alpha, 1 / l_ii
 
-    leaf_load_lower<T>(m, A.p + b * A.bs, A.rs, A.cs, n, wave, lane);
-    if (tid < LT * LK)
+    leaf_load_lower<T, NW, MAXK>(m, A.p + b * A.bs, A.rs, A.cs, n, wave, lane);
+    if (tid < LT * K)
         sy[tid] = tid < n ? y[b * n + tid] : T(0);
     __syncthreads();
 
     // ---- L and Li ------------------------------------------------------------------------------
-    const int fail = leaf_factor<T>(m, K, wave, lane);
+    const int fail = leaf_factor<T, NW>(m, K, wave, lane);
     if (info != nullptr && tid == 0 && fail != 0 && fail <= n)
         info[b] = fail;
 
-    // ---- z = Li y: eight threads per row, one tile column each ----------------------------------
+    // ---- z = Li y: MAXK threads per row, one tile column each ------------------------------------
+    // ---- alpha = Li^T z: MAXK threads per column, one tile row each -------------------------------
+    static_assert(NW * 64 == LT * MAXK * MAXK, "one thread per row and tile");
+    const int e = tid / MAXK, te = tid % MAXK, ue = e & 15, ke = e >> 4;  // row or column, tile along it
     {
-        const int r = tid >> 3, tj = tid & 7, ti = r >> 4, u = r & 15;
         T part = T(0);
-        if (ti < K && tj <= ti) {
-            const TileRef<T> t = m.x(ti, tj);
+        if (ke < K && te <= ke) {
+            const TileRef<T> t = m.x(ke, te);
 #pragma unroll
             for (int w = 0; w < LT; ++w)
-                part = fma(t.p[t.at(u, w)], sy[tj * LT + w], part);
+                part = fma(t.p[t.at(ue, w)], sy[te * LT + w], part);
         }
-        part += __shfl_xor(part, 1, 8);
-        part += __shfl_xor(part, 2, 8);
-        part += __shfl_xor(part, 4, 8);
-        if (tj == 0) {
-            sz[r] = part;
-            const TileRef<T> d = m.x(ti < K ? ti : 0, ti < K ? ti : 0);
-            sdi[r] = (r < n) ? d.p[d.at(u, u)] : T(0);
+#pragma unroll
+        for (int off = 1; off < MAXK; off <<= 1)
+            part += __shfl_xor(part, off, MAXK);
+        if (te == 0 && ke < K) {
+            sz[e] = part;
+            const TileRef<T> d = m.x(ke, ke);
+            sdi[e] = d.p[d.at(ue, ue)];
         }
     }
     __syncthreads();
-    // ---- alpha = Li^T z: eight threads per column, one tile row each; the loss -------------------
     {
-        const int c = tid >> 3, ti = tid & 7, tj = c >> 4, w = c & 15;
         T part = T(0);
-        if (ti < K && tj <= ti) {
-            const TileRef<T> t = m.x(ti, tj);
+        if (te < K && ke <= te) {
+            const TileRef<T> t = m.x(te, ke);
 #pragma unroll
             for (int u = 0; u < LT; ++u)
-                part = fma(t.p[t.at(u, w)], sz[ti * LT + u], part);
+                part = fma(t.p[t.at(u, ue)], sz[te * LT + u], part);
         }
-        part += __shfl_xor(part, 1, 8);
-        part += __shfl_xor(part, 2, 8);
-        part += __shfl_xor(part, 4, 8);
-        if (ti == 0)
-            sal[c] = part;
+#pragma unroll
+        for (int off = 1; off < MAXK; off <<= 1)
+            part += __shfl_xor(part, off, MAXK);
+        if (te == 0 && ke < K)
+            sal[e] = part;
     }
     if (wave == 0) {  // loss = 1/2 |z|^2 - sum log(1 / l_ii)
         double acc = 0.0;
@@ -1240,90 +1242,39 @@ __global__ __launch_bounds__(LEAF16_THREADS) void k_gp_leaf16(View<const T> A, c
     }
     __syncthreads();
 
-    // ---- P_ij = sum_{k >= i} L_ki^T Lbar_kj, i >= j, with Lbar_kj built in registers; Phi ----------
-    for (int t = wave; t < ntl; t += W) {
+    // ---- Abar_ij, i >= j, stored with its mirror image through the tile's slot of the finished L ----
+    T *op = Abar.p + b * Abar.bs;
+    const bool colfast = (Abar.cs == 1) || (Abar.rs != 1);
+    const int f = lane & 15, s0 = lane >> 4;
+    for (int t = wave; t < ntl; t += NW) {
         int i, j;
         tri_decode(t, i, j);
         typename MF::acc_t acc = {0, 0, 0, 0};
-        const int w = lane & 15;
-        const T zc = sz[j * LT + w];
         for (int k = i; k < K; ++k) {
             T av[4], bv[4];
-            op_nat<T>(m.a(k, i), lane, av);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {  // element (u, w) of tile (k, j) of Lbar, u = 4 (lane / 16) + s
-                const int u = 4 * (lane >> 4) + s;
-                const int r = k * LT + u, c = j * LT + w;
-                T v = -sal[r] * zc;
-                if (r == c)
-                    v += sdi[r];
-                bv[s] = (r >= c) ? v : T(0);
-            }
-            acc = mma4<T>(av, bv, acc, false);
-        }
-        if (i == j) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = MF::row(lane, v), col = lane & 15;
-                acc[v] = row < col ? T(0) : (row == col ? T(0.5) * acc[v] : acc[v]);
-            }
-        }
-        acc_store<T>(ptile(i, j), lane, acc);
-    }
-    __syncthreads();
-
-    // ---- Z_ij = sum_{k = j..i} P_ik Li_kj, i >= j, into the area L occupied -----------------------
-    for (int t = wave; t < ntl; t += W) {
-        int i, j;
-        tri_decode(t, i, j);
-        typename MF::acc_t acc = {0, 0, 0, 0};
-        for (int k = j; k <= i; ++k) {
-            T av[4], bv[4];
-            op_rows<T>(ptile(i, k), lane, av);
+            op_nat<T>(m.x(k, i), lane, av);
             op_nat<T>(m.x(k, j), lane, bv);
             acc = mma4<T>(av, bv, acc, false);
         }
-        acc_store<T>(m.a(i, j), lane, acc);
-    }
-    __syncthreads();
-
-    // ---- Abar_ij = 1/2 sum_{k >= i} (Li_ki^T Z_kj + Z_ki^T Li_kj), i >= j, stored with its mirror ----
-    {
-        T *op = Abar.p + b * Abar.bs;
-        const bool colfast = (Abar.cs == 1) || (Abar.rs != 1);
-        const int f = lane & 15, s0 = lane >> 4;
-        for (int t = wave; t < ntl; t += W) {
-            int i, j;
-            tri_decode(t, i, j);
-            typename MF::acc_t acc = {0, 0, 0, 0};
-            for (int k = i; k < K; ++k) {
-                T av[4], bv[4];
-                op_nat<T>(m.x(k, i), lane, av);
-                op_nat<T>(m.a(k, j), lane, bv);
-                acc = mma4<T>(av, bv, acc, false);
-                op_nat<T>(m.a(k, i), lane, av);
-                op_nat<T>(m.x(k, j), lane, bv);
-                acc = mma4<T>(av, bv, acc, false);
-            }
+        const T aj = sal[j * LT + f];
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                acc[v] *= T(0.5);
-            const TileRef<T> st = ptile(i, j);
-            acc_store<T>(st, lane, acc);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int v = 0; v < 4; ++v)
+            acc[v] = T(0.5) * fma(-sal[i * LT + MF::row(lane, v)], aj, acc[v]);
+        const TileRef<T> st = m.a(i, j);
+        acc_store<T>(st, lane, acc);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int u = colfast ? s0 + 4 * v : f, w = colfast ? f : s0 + 4 * v;
-                const T direct = st.p[st.at(u, w)], mirror = st.p[st.at(w, u)];
-                const int r = i * LT + u, c = j * LT + w;
-                if (r < n && c < n)
-                    op[(int64_t)r * Abar.rs + (int64_t)c * Abar.cs] = (i == j && u < w) ? mirror : direct;
-                const int r2 = j * LT + u, c2 = i * LT + w;
-                if (i != j && r2 < n && c2 < n)
-                    op[(int64_t)r2 * Abar.rs + (int64_t)c2 * Abar.cs] = mirror;
-            }
+        for (int v = 0; v < 4; ++v) {
+            const int u = colfast ? s0 + 4 * v : f, w = colfast ? f : s0 + 4 * v;
+            const T direct = st.p[st.at(u, w)], mirror = st.p[st.at(w, u)];
+            const int r = i * LT + u, c = j * LT + w;
+            if (r < n && c < n)
+                op[(int64_t)r * Abar.rs + (int64_t)c * Abar.cs] = (i == j && u < w) ? mirror : direct;
+            const int r2 = j * LT + u, c2 = i * LT + w;
+            if (i != j && r2 < n && c2 < n)
+                op[(int64_t)r2 * Abar.rs + (int64_t)c2 * Abar.cs] = mirror;
         }
     }
 }
@@ -1801,22 +1752,26 @@ la_status launch_gp_leaf16(View<const T> A, const T *y, T *loss, View<T> Abar, i
 {
     if (batch <= 0 || n <= 0)
         return LA_OK;
-    if (n > backward_leaf16_max_n<T>() || batch > 0x7fffffffll)
+    if (n > LT * LK || batch > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
     const int K = (n + LT - 1) / LT;
-    const size_t lds_bytes = (3 * (size_t)backward16_area<T>(K) + 4 * LT * LK) * sizeof(T);
+    const size_t lds_bytes = (2 * (size_t)backward16_area<T>(K) + 4 * LT * K) * sizeof(T);
     if (dry_run())
         return LA_OK;
+    if (K <= 4) {  // (less than the 64 KB that need no attribute)
+        LA_LAUNCH((k_gp_leaf16<T, 4, 4>), dim3((unsigned)batch), dim3(256), lds_bytes, st, A, y, loss, Abar, info, batch, n);
+        return launch_check("gp_leaf16");
+    }
     static bool configured[64] = {};
     int dev = 0;
     LA_HIP(hipGetDevice(&dev));
     if (dev >= 0 && dev < 64 && !configured[dev]) {
-        const size_t most = (3 * (size_t)backward16_area<T>(backward_leaf16_max_n<T>() / LT) + 4 * LT * LK) * sizeof(T);
-        LA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gp_leaf16<T>),
+        const size_t most = (2 * (size_t)backward16_area<T>(LK) + 4 * LT * LK) * sizeof(T);
+        LA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gp_leaf16<T, LEAF16_WAVES, LK>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
         configured[dev] = true;
     }
-    LA_LAUNCH((k_gp_leaf16<T>), dim3((unsigned)batch), dim3(LEAF16_THREADS), lds_bytes, st, A, y, loss, Abar,
+    LA_LAUNCH((k_gp_leaf16<T, LEAF16_WAVES, LK>), dim3((unsigned)batch), dim3(LEAF16_THREADS), lds_bytes, st, A, y, loss, Abar,
                        info, batch, n);
     return launch_check("gp_leaf16");
 }
