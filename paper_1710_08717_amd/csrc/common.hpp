@@ -612,19 +612,33 @@ la_status launch_fill_i32(int32_t *p, int64_t count, int32_t v, hipStream_t st);
 // Pieces of the sparse-GP criterion (section 3.2).
 constexpr int SGP_PARTIALS = 256;  // fp64 partial sums per reduced quantity
 // kind 0: sum a^2, 1: sum a, 2: sum a b, 3: trace of the ld x ld matrix a (count = ld), 4: sum of the
-// logs of its diagonal; writes SGP_PARTIALS partial sums
+// logs of its diagonal; writes SGP_PARTIALS partial sums (zeros for count 0)
 template <typename T>
-la_status launch_partial_sums(int kind, const T *a, const T *b, int64_t count, int64_t ld, double *partial,
-                              hipStream_t st);
+struct SumOf {
+    int kind;
+    const T *a, *b;
+    int64_t count, ld;
+};
+constexpr int SGP_SUMS = 7;
+template <typename T>
+struct SumList {
+    SumOf<T> q[SGP_SUMS];
+};
+// `nq` quantities at once, quantity i to partial + i * SGP_PARTIALS
+template <typename T>
+la_status launch_partial_sums(const SumList<T> &list, int nq, double *partial, hipStream_t st);
 template <typename T>
 la_status launch_add_diag(T *A, int n, T v, hipStream_t st);
+// on U x U, with Q = A + 2 Ab - 2 I:  A <- the lower triangle of Q with its diagonal halved (nothing above the
+// diagonal is written),  Ab <- Ab - I / 2
+template <typename T>
+la_status launch_sgp_inner(T *A, T *Ab, int U, hipStream_t st);
 template <typename T>
 la_status launch_rank1_add(T *C, const T *u, const T *v, int rows, int cols, hipStream_t st);
 // sums: 7 x SGP_PARTIALS partial sums (|y|^2, |w|^2, |B|^2, sum Kff_diag, sum log La_ii, sum Abar o A,
-// trace Abar); stage 0 writes phi, stage 1 noise_bar and the constant Kff_diag_bar
+// trace Abar); writes phi, noise_bar and the constant Kff_diag_bar
 template <typename T>
-la_status launch_sgp_scalars(int stage, const double *sums, double lam, int n, T *phi, T *noise_bar, T *kff_bar, int nk,
-                             hipStream_t st);
+la_status launch_sgp_scalars(const double *sums, double lam, int n, T *phi, T *noise_bar, T *kff_bar, int nk, hipStream_t st);
 
 // Gaussian-process criterion and gradient, one workgroup per matrix (leaf.hip); n <= 128.
 template <typename T>

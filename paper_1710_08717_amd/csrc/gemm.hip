@@ -475,68 +475,76 @@ __global__ __launch_bounds__(256, 2) void k_gemm(View<const T> A, View<const T> 
 constexpr int GEMV_N = 8;
 constexpr int GEMV_THREADS = 512;
 
-template <typename T>
+// NC: columns computed (N <= NC; the spare ones repeat the last column and are not stored).  The loads of several k
+// go out together, those of B with them: with one k at a time and a branch per column a wavefront waits for
+// memory twice per k (500 x 9568 times one vector, fp64, 27 -> 22 us; its transpose 59 -> 11).
+template <typename T, int NC>
 __global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N,
                                               int K, T alpha, T beta, int triA, int tiles)
 {
     constexpr int NW = GEMV_THREADS / 64;  // wavefronts: rows per block (k contiguous) or slices of k
-    __shared__ T red[NW][64][GEMV_N];
+    constexpr int UN = NC == 1 ? 8 : (NC <= 4 ? 4 : 2);
+    __shared__ T red[NW][64][NC];
     const int64_t b = blockIdx.x / tiles;
     const int tile = (int)(blockIdx.x % tiles);
     const T *Ap = A.item(b);
     const T *Bp = B.item(b);
     T *Cp = C.item(b);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    T acc[GEMV_N];
+    int64_t jo[NC];
+    T acc[NC];
 #pragma unroll
-    for (int j = 0; j < GEMV_N; ++j)
+    for (int j = 0; j < NC; ++j) {
+        jo[j] = (int64_t)(j < N ? j : N - 1) * B.cs;
         acc[j] = T(0);
-    if (A.cs == 1) {
-        const int i = tile * NW + w;
-        if (i < M) {
-            const int kb = triA == 2 ? i : 0, ke = triA == 1 ? min(K, i + 1) : K;
-            const T *ar = Ap + (int64_t)i * A.rs;
-            for (int k = kb + lane; k < ke; k += 64) {
-                const T a = ar[k];
+    }
+    const bool rows = A.cs == 1;
+    const int i = rows ? tile * NW + w : tile * 64 + lane;
+    if (i < M) {
+        const int kb = triA == 2 ? i : 0, ke = triA == 1 ? min(K, i + 1) : K;
+        const int first = rows ? kb + lane : w, step = rows ? 64 : NW, last = rows ? ke : K;
+        const T *ar = Ap + (int64_t)i * A.rs;
+        for (int k0 = first; k0 < last; k0 += UN * step) {
+            T a[UN], x[UN][NC];
 #pragma unroll
-                for (int j = 0; j < GEMV_N; ++j)
-                    if (j < N)
-                        acc[j] = fma(a, Bp[(int64_t)k * B.rs + (int64_t)j * B.cs], acc[j]);
+            for (int u = 0; u < UN; ++u) {
+                const int k = k0 + u * step;
+                const bool in = k >= kb && k < ke;
+                a[u] = in ? ar[(int64_t)k * A.cs] : T(0);
+#pragma unroll
+                for (int j = 0; j < NC; ++j)
+                    x[u][j] = in ? Bp[(int64_t)k * B.rs + jo[j]] : T(0);
             }
 #pragma unroll
-            for (int j = 0; j < GEMV_N; ++j) {
+            for (int u = 0; u < UN; ++u)
 #pragma unroll
-                for (int off = 32; off >= 1; off >>= 1)
-                    acc[j] += __shfl_xor(acc[j], off, WAVE);
-                if (lane == 0 && j < N) {
-                    T *c = Cp + (int64_t)i * C.rs + (int64_t)j * C.cs;
-                    const T upd = alpha * acc[j];
-                    *c = (beta == T(0)) ? upd : fma(beta, *c, upd);
-                }
+                for (int j = 0; j < NC; ++j)
+                    acc[j] = fma(a[u], x[u][j], acc[j]);
+        }
+    }
+    if (rows) {
+        if (i >= M)
+            return;
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1)
+                acc[j] += __shfl_xor(acc[j], off, WAVE);
+            if (lane == 0 && j < N) {
+                T *c = Cp + (int64_t)i * C.rs + (int64_t)j * C.cs;
+                const T upd = alpha * acc[j];
+                *c = (beta == T(0)) ? upd : fma(beta, *c, upd);
             }
         }
         return;
     }
-    const int i = tile * 64 + lane;
-    if (i < M) {
-        const int kb = triA == 2 ? i : 0, ke = triA == 1 ? min(K, i + 1) : K;
-        for (int k = w; k < K; k += NW) {
-            if (k < kb || k >= ke)
-                continue;
-            const T a = Ap[(int64_t)i * A.rs + (int64_t)k * A.cs];
 #pragma unroll
-            for (int j = 0; j < GEMV_N; ++j)
-                if (j < N)
-                    acc[j] = fma(a, Bp[(int64_t)k * B.rs + (int64_t)j * B.cs], acc[j]);
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < GEMV_N; ++j)
+    for (int j = 0; j < NC; ++j)
         red[w][lane][j] = acc[j];
     __syncthreads();
     if (w == 0 && i < M) {
 #pragma unroll
-        for (int j = 0; j < GEMV_N; ++j)
+        for (int j = 0; j < NC; ++j)
             if (j < N) {
                 T sum = T(0);
 #pragma unroll
@@ -557,8 +565,16 @@ static la_status launch_gemv(View<const T> A, View<const T> B, View<T> C, int64_
     const int64_t blocks = (int64_t)tiles * batch;
     if (blocks > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
-    LA_LAUNCH((k_gemv<T>), dim3((unsigned)blocks), dim3(GEMV_THREADS), 0, st, A, B, C, batch, M, N, K, alpha, beta, triA,
-                       tiles);
+#define LA_GO(NC_)                                                                                                     \
+    LA_LAUNCH((k_gemv<T, NC_>), dim3((unsigned)blocks), dim3(GEMV_THREADS), 0, st, A, B, C, batch, M, N, K, alpha, beta, \
+              triA, tiles)
+    if (N == 1)
+        LA_GO(1);
+    else if (N <= 4)
+        LA_GO(4);
+    else
+        LA_GO(GEMV_N);
+#undef LA_GO
     return launch_check("gemv");
 }
 

@@ -262,6 +262,26 @@ static int bwd_base(int64_t batch, size_t elem)
     return b;
 }
 
+// W = 1/2 (Li^T (P + P^T) Li) for lower triangular Li and P (what lies above their diagonals is not read), both triangles
+// of W, exactly symmetric.  X: scratch; W may be P.
+template <typename T>
+static la_status congruence(View<const T> Li, View<const T> P, View<T> X, View<T> W, int64_t batch, int n, hipStream_t st)
+{
+    GemmOpts oz;
+    oz.triA = 1;
+    oz.triB = 1;
+    oz.maskC = 1;
+    oz.reverse = 1;  // K range of tile (i, j) grows with i - j: bottom rows first
+    LA_TRY(launch_gemm<T>(P, Li, X, batch, n, n, n, T(1), T(0), oz, st));
+    // 1/2 (Li^T Z + Z^T Li) in one launch: the tiles on and below the diagonal accumulate both products (K range from the
+    // tile's first row on) and write every entry with its mirror image
+    GemmOpts ow;
+    ow.triA = 2;
+    ow.triB = 1;
+    ow.symsum = 1;
+    return launch_gemm<T>(Li.t(), cv(X), W, batch, n, n, n, T(0.5), T(0), ow, st);
+}
+
 template <typename T>
 static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, int64_t batch, int n, bool aliased,
                                hipStream_t st)
@@ -291,19 +311,7 @@ static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, in
     o.maskC = 1;
     o.halfDiag = 1;
     LA_TRY(launch_gemm<T>(Lam.t(), Gs, W, batch, n, n, n, T(1), T(0), o, st));
-    GemmOpts oz;
-    oz.triA = 1;
-    oz.triB = 1;
-    oz.maskC = 1;
-    oz.reverse = 1;  // K range of tile (i, j) grows with i - j: bottom rows first
-    LA_TRY(launch_gemm<T>(cv(W), cv(Li), X, batch, n, n, n, T(1), T(0), oz, st));
-    // Abar = 1/2 (Li^T Z + Z^T Li) in one launch: the tiles on and below the diagonal accumulate both
-    // products (K range from the tile's first row on) and write every entry with its mirror image
-    GemmOpts ow;
-    ow.triA = 2;
-    ow.triB = 1;
-    ow.symsum = 1;
-    return launch_gemm<T>(cv(Li).t(), cv(X), W, batch, n, n, n, T(0.5), T(0), ow, st);
+    return congruence<T>(cv(Li), cv(W), X, W, batch, n, st);
 }
 
 template <typename T>
@@ -714,21 +722,24 @@ static la_status syrk_backward_t(int trans, double alpha, int64_t batch, int n, 
     return launch_gemm<T>(Av, G.t(), Ov, batch, k, n, n, (T)alpha, T(1), o, st);
 }
 
-// C = alpha A^-1 + beta C for the factor Lam of A, both triangles of C written from the lower one: explicit inverse Li of the
-// factor (into Inv), then the lower tiles of Li^T Li, mirrored.
+// C = alpha Li^T Li + beta C for a lower triangular Li (Li = L^-1: alpha A^-1), both triangles of C written from the lower one
 template <typename T>
-static la_status inverse_gram_add(View<const T> Lam, View<T> Inv, T alpha, View<T> C, T beta, int64_t batch, int n,
-                                  hipStream_t st)
+static la_status gram_add(View<const T> Li, T alpha, View<T> C, T beta, int64_t batch, int n, hipStream_t st)
 {
-    ArenaFrame frame;
-    View<T> Tmp;
-    LA_TRY(scratch_views<T>(batch, n, 1, &Tmp));
-    LA_TRY(inverse_build<T>(Lam, Inv, Tmp, batch, n, n, st));
     GemmOpts o;
     o.triA = 2;
     o.triB = 1;
     o.symsum = 2;
-    return launch_gemm<T>(cv(Inv).t(), cv(Inv), C, batch, n, n, n, alpha, beta, o, st);
+    return launch_gemm<T>(Li.t(), Li, C, batch, n, n, n, alpha, beta, o, st);
+}
+
+// x = Li b or Li^T b for one vector per item, one pass over Li
+template <typename T>
+static la_status inverse_apply1(View<const T> Li, bool trans, T alpha, const T *b, T *x, int64_t batch, int n, hipStream_t st)
+{
+    GemmOpts o;
+    o.triA = trans ? 2 : 1;
+    return launch_gemm<T>(trans ? Li.t() : Li, View<const T>{b, n, 1, 1}, View<T>{x, n, 1, 1}, batch, n, 1, n, alpha, T(0), o, st);
 }
 
 // potri (section 4.2 "potri"): A^-1 = Lam^-T Lam^-1 for A = Lam Lam^T (Lam = L, or R^T for an upper
@@ -742,9 +753,10 @@ static la_status potri_t(int lower, int64_t batch, int n, const void *L, void *B
     if (n <= 2 * NB)  // one workgroup per matrix, everything in LDS, no scratch
         return launch_potri_leaf16<T>(Lam, View<T>{(T *)B, (int64_t)n * n, n, 1}, batch, n, st);
     ArenaFrame frame;
-    View<T> Inv;
-    LA_TRY(scratch_views<T>(batch, n, 1, &Inv));
-    return inverse_gram_add<T>(Lam, Inv, T(1), View<T>{(T *)B, (int64_t)n * n, n, 1}, T(0), batch, n, st);
+    View<T> sc[2];
+    LA_TRY(scratch_views<T>(batch, n, 2, sc));
+    LA_TRY(inverse_build<T>(Lam, sc[0], sc[1], batch, n, n, st));
+    return gram_add<T>(cv(sc[0]), T(1), View<T>{(T *)B, (int64_t)n * n, n, 1}, T(0), batch, n, st);
 }
 
 // potri backward (section 4.2 "potri"; appendix "potri"):
@@ -811,50 +823,66 @@ static la_status sgp_t(int U, int n, const void *Kuu_, const void *Kuf_, const v
     double *sums = reinterpret_cast<double *>(((uintptr_t)(dummy + 16) + 7) & ~(uintptr_t)7);
     const T *Kuf = (const T *)Kuf_, *y = (const T *)y_, *Kff = (const T *)Kff_;
     T *Kuf_bar = (T *)Kuf_bar_, *Kuu_bar = (T *)Kuu_bar_, *y_bar = (T *)y_bar_;
-    auto S = [&](int q) { return sums + q * SGP_PARTIALS; };
+    auto square = [&](T *p) { return View<T>{p, uu, U, 1}; };
+    auto wide = [&](T *p) { return View<T>{p, un, n, 1}; };
+    GemmOpts plain, low, upp;
+    low.triA = 1;
+    low.reverse = 1;
+    upp.triA = 2;
 
     // ---- forward ----------------------------------------------------------------------------
-    LA_TRY(potrf_t<T>(1, 1, U, Kuu_, Lu, nullptr, st));                                        // Lu
-    LA_TRY(tri_apply_t<T>(true, 1, 0, 0, 1.0, 1, U, n, Lu, Kuf, B, st));                       // B = Lu^-1 Kuf
+    // Lu^-1 is applied to n vectors twice and La^-1 is half of A_bar: both are inverted once, explicitly
+    LA_TRY(potrf_t<T>(1, 1, U, Kuu_, Ab, nullptr, st));                                        // Lu (in Ab's buffer)
+    View<T> Liu = square(Lu);
+    {
+        ArenaFrame frame;
+        View<T> Tmp;
+        LA_TRY(scratch_views<T>(1, U, 1, &Tmp));
+        LA_TRY(inverse_build<T>(cv(square(Ab)), Liu, Tmp, 1, U, U, st));                       // Lu^-1
+    }
+    LA_TRY(launch_gemm<T>(cv(Liu), View<const T>{Kuf, un, n, 1}, wide(B), 1, U, n, U, T(1), T(0), low, st));  // B = Lu^-1 Kuf
     LA_TRY(syrk_t<T>(0, 1.0 / lam, 1, U, n, B, A, st));                                        // A = B B^T / lam ...
     LA_TRY(launch_add_diag<T>(A, U, T(1), st));                                                //     ... + I
     LA_TRY(potrf_t<T>(1, 1, U, A, La, nullptr, st));                                           // La
     LA_TRY(gemm2_t<T>(0, 0, 1.0, 1, U, 1, n, B, y, v, st));                                    // v = B y
-    LA_TRY(tri_apply_t<T>(true, 1, 0, 0, 1.0, 1, U, 1, La, v, w, st));                         // w = La^-1 v
-    LA_TRY(launch_partial_sums<T>(0, y, nullptr, n, 0, S(0), st));
-    LA_TRY(launch_partial_sums<T>(0, w, nullptr, U, 0, S(1), st));
-    LA_TRY(launch_partial_sums<T>(0, B, nullptr, un, 0, S(2), st));
-    LA_TRY(launch_partial_sums<T>(1, Kff, nullptr, n, 0, S(3), st));
-    LA_TRY(launch_partial_sums<T>(4, La, nullptr, U, U, S(4), st));
-    LA_TRY(launch_partial_sums<T>(1, Kff, nullptr, 0, 0, S(5), st));  // zero until the backward sweep fills them
-    LA_TRY(launch_partial_sums<T>(1, Kff, nullptr, 0, 0, S(6), st));
-    LA_TRY(launch_sgp_scalars<T>(0, sums, lam, n, (T *)phi_, (T *)nullptr, (T *)nullptr, 0, st));
-
-    // ---- backward ---------------------------------------------------------------------------
-    // w = La^-1 v with w_bar = -w / lam^2:  v_bar = La^-T w_bar;  La_bar = -tril(v_bar w^T) + diag(1 / La_ii)
-    LA_TRY(tri_apply_t<T>(true, 1, 1, 0, -1.0 / (lam * lam), 1, U, 1, La, w, vb, st));
-    LA_TRY(launch_gp_glue<T>(La, w, w, vb, dummy, Ab, 1, U, st));
-    LA_TRY(backward_impl<T>(View<const T>{La, uu, U, 1}, View<const T>{Ab, uu, U, 1}, View<T>{Ab, uu, U, 1}, 1, U, true,
-                            st));                                                              // A_bar (symmetric)
-    LA_TRY(launch_partial_sums<T>(2, Ab, A, uu, 0, S(5), st));
-    LA_TRY(launch_partial_sums<T>(3, Ab, nullptr, U, U, S(6), st));
-    LA_TRY(launch_sgp_scalars<T>(1, sums, lam, n, (T *)nullptr, (T *)lam_bar_, (T *)Kff_bar_, n, st));
-    // B_bar = (2 / lam) A_bar B - B / lam + v_bar y^T   (into Kuf_bar's buffer)
-    View<T> Gb{Kuf_bar, un, n, 1};
-    LA_TRY(launch_copy<T>(View<const T>{B, un, n, 1}, Gb, 1, U, n, (T)(-1.0 / lam), 0, st));
-    GemmOpts o;
-    LA_TRY(launch_gemm<T>(View<const T>{Ab, uu, U, 1}, View<const T>{B, un, n, 1}, Gb, 1, U, n, U, (T)(2.0 / lam), T(1), o,
-                          st));
-    LA_TRY(launch_rank1_add<T>(Kuf_bar, vb, y, U, n, st));
+    {
+        ArenaFrame frame;
+        View<T> sc[2];
+        LA_TRY(scratch_views<T>(1, U, 2, sc));
+        LA_TRY(inverse_build<T>(cv(square(La)), sc[0], sc[1], 1, U, U, st));
+        const View<const T> Lia = cv(sc[0]);
+        LA_TRY(inverse_apply1<T>(Lia, false, T(1), v, w, 1, U, st));                           // w = La^-1 v
+        // ---- backward -----------------------------------------------------------------------
+        // w_bar = -w / lam^2:  v_bar = La^-T w_bar;  La_bar = -tril(v_bar w^T) + diag(1 / La_ii), and as in the GP
+        // criterion (there with alpha in the place of -lam^2 v_bar) A_bar = 1/2 (A^-1 + lam^2 v_bar v_bar^T)
+        LA_TRY(inverse_apply1<T>(Lia, true, (T)(-1.0 / (lam * lam)), w, vb, 1, U, st));
+        LA_TRY(launch_gp_glue<T>(La, w, nullptr, vb, dummy, Ab, 1, U, st, (T)(0.5 * lam * lam)));
+        LA_TRY(gram_add<T>(Lia, T(0.5), square(Ab), T(1), 1, U, st));                          // A_bar (symmetric)
+    }
+    const SumList<T> all{{{0, y, nullptr, n, 0}, {0, w, nullptr, U, 0}, {0, B, nullptr, un, 0}, {1, Kff, nullptr, n, 0},
+                          {4, La, nullptr, U, U}, {2, Ab, A, uu, 0}, {3, Ab, nullptr, U, U}}};
+    LA_TRY(launch_partial_sums<T>(all, SGP_SUMS, sums, st));
+    LA_TRY(launch_sgp_scalars<T>(sums, lam, n, (T *)phi_, (T *)lam_bar_, (T *)Kff_bar_, n, st));
+    // B_bar = (2 / lam) A_bar B - B / lam + v_bar y^T.  Lu_bar = -tril(Lu^-T B_bar B^T) enters the gradient as
+    // Phi(Lu^T Lu_bar) = -Phi(B_bar B^T), and with B B^T = lam (A - I), v = B y that product is
+    //   B_bar B^T = (2 A_bar - I)(A - I) + v_bar v^T = 2 I - A - 2 A_bar,
+    // so neither the product over the n columns nor the one with Lu is needed:
+    //   Kuu_bar = 1/2 Lu^-T (A + 2 A_bar - 2 I) Lu^-1.
+    LA_TRY(launch_sgp_inner<T>(A, Ab, U, st));                      // A <- Phi(A + 2 A_bar - 2 I),  Ab <- A_bar - I / 2
+    {
+        ArenaFrame frame;
+        void *p = nullptr;
+        LA_TRY(arena_take((size_t)un * sizeof(T), &p));
+        const View<T> Bb = wide((T *)p);
+        LA_TRY(launch_gemm<T>(cv(square(Ab)), cv(wide(B)), Bb, 1, U, n, U, (T)(2.0 / lam), T(0), plain, st));
+        LA_TRY(launch_rank1_add<T>(Bb.p, vb, y, U, n, st));
+        LA_TRY(launch_gemm<T>(cv(Liu).t(), cv(Bb), wide(Kuf_bar), 1, U, n, U, T(1), T(0), upp, st));  // Kuf_bar = Lu^-T B_bar
+    }
     // y_bar = B^T v_bar + y / lam
     View<T> yb{y_bar, n, 1, 1};
     LA_TRY(launch_copy<T>(View<const T>{y, n, 1, 1}, yb, 1, n, 1, (T)(1.0 / lam), 0, st));
-    LA_TRY(launch_gemm<T>(View<const T>{B, un, 1, n}, View<const T>{vb, U, 1, 1}, yb, 1, n, 1, U, T(1), T(1), o, st));
-    // B = Lu^-1 Kuf:  Kuf_bar = Lu^-T B_bar (in place),  Lu_bar = -tril(Kuf_bar B^T);  then Kuu_bar
-    LA_TRY(tri_apply_t<T>(true, 1, 1, 0, 1.0, 1, U, n, Lu, Kuf_bar, Kuf_bar, st));
-    LA_TRY(tri_outer_t<T>(1, 0, 0, T(-1), 1, U, n, Kuf_bar, B, Kuu_bar, st));
-    return backward_impl<T>(View<const T>{Lu, uu, U, 1}, View<const T>{Kuu_bar, uu, U, 1}, View<T>{Kuu_bar, uu, U, 1}, 1, U,
-                            true, st);
+    LA_TRY(launch_gemm<T>(View<const T>{B, un, 1, n}, View<const T>{vb, U, 1, 1}, yb, 1, n, 1, U, T(1), T(1), plain, st));
+    return congruence<T>(cv(Liu), cv(square(A)), square(La), square(Kuu_bar), 1, U, st);
 }
 
 template <typename T>
@@ -869,12 +897,18 @@ static la_status gp_t(int64_t batch, int n, const void *A, const void *y, void *
     }
     const int64_t nn = (int64_t)n * n;
     T *Lw = (T *)workspace, *Iw = Lw + batch * nn, *z = Iw + batch * nn, *al = z + batch * n;
+    View<T> Li = tri_view<T>(Iw, n, 1);
     LA_TRY(potrf_t<T>(1, batch, n, A, Lw, info, st));
-    LA_TRY(tri_apply_t<T>(true, 1, 0, 0, 1.0, batch, n, 1, Lw, y, z, st));
-    LA_TRY(tri_apply_t<T>(true, 1, 1, 0, 1.0, batch, n, 1, Lw, z, al, st));
+    {
+        ArenaFrame frame;
+        View<T> Tmp;
+        LA_TRY(scratch_views<T>(batch, n, 1, &Tmp));
+        LA_TRY(inverse_build<T>(tri_view<const T>(Lw, n, 1), Li, Tmp, batch, n, n, st));
+    }
+    LA_TRY(inverse_apply1<T>(cv(Li), false, T(1), (const T *)y, z, batch, n, st));
+    LA_TRY(inverse_apply1<T>(cv(Li), true, T(1), z, al, batch, n, st));
     LA_TRY(launch_gp_glue<T>(Lw, (const T *)y, nullptr, al, (T *)loss, (T *)Abar, batch, n, st));
-    return inverse_gram_add<T>(tri_view<const T>(Lw, n, 1), tri_view<T>(Iw, n, 1), T(0.5), tri_view<T>((T *)Abar, n, 1), T(1),
-                               batch, n, st);
+    return gram_add<T>(cv(Li), T(0.5), tri_view<T>((T *)Abar, n, 1), T(1), batch, n, st);
 }
 
 // ---------------------------------------------------------------------------------

@@ -68,3 +68,57 @@ def test_sgp_argument_errors(la):
     with pytest.raises(la.LaError):
         la.sgp_criterion(dev(w["Kuu"]), dev(w["Kuf"]), dev(w["Kff_diag"]), dev(w["y"]), 0.1,
                          workspace=torch.empty(64, dtype=torch.uint8, device="cuda"))
+
+
+def _long_double_gradient(K, F, y, lam):
+    """Kuu_bar, Kuf_bar, y_bar by column-wise factorisations and substitutions in 80-bit floats."""
+    ld = np.longdouble
+    K, F, y, lam = K.astype(ld), F.astype(ld), y.astype(ld), ld(lam)
+    eye = np.eye(len(K), dtype=ld)
+
+    def chol(S):
+        S, L = S.copy(), np.zeros_like(S)
+        for k in range(len(S)):
+            L[k:, k] = S[k:, k] / np.sqrt(S[k, k])
+            S[k + 1:, k + 1:] -= np.outer(L[k + 1:, k], L[k + 1:, k])
+        return L
+
+    def solve(L, X, trans=False):
+        X, order = X.copy(), range(len(L))
+        for k in (reversed(order) if trans else order):
+            X[k] /= L[k, k]
+            if trans:
+                X[:k] -= np.outer(L[k, :k], X[k])
+            else:
+                X[k + 1:] -= np.outer(L[k + 1:, k], X[k])
+        return X
+
+    Lu = chol(K)
+    B = solve(Lu, F)
+    A = B @ B.T / lam + eye
+    La = chol(A)
+    vb = -solve(La, solve(La, (B @ y)[:, None]), True) / lam**2
+    Ab = (solve(La, solve(La, eye), True) + lam * lam * vb @ vb.T) / 2
+    Kf = solve(Lu, (2 / lam) * ((Ab - eye / 2) @ B) + vb @ y[None], True)
+    W = -(Kf @ B.T) @ solve(Lu, eye) / 2
+    return (W + W.T) / 2, Kf, B.T @ vb[:, 0] + y / lam
+
+
+def test_sgp_gradient_against_80_bit(la):
+    """Rounding errors of the gradient in fp64 against 80-bit arithmetic (an fp64 reference has errors of the same size as
+    the ones looked for).  Bound: the condition numbers of Kuu and A, below 1e3 and 1e5 here, enter as their square roots
+    at least: sqrt(1e8) eps = 2e-12; the tolerance is a fifth of that."""
+    import torch
+
+    g = np.random.default_rng(5)
+    U, n = 90, 1200
+    Z, X = g.uniform(-2, 2, (U, 4)), g.uniform(-2, 2, (n, 4))
+    rbf = lambda P, Q: np.exp(-0.5 * ((P[:, None] - Q[None]) ** 2).sum(-1))
+    K = rbf(Z, Z)
+    np.fill_diagonal(K, 1.1)
+    F, y = rbf(Z, X), g.standard_normal(n)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    out = la.sgp_criterion(dev(K), dev(F), torch.ones(n, device="cuda", dtype=torch.float64), dev(y), 0.1)
+    for name, ref in zip(("Kuu_bar", "Kuf_bar", "y_bar"), _long_double_gradient(K, F, y, np.float64(0.1))):
+        d = out[name].cpu().numpy().astype(np.longdouble) - ref
+        assert float(np.sqrt((d * d).sum() / (ref * ref).sum())) <= 4e-13, name
