@@ -488,6 +488,10 @@ bool outer_leaf_takes(int64_t batch, int n, int k, bool two);
 template <typename T>
 la_status launch_outer_leaf(int tri, T alpha, int64_t batch, int n, int k, View<const T> U, View<const T> V, View<T> C,
                             hipStream_t st);
+// gemm2 of small matrices, C = alpha t(A) t(B), rows and cols <= 64, k <= 128 and both operands' 16 x 16 tiles in 64 KiB
+template <typename T>
+la_status launch_gemm2_leaf(int ta, int tb, T alpha, int64_t batch, int rows, int cols, int k, const T *A, const T *B, T *C,
+                            hipStream_t st);
 // syrk backward in the same form: Out = alpha (G + G^T) A with G n x n, A and Out n x k views
 template <typename T>
 bool symm_leaf_takes(int64_t batch, int n, int k);

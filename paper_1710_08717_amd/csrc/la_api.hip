@@ -603,6 +603,20 @@ static la_status syrk_t(int trans, double alpha, int64_t batch, int n, int k, co
     return launch_mirror_lower<T>(C, batch, n, st);
 }
 
+// The one-workgroup kernel reads an operand as one run, whatever its row length, and pads to 16; the general product
+// loads 64 x 64 tiles row by row.  Measured general -> one-workgroup (8192 items m x n x k, us, fp32 and fp64):
+// 37 x 32 x 37 59 -> 35 and 122 -> 55, 20 x 20 x 80 62 -> 34 and 112 -> 55, 16 x 16 x 48 44 -> 16 and 75 -> 21,
+// 48 x 48 x 32 40 -> 36 and 83 -> 67, 48 x 48 x 48 (18 operand tiles) 51 -> 49 and 105 -> 98, 8 x 37 x 32 (thin
+// products, the second operand plain and transposed) 44 -> 19 and 194 -> 19.  The general one is ahead or equal where it fills
+// its tile (64 x 64 x 16 33 -> 34, 64 x 64 x 64 80 -> 101) and where little LDS is left for other workgroups
+// (33 x 64 x 100, 49 operand tiles, 99 -> 130).  Below 256 items both wait for the launch.
+static bool gemm2_prefers_leaf(int64_t batch, int m, int n, int k)
+{
+    const int tm = (m + 15) / 16, tn = (n + 15) / 16, tk = (k + 15) / 16;
+    return batch >= 256 && batch <= 0x7fffffffll && m >= 4 && n >= 4 && m <= 64 && n <= 64 && tm * tn < 16 && k >= 1 &&
+           k <= 128 && (tm + tn) * tk <= 20;
+}
+
 template <typename T>
 static la_status gemm2_t(int ta, int tb, double alpha, int64_t batch, int m, int n, int k, const void *A, const void *B,
                          void *C, hipStream_t st)
@@ -615,6 +629,8 @@ static la_status gemm2_t(int ta, int tb, double alpha, int64_t batch, int m, int
         return launch_gemm2_tiny<T>(ta, tb, (T)alpha, batch, m, n, k, (const T *)A, (const T *)B, (T *)C, st);
     if (gemm2_rows_takes<T>(m, n, k))  // up to 32 each: 16 lanes per item, two rows per lane
         return launch_gemm2_rows<T>(ta, tb, (T)alpha, batch, m, n, k, (const T *)A, (const T *)B, (T *)C, st);
+    if (gemm2_prefers_leaf(batch, m, n, k))  // one workgroup per item, operands in LDS
+        return launch_gemm2_leaf<T>(ta, tb, (T)alpha, batch, m, n, k, (const T *)A, (const T *)B, (T *)C, st);
     GemmOpts o;
     return launch_gemm<T>(Av, Bv, Cv, batch, m, n, k, (T)alpha, T(0), o, st);
 }
