@@ -615,15 +615,15 @@ la_status launch_fill_i32(int32_t *p, int64_t count, int32_t v, hipStream_t st);
 
 // Pieces of the sparse-GP criterion (section 3.2).
 constexpr int SGP_PARTIALS = 256;  // fp64 partial sums per reduced quantity
-// kind 0: sum a^2, 1: sum a, 2: sum a b, 3: trace of the ld x ld matrix a (count = ld), 4: sum of the
-// logs of its diagonal; writes SGP_PARTIALS partial sums (zeros for count 0)
+// kind 0: sum a^2, 1: sum a, 2: sum a b, 3: sum of the logs of the diagonal of the ld x ld matrix a
+// (count = ld); writes SGP_PARTIALS partial sums
 template <typename T>
 struct SumOf {
     int kind;
     const T *a, *b;
     int64_t count, ld;
 };
-constexpr int SGP_SUMS = 7;
+constexpr int SGP_SUMS = 6;
 template <typename T>
 struct SumList {
     SumOf<T> q[SGP_SUMS];
@@ -631,16 +631,17 @@ struct SumList {
 // `nq` quantities at once, quantity i to partial + i * SGP_PARTIALS
 template <typename T>
 la_status launch_partial_sums(const SumList<T> &list, int nq, double *partial, hipStream_t st);
+// A = E + I on n x n
 template <typename T>
-la_status launch_add_diag(T *A, int n, T v, hipStream_t st);
-// on U x U, with Q = A + 2 Ab - 2 I:  A <- the lower triangle of Q with its diagonal halved (nothing above the
-// diagonal is written),  Ab <- Ab - I / 2
+la_status launch_plus_identity(const T *E, T *A, int n, hipStream_t st);
+// on U x U, with Q + r1 a a^T on and below the diagonal:  Q <- that with its diagonal halved (nothing above the
+// diagonal is read or written),  Ab <- Ab - I / 2,  vb = -r1 a
 template <typename T>
-la_status launch_sgp_inner(T *A, T *Ab, int U, hipStream_t st);
+la_status launch_sgp_inner(T *Q, T *Ab, const T *a, T r1, T *vb, int U, hipStream_t st);
 template <typename T>
 la_status launch_rank1_add(T *C, const T *u, const T *v, int rows, int cols, hipStream_t st);
-// sums: 7 x SGP_PARTIALS partial sums (|y|^2, |w|^2, |B|^2, sum Kff_diag, sum log La_ii, sum Abar o A,
-// trace Abar); writes phi, noise_bar and the constant Kff_diag_bar
+// sums: SGP_SUMS x SGP_PARTIALS partial sums (|y|^2, |w|^2, |B|^2, sum Kff_diag, sum log La_ii,
+// sum Abar o E); writes phi, noise_bar and the constant Kff_diag_bar
 template <typename T>
 la_status launch_sgp_scalars(const double *sums, double lam, int n, T *phi, T *noise_bar, T *kff_bar, int nk, hipStream_t st);
 

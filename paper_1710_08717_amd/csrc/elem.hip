@@ -367,8 +367,8 @@ la_status launch_gp_glue(const T *L, const T *y, const T *z, const T *alpha, T *
 // ---------------------------------------------------------------------------------------
 constexpr int RED_BLOCKS = SGP_PARTIALS;  // partial sums per quantity
 
-// kind 0: sum a_i^2, 1: sum a_i, 2: sum a_i b_i, 3: sum of a_{i (ld + 1)} (trace of an ld x ld matrix),
-// 4: sum log a_{i (ld + 1)}.  One fp64 partial sum per block; k_sgp_scalars adds them up.
+// kind 0: sum a_i^2, 1: sum a_i, 2: sum a_i b_i, 3: sum log a_{i (ld + 1)} (diagonal of
+// an ld x ld matrix).  One fp64 partial sum per block; k_sgp_scalars adds them up.
 // blockIdx.y: which quantity.
 template <typename T>
 __global__ __launch_bounds__(256) void k_partial_sums(SumList<T> list, double *partial)
@@ -386,8 +386,6 @@ __global__ __launch_bounds__(256) void k_partial_sums(SumList<T> list, double *p
             s += (double)a[i];
         else if (d.kind == 2)
             s += (double)a[i] * (double)b[i];
-        else if (d.kind == 3)
-            s += (double)a[i * (d.ld + 1)];
         else
             s += log((double)a[i * (d.ld + 1)]);
     }
@@ -408,40 +406,41 @@ la_status launch_partial_sums(const SumList<T> &list, int nq, double *partial, h
     return launch_check("partial_sums");
 }
 
-// A(i,i) += v on an n x n row-major matrix
+// A = E + I on row-major n x n matrices
 template <typename T>
-__global__ void k_add_diag(T *A, int n, T v)
+__global__ __launch_bounds__(256) void k_plus_identity(const T *E, T *A, int n)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n)
-        A[(int64_t)i * n + i] += v;
+    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (e < (int64_t)n * n)
+        A[e] = e % (n + 1) == 0 ? E[e] + T(1) : E[e];
 }
 template <typename T>
-la_status launch_add_diag(T *A, int n, T v, hipStream_t st)
+la_status launch_plus_identity(const T *E, T *A, int n, hipStream_t st)
 {
-    LA_LAUNCH((k_add_diag<T>), dim3((n + 255) / 256), dim3(256), 0, st, A, n, v);
-    return launch_check("add_diag");
+    LA_LAUNCH((k_plus_identity<T>), dim3((unsigned)(((int64_t)n * n + 255) / 256)), dim3(256), 0, st, E, A, n);
+    return launch_check("plus_identity");
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_sgp_inner(T *A, T *Ab, int U)
+__global__ __launch_bounds__(256) void k_sgp_inner(T *Q, T *Ab, const T *a, T r1, T *vb, int U)
 {
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int i = (int)(e / U), j = (int)(e - (int64_t)i * U);
     if (i >= U || j > i)
         return;
-    const T x = Ab[e];
+    const T ra = r1 * a[i], q = fma(ra, a[j], Q[e]);
     if (j < i) {
-        A[e] = fma(T(2), x, A[e]);
+        Q[e] = q;
     } else {
-        A[e] = T(0.5) * (fma(T(2), x, A[e]) - T(2));
-        Ab[e] = x - T(0.5);
+        Q[e] = T(0.5) * q;
+        Ab[e] -= T(0.5);
+        vb[i] = -ra;
     }
 }
 template <typename T>
-la_status launch_sgp_inner(T *A, T *Ab, int U, hipStream_t st)
+la_status launch_sgp_inner(T *Q, T *Ab, const T *a, T r1, T *vb, int U, hipStream_t st)
 {
-    LA_LAUNCH((k_sgp_inner<T>), dim3((unsigned)(((int64_t)U * U + 255) / 256)), dim3(256), 0, st, A, Ab, U);
+    LA_LAUNCH((k_sgp_inner<T>), dim3((unsigned)(((int64_t)U * U + 255) / 256)), dim3(256), 0, st, Q, Ab, a, r1, vb, U);
     return launch_check("sgp_inner");
 }
 
@@ -463,7 +462,7 @@ la_status launch_rank1_add(T *C, const T *u, const T *v, int rows, int cols, hip
 }
 
 // Scalars of the criterion from the partial sums.  sums[q * RED_BLOCKS ..]: q = 0 |y|^2, 1 |w|^2,
-// 2 |B|_F^2, 3 sum Kff_diag, 4 sum log La_ii, 5 sum Abar o A, 6 trace Abar.
+// 2 |B|_F^2, 3 sum Kff_diag, 4 sum log La_ii, 5 sum Abar o E.
 // Writes phi, noise_bar and the constant Kff_diag_bar.
 template <typename T>
 __global__ __launch_bounds__(256) void k_sgp_scalars(const double *sums, double lam, int n, T *phi, T *noise_bar, T *kff_bar,
@@ -488,7 +487,7 @@ __global__ __launch_bounds__(256) void k_sgp_scalars(const double *sums, double 
     __syncthreads();
     if (threadIdx.x != 0)
         return;
-    const double yy = tot[0], ww = tot[1], bb = tot[2], kk = tot[3], logdet = tot[4], sa = tot[5] - tot[6];
+    const double yy = tot[0], ww = tot[1], bb = tot[2], kk = tot[3], logdet = tot[4], sa = tot[5];
     phi[0] = (T)((1.8378770664093454835606594728112 + log(lam)) * n / 2.0 + logdet + yy / (2.0 * lam) -
                  ww / (2.0 * lam * lam) - (bb - kk) / (2.0 * lam));
     noise_bar[0] = (T)(n / (2.0 * lam) - yy / (2.0 * lam * lam) + ww / (lam * lam * lam) + (bb - kk) / (2.0 * lam * lam) -
@@ -525,8 +524,8 @@ la_status launch_fill_i32(int32_t *p, int64_t count, int32_t v, hipStream_t st)
     template la_status launch_mirror_lower<T>(View<T>, int64_t, int, hipStream_t);                              \
     template la_status launch_sumlogdiag<T>(const T *, T *, int64_t, int, hipStream_t);                         \
     template la_status launch_partial_sums<T>(const SumList<T> &, int, double *, hipStream_t); \
-    template la_status launch_sgp_inner<T>(T *, T *, int, hipStream_t);                                         \
-    template la_status launch_add_diag<T>(T *, int, T, hipStream_t);                                            \
+    template la_status launch_sgp_inner<T>(T *, T *, const T *, T, T *, int, hipStream_t);                      \
+    template la_status launch_plus_identity<T>(const T *, T *, int, hipStream_t);                               \
     template la_status launch_rank1_add<T>(T *, const T *, const T *, int, int, hipStream_t);                   \
     template la_status launch_sgp_scalars<T>(const double *, double, int, T *, T *, T *, int, hipStream_t); \
     template la_status launch_gp_glue<T>(const T *, const T *, const T *, const T *, T *, T *, int64_t, int,    \

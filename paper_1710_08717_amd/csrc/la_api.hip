@@ -443,6 +443,49 @@ static la_status potrf_t(int lower, int64_t batch, int n, const void *A, void *L
     return potrf_rec<T>(sc[1], Lv, info, 0, batch, n, sc[0], sc[2], false, st);
 }
 
+// Edge of the diagonal blocks of a solve with m vectors that get an explicit inverse; block
+// substitution above it.  A merge level of the inverse costs n b^2 multiply-adds per matrix whatever the
+// number of vectors, a substitution step three short launches: with few vectors the merges stop paying
+// early.  Measured (fp64, us; edge 256 / 512 / 1024): 32 x 512, 64 vectors 93 / 118 / 118; 8 x 1024, 64:
+// 112 / 118 / 166; 4 x 2048, 128: 223 / 196 / 234; 1 x 4096, 512: 548 / 431 / 396.
+static inline int solve_block(int m)
+{
+    int b = 256;
+    while (b < 1024 && b < 4 * m)
+        b *= 2;
+    return b;
+}
+
+// X <- Lam^-1 X (fwd) or Lam^-T X by blocks of `edge` rows, whose explicit inverses Inv holds.  S: a panel
+// that takes one block's solution (a product cannot overwrite its own operand across several tiles).
+template <typename T>
+static la_status block_substitution(bool fwd, int64_t batch, int n, int m, int edge, View<const T> Lam, View<const T> Inv,
+                                    View<T> X, View<T> S, hipStream_t st)
+{
+    GemmOpts o;
+    o.triA = fwd ? 1 : 2;
+    o.reverse = fwd ? 1 : 0;
+    const int nblk = (n + edge - 1) / edge;
+    GemmOpts plain;
+    for (int step = 0; step < nblk; ++step) {
+        const int j = fwd ? step : nblk - 1 - step;
+        const int64_t o0 = (int64_t)j * edge;
+        const int nbj = (int)((n - o0) < edge ? (n - o0) : edge);
+        View<const T> Ij = Inv.sub(o0, o0);
+        View<T> Xj = X.sub(o0, 0);
+        LA_TRY(launch_gemm<T>(fwd ? Ij : Ij.t(), cv(Xj), S, batch, nbj, m, nbj, T(1), T(0), o, st));
+        if (fwd && o0 + nbj < n) {  // rows below: X -= Lam[below, j] S
+            const int rest = (int)(n - o0 - nbj);
+            LA_TRY(launch_gemm<T>(Lam.sub(o0 + nbj, o0), cv(S), X.sub(o0 + nbj, 0), batch, rest, m, nbj, T(-1), T(1),
+                                  plain, st));
+        } else if (!fwd && o0 > 0) {  // rows above: X -= Lam[j, above]^T S
+            LA_TRY(launch_gemm<T>(Lam.sub(o0, 0).t(), cv(S), X, batch, (int)o0, m, nbj, T(-1), T(1), plain, st));
+        }
+        LA_TRY(launch_copy<T>(cv(S), Xj, batch, nbj, m, T(1), 0, st));
+    }
+    return LA_OK;
+}
+
 // trsm / trmm (section 4.2).  vectors: columns of A/B (left) or rows (right); X(e, v) = element e
 // of vector v, so that every case is "apply Lam, Lam^T or one of their inverses to vectors".
 //   trmm: one GEMM with the triangular operand masked.
@@ -520,14 +563,7 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
     View<T> S = X.rs <= X.cs ? View<T>{base + (solve ? 2 * batch * nn : 0), nm, 1, n}
                              : View<T>{base + (solve ? 2 * batch * nn : 0), nm, m, 1};
 
-    // Edge of the diagonal blocks that get an explicit inverse; block substitution above it.  A merge
-    // level of the inverse costs n b^2 multiply-adds per matrix whatever the number of vectors, a
-    // substitution step three short launches: with few vectors the merges stop paying early.
-    // Measured (fp64, us; edge 256 / 512 / 1024): 32 x 512, 64 vectors 93 / 118 / 118; 8 x 1024, 64:
-    // 112 / 118 / 166; 4 x 2048, 128: 223 / 196 / 234; 1 x 4096, 512: 548 / 431 / 396.
-    int NBI = 256;
-    while (NBI < 1024 && NBI < 4 * m)
-        NBI *= 2;
+    const int NBI = solve_block(m);
     if (!solve || n <= NBI) {
         View<const T> M = Lam;
         if (solve) {
@@ -545,25 +581,7 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
     LA_TRY(inverse_build<T>(Lam, Inv, Tmp, batch, n, NBI, st));
     if (!inplace || alpha != T(1))
         LA_TRY(launch_copy<T>(Xin, X, batch, n, m, alpha, 0, st));
-    const int nblk = (n + NBI - 1) / NBI;
-    GemmOpts plain;
-    for (int step = 0; step < nblk; ++step) {
-        const int j = fwd ? step : nblk - 1 - step;
-        const int64_t o0 = (int64_t)j * NBI;
-        const int nbj = (int)((n - o0) < NBI ? (n - o0) : NBI);
-        View<const T> Ij = cv(Inv).sub(o0, o0);
-        View<T> Xj = X.sub(o0, 0);
-        LA_TRY(launch_gemm<T>(fwd ? Ij : Ij.t(), cv(Xj), S, batch, nbj, m, nbj, T(1), T(0), o, st));
-        if (fwd && o0 + nbj < n) {  // rows below: X -= Lam[below, j] S
-            const int rest = (int)(n - o0 - nbj);
-            LA_TRY(launch_gemm<T>(Lam.sub(o0 + nbj, o0), cv(S), X.sub(o0 + nbj, 0), batch, rest, m, nbj, T(-1), T(1),
-                                  plain, st));
-        } else if (!fwd && o0 > 0) {  // rows above: X -= Lam[j, above]^T S
-            LA_TRY(launch_gemm<T>(Lam.sub(o0, 0).t(), cv(S), X, batch, (int)o0, m, nbj, T(-1), T(1), plain, st));
-        }
-        LA_TRY(launch_copy<T>(cv(S), Xj, batch, nbj, m, T(1), 0, st));
-    }
-    return LA_OK;
+    return block_substitution<T>(fwd, batch, n, m, NBI, Lam, cv(Inv), X, S, st);
 }
 
 template <typename T>
@@ -827,12 +845,20 @@ static la_status gemm2_backward_t(int ta, int tb, double alpha, int64_t batch, i
 
 // ---------------------------------------------------------------------------------
 // Variational sparse Gaussian-process criterion (section 3.2) and its gradient through two Cholesky
-// factors of U x U matrices -- the evaluation that makes the criterion cost O(n U^2) -- as a chain of
-// the operators above; the gradient is the reverse sweep over that chain with the operators' backward
-// rules (section 4.2), the two places where gradients meet written out.  One problem per call.  The
-// caller's workspace holds
-//   Lu (U^2), B (U n), A (U^2), La (U^2), La_bar -> A_bar (U^2), v, w, v_bar (U each), one scalar,
-// then 7 x SGP_PARTIALS fp64 partial sums.
+// factors of U x U matrices -- the evaluation that makes the criterion cost O(n U^2).  One problem per
+// call.  With E = B B^T / lam, A = I + E = La La^T and a = A^-1 B y the reverse sweep over the operators'
+// backward rules (section 4.2) comes to
+//   A_bar   = 1/2 (A^-1 + a a^T / lam^2),     v_bar = -a / lam^2,
+//   B_bar   = (2 / lam) (A_bar - I / 2) B + v_bar y^T,
+//   Kuf_bar = Lu^-T B_bar,     Kuu_bar = 1/2 Lu^-T Q Lu^-1,     Q = -B_bar B^T.
+// Q needs no product over the n columns: with B B^T = lam E and v = B y it is E + A^-1 - I + a a^T / lam^2,
+// and E + A^-1 - I = E A^-1 E = S^T S with S = La^-1 E.  Only the last form is accurate for every noise: the sum
+// before it is a difference of terms of order one where E is small, and its relative error grows with 1 / E^2
+// (fp32, U = n = 100, noise 1000 against a signal of 1: 8e-2 in Kuu_bar, from S 2e-6).
+//
+// The caller's workspace holds Lu (U^2), B (U n), E (U^2), A -> La -> Q (U^2), A_bar (U^2), v -> a, w, v_bar (U each),
+// one scalar, then SGP_SUMS x SGP_PARTIALS fp64 partial sums; what follows (the inverse of Lu, scratch of the
+// steps, B_bar) comes from the arena behind it.
 // ---------------------------------------------------------------------------------
 template <typename T>
 static size_t sgp_workspace_elems(int U, int n)
@@ -846,71 +872,90 @@ static la_status sgp_t(int U, int n, const void *Kuu_, const void *Kuf_, const v
                        void *ws, hipStream_t st)
 {
     const int64_t uu = (int64_t)U * U, un = (int64_t)U * n;
-    T *Lu = (T *)ws, *B = Lu + uu, *A = B + un, *La = A + uu, *Ab = La + uu, *v = Ab + uu, *w = v + U, *vb = w + U,
+    T *Lu = (T *)ws, *B = Lu + uu, *E = B + un, *La = E + uu, *Ab = La + uu, *v = Ab + uu, *w = v + U, *vb = w + U,
       *dummy = vb + U;
     double *sums = reinterpret_cast<double *>(((uintptr_t)(dummy + 16) + 7) & ~(uintptr_t)7);
     const T *Kuf = (const T *)Kuf_, *y = (const T *)y_, *Kff = (const T *)Kff_;
     T *Kuf_bar = (T *)Kuf_bar_, *Kuu_bar = (T *)Kuu_bar_, *y_bar = (T *)y_bar_;
+    const T r1 = (T)(1.0 / (lam * lam));
     auto square = [&](T *p) { return View<T>{p, uu, U, 1}; };
     auto wide = [&](T *p) { return View<T>{p, un, n, 1}; };
-    GemmOpts plain, low, upp;
+    GemmOpts plain, low, upp, below;
     low.triA = 1;
     low.reverse = 1;
     upp.triA = 2;
+    below.maskC = 1;
+    // The two solves with Lu and n vectors in the form the operator has for these sizes: where that takes explicit inverses of
+    // large blocks (or of the whole) they share the inverse that Kuu_bar needs, where it is a finer substitution they call
+    // it.  The whole inverse everywhere is faster but less accurate: U = 333, n = 7777, fp64 796 -> 639 us; U = 500, n = 1000,
+    // fp32, 1e-3 on Kuu's diagonal 2.3e-5 -> 2.1e-4 in Kuf_bar at noise 10.
+    const int edge = solve_block(n);
+    const bool fine = U <= 2 * NB ? n <= 48 : trsm_stream_takes<T>(1, U, n);
+
+    ArenaFrame outer;
+    View<T> Liu;
+    auto solve_u = [&](bool fwd, const T *src, T *dst) -> la_status {  // dst = Lu^-1 src or Lu^-T src
+        if (fine)
+            return tri_apply_t<T>(true, 1, !fwd, 0, 1.0, 1, U, n, Lu, src, dst, st);
+        const View<const T> in{src, un, n, 1};
+        if (U <= edge)
+            return launch_gemm<T>(fwd ? cv(Liu) : cv(Liu).t(), in, wide(dst), 1, U, n, U, T(1), T(0), fwd ? low : upp, st);
+        ArenaFrame frame;
+        void *p = nullptr;
+        LA_TRY(arena_take((size_t)edge * n * sizeof(T), &p));
+        LA_TRY(launch_copy<T>(in, wide(dst), 1, U, n, T(1), 0, st));
+        return block_substitution<T>(fwd, 1, U, n, edge, cv(square(Lu)), cv(Liu), wide(dst),
+                                     View<T>{(T *)p, (int64_t)edge * n, n, 1}, st);
+    };
 
     // ---- forward ----------------------------------------------------------------------------
-    // Lu^-1 is applied to n vectors twice and La^-1 is half of A_bar: both are inverted once, explicitly
-    LA_TRY(potrf_t<T>(1, 1, U, Kuu_, Ab, nullptr, st));                                        // Lu (in Ab's buffer)
-    View<T> Liu = square(Lu);
+    LA_TRY(potrf_t<T>(1, 1, U, Kuu_, Lu, nullptr, st));                                        // Lu
+    LA_TRY(scratch_views<T>(1, U, 1, &Liu));
     {
         ArenaFrame frame;
         View<T> Tmp;
         LA_TRY(scratch_views<T>(1, U, 1, &Tmp));
-        LA_TRY(inverse_build<T>(cv(square(Ab)), Liu, Tmp, 1, U, U, st));                       // Lu^-1
+        LA_TRY(inverse_build<T>(cv(square(Lu)), Liu, Tmp, 1, U, U, st));                       // Lu^-1
     }
-    LA_TRY(launch_gemm<T>(cv(Liu), View<const T>{Kuf, un, n, 1}, wide(B), 1, U, n, U, T(1), T(0), low, st));  // B = Lu^-1 Kuf
-    LA_TRY(syrk_t<T>(0, 1.0 / lam, 1, U, n, B, A, st));                                        // A = B B^T / lam ...
-    LA_TRY(launch_add_diag<T>(A, U, T(1), st));                                                //     ... + I
-    LA_TRY(potrf_t<T>(1, 1, U, A, La, nullptr, st));                                           // La
+    LA_TRY(solve_u(true, Kuf, B));                                                             // B = Lu^-1 Kuf
+    LA_TRY(syrk_t<T>(0, 1.0 / lam, 1, U, n, B, E, st));                                        // E = B B^T / lam
+    LA_TRY(launch_plus_identity<T>(E, La, U, st));
+    LA_TRY(potrf_t<T>(1, 1, U, La, La, nullptr, st));                                          // La
     LA_TRY(gemm2_t<T>(0, 0, 1.0, 1, U, 1, n, B, y, v, st));                                    // v = B y
+    LA_TRY(tri_apply_t<T>(true, 1, 0, 0, 1.0, 1, U, 1, La, v, w, st));                         // w = La^-1 v
+    // ---- backward ---------------------------------------------------------------------------
+    LA_TRY(tri_apply_t<T>(true, 1, 1, 0, 1.0, 1, U, 1, La, w, v, st));                         // a = La^-T w (in v's buffer)
+    const T *a = v;
     {
         ArenaFrame frame;
         View<T> sc[2];
         LA_TRY(scratch_views<T>(1, U, 2, sc));
         LA_TRY(inverse_build<T>(cv(square(La)), sc[0], sc[1], 1, U, U, st));
         const View<const T> Lia = cv(sc[0]);
-        LA_TRY(inverse_apply1<T>(Lia, false, T(1), v, w, 1, U, st));                           // w = La^-1 v
-        // ---- backward -----------------------------------------------------------------------
-        // w_bar = -w / lam^2:  v_bar = La^-T w_bar;  La_bar = -tril(v_bar w^T) + diag(1 / La_ii), and as in the GP
-        // criterion (there with alpha in the place of -lam^2 v_bar) A_bar = 1/2 (A^-1 + lam^2 v_bar v_bar^T)
-        LA_TRY(inverse_apply1<T>(Lia, true, (T)(-1.0 / (lam * lam)), w, vb, 1, U, st));
-        LA_TRY(launch_gp_glue<T>(La, w, nullptr, vb, dummy, Ab, 1, U, st, (T)(0.5 * lam * lam)));
+        LA_TRY(launch_gp_glue<T>(La, w, nullptr, a, dummy, Ab, 1, U, st, T(0.5) * r1));
         LA_TRY(gram_add<T>(Lia, T(0.5), square(Ab), T(1), 1, U, st));                          // A_bar (symmetric)
+        const SumList<T> all{{{0, y, nullptr, n, 0}, {0, w, nullptr, U, 0}, {0, B, nullptr, un, 0}, {1, Kff, nullptr, n, 0},
+                              {3, La, nullptr, U, U}, {2, Ab, E, uu, 0}}};
+        LA_TRY(launch_partial_sums<T>(all, SGP_SUMS, sums, st));
+        LA_TRY(launch_sgp_scalars<T>(sums, lam, n, (T *)phi_, (T *)lam_bar_, (T *)Kff_bar_, n, st));
+        LA_TRY(launch_gemm<T>(Lia, View<const T>{E, uu, U, 1}, sc[1], 1, U, U, U, T(1), T(0), low, st));  // S = La^-1 E
+        LA_TRY(launch_gemm<T>(cv(sc[1]).t(), cv(sc[1]), square(La), 1, U, U, U, T(1), T(0), below, st));  // S^T S
     }
-    const SumList<T> all{{{0, y, nullptr, n, 0}, {0, w, nullptr, U, 0}, {0, B, nullptr, un, 0}, {1, Kff, nullptr, n, 0},
-                          {4, La, nullptr, U, U}, {2, Ab, A, uu, 0}, {3, Ab, nullptr, U, U}}};
-    LA_TRY(launch_partial_sums<T>(all, SGP_SUMS, sums, st));
-    LA_TRY(launch_sgp_scalars<T>(sums, lam, n, (T *)phi_, (T *)lam_bar_, (T *)Kff_bar_, n, st));
-    // B_bar = (2 / lam) A_bar B - B / lam + v_bar y^T.  Lu_bar = -tril(Lu^-T B_bar B^T) enters the gradient as
-    // Phi(Lu^T Lu_bar) = -Phi(B_bar B^T), and with B B^T = lam (A - I), v = B y that product is
-    //   B_bar B^T = (2 A_bar - I)(A - I) + v_bar v^T = 2 I - A - 2 A_bar,
-    // so neither the product over the n columns nor the one with Lu is needed:
-    //   Kuu_bar = 1/2 Lu^-T (A + 2 A_bar - 2 I) Lu^-1.
-    LA_TRY(launch_sgp_inner<T>(A, Ab, U, st));                      // A <- Phi(A + 2 A_bar - 2 I),  Ab <- A_bar - I / 2
+    LA_TRY(launch_sgp_inner<T>(La, Ab, a, r1, vb, U, st));  // La <- Phi(Q),  Ab <- A_bar - I / 2,  v_bar
     {
         ArenaFrame frame;
         void *p = nullptr;
         LA_TRY(arena_take((size_t)un * sizeof(T), &p));
         const View<T> Bb = wide((T *)p);
         LA_TRY(launch_gemm<T>(cv(square(Ab)), cv(wide(B)), Bb, 1, U, n, U, (T)(2.0 / lam), T(0), plain, st));
-        LA_TRY(launch_rank1_add<T>(Bb.p, vb, y, U, n, st));
-        LA_TRY(launch_gemm<T>(cv(Liu).t(), cv(Bb), wide(Kuf_bar), 1, U, n, U, T(1), T(0), upp, st));  // Kuf_bar = Lu^-T B_bar
+        LA_TRY(launch_rank1_add<T>(Bb.p, vb, y, U, n, st));                                    // B_bar
+        LA_TRY(solve_u(false, Bb.p, Kuf_bar));                                                 // Kuf_bar = Lu^-T B_bar
     }
     // y_bar = B^T v_bar + y / lam
     View<T> yb{y_bar, n, 1, 1};
     LA_TRY(launch_copy<T>(View<const T>{y, n, 1, 1}, yb, 1, n, 1, (T)(1.0 / lam), 0, st));
     LA_TRY(launch_gemm<T>(View<const T>{B, un, 1, n}, View<const T>{vb, U, 1, 1}, yb, 1, n, 1, U, T(1), T(1), plain, st));
-    return congruence<T>(cv(Liu), cv(square(A)), square(La), square(Kuu_bar), 1, U, st);
+    return congruence<T>(cv(Liu), cv(square(La)), square(E), square(Kuu_bar), 1, U, st);
 }
 
 template <typename T>
@@ -1546,7 +1591,7 @@ size_t la_sgp_workspace_bytes(la_dtype dt, int U, int n)
     if (bad_dtype(dt) || U <= 0 || n <= 0 || U > MAX_N || n > MAX_N)
         return 0;
     const size_t e = dt == LA_F32 ? sgp_workspace_elems<float>(U, n) : sgp_workspace_elems<double>(U, n);
-    const size_t fixed = align256(e * esize(dt) + 8 + 7 * SGP_PARTIALS * sizeof(double));
+    const size_t fixed = align256(e * esize(dt) + 8 + SGP_SUMS * SGP_PARTIALS * sizeof(double));
     void *p[10];
     for (int i = 0; i < 10; ++i)
         p[i] = fake_operand(i);
@@ -1572,7 +1617,7 @@ la_status la_sgp_criterion(la_dtype dt, int U, int n, const void *Kuu, const voi
         !workspace || ((uintptr_t)workspace & 255))
         return LA_ERR_INVALID_ARG;
     const size_t e = dt == LA_F32 ? sgp_workspace_elems<float>(U, n) : sgp_workspace_elems<double>(U, n);
-    const size_t fixed = align256(e * esize(dt) + 8 + 7 * SGP_PARTIALS * sizeof(double));
+    const size_t fixed = align256(e * esize(dt) + 8 + SGP_SUMS * SGP_PARTIALS * sizeof(double));
     if (workspace_bytes < fixed) {
         snprintf(g_err, sizeof(g_err), "this call needs a workspace of la_sgp_workspace_bytes bytes, %zu given",
                  workspace_bytes);

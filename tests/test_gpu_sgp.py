@@ -122,3 +122,68 @@ def test_sgp_gradient_against_80_bit(la):
     for name, ref in zip(("Kuu_bar", "Kuf_bar", "y_bar"), _long_double_gradient(K, F, y, np.float64(0.1))):
         d = out[name].cpu().numpy().astype(np.longdouble) - ref
         assert float(np.sqrt((d * d).sum() / (ref * ref).sum())) <= 4e-13, name
+
+
+@pytest.mark.parametrize("U,n,noise,signal,jitter", [
+    (1, 3, 100.0, 1.0, 0.1), (7, 20, 1000.0, 1.0, 0.1), (100, 100, 10.0, 1.0, 0.1), (100, 100, 100.0, 1.0, 0.1),
+    (100, 100, 1000.0, 1.0, 0.1), (60, 200, 1e4, 1.0, 0.1), (100, 213, 1.0, 0.01, 0.1),
+    (200, 40, 10.0, 1.0, 1e-3), (140, 300, 10.0, 1.0, 1e-3), (140, 20, 0.1, 1.0, 1e-3), (100, 30, 10.0, 1.0, 1e-3)])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_sgp_gradient_away_from_small_noise(la, dtype, U, n, noise, signal, jitter):
+    """The gradient where the noise is large against the signal (the inner matrix of Kuu_bar is of second order in
+    E = B B^T / noise there) and on an ill-conditioned Kuu.  First-order bounds, in units of eps, with k = cond(Kuu):
+    Kuu_bar sqrt(k) from the substitutions on either side (an error of the columns, which is far below k), and what A_bar - I / 2
+    loses to I / 2 in Kuf_bar, 1 / |E| with E's root mean square eigenvalue.  The factor of 16 covers the
+    accumulation over up to 300 terms; the explicit inverse of Lu in place of a substitution, and the inner matrix as a
+    difference of terms of order one, are outside by 2 to 10 and by up to 1e4."""
+    import torch
+
+    g = np.random.default_rng(11)
+    Z, X = g.uniform(-2, 2, (U, 4)), g.uniform(-2, 2, (n, 4))
+    rbf = lambda P, Q: np.exp(-0.5 * ((P[:, None] - Q[None]) ** 2).sum(-1))
+    dt = np.float32 if dtype == "f32" else np.float64
+    K = (signal * (rbf(Z, Z) + jitter * np.eye(U))).astype(dt)
+    F = (signal * rbf(Z, X)).astype(dt)
+    y = (np.sqrt(signal) * np.sin(X.sum(1)) + 0.3 * g.standard_normal(n)).astype(dt)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    out = la.sgp_criterion(dev(K), dev(F), dev(np.ones(n, dtype=dt)), dev(y), noise)
+    ref = _long_double_gradient(K, F, y, np.float64(noise))
+    K64, F64 = K.astype(np.float64), F.astype(np.float64)
+    E = np.linalg.svd(np.linalg.solve(np.linalg.cholesky(K64), F64), compute_uv=False) ** 2 / noise
+    spread = np.sqrt((E ** 2).sum() / U)
+    eps, root = np.finfo(dt).eps, np.sqrt(np.linalg.cond(K64))
+    bounds = {"Kuu_bar": 16 * root, "Kuf_bar": 16 * (root + 1 / spread), "y_bar": 16 * root}
+    for name, r in zip(("Kuu_bar", "Kuf_bar", "y_bar"), ref):
+        d = out[name].cpu().numpy().astype(np.longdouble) - r
+        err = float(np.sqrt((d * d).sum() / (r * r).sum())) / eps
+        sys.stderr.write(f"{name} {err:.1f} of {bounds[name]:.1f} eps\n")
+        assert err <= bounds[name], name
+
+
+def test_sgp_huge_noise_stays_finite(la):
+    """noise^2 beyond the range of fp32 (noise itself within it): everything is the noise's own part."""
+    import torch
+
+    w = workloads.make_sgp(20, 50, dtype="f32")
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    out = la.sgp_criterion(dev(w["Kuu"]), dev(w["Kuf"]), dev(w["Kff_diag"]), dev(w["y"]), 1e25)
+    assert all(bool(torch.isfinite(v).all()) for v in out.values())
+    assert rel(out["y_bar"].cpu().numpy(), w["y"].astype(np.float64) / 1e25) <= 1e-6
+    assert rel(out["Kff_diag_bar"].cpu().numpy(), np.full(50, 0.5e-25)) <= 1e-6
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("U,n", [(1061, 270), (1027, 300), (530, 45), (513, 70), (129, 8195), (128, 49), (128, 48)])
+def test_sgp_forms_of_the_solve(la, orc, dtype, U, n):
+    """Both solves with Lu in blocks of 256 and 1024 rows with a ragged last one, and the sizes next to the limits
+    between the substitutions and the inverse."""
+    import torch
+
+    w = workloads.make_sgp(U, n, dtype=dtype, jitter=0.3)
+    ref = orc.sgp_criterion(w["Kuu"], w["Kuf"], w["Kff_diag"], w["y"], w["noise_var"]) if n < 5000 else None
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    out = la.sgp_criterion(dev(w["Kuu"]), dev(w["Kuf"]), dev(w["Kff_diag"]), dev(w["y"]), w["noise_var"])
+    if ref is None:  # (the oracle's dense n x n form is out of reach)
+        ref = dict(zip(("Kuu_bar", "Kuf_bar", "y_bar"), _long_double_gradient(w["Kuu"], w["Kuf"], w["y"], np.float64(0.1))))
+    for key in ("Kuu_bar", "Kuf_bar", "y_bar"):
+        assert rel(out[key].cpu().numpy(), np.asarray(ref[key], dtype=np.float64)) <= TOL[dtype], key
