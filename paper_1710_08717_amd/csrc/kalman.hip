@@ -390,10 +390,14 @@ static la_status launch_kalman_d(const KfArgs<T> &a, hipStream_t st)
 //   CL(F^T A^T) = CL(F) . RL(A)                       RL(S_hh) = RL(A) . CL(F^T A^T) + CL(S_h^T)
 //   CL(M) = RL(S_hh) . RL(B),  M = S_hh B^T           CL(M^T) = RL(B) . RL(S_hh)
 //   CL(S_vv) = RL(B) . CL(M) + CL(S_v)                S_vv = L L^T, L^-1: registers, by way of LDS
-//   CL(X) = RL(L^-1) . CL(M^T)                        RL(K) = CL(L^-1) . CL(X),  K = X^T L^-1
+//   CL(X) = RL(L^-1) . CL(M^T)                        RL(K) = CL(L^-1) . CL(X),  K = X^T L^-1   (d_v <= d_h)
 //   RL(G) = CL(B) . RL(-K) + 1,  G = 1 - K B          CL(W) = RL(S_hh) . RL(G),  W = S_hh G^T
 //   CL(F) = RL(G) . CL(W) + RL(K) . (RL(S_v) . RL(K))
-// and per 16 sequences (means and innovations as the columns of a tile)
+// For d_v > d_h S_vv is factored column by column and the gain substituted row by row instead: B S_hh B^T is a thin product there,
+// and with little noise the explicit L^-1 (and pivots that are not scaled by their square roots) made K, hence F, up to 16
+// times less accurate (fp32, d_h = 2, d_v = 16, S_v = 1e-4); for d_v <= d_h both are equally accurate.  It costs 0.9 us a
+// step: 4096 sequences x 24 steps, d_h = 4, d_v = 16, fp32 45 -> 66 us, fp64 71 -> 95 (one recursion per sequence: 158, 165).
+// And per 16 sequences (means and innovations as the columns of a tile)
 //   mu = A f,  d = v - B mu,  f = mu + K d,  z = L^-1 d.
 //
 // Bound by writing F for large batches, by the serial covariance step for small ones.
@@ -480,7 +484,60 @@ __device__ __forceinline__ void ks_store(T *p, int n, int lane, typename Mfma<T>
             p[Mfma<T>::row(lane, s)] = v[s];
 }
 
+// Row r of K = M S^-1 in place of row r of M by way of S = L L^T, S and L one row per lane (the four lane rows hold copies);
+// rows and columns from dv on are those of the identity.  Also gives L, and L_rr in lrr.  False: a pivot that is not > 0.
 template <typename T>
+__device__ __forceinline__ bool ks_factor_gain(T (&S)[16], T (&M)[16], T &lrr, int r, int dv)
+{
+    bool good = true;
+    const T one = T(1);
+    T invd = one;
+    lrr = one;
+    static_for<0, 4>([&](auto bc) {
+        constexpr int b0 = 4 * decltype(bc)::value;
+        if (b0 >= dv)
+            return;
+        kf_settle(S);
+        static_for<b0, b0 + 4>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            kf_settle1(S[k]);
+            const T d = mul_row<k>(S[k], one);
+            good = good && d > T(0);
+            const T rs = rsqrt_acc(d);
+            S[k] *= rs;
+            invd = r == k ? rs : invd;
+            lrr = r == k ? S[k] : lrr;
+            const T x = M[k] * rs;  // X L^T = M
+            M[k] = x;
+            kf_settle1(S[k]);
+            static_for<k + 1, 16>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                fnmac_row<j>(S[j], S[k], S[k]);  // S[r][j] -= L[r][k] L[j][k]
+                fnmac_row<j>(M[j], S[k], x);     // M[r][j] -= x L[j][k]
+            });
+        });
+    });
+    static_for<0, 4>([&](auto bc) {
+        constexpr int b0 = 12 - 4 * decltype(bc)::value;
+        if (b0 >= dv)
+            return;
+        kf_settle(S);
+        kf_settle1(invd);
+        static_for<0, 4>([&](auto tc) {  // K L = X
+            constexpr int j = b0 + 3 - decltype(tc)::value;
+            const T y = mul_row<j>(invd, M[j]);
+            M[j] = y;
+            static_for<0, j>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                fnmac_row<j>(M[i], S[i], y);  // M[r][i] -= y L[j][i]
+            });
+        });
+    });
+    return good;
+}
+
+// THIN: d_v > d_h
+template <typename T, bool THIN>
 __global__ __launch_bounds__(64 * (1 + KS_MAX_WORKERS), sizeof(T) == 4 ? 3 : 2) void k_kalman_shared(KfArgs<T> a, int per_worker)
 {
     using MF = Mfma<T>;
@@ -532,10 +589,24 @@ __global__ __launch_bounds__(64 * (1 + KS_MAX_WORKERS), sizeof(T) == 4 ? 3 : 2) 
                 for (int s = 0; s < 4; ++s)
                     sm.S[kk[s] * PS + r] = cS[s];
                 const acc_t cMT = ks_mul<T>(rB, rS, zero);
+                if constexpr (THIN) {  // (M's rows by way of K's place)
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        st.K[r * PS + kk[s]] = cMT[s];
+                }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-                T S[16], x[4];
+                T S[16], M[16], x[4];
                 kf_row(S, sm.S + r * PS);
-                if (diag_factor_invert<T, true>(S, x, r, g, dv) && bad == 0)
+                bool failed;
+                if constexpr (THIN) {
+                    T lrr;
+                    kf_row(M, st.K + r * PS);
+                    failed = !ks_factor_gain(S, M, lrr, r, dv);
+                    diag_invert<T>(S, lrr, x, r, g);
+                } else {
+                    failed = diag_factor_invert<T, true>(S, x, r, g, dv) != 0;
+                }
+                if (failed && bad == 0)
                     bad = t + 1;
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
@@ -544,9 +615,18 @@ __global__ __launch_bounds__(64 * (1 + KS_MAX_WORKERS), sizeof(T) == 4 ? 3 : 2) 
                 const acc_t rLi = ks_rl<T>(st.Li, lane), cLi = ks_cl<T>(st.Li, lane);
                 if (r < dv)
                     logdet -= (double)log(st.Li[r * PS + r]);
-                const acc_t cX = ks_mul<T>(rLi, cMT, zero);
-                const acc_t rK = ks_mul<T>(cLi, cX, zero);
-                acc_t nK;
+                acc_t rK, nK;
+                if constexpr (THIN) {
+                    if (g == 0) {
+#pragma unroll
+                        for (int j = 0; j < 16; ++j)
+                            st.K[r * PS + j] = M[j];
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+                    rK = ks_rl<T>(st.K, lane);
+                } else {
+                    rK = ks_mul<T>(cLi, ks_mul<T>(rLi, cMT, zero), zero);
+                }
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     nK[s] = -rK[s];
@@ -688,7 +768,10 @@ static la_status launch_kalman_shared(const KfArgs<T> &a, hipStream_t st)
     const int64_t per_wg = (int64_t)workers * per_worker, blocks = (a.batch + per_wg - 1) / per_wg;
     if (blocks > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
-    LA_LAUNCH((k_kalman_shared<T>), dim3((unsigned)blocks), dim3(64 * (1 + workers)), 0, st, a, per_worker);
+    if (a.dv > a.dh)
+        LA_LAUNCH((k_kalman_shared<T, true>), dim3((unsigned)blocks), dim3(64 * (1 + workers)), 0, st, a, per_worker);
+    else
+        LA_LAUNCH((k_kalman_shared<T, false>), dim3((unsigned)blocks), dim3(64 * (1 + workers)), 0, st, a, per_worker);
     return launch_check("kalman");
 }
 

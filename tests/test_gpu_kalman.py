@@ -150,3 +150,47 @@ def test_kalman_one_model_bad_pivot(la):
     for k in ("A", "B", "Sh", "Sv", "mu0", "S0"):
         rep[k] = np.repeat(w[k][None], 20, axis=0)
     assert np.array_equal(run(la, w)[3], run(la, rep)[3])
+
+
+def _filter_80_bit(w):
+    """Filtered means and covariances of one model over its sequences in 80-bit floats."""
+    ld = np.longdouble
+    A, B, Sh, Sv, mu, S, v = (w[k].astype(ld) for k in ("A", "B", "Sh", "Sv", "mu0", "S0", "v"))
+    f, fs, Fs, eye = np.repeat(mu[None], len(v), 0), [], [], np.eye(len(A), dtype=ld)
+    for t in range(v.shape[1]):
+        if t > 0:
+            f, S = f @ A.T, A @ F @ A.T + Sh
+        X, M = B @ S @ B.T + Sv, (S @ B.T).T  # K^T = X^-1 M by elimination
+        for k in range(len(X)):
+            m = X[k + 1:, k:k + 1] / X[k, k]
+            X[k + 1:], M[k + 1:] = X[k + 1:] - m * X[k], M[k + 1:] - m * M[k]
+        for k in reversed(range(len(X))):
+            M[k] = (M[k] - X[k, k + 1:] @ M[k + 1:]) / X[k, k]
+        K = M.T
+        f = f + (v[:, t] - f @ B.T) @ K.T
+        F = (eye - K @ B) @ S @ (eye - K @ B).T + K @ Sv @ K.T
+        fs.append(f)
+        Fs.append(F)
+    return np.stack(fs, 1), np.stack(Fs)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("dh,dv", [(1, 16), (2, 16), (4, 16), (8, 16), (4, 4), (13, 9), (3, 7), (12, 13)])
+def test_kalman_one_model_is_as_accurate_as_repeated_model(la, dtype, dh, dv):
+    """Little observation noise makes S_vv ill-conditioned.  The gain of the shared recursion then has to be as accurate as
+    the row-wise substitution of the per-sequence kernel: the mean error over ten models within 1.6 of its (two sums of
+    roundings of the same size, in another order); from an explicit inverse it is 2 to 16 times as large for dv > dh."""
+    errs = np.zeros((2, 2))
+    for seed in range(10):
+        w = workloads.make_kalman(12, 15, dh, dv, dtype=dtype, shared=True, seed=seed)
+        w["Sv"] = (w["Sv"] * 1e-4).astype(w["Sv"].dtype)
+        rep = dict(w)
+        for k in ("A", "B", "Sh", "Sv", "mu0", "S0"):
+            rep[k] = np.repeat(w[k][None], 12, axis=0)
+        rf, rF = _filter_80_bit(w)
+        for i, x in enumerate((w, rep)):
+            _, f, F, _ = run(la, x)
+            d, D = f.astype(np.longdouble) - rf, F[0].astype(np.longdouble) - rF
+            errs[i] += [float(np.sqrt((d * d).sum() / (rf * rf).sum())), float(np.sqrt((D * D).sum() / (rF * rF).sum()))]
+    sys.stderr.write(f"f {errs[0, 0] / errs[1, 0]:.2f} F {errs[0, 1] / errs[1, 1]:.2f}\n")
+    assert errs[0, 0] <= 1.6 * errs[1, 0] and errs[0, 1] <= 1.6 * errs[1, 1]
