@@ -39,7 +39,10 @@
  *    along a long inner dimension): la_workspace_bytes() says how many bytes a call
  *    takes, and the caller passes that much device memory to the entry point's _ws form.
  *    The plain form of an entry point is its _ws form without a workspace: it returns
- *    LA_ERR_WORKSPACE (and launches nothing) when the call needs one.
+ *    LA_ERR_WORKSPACE (and launches nothing) when the call needs one.  A product over a long
+ *    inner dimension whose sizes or addresses are off the 16-byte grid is split only where the
+ *    workspace has room for it: la_workspace_bytes() counts that room, but the call also runs
+ *    without it (slower).
  *    A workspace is device memory, 256-byte aligned, disjoint from every operand; its
  *    contents are undefined after the call; it may be reused by the next call on the
  *    same stream and must not be shared by calls that may run at the same time.
@@ -77,7 +80,7 @@ typedef enum {
     LA_OP_POTRI_BACKWARD = 11
 } la_op;
 
-/* Scratch memory, in bytes, that one call of operator `op` takes for these sizes (0: none).  The
+/* Scratch memory, in bytes, that one call of operator `op` uses for these sizes (0: none).  The
  * sizes carry the names they have in the operator's own signature: n for potrf, its backward,
  * potri and its backward; n and m for trsm / trmm and their backward rules; n and k for syrk and
  * its backward; m, n and k for gemm2 and its backward; the others are ignored.  The answer holds

@@ -64,6 +64,7 @@ struct Arena {
     char *base = nullptr;
     size_t cap = 0, used = 0, peak = 0;
     bool dry = false;
+    bool needed_only = false;  // (sizing) leave out what arena_room offers
 };
 Arena *&current_arena();
 inline bool dry_run()
@@ -73,6 +74,8 @@ inline bool dry_run()
 }
 // `bytes` of scratch (256-byte aligned) from the current call's workspace; LA_ERR_WORKSPACE if it is too small
 la_status arena_take(size_t bytes, void **out);
+// Is there room for `bytes` of scratch that the caller can do without?
+bool arena_room(size_t bytes);
 struct ArenaFrame {
     size_t mark;
     ArenaFrame() : mark(current_arena() ? current_arena()->used : 0) {}

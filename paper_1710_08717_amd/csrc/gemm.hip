@@ -743,7 +743,8 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             const int Kc = (((K + 15) / 16 + splits - 1) / splits) * 16;
             splits = (K + Kc - 1) / Kc;
             const size_t bytes = (size_t)batch * splits * M * N * sizeof(T);
-            if (splits >= 2 && bytes <= SPLITK_MAX_BYTES) {
+            // (an unaligned or odd-sized product goes without the split where the caller gave no memory for it)
+            if (splits >= 2 && bytes <= SPLITK_MAX_BYTES && (!f.rag || arena_room(bytes))) {
                 ArenaFrame frame;
                 void *buf = nullptr;
                 LA_TRY(arena_take(bytes, &buf));

@@ -52,6 +52,16 @@ la_status arena_take(size_t bytes, void **out)
     return LA_OK;
 }
 
+bool arena_room(size_t bytes)
+{
+    const Arena *a = current_arena();
+    if (!a)
+        return false;
+    if (a->dry)
+        return !a->needed_only;
+    return a->used + ((bytes + 255) & ~(size_t)255) <= a->cap;
+}
+
 template <typename T>
 static la_status scratch_views(int64_t batch, int n, int count, View<T> *out)
 {
@@ -987,13 +997,16 @@ static la_status gp_t(int64_t batch, int n, const void *A, const void *y, void *
 // ---------------------------------------------------------------------------------
 // Workspace handling of the entry points.  An operator body `op` (host code that enqueues the
 // kernels) runs twice: a sizing pass that launches nothing and records how much scratch the body
-// takes, then, if the caller's workspace holds that much, for real on that workspace.
+// cannot do without, then, if the caller's workspace holds that much, for real on that workspace.
+// What the body can also use (arena_room) is in the answer of la_workspace_bytes, but nothing is
+// refused for the lack of it.
 // ---------------------------------------------------------------------------------
 template <class F>
-static la_status sizing_pass(F &&op, size_t *peak)
+static la_status sizing_pass(F &&op, size_t *peak, bool needed_only = false)
 {
     Arena a;
     a.dry = true;
+    a.needed_only = needed_only;
     a.base = reinterpret_cast<char *>((uintptr_t)1 << 46);  // never dereferenced
     Arena *prev = current_arena();
     current_arena() = &a;
@@ -1007,7 +1020,7 @@ template <class F>
 static la_status with_workspace(void *ws, size_t ws_bytes, F &&op)
 {
     size_t need = 0;
-    LA_TRY(sizing_pass(op, &need));
+    LA_TRY(sizing_pass(op, &need, true));
     if (need > 0) {
         if (!ws || need > ws_bytes) {
             snprintf(g_err, sizeof(g_err), "this call needs a workspace of %zu bytes (la_workspace_bytes), %zu given", need,
@@ -1021,7 +1034,7 @@ static la_status with_workspace(void *ws, size_t ws_bytes, F &&op)
     }
     Arena a;
     a.base = (char *)ws;
-    a.cap = need > 0 ? ws_bytes : 0;
+    a.cap = ws && ((uintptr_t)ws & 255) == 0 ? ws_bytes : 0;
     Arena *prev = current_arena();
     current_arena() = &a;
     const la_status s = op();

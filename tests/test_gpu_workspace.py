@@ -202,3 +202,50 @@ def test_calls_with_a_workspace_can_be_captured_in_a_graph(la, batch, n, m, dtyp
         other = la.potrf(A[:, : n // 2, : n // 2].contiguous())
         torch.cuda.synchronize()
         assert torch.isfinite(other).all()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_products_of_odd_sizes_run_without_a_workspace(la, dtype):
+    """A long inner dimension is split over workgroups with scratch for the partial results; where sizes are odd the plain
+    entry points and a workspace with too little room do the same product in one piece."""
+    import torch
+
+    from paper_1710_08717_amd import binding
+
+    lib, vp = binding.load(), ctypes.c_void_p
+    dt, code = (torch.float64, 1) if dtype == "f64" else (torch.float32, 0)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    R = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=dt)
+    st = vp(torch.cuda.current_stream().cuda_stream)
+    p = lambda t: vp(t.data_ptr())
+    tol = {"f32": 2e-4, "f64": 1e-10}[dtype]
+    rel = lambda x, r: float((x.double() - r).norm() / r.norm())
+    small = torch.empty(512, dtype=torch.uint8, device="cuda")
+
+    A, B, C = R(35, 4099), R(4099, 45), R(35, 45)
+    ref = A.double() @ B.double()
+    need = la.workspace_bytes(binding.OP_GEMM2, A, 1, 45, 35, 4099)
+    assert need > 512
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    for w, wb in ((vp(0), 0), (p(small), 512), (p(ws), need)):
+        C.fill_(float("nan"))
+        assert lib.la_gemm2_batched_ws(code, 0, 0, 1.0, 1, 35, 45, 4099, p(A), p(B), p(C), w, wb, st) == 0
+        assert rel(C, ref) <= tol
+    assert lib.la_gemm2_batched(code, 0, 0, 1.0, 1, 35, 45, 4099, p(A), p(B), p(C), st) == 0
+    assert rel(C, ref) <= tol
+
+    X, S = R(45, 4099), R(45, 45)
+    assert lib.la_syrk_batched(code, 0, 1.0, 1, 45, 4099, p(X), p(S), st) == 0
+    assert rel(S, X.double() @ X.double().t()) <= tol
+
+    n, m = 129, 4099
+    L = torch.tril(R(n, n)) / n + 2 * torch.eye(n, device="cuda", dtype=dt)
+    Bm, G, Ab, Lb = R(n, m), R(n, m), R(n, m), R(n, n)
+    assert lib.la_trsm_backward(code, 1, 0, 0, 1.0, 1, n, m, p(L), p(Bm), p(G), p(Ab), p(Lb), st) == 0
+    Y = torch.linalg.solve_triangular(L.double().t(), G.double(), upper=True)
+    assert rel(Ab, Y) <= tol
+    assert rel(Lb, -torch.tril(Y @ Bm.double().t())) <= tol
+
+    # aligned sizes: the scratch is needed, as before
+    A, B, C = R(64, 4096), R(4096, 64), R(64, 64)
+    assert lib.la_gemm2_batched(code, 0, 0, 1.0, 1, 64, 64, 4096, p(A), p(B), p(C), st) == 4
