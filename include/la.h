@@ -32,8 +32,8 @@
  *    their workspaces differ.  Small problems (potrf and potri with n <= 128, backward with
  *    n <= 128 in fp32 and <= 96 in fp64, trsm with n <= 128 and at most 48 right-hand
  *    sides and with n <= 512 and at most 512 of them, every operator with n <= 32 on operands of at
- *    most 16 vectors / an inner dimension of at most 32, sumlogdiag, gp_glue, gp_criterion up to the
- *    same n as backward, kalman_filter) need no scratch memory; la_workspace_bytes() is the authority.  The blocked paths for larger
+ *    most 16 vectors / an inner dimension of at most 32, sumlogdiag, gp_glue, gp_criterion with n <= 128,
+ *    kalman_filter) need no scratch memory; la_workspace_bytes() is the authority.  The blocked paths for larger
  *    n do (explicit inverses of the factor or of its diagonal blocks, a working copy of
  *    the triangle being factored or one work panel, partial results of products split
  *    along a long inner dimension): la_workspace_bytes() says how many bytes a call
@@ -276,9 +276,9 @@ la_status la_gp_glue(la_dtype dt, int64_t batch, int n, const void *L, const voi
  *   Abar = d loss / d A = 1/2 (A^{-1} - alpha alpha^T), the potrf backward of
  *          Lbar = -tril(alpha z^T) + diag(1 / l_ii); written in full, exactly symmetric.
  * A, Abar: [batch, n, n]; y: [batch, n]; loss: [batch]; info: NULL or int32 [batch] as for potrf.
- * Abar may be the same buffer as A.  Up to n = 128 this is ONE kernel per call; beyond that it is
- * la_potrf_batched, two la_trsm_batched and the inverse of the factor times its transpose.  From
- * n = 129 (fp32) / 97 (fp64) on the call takes a `workspace` (device memory, 256-byte aligned, at least
+ * Abar may be the same buffer as A.  Up to n = 128 this is ONE kernel per call and needs no
+ * workspace; beyond that it is la_potrf_batched, the inverse of the factor, its products with y and z, and
+ * its product with its own transpose, on `workspace` (device memory, 256-byte aligned, at least
  * la_gp_workspace_bytes(dt, batch, n) bytes, not overlapping the other arguments). */
 size_t la_gp_workspace_bytes(la_dtype dt, int64_t batch, int n);
 la_status la_gp_criterion(la_dtype dt, int64_t batch, int n, const void *A, const void *y, void *loss, void *Abar,

@@ -968,11 +968,13 @@ static la_status sgp_t(int U, int n, const void *Kuu_, const void *Kuf_, const v
     return congruence<T>(cv(Liu), cv(square(La)), square(E), square(Kuu_bar), 1, U, st);
 }
 
+constexpr int GP_FUSED_N = 128;  // the sizes that launch_gp_leaf16 takes: one launch, no workspace
+
 template <typename T>
 static la_status gp_t(int64_t batch, int n, const void *A, const void *y, void *loss, void *Abar, int32_t *info,
                       void *workspace, hipStream_t st)
 {
-    if (n <= 2 * NB) {
+    if (n <= GP_FUSED_N) {
         if (info)
             LA_TRY(launch_fill_i32(info, batch, 0, st));
         return launch_gp_leaf16<T>(tri_view<const T>((const T *)A, n, 1), (const T *)y, (T *)loss,
@@ -1704,7 +1706,7 @@ la_status la_gp_glue(la_dtype dt, int64_t batch, int n, const void *L, const voi
                                                  (const double *)alpha, (double *)loss, (double *)Lbar, batch, n, st);
 }
 
-// fixed part of the GP criterion's workspace above the one-launch sizes: L, Lbar, z, alpha
+// fixed part of the GP criterion's workspace above the one-launch sizes: L, L^-1, z, alpha
 static size_t gp_fixed_bytes(la_dtype dt, int64_t batch, int n)
 {
     return align256(((size_t)batch * n * n * 2 + (size_t)batch * n * 2) * esize(dt));
@@ -1714,8 +1716,7 @@ size_t la_gp_workspace_bytes(la_dtype dt, int64_t batch, int n)
 {
     if (bad_dtype(dt) || batch <= 0 || n <= 0 || n > MAX_N)
         return 0;
-    const int fused = dt == LA_F32 ? backward_leaf16_max_n<float>() : backward_leaf16_max_n<double>();
-    if (n <= fused)
+    if (n <= GP_FUSED_N)
         return 0;
     size_t peak = 0;
     const la_status s = sizing_pass(
@@ -1743,8 +1744,7 @@ la_status la_gp_criterion(la_dtype dt, int64_t batch, int n, const void *A, cons
         return dt == LA_F32 ? launch_gp_glue<float>(nullptr, nullptr, nullptr, nullptr, (float *)loss, nullptr, batch, 0, st)
                             : launch_gp_glue<double>(nullptr, nullptr, nullptr, nullptr, (double *)loss, nullptr, batch, 0,
                                                      st);
-    const int fused = dt == LA_F32 ? backward_leaf16_max_n<float>() : backward_leaf16_max_n<double>();
-    const size_t fixed = n <= fused ? 0 : gp_fixed_bytes(dt, batch, n);
+    const size_t fixed = n <= GP_FUSED_N ? 0 : gp_fixed_bytes(dt, batch, n);
     const size_t bytes = (size_t)batch * n * n * esize(dt);
     if (fixed > 0) {
         if (!workspace || workspace_bytes < fixed) {

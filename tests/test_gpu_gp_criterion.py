@@ -118,3 +118,20 @@ def test_gp_criterion_reports_a_failing_pivot_and_bad_arguments(la):
     assert lib.la_gp_criterion(1, 2, 40, p, p, z, q, z, z, 0, z) == 1       # no loss buffer
     assert lib.la_gp_criterion(5, 2, 40, p, p, p, q, z, z, 0, z) == 1       # bad dtype
     assert lib.la_gp_criterion(1, 0, 40, z, z, z, z, z, z, 0, z) == 0       # empty batch
+
+
+@pytest.mark.parametrize("dtype,n", [("f64", 97), ("f64", 128), ("f32", 128)])
+def test_gp_criterion_in_one_launch_needs_no_workspace(la, orc, dtype, n):
+    import ctypes
+
+    import torch
+
+    lib, code = la.load(), 1 if dtype == "f64" else 0
+    assert lib.la_gp_workspace_bytes(code, 3, n) == 0 and lib.la_gp_workspace_bytes(code, 3, 129) > 0
+    A, y = kernel_inputs(3, n, dtype, 1.5, 0.3, seed=2)
+    a, yy = torch.from_numpy(A).cuda(), torch.from_numpy(y).cuda()
+    loss, G = torch.empty_like(yy[:, 0]).contiguous(), torch.empty_like(a)
+    p, z = (lambda t: ctypes.c_void_p(t.data_ptr())), ctypes.c_void_p(0)
+    assert lib.la_gp_criterion(code, 3, n, p(a), p(yy), p(loss), p(G), z, z, 0, torch.cuda.current_stream().cuda_stream) == 0
+    loss_r, G_r = oracle_chain(orc, A, y)
+    assert rel(G.cpu().numpy(), G_r) <= TOL[dtype] and rel(loss.cpu().numpy(), loss_r) <= TOL[dtype]
