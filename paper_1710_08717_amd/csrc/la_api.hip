@@ -777,13 +777,31 @@ static la_status gram_add(View<const T> Li, T alpha, View<T> C, T beta, int64_t 
     return launch_gemm<T>(Li.t(), Li, C, batch, n, n, n, alpha, beta, o, st);
 }
 
-// x = Li b or Li^T b for one vector per item, one pass over Li
+// dst = L^-1 src or L^-T src (m vectors, dst not src) where the whole inverse Li of L is at hand: the form that trsm has for
+// these sizes.  Where that takes explicit inverses, of the whole or of blocks on the diagonal, they are those of Li (the inverse of a
+// diagonal block is the diagonal block of the inverse); where it is a finer substitution it is called.
 template <typename T>
-static la_status inverse_apply1(View<const T> Li, bool trans, T alpha, const T *b, T *x, int64_t batch, int n, hipStream_t st)
+static la_status solve_beside_inverse(bool fwd, int64_t batch, int n, int m, const T *L, View<const T> Li, const T *src, T *dst,
+                                      hipStream_t st)
 {
-    GemmOpts o;
-    o.triA = trans ? 2 : 1;
-    return launch_gemm<T>(trans ? Li.t() : Li, View<const T>{b, n, 1, 1}, View<T>{x, n, 1, 1}, batch, n, 1, n, alpha, T(0), o, st);
+    const int64_t nm = (int64_t)n * m;
+    if (n <= 2 * NB ? m <= 48 : trsm_stream_takes<T>(batch, n, m))
+        return tri_apply_t<T>(true, 1, !fwd, 0, 1.0, batch, n, m, L, src, dst, st);
+    const View<const T> in{src, nm, m, 1};
+    const View<T> out{dst, nm, m, 1};
+    const int edge = solve_block(m);
+    if (n <= edge) {
+        GemmOpts o;
+        o.triA = fwd ? 1 : 2;
+        o.reverse = fwd ? 1 : 0;
+        return launch_gemm<T>(fwd ? Li : Li.t(), in, out, batch, n, m, n, T(1), T(0), o, st);
+    }
+    ArenaFrame frame;
+    void *p = nullptr;
+    LA_TRY(arena_take((size_t)batch * edge * m * sizeof(T), &p));
+    LA_TRY(launch_copy<T>(in, out, batch, n, m, T(1), 0, st));
+    return block_substitution<T>(fwd, batch, n, m, edge, tri_view<const T>(L, n, 1), Li, out,
+                                 View<T>{(T *)p, (int64_t)edge * m, m, 1}, st);
 }
 
 // potri (section 4.2 "potri"): A^-1 = Lam^-T Lam^-1 for A = Lam Lam^T (Lam = L, or R^T for an upper
@@ -890,32 +908,16 @@ static la_status sgp_t(int U, int n, const void *Kuu_, const void *Kuf_, const v
     const T r1 = (T)(1.0 / (lam * lam));
     auto square = [&](T *p) { return View<T>{p, uu, U, 1}; };
     auto wide = [&](T *p) { return View<T>{p, un, n, 1}; };
-    GemmOpts plain, low, upp, below;
+    GemmOpts plain, low, below;
     low.triA = 1;
     low.reverse = 1;
-    upp.triA = 2;
     below.maskC = 1;
-    // The two solves with Lu and n vectors in the form the operator has for these sizes: where that takes explicit inverses of
-    // large blocks (or of the whole) they share the inverse that Kuu_bar needs, where it is a finer substitution they call
-    // it.  The whole inverse everywhere is faster but less accurate: U = 333, n = 7777, fp64 796 -> 639 us; U = 500, n = 1000,
-    // fp32, 1e-3 on Kuu's diagonal 2.3e-5 -> 2.1e-4 in Kuf_bar at noise 10.
-    const int edge = solve_block(n);
-    const bool fine = U <= 2 * NB ? n <= 48 : trsm_stream_takes<T>(1, U, n);
-
     ArenaFrame outer;
     View<T> Liu;
-    auto solve_u = [&](bool fwd, const T *src, T *dst) -> la_status {  // dst = Lu^-1 src or Lu^-T src
-        if (fine)
-            return tri_apply_t<T>(true, 1, !fwd, 0, 1.0, 1, U, n, Lu, src, dst, st);
-        const View<const T> in{src, un, n, 1};
-        if (U <= edge)
-            return launch_gemm<T>(fwd ? cv(Liu) : cv(Liu).t(), in, wide(dst), 1, U, n, U, T(1), T(0), fwd ? low : upp, st);
-        ArenaFrame frame;
-        void *p = nullptr;
-        LA_TRY(arena_take((size_t)edge * n * sizeof(T), &p));
-        LA_TRY(launch_copy<T>(in, wide(dst), 1, U, n, T(1), 0, st));
-        return block_substitution<T>(fwd, 1, U, n, edge, cv(square(Lu)), cv(Liu), wide(dst),
-                                     View<T>{(T *)p, (int64_t)edge * n, n, 1}, st);
+    // Both solves with Lu and n vectors: the whole inverse everywhere is faster but less accurate (U = 333, n = 7777, fp64
+    // 796 -> 639 us; U = 500, n = 1000, fp32, 1e-3 on Kuu's diagonal 2.3e-5 -> 2.1e-4 in Kuf_bar at noise 10).
+    auto solve_u = [&](bool fwd, const T *src, T *dst) {  // dst = Lu^-1 src or Lu^-T src
+        return solve_beside_inverse<T>(fwd, 1, U, n, Lu, cv(Liu), src, dst, st);
     };
 
     // ---- forward ----------------------------------------------------------------------------
@@ -990,8 +992,8 @@ static la_status gp_t(int64_t batch, int n, const void *A, const void *y, void *
         LA_TRY(scratch_views<T>(batch, n, 1, &Tmp));
         LA_TRY(inverse_build<T>(tri_view<const T>(Lw, n, 1), Li, Tmp, batch, n, n, st));
     }
-    LA_TRY(inverse_apply1<T>(cv(Li), false, T(1), (const T *)y, z, batch, n, st));
-    LA_TRY(inverse_apply1<T>(cv(Li), true, T(1), z, al, batch, n, st));
+    LA_TRY(solve_beside_inverse<T>(true, batch, n, 1, Lw, cv(Li), (const T *)y, z, st));
+    LA_TRY(solve_beside_inverse<T>(false, batch, n, 1, Lw, cv(Li), z, al, st));
     LA_TRY(launch_gp_glue<T>(Lw, (const T *)y, nullptr, al, (T *)loss, (T *)Abar, batch, n, st));
     return gram_add<T>(cv(Li), T(0.5), tri_view<T>((T *)Abar, n, 1), T(1), batch, n, st);
 }

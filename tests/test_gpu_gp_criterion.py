@@ -135,3 +135,30 @@ def test_gp_criterion_in_one_launch_needs_no_workspace(la, orc, dtype, n):
     assert lib.la_gp_criterion(code, 3, n, p(a), p(yy), p(loss), p(G), z, z, 0, torch.cuda.current_stream().cuda_stream) == 0
     loss_r, G_r = oracle_chain(orc, A, y)
     assert rel(G.cpu().numpy(), G_r) <= TOL[dtype] and rel(loss.cpu().numpy(), loss_r) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("n,dim,noise,width", [(200, 2, 1e-4, 20.0), (333, 1, 1e-3, 100.0), (500, 1, 1e-3, 100.0),
+                                               (800, 2, 1e-3, 10.0), (800, 1, 1e-3, 100.0)])
+def test_gp_gradient_is_as_accurate_as_the_operators(la, n, dim, noise, width):
+    """Targets far above the noise: alpha alpha^T dominates the gradient, so alpha has to be what the solves with the factor
+    give, not products with its explicit inverse (1.15 to 1.3 times as far off).  Both sides share the factor and alpha's
+    rounding; the rest of the gradient is a tenth of it or less, hence 1.1 for the mean error over eight matrices."""
+    import torch
+
+    errs = np.zeros(2)
+    for seed in range(8):
+        rng = np.random.default_rng(1000 * n + seed)
+        P = rng.uniform(-width, width, (n, dim))
+        A = (np.exp(-0.5 * ((P[:, None] - P[None]) ** 2).sum(-1)) + noise * np.eye(n)).astype(np.float32)
+        y = (30 * np.sin(P.sum(1)) + np.sqrt(noise) * rng.standard_normal(n)).astype(np.float32)
+        Ai = np.linalg.inv(A.astype(np.float64))
+        al = np.linalg.solve(A.astype(np.float64), y.astype(np.float64))
+        ref = 0.5 * (Ai - np.outer(al, al))
+        a, yy = torch.from_numpy(A)[None].cuda(), torch.from_numpy(y)[None].cuda()
+        L = la.potrf(a)
+        z = la.trsm(L, yy[..., None].contiguous())
+        x = la.trsm(L, z, trans=True)
+        _, Lbar = la.gp_glue(L, yy, z[..., 0].contiguous(), x[..., 0].contiguous())
+        errs += [rel(la.gp_criterion(a, yy)[1][0].cpu().numpy(), ref), rel(la.potrf_backward(L, Lbar)[0].cpu().numpy(), ref)]
+    sys.stderr.write(f"criterion / operators {errs[0] / errs[1]:.3f}\n")
+    assert errs[0] <= 1.1 * errs[1]
