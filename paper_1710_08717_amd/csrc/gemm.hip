@@ -763,12 +763,16 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
                 return launch_check("splitk_reduce");
             }
         }
+        // No 128 x 128 tiles where they stick out of C by a quarter more than tiles of 64 do: 130 products of 129 x 129 x 129
+        // 79 -> 41 us in fp64, 40 -> 22 in fp32, 64 of 320 x 320 x 320 146 -> 90 and 75 -> 47, 300 times trmm of 131 with 131
+        // vectors 135 -> 68 and 73 -> 35; 383 x 383 (144 tiles against 180 quarters) is the same in both.
+        const bool padded = (int64_t)((M + 127) / 128) * ((N + 127) / 128) * 16 > (int64_t)((M + 63) / 64) * ((N + 63) / 64) * 5;
         int e;
         if (o.triA | o.triB) {
             // Triangular operands make the K range, hence the time, of a tile vary along the tile
             // list (heaviest first): the 512 workgroup slots only fill evenly if there are several
             // rounds of tiles, so take the largest tile that still gives 1024 workgroups.
-            e = wg128 >= 1024 ? 128 : ((wg64 >= 1024 || !k64 || o.min_tile64) ? 64 : 32);
+            e = wg128 >= 1024 && !padded ? 128 : ((wg64 >= 1024 || !k64 || o.min_tile64) ? 64 : 32);
         } else {
             // Equal tiles: big tiles once they fill the 512 workgroup slots (a compute unit with one workgroup waits for
             // its loads: a sparse GP with 300 tiles of 128 1497 -> 1429 us in 64 x 64 tiles, factor + gradient of
@@ -777,10 +781,15 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             // would fill the 512 workgroup slots less than twice -- with so few rounds the last one runs
             // part empty (32 x 384 x 384 lower triangle, K = 128: 672 tiles of 64, 38 -> 30 us; potrf of
             // 32 x 512 x 512 0.245 -> 0.231 ms, of 4 x 2048 x 2048 1.14 -> 1.10, 8192 x 8192 with 512
-            // vectors trsm 1.19 -> 1.12 ms).
+            // vectors trsm 1.19 -> 1.12 ms).  In fp64 nearly one big tile for each of the 256 compute units is as good as many
+            // rounds, unless k is contiguous in both operands (us, 64 x 64 -> 128 x 128: 2048^3 355 -> 326 and with both k
+            // contiguous 309 -> 338, 8192 x 512 x 1024 181 -> 167, 2304 x 1792 x 512, 252 tiles, 101 -> 88; 7168 x 512 x 1024, 224
+            // tiles, 163 -> 168, 2048 x 1536 x 1024, 192 tiles, 144 -> 167; a batch of 13 x 512^3, 208 tiles, 98 -> 88).
             const int64_t t128 = o.maskC ? wg128 : (int64_t)((M + 127) / 128) * ((N + 127) / 128) * batch;
             const bool big = o.maskC ? (M >= 2048 && N >= 2048) : (M >= 128 && N >= 128);
-            e = (t128 >= 512 && big) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64) ? 32 : 64);
+            const bool one_round = sizeof(T) == 8 && !f.rag && !(f.akf && f.bkf) && !o.maskC && t128 <= 256 &&
+                                   t128 > (batch > 1 ? 192 : 224);
+            e = ((t128 >= 512 || one_round) && big && !padded) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64) ? 32 : 64);
         }
         if (o.symsum && e == 128)  // (the form that stores both triangles has tiles up to 64 only)
             e = 64;

@@ -1,5 +1,5 @@
 """Products whose sizes and leading dimensions are no multiple of a vector or of a tile: the chunks that cross the
-end of an operand, in each operand layout, at the edges of the 16 / 32 / 64 / 128 tiles and of the K slabs."""
+end of an operand, in each operand layout, at the edges of the 16 / 32 / 64 tiles and of the K slabs, and in 128 x 128 tiles."""
 import numpy as np
 import pytest
 import torch
@@ -36,6 +36,36 @@ def test_gemm2_ragged(dt, b, m, n, k, ta, tb):
         ref = torch.matmul(a.mT.contiguous() if ta else a, bb.mT.contiguous() if tb else bb)
         err = (C.double().cpu() - ref).flatten(1).norm(dim=1) / ref.flatten(1).norm(dim=1)
         assert float(err.max()) <= TOL[dt], (off, float(err.max()))
+
+
+# (b, m, n, k): 128 x 128 tiles are taken from 512 of them on, if they stick out of C by less than a quarter more than tiles of
+# 64 do; in fp64, aligned and with k not contiguous in both operands, also for 225 to 256 of them (193 in a batch).
+BIG_TILES = [(130, 255, 253, 33), (130, 254, 255, 15), (64, 383, 381, 77), (33, 509, 511, 130), (13, 512, 512, 64),
+             (64, 256, 256, 16), (1, 1920, 1920, 32)]
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.float64], ids=["f32", "f64"])
+@pytest.mark.parametrize("b,m,n,k", BIG_TILES)
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_gemm2_big_tiles(dt, b, m, n, k, ta, tb):
+    t128, t64 = -(-m // 128) * -(-n // 128), -(-m // 64) * -(-n // 64)
+    one_round = m % 2 == 0 and n % 2 == 0 and k % 16 == 0 and (192 if b > 1 else 224) < b * t128 <= 256
+    assert 16 * t128 <= 5 * t64 and (b * t128 >= 512 or one_round)
+    test_gemm2_ragged(dt, b, m, n, k, ta, tb)
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.float64], ids=["f32", "f64"])
+@pytest.mark.parametrize("b,n,m", [(257, 255, 253), (260, 254, 251), (600, 129, 130)])
+@pytest.mark.parametrize("lower,trans", [(1, 0), (0, 0), (1, 1)])
+def test_trmm_big_tiles(dt, b, n, m, lower, trans):
+    """A masked operand in 128 x 128 tiles (from 1024 of them on) and, at n = 129, in the smaller ones that replace them."""
+    rng = np.random.default_rng(n + m)
+    L, X = _operand(rng, dt, b, n, n, 1), _operand(rng, dt, b, n, m, 0)
+    Y = la.trmm(L, X, lower=bool(lower), trans=bool(trans))
+    t = L.double().tril() if lower else L.double().triu()
+    ref = torch.matmul((t.mT if trans else t).contiguous(), X.double())
+    err = (Y.double() - ref).flatten(1).norm(dim=1) / ref.flatten(1).norm(dim=1)
+    assert float(err.max()) <= TOL[dt], float(err.max())
 
 
 @pytest.mark.parametrize("dt", [torch.float32, torch.float64], ids=["f32", "f64"])
