@@ -774,7 +774,8 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             // rounds of tiles, so take the largest tile that still gives 1024 workgroups.
             e = wg128 >= 1024 && !padded ? 128 : ((wg64 >= 1024 || !k64 || o.min_tile64) ? 64 : 32);
         } else {
-            // Equal tiles: big tiles once they fill the 512 workgroup slots (a compute unit with one workgroup waits for
+            // Equal tiles: big tiles once they (nearly) fill the 512 workgroup slots (496 tiles, 3952 x 2048 x 2000, fp64 598 -> 555
+            // us and fp32 310 -> 296 against 64 x 64 tiles, 480 the same, 448 262 -> 291; a compute unit with one workgroup waits for
             // its loads: a sparse GP with 300 tiles of 128 1497 -> 1429 us in 64 x 64 tiles, factor + gradient of
             // n = 5500 with 432 of them 7737 -> 7511, fp64; 8192 with 192 to 256 of them in several products 16.84 -> 16.79 ms,
             // in fp32 10.07 -> 9.81), quarter tiles while 64 x 64 tiles
@@ -789,7 +790,7 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             const bool big = o.maskC ? (M >= 2048 && N >= 2048) : (M >= 128 && N >= 128);
             const bool one_round = sizeof(T) == 8 && !f.rag && !(f.akf && f.bkf) && !o.maskC && t128 <= 256 &&
                                    t128 > (batch > 1 ? 192 : 224);
-            e = ((t128 >= 512 || one_round) && big && !padded) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64) ? 32 : 64);
+            e = ((t128 >= (o.maskC ? 512 : 480) || one_round) && big && !padded) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64) ? 32 : 64);
         }
         if (o.symsum && e == 128)  // (the form that stores both triangles has tiles up to 64 only)
             e = 64;

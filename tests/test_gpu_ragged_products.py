@@ -38,9 +38,21 @@ def test_gemm2_ragged(dt, b, m, n, k, ta, tb):
         assert float(err.max()) <= TOL[dt], (off, float(err.max()))
 
 
-# (b, m, n, k): 128 x 128 tiles are taken from 512 of them on, if they stick out of C by less than a quarter more than tiles of
+@pytest.mark.parametrize("dt", [torch.float32, torch.float64], ids=["f32", "f64"])
+@pytest.mark.parametrize("cols", range(1, 10))
+@pytest.mark.parametrize("m,k", [(200, 5), (70, 131), (9, 1025)])
+def test_thin_products(dt, cols, m, k):
+    """One instance of the kernel per number of columns up to eight, plain and with a triangular operand."""
+    for ta, tb in ((0, 0), (0, 1), (1, 0), (1, 1)):
+        test_gemm2_ragged(dt, 3, m, cols, k, ta, tb)
+        test_gemm2_ragged(dt, 3, cols, m, k, ta, tb)
+    for trans in (0, 1):
+        test_trmm_big_tiles(dt, 2, 140 + m, cols, 1, trans)
+
+
+# (b, m, n, k): 128 x 128 tiles are taken from 480 of them on, if they stick out of C by less than a quarter more than tiles of
 # 64 do; in fp64, aligned and with k not contiguous in both operands, also for 225 to 256 of them (193 in a batch).
-BIG_TILES = [(130, 255, 253, 33), (130, 254, 255, 15), (64, 383, 381, 77), (33, 509, 511, 130), (13, 512, 512, 64),
+BIG_TILES = [(130, 255, 253, 33), (130, 254, 255, 15), (55, 383, 381, 77), (33, 509, 511, 130), (13, 512, 512, 64),
              (64, 256, 256, 16), (1, 1920, 1920, 32)]
 
 
@@ -50,7 +62,7 @@ BIG_TILES = [(130, 255, 253, 33), (130, 254, 255, 15), (64, 383, 381, 77), (33, 
 def test_gemm2_big_tiles(dt, b, m, n, k, ta, tb):
     t128, t64 = -(-m // 128) * -(-n // 128), -(-m // 64) * -(-n // 64)
     one_round = m % 2 == 0 and n % 2 == 0 and k % 16 == 0 and (192 if b > 1 else 224) < b * t128 <= 256
-    assert 16 * t128 <= 5 * t64 and (b * t128 >= 512 or one_round)
+    assert 16 * t128 <= 5 * t64 and (b * t128 >= 480 or one_round)
     test_gemm2_ragged(dt, b, m, n, k, ta, tb)
 
 
