@@ -475,27 +475,28 @@ __global__ __launch_bounds__(256, 2) void k_gemm(View<const T> A, View<const T> 
 constexpr int GEMV_N = 8;
 constexpr int GEMV_THREADS = 512;
 
-// NC: columns computed (N <= NC; the spare ones repeat the last column and are not stored).  The loads of several k
-// go out together, those of B with them: with one k at a time and a branch per column a wavefront waits for
-// memory twice per k (500 x 9568 times one vector, fp64, 27 -> 22 us; its transpose 59 -> 11).
-template <typename T, int NC>
-__global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N,
-                                              int K, T alpha, T beta, int triA, int tiles)
+// The loads of several k go out together, those of B with them: with one k at a time and a branch per column a wavefront
+// waits for memory twice per k (500 x 9568 times one vector, fp64, 27 -> 22 us; its transpose 59 -> 11).  A
+// column more than there are costs its loads (300 items 5 x 200 times 7 columns with A transposed, fp64, bound by the
+// loads of B: 31 us with eight), so every count has its own instance.
+template <typename T, int N>
+__global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int K,
+                                              T alpha, T beta, int triA, int tiles)
 {
     constexpr int NW = GEMV_THREADS / 64;  // wavefronts: rows per block (k contiguous) or slices of k
-    constexpr int UN = NC == 1 ? 8 : (NC <= 4 ? 4 : 2);
-    __shared__ T red[NW][64][NC];
+    constexpr int UN = N == 1 ? 8 : (N <= 4 ? 4 : 2);
+    __shared__ T red[NW][64][N];
     const int64_t b = blockIdx.x / tiles;
     const int tile = (int)(blockIdx.x % tiles);
     const T *Ap = A.item(b);
     const T *Bp = B.item(b);
     T *Cp = C.item(b);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int64_t jo[NC];
-    T acc[NC];
+    int64_t jo[N];
+    T acc[N];
 #pragma unroll
-    for (int j = 0; j < NC; ++j) {
-        jo[j] = (int64_t)(j < N ? j : N - 1) * B.cs;
+    for (int j = 0; j < N; ++j) {
+        jo[j] = j * B.cs;
         acc[j] = T(0);
     }
     const bool rows = A.cs == 1;
@@ -505,20 +506,20 @@ __global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<con
         const int first = rows ? kb + lane : w, step = rows ? 64 : NW, last = rows ? ke : K;
         const T *ar = Ap + (int64_t)i * A.rs;
         for (int k0 = first; k0 < last; k0 += UN * step) {
-            T a[UN], x[UN][NC];
+            T a[UN], x[UN][N];
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
                 const int k = k0 + u * step;
                 const bool in = k >= kb && k < ke;
                 a[u] = in ? ar[(int64_t)k * A.cs] : T(0);
 #pragma unroll
-                for (int j = 0; j < NC; ++j)
+                for (int j = 0; j < N; ++j)
                     x[u][j] = in ? Bp[(int64_t)k * B.rs + jo[j]] : T(0);
             }
 #pragma unroll
             for (int u = 0; u < UN; ++u)
 #pragma unroll
-                for (int j = 0; j < NC; ++j)
+                for (int j = 0; j < N; ++j)
                     acc[j] = fma(a[u], x[u][j], acc[j]);
         }
     }
@@ -526,11 +527,11 @@ __global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<con
         if (i >= M)
             return;
 #pragma unroll
-        for (int j = 0; j < NC; ++j) {
+        for (int j = 0; j < N; ++j) {
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1)
                 acc[j] += __shfl_xor(acc[j], off, WAVE);
-            if (lane == 0 && j < N) {
+            if (lane == 0) {
                 T *c = Cp + (int64_t)i * C.rs + (int64_t)j * C.cs;
                 const T upd = alpha * acc[j];
                 *c = (beta == T(0)) ? upd : fma(beta, *c, upd);
@@ -539,21 +540,20 @@ __global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<con
         return;
     }
 #pragma unroll
-    for (int j = 0; j < NC; ++j)
+    for (int j = 0; j < N; ++j)
         red[w][lane][j] = acc[j];
     __syncthreads();
     if (w == 0 && i < M) {
 #pragma unroll
-        for (int j = 0; j < NC; ++j)
-            if (j < N) {
-                T sum = T(0);
+        for (int j = 0; j < N; ++j) {
+            T sum = T(0);
 #pragma unroll
-                for (int q = 0; q < NW; ++q)
-                    sum += red[q][lane][j];
-                T *c = Cp + (int64_t)i * C.rs + (int64_t)j * C.cs;
-                const T upd = alpha * sum;
-                *c = (beta == T(0)) ? upd : fma(beta, *c, upd);
-            }
+            for (int q = 0; q < NW; ++q)
+                sum += red[q][lane][j];
+            T *c = Cp + (int64_t)i * C.rs + (int64_t)j * C.cs;
+            const T upd = alpha * sum;
+            *c = (beta == T(0)) ? upd : fma(beta, *c, upd);
+        }
     }
 }
 
@@ -565,15 +565,23 @@ static la_status launch_gemv(View<const T> A, View<const T> B, View<T> C, int64_
     const int64_t blocks = (int64_t)tiles * batch;
     if (blocks > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
-#define LA_GO(NC_)                                                                                                     \
-    LA_LAUNCH((k_gemv<T, NC_>), dim3((unsigned)blocks), dim3(GEMV_THREADS), 0, st, A, B, C, batch, M, N, K, alpha, beta, \
-              triA, tiles)
-    if (N == 1)
+#define LA_GO(N_)                                                                                                      \
+    case N_:                                                                                                           \
+        LA_LAUNCH((k_gemv<T, N_>), dim3((unsigned)blocks), dim3(GEMV_THREADS), 0, st, A, B, C, batch, M, K, alpha, beta, triA, \
+                  tiles);                                                                                              \
+        break
+    switch (N) {
         LA_GO(1);
-    else if (N <= 4)
+        LA_GO(2);
+        LA_GO(3);
         LA_GO(4);
-    else
-        LA_GO(GEMV_N);
+        LA_GO(5);
+        LA_GO(6);
+        LA_GO(7);
+        LA_GO(8);
+    default:
+        return LA_ERR_UNSUPPORTED;
+    }
 #undef LA_GO
     return launch_check("gemv");
 }
