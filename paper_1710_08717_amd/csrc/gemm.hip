@@ -700,6 +700,8 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             return LA_ERR_UNSUPPORTED;
         o.maskC = 0;
         o.halfDiag = 0;
+        if (C.cs != 1 && beta != T(0))  // (the lower triangle that beta scales would be the upper one of C.t())
+            return LA_ERR_UNSUPPORTED;
         if (C.cs != 1 && C.rs == 1)  // the result is symmetric: its transpose is the same matrix
             C = C.t();
     }
