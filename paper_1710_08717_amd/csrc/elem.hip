@@ -231,8 +231,9 @@ __global__ __launch_bounds__(THREADS) void k_sumlogdiag(const T *L, T *out, int6
 {
     const int64_t b = blockIdx.x;
     const T *lp = L + b * (int64_t)n * n;
+    constexpr int UN = THREADS > WAVE ? 4 : 1;
     double s = 0.0;
-#pragma unroll 4
+#pragma unroll UN
     for (int i = threadIdx.x; i < n; i += THREADS)
         s += (double)log(lp[(int64_t)i * n + i]);
 #pragma unroll
@@ -286,8 +287,9 @@ la_status launch_sumlogdiag(const T *L, T *out, int64_t batch, int n, hipStream_
         return launch_check("sumlogdiag_small");
     }
     // a diagonal of some hundred entries and more is read by sixteen wavefronts: every load is a cache line of its own,
-    // and one wavefront waits for them in turn (n = 3001, fp64: 24.8 -> 5.8 us)
-    if (n > 256)
+    // and one wavefront waits for them in turn (n = 3001, fp64: 24.8 -> 5.8 us).  Up to n = 512 many matrices do as well with
+    // one each (4000 of n = 300, fp64: 24.3 us with sixteen, 23.0 with one).
+    if (n > 256 && (n > 512 || batch <= 512))
         LA_LAUNCH((k_sumlogdiag<T, 1024>), dim3((unsigned)batch), dim3(1024), 0, st, L, out, batch, n);
     else
         LA_LAUNCH((k_sumlogdiag<T, WAVE>), dim3((unsigned)batch), dim3(WAVE), 0, st, L, out, batch, n);
