@@ -1808,12 +1808,19 @@ static size_t symm_leaf_lds(int n, int k, int nw)
     const int Kn = (n + LT - 1) / LT, Kk = (k + LT - 1) / LT;
     return ((size_t)Kn * Kn + (size_t)Kn * Kk + nw) * Leaf16<T>::OT * sizeof(T);
 }
+// Many small items, or where sixteen wavefronts' areas do not fit (fp64, 32 < n <= 48: the general product on such odd sizes takes
+// 29 to 54 us for syrk backward of 512 to 1000 matrices of 33 x 40, four wavefronts 10 to 17): four wavefronts each.
+template <typename T>
+static int symm_leaf_waves(int64_t batch, int n, int k)
+{
+    const int Kn = (n + LT - 1) / LT, Kk = (k + LT - 1) / LT;
+    return Kn * Kk <= 16 && (batch > 1024 || symm_leaf_lds<T>(n, k, LEAF16_WAVES) > 64 * 1024) ? 4 : LEAF16_WAVES;
+}
 template <typename T>
 bool symm_leaf_takes(int64_t batch, int n, int k)
 {
-    const int Kn = (n + LT - 1) / LT, Kk = (k + LT - 1) / LT;
-    const int nw = (Kn * Kk <= 16 && batch > 1024) ? 4 : LEAF16_WAVES;  // as launch_symm_leaf chooses
-    return n > 16 && n <= 128 && k >= 1 && k <= 128 && batch >= 64 && symm_leaf_lds<T>(n, k, nw) <= 64 * 1024;
+    return n > 16 && n <= 128 && k >= 1 && k <= 128 && batch >= 64 &&
+           symm_leaf_lds<T>(n, k, symm_leaf_waves<T>(batch, n, k)) <= 64 * 1024;
 }
 template bool symm_leaf_takes<float>(int64_t, int, int);
 template bool symm_leaf_takes<double>(int64_t, int, int);
@@ -1828,8 +1835,7 @@ la_status launch_symm_leaf(T alpha, int64_t batch, int n, int k, View<const T> G
         return LA_ERR_UNSUPPORTED;
     if (dry_run())
         return LA_OK;
-    const int Kn = (n + LT - 1) / LT, Kk = (k + LT - 1) / LT;
-    if (Kn * Kk <= 16 && batch > 1024) {  // many small items: four wavefronts each
+    if (symm_leaf_waves<T>(batch, n, k) == 4) {
         LA_LAUNCH((k_symm_leaf16<T, 4>), dim3((unsigned)batch), dim3(4 * 64), symm_leaf_lds<T>(n, k, 4), st, G, A, Out, batch,
                   n, k, alpha);
     } else {

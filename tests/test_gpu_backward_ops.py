@@ -182,10 +182,10 @@ def test_syrk_backward_parity(la, orc, dtype, trans, n, k):
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 @pytest.mark.parametrize("trans", [False, True])
 @pytest.mark.parametrize("n,k,batch", [(33, 8, 70), (48, 32, 1030), (40, 50, 64), (64, 64, 65), (100, 17, 64), (57, 1, 1100),
-                                       (128, 16, 64)])
+                                       (128, 16, 64), (33, 40, 1000), (48, 64, 70), (41, 33, 64)])
 def test_syrk_backward_one_workgroup_per_matrix(la, orc, dtype, trans, n, k, batch):
     """From 64 matrices of 32 < n <= 128 on, the rule keeps Bbar and A in LDS, one workgroup per matrix (where both fit
-    64 KB; four wavefronts above 1024 matrices of at most 16 output tiles)."""
+    64 KB; four wavefronts for at most 16 output tiles above 1024 matrices or where sixteen wavefronts' areas do not fit)."""
     rng = np.random.default_rng(n * k + batch + 1)
     A = rng.standard_normal((batch, k, n) if trans else (batch, n, k)).astype(npdt(dtype))
     G = (rng.standard_normal((batch, n, n)) / np.sqrt(n)).astype(npdt(dtype))  # not symmetric
