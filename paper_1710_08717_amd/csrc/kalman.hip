@@ -183,13 +183,12 @@ __global__ __launch_bounds__(64) void k_kalman(KfArgs<T> a)
     const int64_t b_raw = (int64_t)blockIdx.x * KF_GROUPS + g;
     const bool live = b_raw < a.batch;
     const int64_t b = live ? b_raw : a.batch - 1;  // a spare group repeats the last sequence and stores nothing
-    const int64_t pb = b;
 
     // one copy of the parameters per sequence
     T *sA = reinterpret_cast<T *>(kf_smem) + g * Lds::GROUP, *sB = sA + Lds::MAT, *sSh = sB + Lds::MAT,
       *sSv = sSh + Lds::MAT;
     {   // zero padded (S_v: identity padded, so that the padded S_vv keeps a unit pivot)
-        const T *Ap = a.A + pb * dh * dh, *Bp = a.B + pb * dv * dh, *Shp = a.Sh + pb * dh * dh, *Svp = a.Sv + pb * dv * dv;
+        const T *Ap = a.A + b * dh * dh, *Bp = a.B + b * dv * dh, *Shp = a.Sh + b * dh * dh, *Svp = a.Sv + b * dv * dv;
 #pragma unroll
         for (int j = 0; j < KF_D; ++j) {
             sA[r * Lds::PS + j] = (r < dh && j < dh) ? Ap[r * dh + j] : T(0);
@@ -201,10 +200,10 @@ __global__ __launch_bounds__(64) void k_kalman(KfArgs<T> a)
     __syncthreads();
 
     T F[KF_D];  // filtered covariance, row r
-    T f = (r < dh) ? a.mu0[pb * dh + r] : T(0);
+    T f = (r < dh) ? a.mu0[b * dh + r] : T(0);
 #pragma unroll
     for (int j = 0; j < KF_D; ++j)
-        F[j] = (r < dh && j < dh) ? a.S0[pb * dh * dh + r * dh + j] : T(0);
+        F[j] = (r < dh && j < dh) ? a.S0[b * dh * dh + r * dh + j] : T(0);
 
     const T *vp = a.v + b * (int64_t)steps * dv;
     T vnext = (steps > 0 && r < dv) ? vp[r] : T(0);
@@ -758,13 +757,18 @@ template <typename T>
 static la_status launch_kalman_shared(const KfArgs<T> &a, hipStream_t st)
 {
     // Few sequences: two workers of 16 each, so that writing F does not hold a step up (8192 sequences, dh = dv = 16, fp32:
-    // 97 us, 121 with 32 each, 193 with 64).  From 32768 on the workgroups should all be resident (12 wavefronts per
+    // 97 us, 121 with 32 each, 193 with 64).  32 each where 16 give more workgroups than are resident (fp64 above 16384
+    // sequences: 32767 x 24 steps, d = 4, 163 -> 84 us, d = 16 323 -> 314) or than compute units and a step is short
+    // (d_h <= 4 above 8192: 16384 x 24, d = 4, fp32 43 -> 38, fp64 71 -> 59; d_h = 12 79 -> 113 and 115 -> 127).  The kernel
+    // with a recursion per sequence takes 114 us for the first and 43, 80 for the last; it is ahead of this one only in fp32
+    // above 16384 sequences of d <= 4 without states, by up to 6 %.  From 32768 on the workgroups should all be resident (12 wavefronts per
     // compute unit in fp32, 8 in fp64): one worker of 64 where F is large, so that more of them write (65536, dh = 16, fp64:
     // 1000 us against 1052 with two of 32), else two workers of 32, in fp64 of 64 (dh = 4, dv = 3: fp32 100 us
     // against 115 with one worker of 64; fp64 207 against 248 with two of 32).
     const bool many = a.batch >= 32768;
     const int workers = many && a.dh > 8 ? 1 : 2;
-    const int per_worker = !many ? 16 : (workers == 1 || sizeof(T) == 8 ? 64 : 32);
+    const bool wide = (a.dh <= 4 && a.batch > 8192) || (sizeof(T) == 8 && a.batch > 16384);
+    const int per_worker = !many ? (wide ? 32 : 16) : (workers == 1 || sizeof(T) == 8 ? 64 : 32);
     const int64_t per_wg = (int64_t)workers * per_worker, blocks = (a.batch + per_wg - 1) / per_wg;
     if (blocks > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;

@@ -150,6 +150,40 @@ def test_kalman_one_model_bad_pivot(la):
     for k in ("A", "B", "Sh", "Sv", "mu0", "S0"):
         rep[k] = np.repeat(w[k][None], 20, axis=0)
     assert np.array_equal(run(la, w)[3], run(la, rep)[3])
+    assert np.all(run(la, w)[3] == 1)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("dh,dv", [(5, 3), (2, 4), (16, 16)])
+def test_kalman_one_model_pivot_of_a_later_step(la, dtype, dh, dv):
+    """An indefinite state noise makes one variance negative after some steps: info names the first step whose S_vv is not
+    positive definite (its least eigenvalue is 0.1 the step before and -8 there), in both kernels, and no later one."""
+    w = workloads.make_kalman(20, 9, dh, dv, dtype=dtype, shared=True, seed=3)
+    w["A"], w["B"], w["Sv"] = np.eye(dh), np.eye(dv, dh), np.eye(dv)
+    w["Sh"], w["S0"] = np.diag(np.where(np.arange(dh) == 1, -0.9, 0.1)), 10.0 * np.eye(dh)
+    S, first = w["S0"], 0
+    for t in range(9):
+        if t > 0:
+            S = F + w["Sh"]
+        Svv = w["B"] @ S @ w["B"].T + w["Sv"]
+        if np.linalg.eigvalsh(Svv)[0] <= 0:
+            first = t + 1
+            break
+        F = S - S @ w["B"].T @ np.linalg.solve(Svv, w["B"] @ S)
+    assert first == 4
+    for k in ("A", "B", "Sh", "Sv", "S0"):
+        w[k] = w[k].astype(workloads.np_dtype(dtype))
+    rep = dict(w)
+    for k in ("A", "B", "Sh", "Sv", "mu0", "S0"):
+        rep[k] = np.repeat(w[k][None], 20, axis=0)
+    assert np.all(run(la, w)[3] == first) and np.all(run(la, rep)[3] == first)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("batch,dh,dv", [(8193, 4, 3), (8197, 2, 9), (16385, 7, 5), (16385, 16, 16)])
+def test_kalman_one_model_with_32_sequences_a_wavefront(la, dtype, batch, dh, dv):
+    """The split for batches of more workgroups than the chip holds, ragged at its end."""
+    test_kalman_one_model_equals_repeated_model(la, dtype, batch, 3, dh, dv, True)
 
 
 def _filter_80_bit(w):
