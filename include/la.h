@@ -277,9 +277,10 @@ la_status la_gp_glue(la_dtype dt, int64_t batch, int n, const void *L, const voi
  *          Lbar = -tril(alpha z^T) + diag(1 / l_ii); written in full, exactly symmetric.
  * A, Abar: [batch, n, n]; y: [batch, n]; loss: [batch]; info: NULL or int32 [batch] as for potrf.
  * Abar may be the same buffer as A.  Up to n = 128 this is ONE kernel per call and needs no
- * workspace; beyond that it is la_potrf_batched, the inverse of the factor, its products with y and z, and
- * its product with its own transpose, on `workspace` (device memory, 256-byte aligned, at least
- * la_gp_workspace_bytes(dt, batch, n) bytes, not overlapping the other arguments). */
+ * workspace; beyond that it is la_potrf_batched, the inverse of the factor, two solves for z and alpha
+ * in the form la_trsm_batched has for these sizes, and the inverse's product with its own transpose, on
+ * `workspace` (device memory, 256-byte aligned, at least la_gp_workspace_bytes(dt, batch, n) bytes, not
+ * overlapping the other arguments). */
 size_t la_gp_workspace_bytes(la_dtype dt, int64_t batch, int n);
 la_status la_gp_criterion(la_dtype dt, int64_t batch, int n, const void *A, const void *y, void *loss, void *Abar,
                           int32_t *info, void *workspace, size_t workspace_bytes, void *stream);
