@@ -16,7 +16,8 @@
 // That is k_kalman.  Where one model is filtered over all sequences, the covariance recursion --
 // F_t, the gain, the factor of S_vv -- does not depend on the observations and is the same for
 // every sequence: k_kalman_shared runs it once per workgroup and only the means and the
-// likelihood per sequence.
+// likelihood per sequence.  (In fp32 with dimensions up to 4 that saves little; there k_kalman
+// takes one model as well, for the batches where it is the faster one.)
 #include "common.hpp"
 #include "leaf_dpp.hpp"
 
@@ -84,7 +85,7 @@ struct KfArgs {
     T *f, *F, *nll;
     int32_t *info;
     int64_t batch;
-    int T_, dh, dv;
+    int T_, dh, dv, shared;  // shared: one model for all sequences
 };
 
 // f(k) for k = 0 .. D-1 in ascending (or descending) order, in blocks of four; a block is skipped
@@ -183,12 +184,13 @@ __global__ __launch_bounds__(64) void k_kalman(KfArgs<T> a)
     const int64_t b_raw = (int64_t)blockIdx.x * KF_GROUPS + g;
     const bool live = b_raw < a.batch;
     const int64_t b = live ? b_raw : a.batch - 1;  // a spare group repeats the last sequence and stores nothing
+    const int64_t pb = a.shared ? 0 : b;
 
-    // one copy of the parameters per sequence
-    T *sA = reinterpret_cast<T *>(kf_smem) + g * Lds::GROUP, *sB = sA + Lds::MAT, *sSh = sB + Lds::MAT,
+    // one copy of the parameters per sequence, or one for the workgroup
+    T *sA = reinterpret_cast<T *>(kf_smem) + (a.shared ? 0 : g * Lds::GROUP), *sB = sA + Lds::MAT, *sSh = sB + Lds::MAT,
       *sSv = sSh + Lds::MAT;
-    {   // zero padded (S_v: identity padded, so that the padded S_vv keeps a unit pivot)
-        const T *Ap = a.A + b * dh * dh, *Bp = a.B + b * dv * dh, *Shp = a.Sh + b * dh * dh, *Svp = a.Sv + b * dv * dv;
+    if (!a.shared || g == 0) {   // zero padded (S_v: identity padded, so that the padded S_vv keeps a unit pivot)
+        const T *Ap = a.A + pb * dh * dh, *Bp = a.B + pb * dv * dh, *Shp = a.Sh + pb * dh * dh, *Svp = a.Sv + pb * dv * dv;
 #pragma unroll
         for (int j = 0; j < KF_D; ++j) {
             sA[r * Lds::PS + j] = (r < dh && j < dh) ? Ap[r * dh + j] : T(0);
@@ -200,10 +202,10 @@ __global__ __launch_bounds__(64) void k_kalman(KfArgs<T> a)
     __syncthreads();
 
     T F[KF_D];  // filtered covariance, row r
-    T f = (r < dh) ? a.mu0[b * dh + r] : T(0);
+    T f = (r < dh) ? a.mu0[pb * dh + r] : T(0);
 #pragma unroll
     for (int j = 0; j < KF_D; ++j)
-        F[j] = (r < dh && j < dh) ? a.S0[b * dh * dh + r * dh + j] : T(0);
+        F[j] = (r < dh && j < dh) ? a.S0[pb * dh * dh + r * dh + j] : T(0);
 
     const T *vp = a.v + b * (int64_t)steps * dv;
     T vnext = (steps > 0 && r < dv) ? vp[r] : T(0);
@@ -371,7 +373,8 @@ static la_status launch_kalman_d(const KfArgs<T> &a, hipStream_t st)
     const int64_t blocks = (a.batch + Lds::GROUPS - 1) / Lds::GROUPS;
     if (blocks > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
-    LA_LAUNCH((k_kalman<T, D>), dim3((unsigned)blocks), dim3(64), Lds::BYTES, st, a);
+    const size_t lds = a.shared ? Lds::BYTES / Lds::GROUPS : Lds::BYTES;
+    LA_LAUNCH((k_kalman<T, D>), dim3((unsigned)blocks), dim3(64), lds, st, a);
     return launch_check("kalman");
 }
 
@@ -759,16 +762,16 @@ static la_status launch_kalman_shared(const KfArgs<T> &a, hipStream_t st)
     // Few sequences: two workers of 16 each, so that writing F does not hold a step up (8192 sequences, dh = dv = 16, fp32:
     // 97 us, 121 with 32 each, 193 with 64).  32 each where 16 give more workgroups than are resident (fp64 above 16384
     // sequences: 32767 x 24 steps, d = 4, 163 -> 84 us, d = 16 323 -> 314) or than compute units and a step is short
-    // (d_h <= 4 above 8192: 16384 x 24, d = 4, fp32 43 -> 38, fp64 71 -> 59; d_h = 12 79 -> 113 and 115 -> 127).  The kernel
-    // with a recursion per sequence takes 114 us for the first and 43, 80 for the last; it is ahead of this one only in fp32
-    // above 16384 sequences of d <= 4 without states, by up to 6 %.  From 32768 on the workgroups should all be resident (12 wavefronts per
-    // compute unit in fp32, 8 in fp64): one worker of 64 where F is large, so that more of them write (65536, dh = 16, fp64:
-    // 1000 us against 1052 with two of 32), else two workers of 32, in fp64 of 64 (dh = 4, dv = 3: fp32 100 us
-    // against 115 with one worker of 64; fp64 207 against 248 with two of 32).
+    // (d_h <= 4 above 8192: 16384 x 24, d = 4, fp32 43 -> 38, fp64 71 -> 59; d_h = 12 79 -> 113 and 115 -> 127).  From 32768 on
+    // the workgroups should all be resident (12 wavefronts per compute unit in fp32, 8 in fp64): one worker of 64 where F is
+    // large, so that more of them write (65536, dh = 16, fp64: 1000 us against 1052 with two of 32), else two workers of 32, in
+    // fp64 of 64 (dh = 4, dv = 3: fp32 100 us against 115 with one worker of 64; fp64 207 against 248 with two of 32), and
+    // in fp32 above 65536 as well where a step is short (131072 x 24, d = 4, without states 150 -> 99, with them 161 -> 114;
+    // larger d_h gains nothing).
     const bool many = a.batch >= 32768;
     const int workers = many && a.dh > 8 ? 1 : 2;
     const bool wide = (a.dh <= 4 && a.batch > 8192) || (sizeof(T) == 8 && a.batch > 16384);
-    const int per_worker = !many ? (wide ? 32 : 16) : (workers == 1 || sizeof(T) == 8 ? 64 : 32);
+    const int per_worker = !many ? (wide ? 32 : 16) : (workers == 1 || sizeof(T) == 8 || (a.dh <= 4 && a.batch > 65536) ? 64 : 32);
     const int64_t per_wg = (int64_t)workers * per_worker, blocks = (a.batch + per_wg - 1) / per_wg;
     if (blocks > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
@@ -777,6 +780,25 @@ static la_status launch_kalman_shared(const KfArgs<T> &a, hipStream_t st)
     else
         LA_LAUNCH((k_kalman_shared<T, false>), dim3((unsigned)blocks), dim3(64 * (1 + workers)), 0, st, a, per_worker);
     return launch_check("kalman");
+}
+
+// fp32, one model, dimensions up to 4: the recursion per sequence with 4 lanes each (16 sequences a wavefront) is ahead of the
+// common one (24 steps, us, own -> common recursion):
+//  * for d_v > d_h, where the gain's substitution is the common recursion's chain: 4096 sequences of d = (1, 3) 34 -> 42, 131072
+//    134 -> 174;
+//  * on two and three of its wavefronts per SIMD where little is written: d = (3, 2) with states, 32704 50 -> 56, 40960 64 -> 66;
+//    without states 45 -> 47 and the same;
+//  * on more than four where F's items are not whole runs of 16 bytes, or one: (3, 2) 163840 172 -> 208, (1, 1) 166 -> 188.
+// On the fourth (49153 to 65536) the common one is ahead everywhere: (1, 3) 74 -> 68, (4, 2) with states 82 -> 72.
+static bool small_dims_prefer_own_recursion(int64_t batch, int dh, int dv, bool states)
+{
+    if (dh > 4 || dv > 4 || (batch > 49152 && batch <= 65536))
+        return false;
+    if (dv > dh)
+        return true;
+    if (batch <= 65536)
+        return batch > 16384 && (dh <= 3 || !states);
+    return states && dh <= 3;
 }
 
 template <typename T>
@@ -788,8 +810,8 @@ la_status launch_kalman(const T *A, const T *B, const T *Sh, const T *Sv, const 
         return LA_OK;
     if (dh < 1 || dv < 1 || dh > 16 || dv > 16)
         return LA_ERR_UNSUPPORTED;
-    KfArgs<T> a{A, B, Sh, Sv, mu0, S0, v, f, F, nll, info, batch, steps, dh, dv};
-    if (shared)
+    KfArgs<T> a{A, B, Sh, Sv, mu0, S0, v, f, F, nll, info, batch, steps, dh, dv, shared};
+    if (shared && !(sizeof(T) == 4 && small_dims_prefer_own_recursion(batch, dh, dv, F != nullptr)))
         return launch_kalman_shared<T>(a, st);
     if (dh <= 4 && dv <= 4)
         return launch_kalman_d<T, 4>(a, st);

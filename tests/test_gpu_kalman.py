@@ -186,6 +186,14 @@ def test_kalman_one_model_with_32_sequences_a_wavefront(la, dtype, batch, dh, dv
     test_kalman_one_model_equals_repeated_model(la, dtype, batch, 3, dh, dv, True)
 
 
+@pytest.mark.parametrize("batch,dh,dv,want", [(50, 1, 3, True), (37, 3, 4, False), (16387, 3, 2, True), (16401, 4, 4, False),
+                                              (49155, 2, 4, True), (65539, 3, 3, True), (65551, 4, 4, True), (65537, 2, 2, False),
+                                              (65543, 4, 5, True)])
+def test_kalman_one_model_of_small_dimensions(la, batch, dh, dv, want):
+    """fp32: one recursion per sequence or a common one by size, and up to 64 sequences per wavefront in the common one."""
+    test_kalman_one_model_equals_repeated_model(la, "f32", batch, 3, dh, dv, want)
+
+
 def _filter_80_bit(w):
     """Filtered means and covariances of one model over its sequences in 80-bit floats."""
     ld = np.longdouble
