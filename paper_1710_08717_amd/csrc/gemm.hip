@@ -797,7 +797,10 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             // contiguous 309 -> 338, 8192 x 512 x 1024 181 -> 167, 2304 x 1792 x 512, 252 tiles, 101 -> 88; 7168 x 512 x 1024, 224
             // tiles, 163 -> 168, 2048 x 1536 x 1024, 192 tiles, 144 -> 167; a batch of 13 x 512^3, 208 tiles, 98 -> 88).
             const int64_t t128 = o.maskC ? wg128 : (int64_t)((M + 127) / 128) * ((N + 127) / 128) * batch;
-            const bool big = o.maskC ? (M >= 2048 && N >= 2048) : (M >= 128 && N >= 128);
+            // Up to K = 32 writing C is most of the work, and more, smaller workgroups overlap it with their loads (us, 128 x 128 ->
+            // 64 x 64: 83 items of 1033 x 251, K = 2, fp64 48 -> 39, K = 32 72 -> 58, fp32 28 -> 25 and 37 -> 32; 64 x 512 x 512, K = 16,
+            // 32 -> 30 and 22 -> 18; from K = 33 on it depends: 64 x 512 x 512 51 -> 64, 83 x 1033 x 251 89 -> 86).
+            const bool big = K > 32 && (o.maskC ? (M >= 2048 && N >= 2048) : (M >= 128 && N >= 128));
             const bool one_round = sizeof(T) == 8 && !f.rag && !(f.akf && f.bkf) && !o.maskC && t128 <= 256 &&
                                    t128 > (batch > 1 ? 192 : 224);
             e = ((t128 >= (o.maskC ? 512 : 480) || one_round) && big && !padded) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64) ? 32 : 64);

@@ -50,10 +50,10 @@ def test_thin_products(dt, cols, m, k):
         test_trmm_big_tiles(dt, 2, 140 + m, cols, 1, trans)
 
 
-# (b, m, n, k): 128 x 128 tiles are taken from 480 of them on, if they stick out of C by less than a quarter more than tiles of
+# (b, m, n, k): with K above 32, 128 x 128 tiles are taken from 480 of them on, if they stick out of C by less than a quarter more than tiles of
 # 64 do; in fp64, aligned and with k not contiguous in both operands, also for 225 to 256 of them (193 in a batch).
-BIG_TILES = [(130, 255, 253, 33), (130, 254, 255, 15), (55, 383, 381, 77), (33, 509, 511, 130), (13, 512, 512, 64),
-             (64, 256, 256, 16), (1, 1920, 1920, 32)]
+BIG_TILES = [(130, 255, 253, 33), (130, 254, 255, 35), (55, 383, 381, 77), (33, 509, 511, 130), (13, 512, 512, 64),
+             (64, 256, 256, 48), (1, 1920, 1920, 48)]
 
 
 @pytest.mark.parametrize("dt", [torch.float32, torch.float64], ids=["f32", "f64"])
@@ -62,7 +62,16 @@ BIG_TILES = [(130, 255, 253, 33), (130, 254, 255, 15), (55, 383, 381, 77), (33, 
 def test_gemm2_big_tiles(dt, b, m, n, k, ta, tb):
     t128, t64 = -(-m // 128) * -(-n // 128), -(-m // 64) * -(-n // 64)
     one_round = m % 2 == 0 and n % 2 == 0 and k % 16 == 0 and (192 if b > 1 else 224) < b * t128 <= 256
-    assert 16 * t128 <= 5 * t64 and (b * t128 >= 480 or one_round)
+    assert k > 32 and 16 * t128 <= 5 * t64 and (b * t128 >= 480 or one_round)
+    test_gemm2_ragged(dt, b, m, n, k, ta, tb)
+
+
+# next to the rule that keeps 64 x 64 tiles: K up to 32 where there are enough big ones
+@pytest.mark.parametrize("dt", [torch.float32, torch.float64], ids=["f32", "f64"])
+@pytest.mark.parametrize("b,m,n,k", [(130, 254, 255, 15), (64, 256, 256, 16), (1, 1920, 1920, 32),
+                                     (130, 254, 255, 32), (55, 383, 381, 1)])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_gemm2_kept_tiles(dt, b, m, n, k, ta, tb):
     test_gemm2_ragged(dt, b, m, n, k, ta, tb)
 
 
