@@ -803,7 +803,13 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             const bool big = K > 32 && (o.maskC ? (M >= 2048 && N >= 2048) : (M >= 128 && N >= 128));
             const bool one_round = sizeof(T) == 8 && !f.rag && !(f.akf && f.bkf) && !o.maskC && t128 <= 256 &&
                                    t128 > (batch > 1 ? 192 : 224);
-            e = ((t128 >= (o.maskC ? 512 : 480) || one_round) && big && !padded) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64) ? 32 : 64);
+            // Two nearly full rounds of 64 x 64 tiles are better than quarter tiles where the chunks are ragged, which costs address arithmetic
+            // per load, and the quarters save no padding (b items of 61 x 174, K = 147, us, 32 x 32 -> 64 x 64: b = 331, 993 tiles, fp64
+            // 60 -> 44, fp32 29 -> 22; with one round and a half the products of potri's backward rule, 30 x 297 x 297, 220 -> 232; 26 x 2478 x 22, 1014
+            // tiles that the quarters halve, fp32 36 -> 54).
+            const bool two_rounds = f.rag && !o.maskC && !o.symsum && wg64 >= 960 &&
+                                    (int64_t)((M + 63) / 64) * ((N + 63) / 64) * 4 == (int64_t)((M + 31) / 32) * ((N + 31) / 32);
+            e = ((t128 >= (o.maskC ? 512 : 480) || one_round) && big && !padded) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64 && !two_rounds) ? 32 : 64);
         }
         if (o.symsum && e == 128)  // (the form that stores both triangles has tiles up to 64 only)
             e = 64;

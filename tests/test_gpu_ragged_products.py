@@ -66,10 +66,11 @@ def test_gemm2_big_tiles(dt, b, m, n, k, ta, tb):
     test_gemm2_ragged(dt, b, m, n, k, ta, tb)
 
 
-# next to the rule that keeps 64 x 64 tiles: K up to 32 where there are enough big ones
+# next to the rules that keep 64 x 64 tiles: K up to 32 where there are enough big ones, and ragged products of 960 tiles and more
 @pytest.mark.parametrize("dt", [torch.float32, torch.float64], ids=["f32", "f64"])
 @pytest.mark.parametrize("b,m,n,k", [(130, 254, 255, 15), (64, 256, 256, 16), (1, 1920, 1920, 32),
-                                     (130, 254, 255, 32), (55, 383, 381, 1)])
+                                     (130, 254, 255, 32), (55, 383, 381, 1), (319, 61, 174, 147),
+                                     (320, 61, 174, 147), (331, 63, 187, 255), (26, 2478, 22, 130)])
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
 def test_gemm2_kept_tiles(dt, b, m, n, k, ta, tb):
     test_gemm2_ragged(dt, b, m, n, k, ta, tb)
