@@ -175,12 +175,14 @@ static la_status inverse_merge(View<const T> Lam, View<T> Inv, View<T> Tmp, int6
 // ---------------------------------------------------------------------------------
 template <typename T>
 static la_status potrf_right_looking(View<T> Wk, View<T> L, int32_t *info, int off, int64_t batch, int n, View<T> Inv,
-                                     hipStream_t st)
+                                     bool need_inv, hipStream_t st)
 {
     constexpr int P = 2 * NB;
     for (int o = 0; o < n; o += P) {
         const int nb = n - o < P ? n - o : P, r = n - o - nb;
-        LA_TRY(launch_potrf_leaf16<T>(cv(Wk).sub(o, o), L.sub(o, o), Inv.sub(o, o), info, off + o, batch, nb, false, st));
+        // (nothing below the last block is solved with it: no inverse unless the caller merges them)
+        const View<T> inv = r > 0 || need_inv ? Inv.sub(o, o) : View<T>{nullptr, 0, 0, 0};
+        LA_TRY(launch_potrf_leaf16<T>(cv(Wk).sub(o, o), L.sub(o, o), inv, info, off + o, batch, nb, false, st));
         if (r == 0)
             break;
         View<T> L21 = L.sub(o + nb, o);
@@ -216,12 +218,12 @@ static la_status potrf_rec(View<T> Wk, View<T> L, int32_t *info, int off, int64_
                            View<T> Tmp, bool need_inv, hipStream_t st)
 {
     if (n <= 2 * NB)  // factor and inverse in one launch
-        return launch_potrf_leaf16<T>(cv(Wk), L, Inv, info, off, batch, n, false, st);
+        return launch_potrf_leaf16<T>(cv(Wk), L, need_inv ? Inv : View<T>{nullptr, 0, 0, 0}, info, off, batch, n, false, st);
     // Blocks of up to 2304 rows: panel by panel.  Measured against halving all the way down: one matrix
     // of n = 2048 0.95 -> 0.77 ms, 3000 1.78 -> 1.38, 4096 2.58 -> 2.19, 8192 8.62 -> 7.89 (fp64); with many
     // matrices in the batch the short products of the panels stop paying (32 x 1024: 0.91 -> 0.93).
     if (n <= 2304 && (double)batch * n * n < 24e6) {
-        LA_TRY(potrf_right_looking<T>(Wk, L, info, off, batch, n, Inv, st));
+        LA_TRY(potrf_right_looking<T>(Wk, L, info, off, batch, n, Inv, need_inv, st));
         return need_inv ? inverse_merge<T>(cv(L), Inv, Tmp, batch, n, n, st) : LA_OK;
     }
     const int n1 = split_point(n), n2 = n - n1;

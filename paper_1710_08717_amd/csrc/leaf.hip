@@ -2,25 +2,21 @@
 // one workgroup factors a block of edge nb <= 128 AND inverts the factor, because every panel
 // solve against this block later multiplies by that inverse.
 //
-// The block is cut into 16 x 16 tiles that live in LDS for the whole kernel.  Step k of the
-// right-looking sweep over the K = ceil(nb / 16) tile columns:
-//   (a) one wavefront factors the diagonal tile A_kk and inverts the factor in registers
-//       (lane = row, registers = columns, column broadcasts are DPP operands of the
-//       multiply-adds): L_kk, Li_kk;
-//   (b) panel      L_ik = A_ik Li_kk^T  (i > k)   and   X_kj <- Li_kk X_kj  (j < k), which
+// The block is cut into 16 x 16 tiles.  Step k of the right-looking sweep over the K = ceil(nb / 16) tile columns:
+//   (a) one wavefront factors the diagonal tile A_kk and inverts the factor: L_kk, Li_kk;
+//   (b) panel      L_ik = A_ik Li_kk^T  (i > k)   and   X_kj <- -Li_kk sum_m L_km X_mj  (j < k), which
 //       completes row k of the inverse X = L^-1;
-//   (c) trailing   A_ij -= L_ik L_jk^T  (k < j <= i)   and   X_ij -= L_ik X_kj  (i > k, j <= k).
-// (b) and (c) are 16 x 16 x 16 products on the matrix cores, one tile per wavefront at a
-// time.  The 16 * K pivots are strictly sequential, so what counts is the chain
-//   (a) -> panel tile (k+1, k) -> update of tile (k+1, k+1) -> (a) of the next step:
-// wavefront 0 walks exactly that chain while the other seven do the rest of (b) and (c) of
-// step k behind it (two workgroup barriers per step).
+//   (c) trailing   A_ij -= L_ik L_jk^T  (k < j <= i).
+// (b) and (c) are 16 x 16 x 16 products on the matrix cores.  The 16 * K pivots are strictly sequential, so what counts is the chain
+//   (a) -> panel tile (k+1, k) -> update of tile (k+1, k+1) -> (a) of the next step,
+// which wavefront 0 walks in registers (leaf_frag.hpp, leaf_dpp.hpp).  What bounds it: in fp32 the chain, 2.3 thousand cycles for (a) (140 per
+// pivot, fp64 the same) and 0.6 for the rest of a step; in fp64 the products of the three SIMDs beside it (217 of 256 cycles
+// each) and 0.95 thousand for the rest of a step.  Measured against tiles that all wavefronts take from LDS
+// and give back to it, one row per lane in (a) (us, fp64 and fp32): 32 blocks of 128, factor alone 26.8 -> 16.6 and 20.1 -> 12.5; potrf
+// of 32 x 512^2 206 -> 174 and 149 -> 123, of 1 x 3001^2 1392 -> 1121 and 1048 -> 811; the GP criterion of 256 x 128^2
+// 44.6 -> 31.3 and 31.2 -> 21.1.
 #include "common.hpp"
-#include "leaf_dpp.hpp"
-
-#ifndef LEAF16_STAMP
-#define LEAF16_STAMP(i)
-#endif
+#include "leaf_frag.hpp"
 
 namespace la {
 
@@ -440,97 +436,24 @@ __device__ __forceinline__ void leaf_store_lower(const LeafLds<T> &m, bool inver
     }
 }
 
-// The factorisation loop shared by the kernels below: on entry the lower tiles of the block are in
-// the A / L areas of m (and a workgroup barrier has passed), on return they hold the factor and the
-// X areas its inverse.  Returns, in wavefront 0, the 1-based index of the first pivot that is not
-// > 0 (0: none); ends with a workgroup barrier.
-template <typename T, int W = LEAF16_WAVES>
-__device__ __forceinline__ int leaf_factor(const LeafLds<T> &m, int K, int wave, int lane)
-{
-    int fail = 0;
-    if (wave == 0)
-        fail = leaf_diag<T>(m, 0, lane);
-    __syncthreads();
-    LEAF16_STAMP(1);
-
-    for (int k = 0; k < K; ++k) {
-        const int rows = K - 1 - k;  // tile rows below the pivot row
-        // ---- (b): wavefront 0 takes the panel tile the next diagonal tile depends on ------------
-        if (wave == 0) {
-            if (rows > 0)
-                leaf_panel<T>(m, k + 1, k, lane);
-        } else {
-            const int np = rows > 0 ? rows - 1 : 0;
-            for (int it = wave - 1; it < np + k; it += W - 1) {
-                if (it < np)
-                    leaf_panel<T>(m, k + 2 + it, k, lane);
-                else
-                    leaf_xrow<T>(m, k, it - np, lane);
-            }
-        }
-        __syncthreads();
-        LEAF16_STAMP(2 + 2 * k);
-        if (rows == 0)
-            break;
-        // ---- (c): wavefront 0 updates the next diagonal tile and factors it -----------------------
-        if (wave == 0) {
-            leaf_update_a<T>(m, k + 1, k + 1, k, lane);
-            const int f = leaf_diag<T>(m, k + 1, lane);
-            if (fail == 0 && f != 0)
-                fail = (k + 1) * LT + f;
-        } else {
-            const int nx = rows * (k + 1);           // tiles of the inverse to update
-            const int na = rows * (rows + 1) / 2 - 1;  // tiles of A, without tile (k+1, k+1)
-            int xi = 0, xj = wave - 1;                // item number it = xi * (k + 1) + xj
-            for (int it = wave - 1; it < nx + na; it += W - 1) {
-                if (it < nx) {
-                    while (xj > k) {
-                        xj -= k + 1;
-                        ++xi;
-                    }
-                    leaf_update_x<T>(m, k + 1 + xi, xj, k, lane);
-                    xj += W - 1;
-                } else {
-                    int ii, jj;
-                    tri_decode(it - nx + 1, ii, jj);
-                    leaf_update_a<T>(m, k + 1 + ii, k + 1 + jj, k, lane);
-                }
-            }
-        }
-        __syncthreads();
-        LEAF16_STAMP(3 + 2 * k);
-    }
-    return fail;
-}
-
 template <typename T>
 __global__ __launch_bounds__(LEAF16_THREADS) void k_potrf_leaf16(View<const T> A, View<T> L, View<T> Inv, int32_t *info,
                                                                  int info_off, int64_t batch, int nb, int zero_upper)
 {
-    using C = Leaf16<T>;
     extern __shared__ __align__(16) unsigned char leaf16_lds[];
-    T *lds = reinterpret_cast<T *>(leaf16_lds);
-    const LeafLds<T> m{lds + C::OFF_D, lds + C::OFF_XD, lds + C::OFF_A, lds + C::OFF_X};
-
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int K = (nb + LT - 1) / LT;  // tile columns in use
+    const FactorLds<T> m(reinterpret_cast<T *>(leaf16_lds), (nb + LT - 1) / LT);
     const int64_t b = blockIdx.x;
-    LEAF16_STAMP(31);
-
-    leaf_load_lower<T>(m, A.p + b * A.bs, A.rs, A.cs, nb, wave, lane);
-    __syncthreads();
-    LEAF16_STAMP(0);
-
-    const int fail = leaf_factor<T>(m, K, wave, lane);
-
-    // ---- factor and inverse back to memory (lower tiles; zeros above the diagonal inside the
-    //      diagonal tiles) -----------------------------------------------------------------------
-    leaf_store_lower<T>(m, false, L.p + b * L.bs, L.rs, L.cs, nb, zero_upper != 0, wave, lane);
-    if (Inv.p != nullptr)  // a stand-alone factorisation has no use for the inverse
-        leaf_store_lower<T>(m, true, Inv.p + b * Inv.bs, Inv.rs, Inv.cs, nb, false, wave, lane);
-    LEAF16_STAMP(30);
+    LEAF16_STAMP(63);
+    const bool inverse = Inv.p != nullptr;  // (a stand-alone factorisation has no use for it)
+    const TileIO<T> in(const_cast<T *>(A.p) + b * A.bs, A.rs, A.cs, nb, lane);
+    L.p += b * L.bs;
+    if (inverse)
+        Inv.p += b * Inv.bs;
+    const int fail = leaf_factor<T, LEAF16_WAVES, true>(m, in, L, Inv, nb, inverse, zero_upper != 0, wave, lane);
+    LEAF16_STAMP(61);
     if (info != nullptr && tid == 0 && fail != 0 && fail <= nb) {
         if (info[b] == 0)
             info[b] = info_off + fail;
@@ -1289,68 +1212,73 @@ template <typename T, int NW, int MAXK>
 __global__ __launch_bounds__(NW * 64) void k_gp_leaf16(View<const T> A, const T *y, T *loss, View<T> Abar, int32_t *info,
                                                        int64_t batch, int n)
 {
-    using C = Leaf16<T>;
     using MF = Mfma<T>;
+    using F = Frag<T>;
     extern __shared__ __align__(16) unsigned char leaf16_lds[];
     T *lds = reinterpret_cast<T *>(leaf16_lds);
-    constexpr int DT = C::DT;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t b = blockIdx.x;
     const int K = (n + LT - 1) / LT;
     const int ntl = K * (K + 1) / 2;
-    const int area = backward16_area<T>(K);
-    const LeafLds<T> m{lds, lds + area, lds + K * DT, lds + area + K * DT};
-    T *sy = lds + 2 * area, *sz = sy + LT * K, *sal = sz + LT * K, *sdi = sal + LT * K;  // y, z, alpha, 1 / l_ii
-
-    leaf_load_lower<T, NW, MAXK>(m, A.p + b * A.bs, A.rs, A.cs, n, wave, lane);
-    if (tid < LT * K)
-        sy[tid] = tid < n ? y[b * n + tid] : T(0);
-    __syncthreads();
+    const FactorLds<T> m(lds, K);
+    // y, z, alpha, 1 / l_ii in the two tiles that the factorisation passes operands through
+    T *sy = m.sH, *sz = sy + LT * K, *sal = sz + LT * K, *sdi = sal + LT * K;
+    static_assert(4 * LT * MAXK <= 2 * F::ELEMS, "the vectors fit two tiles");
 
     // ---- L and Li ------------------------------------------------------------------------------
-    const int fail = leaf_factor<T, NW>(m, K, wave, lane);
+    LEAF16_STAMP(63);
+    const T yv = tid < n ? y[b * n + tid] : T(0);
+    const TileIO<T> in(const_cast<T *>(A.p) + b * A.bs, A.rs, A.cs, n, lane);
+    const int fail = leaf_factor<T, NW, false>(m, in, View<T>{}, View<T>{}, n, true, false, wave, lane);
     if (info != nullptr && tid == 0 && fail != 0 && fail <= n)
         info[b] = fail;
+    if (tid < LT * K)
+        sy[tid] = yv;
+    __syncthreads();
 
-    // ---- z = Li y: MAXK threads per row, one tile column each ------------------------------------
-    // ---- alpha = Li^T z: MAXK threads per column, one tile row each -------------------------------
-    static_assert(NW * 64 == LT * MAXK * MAXK, "one thread per row and tile");
-    const int e = tid / MAXK, te = tid % MAXK, ue = e & 15, ke = e >> 4;  // row or column, tile along it
-    {
-        T part = T(0);
-        if (ke < K && te <= ke) {
-            const TileRef<T> t = m.x(ke, te);
+    // ---- z = Li y, a wavefront per tile row; 1 / l_ii -----------------------------------------------
+    const int r = chain_nat<T>(lane & 15), g = lane >> 4, fo = F::lane_at(lane);
+    if (wave < K) {
+        T part[4] = {};
+        for (int j = 0; j <= wave; ++j) {
+            T x[4];
+            F::load(m.x(wave, j), fo, x);
+            const T yj = sy[j * LT + r];
 #pragma unroll
-            for (int w = 0; w < LT; ++w)
-                part = fma(t.p[t.at(ue, w)], sy[te * LT + w], part);
+            for (int v = 0; v < 4; ++v) {
+                part[v] = fma(x[v], yj, part[v]);
+                if (j == wave && 4 * v + g == r)
+                    sdi[j * LT + r] = x[v];
+            }
         }
 #pragma unroll
-        for (int off = 1; off < MAXK; off <<= 1)
-            part += __shfl_xor(part, off, MAXK);
-        if (te == 0 && ke < K) {
-            sz[e] = part;
-            const TileRef<T> d = m.x(ke, ke);
-            sdi[e] = d.p[d.at(ue, ue)];
+        for (int v = 0; v < 4; ++v) {
+#pragma unroll
+            for (int off = 1; off < LT; off <<= 1)
+                part[v] += __shfl_xor(part[v], off, WAVE);
+            if ((lane & 15) == 0)
+                sz[wave * LT + 4 * v + g] = part[v];
         }
     }
     __syncthreads();
-    {
+    // ---- alpha = Li^T z, a wavefront per tile column ------------------------------------------------
+    if (wave < K) {
         T part = T(0);
-        if (te < K && ke <= te) {
-            const TileRef<T> t = m.x(te, ke);
+        for (int k = wave; k < K; ++k) {
+            T x[4];
+            F::load(m.x(k, wave), fo, x);
 #pragma unroll
-            for (int u = 0; u < LT; ++u)
-                part = fma(t.p[t.at(u, ue)], sz[te * LT + u], part);
+            for (int v = 0; v < 4; ++v)
+                part = fma(x[v], sz[k * LT + 4 * v + g], part);
         }
-#pragma unroll
-        for (int off = 1; off < MAXK; off <<= 1)
-            part += __shfl_xor(part, off, MAXK);
-        if (te == 0 && ke < K)
-            sal[e] = part;
+        part += __shfl_xor(part, 16, WAVE);
+        part += __shfl_xor(part, 32, WAVE);
+        if (lane < LT)
+            sal[wave * LT + r] = part;
     }
-    if (wave == 0) {  // loss = 1/2 |z|^2 - sum log(1 / l_ii)
+    if (wave == NW - 1) {  // loss = 1/2 |z|^2 - sum log(1 / l_ii)
         double acc = 0.0;
         for (int r = lane; r < n; r += 64)
             acc += 0.5 * (double)sz[r] * (double)sz[r] - (double)log(sdi[r]);
@@ -1362,41 +1290,42 @@ __global__ __launch_bounds__(NW * 64) void k_gp_leaf16(View<const T> A, const T 
     }
     __syncthreads();
 
-    // ---- Abar_ij, i >= j, stored with its mirror image through the tile's slot of the finished L ----
+    LEAF16_STAMP(59);
+    // ---- Abar_ij, i >= j, symmetric on the diagonal tiles as it stands; the others are stored with their mirror image, which
+    //      is turned in the tile's slot of the finished L ---------------------------------------------
     T *op = Abar.p + b * Abar.bs;
-    const bool colfast = (Abar.cs == 1) || (Abar.rs != 1);
-    const int f = lane & 15, s0 = lane >> 4;
     for (int t = wave; t < ntl; t += NW) {
         int i, j;
         tri_decode(t, i, j);
         typename MF::acc_t acc = {0, 0, 0, 0};
         for (int k = i; k < K; ++k) {
             T av[4], bv[4];
-            op_nat<T>(m.x(k, i), lane, av);
-            op_nat<T>(m.x(k, j), lane, bv);
-            acc = mma4<T>(av, bv, acc, false);
+            F::load(m.x(k, i), fo, av);
+            F::load(m.x(k, j), fo, bv);
+            acc = frag_mma<T>(av, bv, acc);
         }
-        const T aj = sal[j * LT + f];
+        const T aj = sal[j * LT + r];
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            acc[v] = T(0.5) * fma(-sal[i * LT + MF::row(lane, v)], aj, acc[v]);
-        const TileRef<T> st = m.a(i, j);
-        acc_store<T>(st, lane, acc);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            acc[v] = T(0.5) * fma(-sal[i * LT + 4 * v + g], aj, acc[v]);
+        T *st = i == j ? nullptr : m.l(i, j);
+        if (i != j) {
+            F::store(st, fo, acc);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int u = colfast ? s0 + 4 * v : f, w = colfast ? f : s0 + 4 * v;
-            const T direct = st.p[st.at(u, w)], mirror = st.p[st.at(w, u)];
-            const int r = i * LT + u, c = j * LT + w;
-            if (r < n && c < n)
-                op[(int64_t)r * Abar.rs + (int64_t)c * Abar.cs] = (i == j && u < w) ? mirror : direct;
-            const int r2 = j * LT + u, c2 = i * LT + w;
-            if (i != j && r2 < n && c2 < n)
-                op[(int64_t)r2 * Abar.rs + (int64_t)c2 * Abar.cs] = mirror;
+            const int row = i * LT + 4 * v + g, col = j * LT + r;
+            if (row < n && col < n)
+                op[(int64_t)row * Abar.rs + (int64_t)col * Abar.cs] = acc[v];
+            const int row2 = j * LT + 4 * v + g, col2 = i * LT + r;
+            if (i != j && row2 < n && col2 < n)
+                op[(int64_t)row2 * Abar.rs + (int64_t)col2 * Abar.cs] = st[F::at(4 * v + g, r)];
         }
     }
+    LEAF16_STAMP(61);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1546,7 +1475,7 @@ la_status launch_potrf_leaf16(View<const T> A, View<T> L, View<T> Inv, int32_t *
         return LA_OK;
     if (nb > LT * LK || batch > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
-    constexpr size_t lds_bytes = (size_t)Leaf16<T>::TOTAL * sizeof(T);
+    const size_t lds_bytes = (size_t)FactorLds<T>::elems((nb + LT - 1) / LT) * sizeof(T);
     if (dry_run())
         return LA_OK;
     static bool configured[64] = {};
@@ -1554,7 +1483,7 @@ la_status launch_potrf_leaf16(View<const T> A, View<T> L, View<T> Inv, int32_t *
     LA_HIP(hipGetDevice(&dev));
     if (dev >= 0 && dev < 64 && !configured[dev]) {
         LA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_potrf_leaf16<T>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)(FactorLds<T>::elems(LK) * sizeof(T))));
         configured[dev] = true;
     }
     LA_LAUNCH((k_potrf_leaf16<T>), dim3((unsigned)batch), dim3(LEAF16_THREADS), lds_bytes, st, A, L, Inv, info,
@@ -1897,7 +1826,7 @@ la_status launch_gp_leaf16(View<const T> A, const T *y, T *loss, View<T> Abar, i
     if (n > LT * LK || batch > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
     const int K = (n + LT - 1) / LT;
-    const size_t lds_bytes = (2 * (size_t)backward16_area<T>(K) + 4 * LT * K) * sizeof(T);
+    const size_t lds_bytes = (size_t)FactorLds<T>::elems(K) * sizeof(T);
     if (dry_run())
         return LA_OK;
     if (K <= 4) {  // (less than the 64 KB that need no attribute)
@@ -1908,7 +1837,7 @@ la_status launch_gp_leaf16(View<const T> A, const T *y, T *loss, View<T> Abar, i
     int dev = 0;
     LA_HIP(hipGetDevice(&dev));
     if (dev >= 0 && dev < 64 && !configured[dev]) {
-        const size_t most = (2 * (size_t)backward16_area<T>(LK) + 4 * LT * LK) * sizeof(T);
+        const size_t most = (size_t)FactorLds<T>::elems(LK) * sizeof(T);
         LA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gp_leaf16<T, LEAF16_WAVES, LK>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
         configured[dev] = true;

@@ -53,6 +53,21 @@ __device__ __forceinline__ double mul_row(double src, double other)
                  : "v"(src), "v"(other), "n"(K));
     return d;
 }
+// acc += (value of src in lane K of the row) * other
+template <int K>
+__device__ __forceinline__ void fmac_row(float &acc, float src, float other)
+{
+    asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+                 : "+v"(acc)
+                 : "v"(src), "v"(other), "n"(K));
+}
+template <int K>
+__device__ __forceinline__ void fmac_row(double &acc, double src, double other)
+{
+    asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+                 : "+v"(acc)
+                 : "v"(src), "v"(other), "n"(K));
+}
 // two wait states, with v routed through the statement so that whatever computes it stays before
 template <typename T>
 __device__ __forceinline__ void settle(T &v)
@@ -61,13 +76,12 @@ __device__ __forceinline__ void settle(T &v)
 }
 
 __device__ __forceinline__ float rcp_newton(float x) { return __builtin_amdgcn_rcpf(x); }
+// seed good to 2^-24, one third-order step r (1 + e + e^2), e = 1 - x r: three dependent multiply-adds
 __device__ __forceinline__ double rcp_newton(double x)
 {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 
 // x = row r of the inverse of a 16 x 16 lower-triangular tile (a[c] = row r of the tile, dr its
@@ -165,6 +179,118 @@ __device__ __forceinline__ int diag_factor_invert(T (&a)[LT], T (&x)[4], int r, 
         x[j] *= rs;  // row r times d_r^-1/2
     const unsigned first = (unsigned)(bad & 0xffffu);
     return first ? __builtin_ctz(first) + 1 : 0;
+}
+
+// acc += (value of acc in lane K of the row) * other
+template <int K>
+__device__ __forceinline__ void fmac_row_self(float &acc, float other)
+{
+    asm volatile("v_fmac_f32_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(other), "n"(K));
+}
+template <int K>
+__device__ __forceinline__ void fmac_row_self(double &acc, double other)
+{
+    asm volatile("v_fmac_f64_dpp %0, %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(other), "n"(K));
+}
+
+// ---------------------------------------------------------------------------------------
+// Factor and invert one 16 x 16 tile that a wavefront holds as a matrix-core accumulator.
+//
+// A single wavefront issues one instruction per 6 to 9 cycles whatever it is, so the chain of pivots is bound by their number.
+// The symmetric tile S is therefore shared out over the four lane groups: register v of group g (g = lane / 16) is column
+// 4 v + g, lane = row, which is the accumulator layout of the matrix cores.  A rank-1 update of the whole tile is then four multiply-adds
+// at most, whose second factor a_kc is the tile's own row k, a row broadcast of the register that is updated (S is symmetric,
+// so both triangles are kept up).  Only the first factor, column k, has to be known to all groups: four columns at a time go through
+// LDS, and the pivots of those four run on the copies.
+//
+// Rows and columns are numbered by chain_nat: the row of the tile that lane position l (of 16) stands for.  In fp64 it is l
+// itself; the fp32 accumulator holds rows 4 g + v instead of g + 4 v, so there the positions are relabelled,
+// which turns one layout into the other (the map is its own inverse).
+// ---------------------------------------------------------------------------------------
+template <typename T>
+__host__ __device__ constexpr int chain_nat(int l)
+{
+    return sizeof(T) == 8 ? l : 4 * (l % 4) + l / 4;
+}
+
+// t where keep, otherwise zero or (fp64, whose lower half is left alone) a number below the normal range: as good as zero
+// beside multipliers of order one, for one instruction
+__device__ __forceinline__ float keep_if(float t, bool keep) { return keep ? t : 0.0f; }
+__device__ __forceinline__ double keep_if(double t, bool keep)
+{
+    uint2 w = __builtin_bit_cast(uint2, t);
+    w.y = keep ? w.y : 0u;
+    return __builtin_bit_cast(double, w);
+}
+
+// In: S as above, both triangles.  r = chain_nat(lane % 16), g = lane / 16; row = row r of a tile in LDS (16-byte aligned, the
+// rows of different lanes apart).
+// Out: the tile's row r holds the columns of the factor times the square roots of their pivots (what lies above the diagonal is
+// left over), d = pivot r, X[v] = element (r, 4 v + g) of the inverse of the factor times the square root of pivot r (zero or as good
+// as zero above the diagonal).
+//
+// The pivots run on the unscaled matrix,   a_rc -= t_r a_kc,   x_rc -= t_r x_kc (r > k),   t_r = a_rk / a_kk.
+template <typename T>
+__device__ __forceinline__ void chain_diag(T (&S)[4], T *row, T &d, T (&X)[4], int r, int g)
+{
+    using V = typename Mfma<T>::vec_t;
+    constexpr int VW = Mfma<T>::VW;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        X[v] = (4 * v + g == r) ? T(1) : T(0);
+        asm volatile("" : "+v"(S[v]), "+v"(X[v]));  // their own registers from here on: no copies next to the broadcasts below
+    }
+    asm volatile("s_nop 1");
+    static_for<0, 4>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        T c[4];
+        row[4 * p + g] = S[p];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int h = 0; h < 4; h += VW) {
+            const V w = *reinterpret_cast<const V *>(row + 4 * p + h);
+            c[h] = w.x;
+            c[h + 1] = w.y;
+            if constexpr (VW == 4) {
+                c[2] = w.z;
+                c[3] = w.w;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        T rinv = rcp_newton(c[0]);  // meaningful in the pivot's lane only
+        static_for<0, 4>([&](auto qc) {
+            constexpr int q = decltype(qc)::value, k = 4 * p + q, K = chain_nat<T>(k);
+            T nt = T(0);  // -t
+            settle(rinv);
+            fnmac_row<K>(nt, rinv, c[q]);
+            if constexpr (q < 3) {
+                fmac_row<chain_nat<T>(k + 1)>(c[q + 1], c[q], nt);
+                rinv = rcp_newton(c[q + 1]);  // overlaps the rest of this pivot's updates
+            }
+            if constexpr (q < 2)
+                fmac_row<chain_nat<T>(k + 2)>(c[q + 2], c[q], nt);
+            if constexpr (q < 1)
+                fmac_row<chain_nat<T>(k + 3)>(c[q + 3], c[q], nt);
+            static_for<p + 1, 4>([&](auto vc) { fmac_row_self<K>(S[decltype(vc)::value], nt); });
+            if constexpr (k + 1 < LT) {
+                const T tm = keep_if(nt, r > k);
+                static_for<0, p + 1>([&](auto vc) { fmac_row_self<K>(X[decltype(vc)::value], tm); });
+            }
+        });
+#pragma unroll
+        for (int h = 0; h < 4; h += VW) {
+            V w;
+            w.x = c[h];
+            w.y = c[h + 1];
+            if constexpr (VW == 4) {
+                w.z = c[2];
+                w.w = c[3];
+            }
+            *reinterpret_cast<V *>(row + 4 * p + h) = w;
+        }
+    });
+    __builtin_amdgcn_wave_barrier();
+    d = row[r];
 }
 
 }  // namespace la
