@@ -648,6 +648,27 @@ la_status launch_rank1_add(T *C, const T *u, const T *v, int rows, int cols, hip
 template <typename T>
 la_status launch_sgp_scalars(const double *sums, double lam, int n, T *phi, T *noise_bar, T *kff_bar, int nk, hipStream_t st);
 
+// Many matrices of 32 < n <= 64, one wavefront each (small_wave.hip).
+enum class SmallWaveOp { potrf, backward, potri, potri_backward };
+template <typename T>
+bool small_wave_takes(SmallWaveOp op, int64_t batch, int n);
+template <typename T>
+bool trsm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out);
+template <typename T>
+la_status launch_potrf_wave(View<const T> A, View<T> L, int32_t *info, int64_t batch, int n, hipStream_t st);
+template <typename T>
+la_status launch_backward_wave(View<const T> Lam, View<const T> G, View<T> Abar, int64_t batch, int n, hipStream_t st);
+template <typename T>
+la_status launch_potri_wave(View<const T> Lam, View<T> B, int64_t batch, int n, hipStream_t st);
+// any number of vectors; X may be Xin
+template <typename T>
+la_status launch_trsm_wave(View<const T> Lam, View<const T> Xin, View<T> X, int64_t batch, int n, int m, T alpha, bool fwd,
+                           hipStream_t st);
+// out = -(upper triangle, with the diagonal, of Lam^-1 (Bbar + Bbar^T) B), zeros below it
+template <typename T>
+la_status launch_potri_backward_wave(View<const T> Lam, View<const T> B, View<const T> Bbar, View<T> out, int64_t batch, int n,
+                                     hipStream_t st);
+
 // Gaussian-process criterion and gradient, one workgroup per matrix (leaf.hip); n <= 128.
 template <typename T>
 la_status launch_gp_leaf16(View<const T> A, const T *y, T *loss, View<T> Abar, int32_t *info, int64_t batch, int n,

@@ -305,6 +305,8 @@ static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, in
     // (25 against 37 us), so the batch size decides.
     if (n <= 16 || (n <= 32 && batch > 2048))
         return launch_backward_tiny<T>(Lam, G, W, batch, n, st);
+    if (small_wave_takes<T>(SmallWaveOp::backward, batch, n))  // one wavefront per matrix
+        return launch_backward_wave<T>(Lam, G, W, batch, n, st);
     if (n <= backward_leaf16_max_n<T>())  // one workgroup per matrix, everything in LDS, no scratch
         return launch_backward_leaf16<T>(Lam, G, W, batch, n, st);
     ArenaFrame frame;
@@ -408,11 +410,11 @@ static la_status potrf_t(int lower, int64_t batch, int n, const void *A, void *L
     View<T> Lv = tri_view<T>((T *)L, n, lower);
     if (info)
         LA_TRY(launch_fill_i32(info, batch, 0, st));
-    // Many matrices of up to four tile rows: four wavefronts per matrix, tiles in LDS.  Measured against the lane-group
-    // kernels at equal data volume, n = 33 ... 64 (us, fp32: 146 -> 111, 113 -> 84 at 38, 146 -> 71 at 41, 57 -> 42 at 48,
-    // 90 -> 59 at 56, 56 -> 38 at 64; fp64: 334 -> 180, 161 -> 73 at 48, 123 -> 64 at 64); only fp32 at n = 40, whose rows fill
-    // the three-rows-per-lane kernel exactly, is faster there (54 against 75).
-    if (n > 32 && n <= NB && batch > 1024 && !(sizeof(T) == 4 && n == 40))
+    // Many matrices of three or four tile rows: one wavefront each, or four with the tiles in LDS (against the lane-group kernels at
+    // equal data volume, us: n = 41 fp32 146 -> 71, 48 57 -> 42 and fp64 161 -> 73, 56 90 -> 59, 64 56 -> 38 and 123 -> 64).
+    if (small_wave_takes<T>(SmallWaveOp::potrf, batch, n))
+        return launch_potrf_wave<T>(Av, Lv, info, batch, n, st);
+    if (n > 32 && n <= NB && batch > 1024)
         return launch_potrf_small16<T>(Av, Lv, info, batch, n, st);
     if (n <= NB)
         return launch_potrf_tiny<T>(Av, Lv, info, 0, batch, n, st);
@@ -542,6 +544,9 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
 
     if (leaf_mul)  // (operands the lane-group kernels do not take: other strides)
         return launch_trmm_leaf<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
+
+    if (solve && Lam.nb2 == 1 && trsm_wave_takes<T>(batch, n, m, Xin, X))  // one wavefront per item, no scratch
+        return launch_trsm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
 
     if (solve && n <= 128 && m <= 48)  // small: one workgroup per item does the whole substitution, no scratch
         return launch_trsm_leaf16<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
@@ -817,6 +822,8 @@ static la_status potri_t(int lower, int64_t batch, int n, const void *L, void *B
     View<const T> Lam = tri_view<const T>((const T *)L, n, lower);
     if (n <= 32)  // both solves on the identity in registers, G lanes per matrix (two rows per lane above 16)
         return launch_potri_tiny<T>(Lam, View<T>{(T *)B, (int64_t)n * n, n, 1}, batch, n, st);
+    if (small_wave_takes<T>(SmallWaveOp::potri, batch, n))  // one wavefront per matrix
+        return launch_potri_wave<T>(Lam, View<T>{(T *)B, (int64_t)n * n, n, 1}, batch, n, st);
     if (n <= 2 * NB)  // one workgroup per matrix, everything in LDS, no scratch
         return launch_potri_leaf16<T>(Lam, View<T>{(T *)B, (int64_t)n * n, n, 1}, batch, n, st);
     ArenaFrame frame;
@@ -837,6 +844,11 @@ static la_status potri_backward_t(int lower, int64_t batch, int n, const void *L
     const int64_t nn = (int64_t)n * n;
     View<const T> Bv{(const T *)B, nn, n, 1}, G{(const T *)Bbar, nn, n, 1};
     View<T> X{(T *)Lbar, nn, n, 1};
+    if (small_wave_takes<T>(SmallWaveOp::potri_backward, batch, n)) {  // all of it in one launch, a wavefront per matrix
+        const View<const T> Lam = tri_view<const T>((const T *)L, n, lower);
+        return lower ? launch_potri_backward_wave<T>(Lam, Bv.t(), G, X.t(), batch, n, st)
+                     : launch_potri_backward_wave<T>(Lam, Bv, G, X, batch, n, st);
+    }
     GemmOpts o;
     // Both products in one launch on G + G^T (8192 matrices, the whole rule, us, fp32 and fp64: n = 17 127 -> 73 and 206 -> 89,
     // 40 215 -> 144 and 433 -> 251; 4096 of n = 48 118 -> 90 and 198 -> 146); at n = 64 the tiles of the general product are

@@ -1,0 +1,708 @@
+// Many matrices of 32 < n <= 64: one wavefront per matrix, the whole operator in registers.
+//
+// The one-workgroup kernels of leaf.hip give such a matrix four wavefronts and keep its 16 x 16 tiles in LDS; with nine or ten
+// tiles they spend their time in barriers and in LDS round trips between products of one tile each.  Here a wavefront holds all tiles
+// itself and never waits for another.  A tile is held as the matrix cores leave their accumulators (the COLS fragments of
+// leaf_frag.hpp: lane (g, p) has the rows 4 v + g of column nat(p)), and that is the first operand of A^T B and the second of
+// A B.  Every operator is therefore phrased in products  X^T Y  of tiles as they stand, some of them kept transposed; LDS
+// only turns a tile where its transpose is wanted, too, or where memory runs the other way.
+#include "leaf_frag.hpp"
+
+namespace la {
+
+namespace {
+
+constexpr int SW_WAVES = 4;  // matrices per workgroup
+
+constexpr __host__ __device__ int tri_at(int i, int j) { return i * (i + 1) / 2 + j; }  // tile (i, j), i >= j
+
+// order the wavefront's own LDS accesses
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One matrix in memory, R x C elements, any strides.
+template <typename T>
+struct Mat {
+    T *p;
+    unsigned rs, cs;
+    int R, C;
+    __device__ __forceinline__ Mat t() const { return Mat{p, cs, rs, C, R}; }
+};
+
+template <typename T>
+struct Wave {
+    static constexpr int PS = LT + 16 / (int)sizeof(T);  // row stride of a tile in LDS
+    static constexpr int TILE = LT * PS;
+    T *lds;  // one tile's room
+    int r, g, c;  // natural row of the lane, lane group, nat(p)
+
+    __device__ __forceinline__ Wave(T *l, int lane) : lds(l), r(lane & 15), g(lane >> 4), c(chain_nat<T>(lane & 15)) {}
+
+    __device__ __forceinline__ void turn(const T (&x)[4], T (&y)[4]) const
+    {
+        wave_sync();
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            lds[(4 * v + g) * PS + c] = x[v];
+        wave_sync();
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            y[v] = lds[c * PS + 4 * v + g];
+    }
+    // element (4 v + g, c) of tile (i, j) as it lies in memory; zero beyond the matrix (read from addresses inside it)
+    template <typename M>
+    __device__ __forceinline__ void load_direct(const Mat<M> &m, int i, int j, T (&x)[4]) const
+    {
+        const int col = LT * j + c, cc = min(col, m.C - 1);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = LT * i + 4 * v + g, rr = min(row, m.R - 1);
+            const T e = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(m.p) +
+                                                     ((unsigned)rr * m.rs + (unsigned)cc * m.cs) * (unsigned)sizeof(T));
+            x[v] = row < m.R && col < m.C ? e : T(0);
+        }
+    }
+    __device__ __forceinline__ void store_direct(const Mat<T> &m, int i, int j, const T (&x)[4]) const
+    {
+        const int col = LT * j + c;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = LT * i + 4 * v + g;
+            if (row < m.R && col < m.C)
+                *reinterpret_cast<T *>(reinterpret_cast<char *>(m.p) + ((unsigned)row * m.rs + (unsigned)col * m.cs) * (unsigned)sizeof(T)) =
+                    x[v];
+        }
+    }
+    // the same along the direction in which the matrix is contiguous
+    template <typename M>
+    __device__ __forceinline__ void load(const Mat<M> &m, int i, int j, T (&x)[4]) const
+    {
+        if (m.cs == 1 || m.rs != 1) {
+            load_direct(m, i, j, x);
+        } else {
+            T y[4];
+            load_direct(m.t(), j, i, y);
+            turn(y, x);
+        }
+    }
+    __device__ __forceinline__ void store(const Mat<T> &m, int i, int j, const T (&x)[4]) const
+    {
+        if (m.cs == 1 || m.rs != 1) {
+            store_direct(m, i, j, x);
+        } else {
+            T y[4];
+            turn(x, y);
+            store_direct(m.t(), j, i, y);
+        }
+    }
+    // lower triangle of a diagonal tile, `pad` on the diagonal beyond row n
+    __device__ __forceinline__ void keep_lower(T (&x)[4], int i, int n, T pad) const
+    {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = 4 * v + g;
+            x[v] = row < c ? T(0) : x[v];
+            if (row == c && LT * i + row >= n)
+                x[v] = pad;
+        }
+    }
+    // tile (i, j) of a symmetric result and its mirror image
+    __device__ __forceinline__ void store_sym(const Mat<T> &m, int i, int j, T (&x)[4]) const
+    {
+        T y[4];
+        turn(x, y);
+        if (i == j) {  // both halves take the lower half's values: exactly symmetric
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] = 4 * v + g < c ? y[v] : x[v];
+            store_direct(m, i, i, x);
+        } else {
+            store_direct(m, i, j, x);
+            store_direct(m, j, i, y);
+        }
+    }
+    // inverse of a lower-triangular diagonal tile (zeros above the diagonal) and its transpose; in: the tile
+    __device__ __forceinline__ void invert(const T (&l)[4], T (&li)[4], T (&lit)[4]) const
+    {
+        using V = typename Mfma<T>::vec_t;
+        constexpr int VW = Mfma<T>::VW;
+        wave_sync();
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            lds[(4 * v + g) * PS + c] = l[v];
+        wave_sync();
+        T a[LT], x[4];
+        T *row = lds + r * PS;
+#pragma unroll
+        for (int q = 0; q < LT; q += VW) {
+            const V w = *reinterpret_cast<const V *>(row + q);
+            a[q] = w.x;
+            a[q + 1] = w.y;
+            if constexpr (VW == 4) {
+                a[q + 2] = w.z;
+                a[q + 3] = w.w;
+            }
+        }
+        diag_invert<T>(a, row[r], x, r, g);
+        wave_sync();
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            row[4 * j + g] = (4 * j + g <= r) ? x[j] : T(0);
+        wave_sync();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            li[v] = lds[(4 * v + g) * PS + c];
+            lit[v] = lds[c * PS + 4 * v + g];
+        }
+    }
+};
+
+template <typename T>
+using Acc = typename Mfma<T>::acc_t;
+
+template <typename T>
+__device__ __forceinline__ void set(T (&x)[4], const Acc<T> &a)
+{
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        x[v] = a[v];
+}
+template <typename T>
+__device__ __forceinline__ void set_neg(T (&x)[4], const Acc<T> &a)
+{
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        x[v] = -a[v];
+}
+
+// the matrix this wavefront works on
+__device__ __forceinline__ int64_t my_item()
+{
+    return (int64_t)blockIdx.x * SW_WAVES + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+template <typename T>
+__device__ __forceinline__ Mat<T> item_of(const View<T> &v, int64_t b, int R, int C)
+{
+    return Mat<T>{v.p + b * v.bs, (unsigned)v.rs, (unsigned)v.cs, R, C};
+}
+
+// Lower-triangular factor: its tiles, the inverses of the diagonal ones and their transposes.
+template <typename T, int K>
+__device__ __forceinline__ void load_lower(const Wave<T> &w, const Mat<const T> &m, T pad, T (&l)[K * (K + 1) / 2][4])
+{
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j)
+            w.load(m, i, j, l[tri_at(i, j)]);
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+        w.keep_lower(l[tri_at(i, i)], i, m.R, pad);
+}
+
+// Li = L^-1, tile by tile:  Li_ij = -Li_ii sum_{k = j..i-1} L_ik Li_kj
+template <typename T, int K>
+__device__ __forceinline__ void invert_lower(const Wave<T> &w, const T (&l)[K * (K + 1) / 2][4], T (&li)[K * (K + 1) / 2][4])
+{
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        T lit[4];
+        w.invert(l[tri_at(i, i)], li[tri_at(i, i)], lit);
+        T lt[K][4];
+#pragma unroll
+        for (int k = 0; k < i; ++k)
+            w.turn(l[tri_at(i, k)], lt[k]);
+#pragma unroll
+        for (int j = 0; j < i; ++j) {
+            Acc<T> acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = j; k < i; ++k)
+                acc = frag_mma<T>(lt[k], li[tri_at(k, j)], acc);
+            T s[4];
+            set_neg<T>(s, acc);
+            acc = Acc<T>{0, 0, 0, 0};
+            acc = frag_mma<T>(lit, s, acc);
+            set<T>(li[tri_at(i, j)], acc);
+        }
+    }
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------------------------------
+// potrf.  The tiles above the diagonal, U_kj = L_jk^T:  U_kj = L_kk^-1 A_kj,  A_ij -= U_ki^T U_kj (k < i <= j).  chain_diag takes the
+// diagonal tile as it stands in the accumulator and leaves the transpose of its inverse, which is what the next product takes.
+// ---------------------------------------------------------------------------------------
+template <typename T, int K>
+__global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_potrf_wave(View<const T> A, View<T> L, int32_t *info,
+                                                                                          int64_t batch, int n)
+{
+    using W = Wave<T>;
+    __shared__ __align__(16) T lds[SW_WAVES][W::TILE];
+    const int64_t b = my_item();
+    if (b >= batch)
+        return;
+    const W w(lds[threadIdx.x >> 6], threadIdx.x & 63);
+    const Mat<const T> Am = item_of<const T>(A, b, n, n);
+    const Mat<T> Lm = item_of<T>(L, b, n, n);
+
+    T u[K * (K + 1) / 2][4];  // tile (i, j) holds A_ij^T
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j)
+            w.load(Am, i, j, u[tri_at(i, j)]);
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+#pragma unroll
+        for (int j = 0; j < i; ++j)
+            w.turn(u[tri_at(i, j)], u[tri_at(i, j)]);
+        T y[4];
+        T(&x)[4] = u[tri_at(i, i)];
+        w.turn(x, y);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = 4 * v + w.g;
+            x[v] = row < w.c ? y[v] : x[v];
+            if (row == w.c && LT * i + row >= n)
+                x[v] = T(1);
+        }
+    }
+    int fail = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        T d, x[4];
+        wave_sync();
+        chain_diag<T>(u[tri_at(k, k)], w.lds + w.c * W::PS, d, x, w.c, w.g);
+        const unsigned bad = (unsigned)(__ballot(!(d > T(0))) & 0xffffu);
+        if (bad && fail == 0) {
+#pragma unroll
+            for (int q = LT - 1; q >= 0; --q)
+                fail = (bad >> chain_nat<T>(q)) & 1 ? LT * k + q + 1 : fail;
+        }
+        const T rs = rsqrt_acc(d);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            x[v] *= rs;
+        T dt[4];
+        wave_sync();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const T e = w.lds[(4 * v + w.g) * W::PS + w.c] * rs;
+            dt[v] = 4 * v + w.g < w.c ? T(0) : e;
+        }
+#pragma unroll
+        for (int j = k + 1; j < K; ++j) {
+            Acc<T> acc = {0, 0, 0, 0};
+            acc = frag_mma<T>(x, u[tri_at(j, k)], acc);
+            set<T>(u[tri_at(j, k)], acc);
+        }
+#pragma unroll
+        for (int j = k + 1; j < K; ++j) {
+            T nu[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                nu[v] = -u[tri_at(j, k)][v];
+#pragma unroll
+            for (int i = k + 1; i <= j; ++i) {
+                T(&t)[4] = u[tri_at(j, i)];
+                Acc<T> acc = {t[0], t[1], t[2], t[3]};
+                acc = frag_mma<T>(u[tri_at(i, k)], nu, acc);
+                set<T>(t, acc);
+            }
+        }
+        w.store(Lm, k, k, dt);
+    }
+    const T zero[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = 0; j < i; ++j) {
+            w.store(Lm.t(), j, i, u[tri_at(i, j)]);
+            if (Lm.cs == 1 || Lm.rs != 1)
+                w.store_direct(Lm, j, i, zero);
+            else
+                w.store_direct(Lm.t(), i, j, zero);
+        }
+    if (info != nullptr && (threadIdx.x & 63) == 0 && fail != 0 && fail <= n)
+        if (info[b] == 0)
+            info[b] = fail;
+}
+
+// ---------------------------------------------------------------------------------------
+// potrf backward:  Abar = sym(L^-T Phi(L^T Lbar) L^-1).  P is formed transposed, so that Z = P Li and
+// Abar_ij = 1/2 sum_{k >= i} (Li_ki^T Z_kj + Z_ki^T Li_kj) are products of tiles as they stand.
+// ---------------------------------------------------------------------------------------
+template <typename T, int K>
+__global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : (sizeof(T) * K <= 24 ? 3 : 1)) void k_backward_wave(
+    View<const T> Lam, View<const T> G, View<T> Abar, int64_t batch, int n)
+{
+    using W = Wave<T>;
+    constexpr int NT = K * (K + 1) / 2;
+    __shared__ __align__(16) T lds[SW_WAVES][W::TILE];
+    const int64_t b = my_item();
+    if (b >= batch)
+        return;
+    const W w(lds[threadIdx.x >> 6], threadIdx.x & 63);
+    T l[NT][4], pt[NT][4], li[NT][4];
+    {
+        T gb[NT][4];
+        load_lower<T, K>(w, item_of<const T>(Lam, b, n, n), T(1), l);
+        load_lower<T, K>(w, item_of<const T>(G, b, n, n), T(0), gb);
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+#pragma unroll
+            for (int k = 0; k <= i; ++k) {  // (P_ik)^T = sum_{q >= i} Lbar_qk^T L_qi
+                Acc<T> acc = {0, 0, 0, 0};
+#pragma unroll
+                for (int q = i; q < K; ++q)
+                    acc = frag_mma<T>(gb[tri_at(q, k)], l[tri_at(q, i)], acc);
+                if (i == k) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int row = 4 * v + w.g;
+                        acc[v] = row > w.c ? T(0) : (row == w.c ? T(0.5) * acc[v] : acc[v]);
+                    }
+                }
+                set<T>(pt[tri_at(i, k)], acc);
+            }
+    }
+    invert_lower<T, K>(w, l, li);
+    T z[NT][4];
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            Acc<T> acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = j; k <= i; ++k)
+                acc = frag_mma<T>(pt[tri_at(i, k)], li[tri_at(k, j)], acc);
+            set<T>(z[tri_at(i, j)], acc);
+        }
+    Mat<T> out = item_of<T>(Abar, b, n, n);
+    if (out.rs == 1)  // symmetric: the transposed view is the same matrix
+        out = out.t();
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            Acc<T> acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = i; k < K; ++k) {
+                acc = frag_mma<T>(li[tri_at(k, i)], z[tri_at(k, j)], acc);
+                acc = frag_mma<T>(z[tri_at(k, i)], li[tri_at(k, j)], acc);
+            }
+            T x[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] = T(0.5) * acc[v];
+            w.store_sym(out, i, j, x);
+        }
+}
+
+// ---------------------------------------------------------------------------------------
+// potri:  B_ij = sum_{k >= i} Li_ki^T Li_kj
+// ---------------------------------------------------------------------------------------
+template <typename T, int K>
+__global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_potri_wave(View<const T> Lam, View<T> B, int64_t batch,
+                                                                                          int n)
+{
+    using W = Wave<T>;
+    constexpr int NT = K * (K + 1) / 2;
+    __shared__ __align__(16) T lds[SW_WAVES][W::TILE];
+    const int64_t b = my_item();
+    if (b >= batch)
+        return;
+    const W w(lds[threadIdx.x >> 6], threadIdx.x & 63);
+    T l[NT][4], li[NT][4];
+    load_lower<T, K>(w, item_of<const T>(Lam, b, n, n), T(1), l);
+    invert_lower<T, K>(w, l, li);
+    const Mat<T> out = item_of<T>(B, b, n, n);
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            Acc<T> acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = i; k < K; ++k)
+                acc = frag_mma<T>(li[tri_at(k, i)], li[tri_at(k, j)], acc);
+            T x[4];
+            set<T>(x, acc);
+            w.store_sym(out, i, j, x);
+        }
+}
+
+// ---------------------------------------------------------------------------------------
+// trsm:  X = alpha t(L)^-1 B on any number of vectors, 16 at a time.
+//   fwd:  X_k = L_kk^-1 (B_k - sum_{j < k} L_kj X_j);   otherwise  X_k = L_kk^-T (B_k - sum_{i > k} L_ik^T X_i)
+// ---------------------------------------------------------------------------------------
+template <typename T, int K, bool FWD>
+__global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_trsm_wave(View<const T> Lam, View<const T> Xin, View<T> X,
+                                                                                         int64_t batch, int n, int m, T alpha)
+{
+    using W = Wave<T>;
+    constexpr int NT = K * (K + 1) / 2;
+    __shared__ __align__(16) T lds[SW_WAVES][W::TILE];
+    const int64_t b = my_item();
+    if (b >= batch)
+        return;
+    const W w(lds[threadIdx.x >> 6], threadIdx.x & 63);
+    T l[NT][4];  // below the diagonal L_ij^T (fwd) or L_ij, on it L_ii^-T or L_ii^-1
+    load_lower<T, K>(w, item_of<const T>(Lam, b, n, n), T(1), l);
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        T li[4], lit[4];
+        w.invert(l[tri_at(i, i)], li, lit);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            l[tri_at(i, i)][v] = FWD ? lit[v] : li[v];
+        if constexpr (FWD)
+#pragma unroll
+            for (int j = 0; j < i; ++j)
+                w.turn(l[tri_at(i, j)], l[tri_at(i, j)]);
+    }
+    const Mat<const T> in = item_of<const T>(Xin, b, n, m);
+    const Mat<T> out = item_of<T>(X, b, n, m);
+    for (int ct = 0; ct * LT < m; ++ct) {
+        T x[K][4];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            w.load(in, k, ct, x[k]);
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+            const int k = FWD ? q : K - 1 - q;
+            Acc<T> acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+                if (FWD ? j < k : j > k)
+                    acc = frag_mma<T>(l[FWD ? tri_at(k, j) : tri_at(j, k)], x[j], acc);
+            T s[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                s[v] = fma(alpha, x[k][v], -acc[v]);
+            acc = Acc<T>{0, 0, 0, 0};
+            acc = frag_mma<T>(l[tri_at(k, k)], s, acc);
+            set<T>(x[k], acc);
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            w.store(out, k, ct, x[k]);
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// potri backward:  with S = Bbar + Bbar^T and Q = L^-1 S B^T (lower; B for an upper factor) the result is minus the
+// part of Q on and above its diagonal, transposed for a lower factor, and zeros.
+// ---------------------------------------------------------------------------------------
+template <typename T, int K>
+__global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 12 ? 4 : (sizeof(T) * K <= 24 ? 2 : 1)) void k_potri_backward_wave(
+    View<const T> Lam, View<const T> B, View<const T> Bbar, View<T> Lbar, int64_t batch, int n)
+{
+    using W = Wave<T>;
+    constexpr int NT = K * (K + 1) / 2;
+    __shared__ __align__(16) T lds[SW_WAVES][W::TILE];
+    const int64_t b = my_item();
+    if (b >= batch)
+        return;
+    const W w(lds[threadIdx.x >> 6], threadIdx.x & 63);
+    T s[K][K][4];
+    {
+        const Mat<const T> m = item_of<const T>(Bbar, b, n, n);
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+                w.load_direct(m, i, j, s[i][j]);
+    }
+    T l[NT][4];  // L_ij^T below the diagonal, L_ii^-T on it
+    load_lower<T, K>(w, item_of<const T>(Lam, b, n, n), T(1), l);
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            T y[4];
+            w.turn(s[j][i], y);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                s[i][j][v] += y[v];
+            if (i != j)
+                w.turn(s[i][j], s[j][i]);
+        }
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        T li[4], lit[4];
+        w.invert(l[tri_at(i, i)], li, lit);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            l[tri_at(i, i)][v] = lit[v];
+#pragma unroll
+        for (int j = 0; j < i; ++j)
+            w.turn(l[tri_at(i, j)], l[tri_at(i, j)]);
+    }
+    const Mat<const T> Bm = item_of<const T>(B, b, n, n);
+    const Mat<T> out = item_of<T>(Lbar, b, n, n);
+    const T zero[4] = {0, 0, 0, 0};
+    T q[NT][4];  // tile (j, i), i <= j, holds Q_ij
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        T bt[K][4];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            w.load(Bm, k, j, bt[k]);
+#pragma unroll
+        for (int i = 0; i <= j; ++i) {
+            Acc<T> y = {0, 0, 0, 0}, acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                y = frag_mma<T>(s[k][i], bt[k], y);
+#pragma unroll
+            for (int k = 0; k < i; ++k)
+                acc = frag_mma<T>(l[tri_at(i, k)], q[tri_at(j, k)], acc);
+            T e[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                e[v] = y[v] - acc[v];
+            acc = Acc<T>{0, 0, 0, 0};
+            acc = frag_mma<T>(l[tri_at(i, i)], e, acc);
+            set<T>(q[tri_at(j, i)], acc);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j)
+#pragma unroll
+        for (int i = 0; i <= j; ++i) {
+            T e[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                e[v] = i == j && 4 * v + w.g > w.c ? T(0) : -q[tri_at(j, i)][v];
+            w.store(out, i, j, e);
+            if (i != j) {
+                if (out.cs == 1)
+                    w.store_direct(out, j, i, zero);
+                else
+                    w.store_direct(out.t(), i, j, zero);
+            }
+        }
+}
+
+// ---------------------------------------------------------------------------------------
+// launches: 32 < n <= 64, three or four tile rows
+// ---------------------------------------------------------------------------------------
+// Against the four-wavefront kernels (1025 matrices or more; us, fp32 / fp64):
+//   12255 of n = 37: potrf 88 -> 41 / 140 -> 69, backward 142 -> 77 / 214 -> 162, potri 73 -> 39 / 96 -> 65, its backward rule
+//   207 -> 99 / 370 -> 288, trsm of 16 vectors 59 -> 40 / 79 -> 56, of 37 85 -> 79 / 176 -> 142;
+//   5001 of n = 51: 55 -> 32 / 83 -> 56, 109 -> 68 / 205 -> 154, 52 -> 32 / 118 -> 66, 311 -> 135 / 575 -> 347.
+// A wavefront alone takes longer than four: with 1100 matrices of n = 64, fp32, potrf 16 -> 20, backward 34 -> 36 (1600: 21 -> 21, 41 -> 38;
+// 1100 of n = 37: 14 -> 10, 22 -> 15), hence the second line.  Where nothing is ragged the four-wavefront kernels move
+// 16-byte pieces, and from memory (not the last-level cache) they are then the faster ones: 16384 of n = 64, fp32, potrf 141 -> 180,
+// 4096 37 -> 30; 20000 of n = 48 109 -> 120, 7281 42 -> 33; backward 7281 of n = 48, fp64, 121 -> 138, 2048 39 -> 34.
+// potrf in fp64 with four tile rows is equal there: 8000 of n = 60 133 -> 142, 5001 of n = 51 83 -> 56.
+template <typename T>
+bool small_wave_takes(SmallWaveOp op, int64_t batch, int n)
+{
+    if (n <= 2 * LT || n > 4 * LT || batch <= 1024 || batch > 0x7fffffffll)
+        return false;
+    if (op == SmallWaveOp::potri_backward)
+        return true;
+    if (n > 40 && batch <= 1536)
+        return false;
+    const double mib = (double)batch * n * n * sizeof(T) / 1048576.0;
+    if (n % LT == 0)
+        return mib <= 64.0;
+    return !(op == SmallWaveOp::potrf && sizeof(T) == 8 && n > 3 * LT && mib > 128.0);
+}
+template bool small_wave_takes<float>(SmallWaveOp, int64_t, int);
+template bool small_wave_takes<double>(SmallWaveOp, int64_t, int);
+
+// More than 48 vectors went through the inverse and a product before: 5001 of n = 51 with 51 vectors 167 -> 81 / 317 -> 167.  Up to
+// 48 the other kernel gives every tile of vectors a wavefront of its own: 9000 of n = 45 with 45 vectors, fp32, 70 -> 79 (with 16
+// 46 -> 36; of n = 40 with 40 75 -> 66), 8000 of n = 60 with 16, fp64, 93 -> 133.  Many vectors of few items are left to the product, too (fp32: 1500 of
+// n = 60 with 1000 468 -> 663, 1100 of n = 64 with 200 83 -> 96; 4096 of n = 64 with 300 437 -> 336).
+template <typename T>
+bool trsm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out)
+{
+    if (n <= 2 * LT || n > 4 * LT || batch <= 1024 || batch > 0x7fffffffll)
+        return false;
+    if (m <= 3 * LT && (n >= 3 * LT || (n > 40 && (m > LT || batch <= 1536))))
+        return false;
+    if (m > 8 * LT && batch <= 3072)
+        return false;
+    auto fits = [&](int64_t rs, int64_t cs) { return ((n - 1) * rs + (m - 1) * cs + 1) * (int64_t)sizeof(T) <= 0xffffffffll; };
+    return in.nb2 == 1 && out.nb2 == 1 && in.rs >= 0 && in.cs >= 0 && out.rs >= 0 && out.cs >= 0 && fits(in.rs, in.cs) &&
+           fits(out.rs, out.cs);
+}
+template bool trsm_wave_takes<float>(int64_t, int, int, const View<const float> &, const View<float> &);
+template bool trsm_wave_takes<double>(int64_t, int, int, const View<const double> &, const View<double> &);
+
+#define LA_GO_WAVE(KERNEL, ...)                                                                                                  \
+    do {                                                                                                                         \
+        const dim3 grid((unsigned)((batch + SW_WAVES - 1) / SW_WAVES)), block(SW_WAVES * 64);                                    \
+        if (n <= 3 * LT)                                                                                                         \
+            LA_LAUNCH((KERNEL(3)), grid, block, 0, st, __VA_ARGS__);                                                             \
+        else                                                                                                                     \
+            LA_LAUNCH((KERNEL(4)), grid, block, 0, st, __VA_ARGS__);                                                             \
+    } while (0)
+
+template <typename T>
+la_status launch_potrf_wave(View<const T> A, View<T> L, int32_t *info, int64_t batch, int n, hipStream_t st)
+{
+#define LA_K(K_) k_potrf_wave<T, K_>
+    LA_GO_WAVE(LA_K, A, L, info, batch, n);
+#undef LA_K
+    return launch_check("potrf_wave");
+}
+template <typename T>
+la_status launch_backward_wave(View<const T> Lam, View<const T> G, View<T> Abar, int64_t batch, int n, hipStream_t st)
+{
+#define LA_K(K_) k_backward_wave<T, K_>
+    LA_GO_WAVE(LA_K, Lam, G, Abar, batch, n);
+#undef LA_K
+    return launch_check("backward_wave");
+}
+template <typename T>
+la_status launch_potri_wave(View<const T> Lam, View<T> B, int64_t batch, int n, hipStream_t st)
+{
+#define LA_K(K_) k_potri_wave<T, K_>
+    LA_GO_WAVE(LA_K, Lam, B, batch, n);
+#undef LA_K
+    return launch_check("potri_wave");
+}
+template <typename T>
+la_status launch_trsm_wave(View<const T> Lam, View<const T> Xin, View<T> X, int64_t batch, int n, int m, T alpha, bool fwd, hipStream_t st)
+{
+#define LA_K(K_) k_trsm_wave<T, K_, true>
+#define LA_K2(K_) k_trsm_wave<T, K_, false>
+    if (fwd)
+        LA_GO_WAVE(LA_K, Lam, Xin, X, batch, n, m, alpha);
+    else
+        LA_GO_WAVE(LA_K2, Lam, Xin, X, batch, n, m, alpha);
+#undef LA_K
+#undef LA_K2
+    return launch_check("trsm_wave");
+}
+// lower: B as it is stored is B^T of what the kernel multiplies by, and the result is written transposed
+template <typename T>
+la_status launch_potri_backward_wave(View<const T> Lam, View<const T> B, View<const T> Bbar, View<T> Lbar, int64_t batch, int n,
+                                     hipStream_t st)
+{
+#define LA_K(K_) k_potri_backward_wave<T, K_>
+    LA_GO_WAVE(LA_K, Lam, B, Bbar, Lbar, batch, n);
+#undef LA_K
+    return launch_check("potri_backward_wave");
+}
+#define LA_INST(T)                                                                                                               \
+    template la_status launch_potrf_wave<T>(View<const T>, View<T>, int32_t *, int64_t, int, hipStream_t);                       \
+    template la_status launch_backward_wave<T>(View<const T>, View<const T>, View<T>, int64_t, int, hipStream_t);                \
+    template la_status launch_potri_wave<T>(View<const T>, View<T>, int64_t, int, hipStream_t);                                  \
+    template la_status launch_trsm_wave<T>(View<const T>, View<const T>, View<T>, int64_t, int, int, T, bool, hipStream_t);      \
+    template la_status launch_potri_backward_wave<T>(View<const T>, View<const T>, View<const T>, View<T>, int64_t, int,         \
+                                                     hipStream_t);
+LA_INST(float)
+LA_INST(double)
+#undef LA_INST
+
+}  // namespace la

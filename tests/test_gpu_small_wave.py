@@ -1,0 +1,102 @@
+"""Many matrices of 32 < n <= 64, one wavefront each: every tile edge of the two sizes of kernel, both triangles with junk in
+the other one, in place, failing pivots, vectors of every remainder and a batch that leaves the last workgroup part empty."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1710_08717_amd as la
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f64": 1e-10, "f32": 2e-4}
+NP = {"f64": np.float64, "f32": np.float32}
+BATCH = 1539
+SIZES = [33, 37, 47, 48, 49, 63, 64]
+
+
+def spd(n, seed, dtype):
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((BATCH, n, 2 * n))
+    return (np.matmul(X, X.transpose(0, 2, 1)) / (2 * n) + np.eye(n)).astype(NP[dtype])
+
+
+def rel(x, ref):
+    x = x.cpu().numpy().astype(np.float64).reshape(x.shape[0], -1)
+    ref = np.asarray(ref).reshape(ref.shape[0], -1)
+    return np.max(np.linalg.norm(x - ref, axis=1) / np.linalg.norm(ref, axis=1))
+
+
+def junk(x, lower):
+    y = x.copy()
+    n = x.shape[-1]
+    y[:, np.triu(np.ones((n, n), bool), 1) if lower else np.tril(np.ones((n, n), bool), -1)] = np.nan
+    return y
+
+
+def factor(n, lower, dtype):
+    L = np.linalg.cholesky(spd(n, n, "f64"))
+    return (L if lower else L.transpose(0, 2, 1).copy()).astype(NP[dtype])
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("lower", [True, False])
+@pytest.mark.parametrize("n", SIZES)
+def test_factor_operators(n, lower, dtype):
+    A = spd(n, n, dtype)
+    ref = np.linalg.cholesky(A.astype(np.float64))
+    buf = torch.from_numpy(junk(A, lower)).cuda()
+    L = la.potrf(buf, lower=lower, out=buf)
+    assert rel(L, ref if lower else ref.transpose(0, 2, 1)) <= TOL[dtype]
+    assert torch.count_nonzero(L.triu(1) if lower else L.tril(-1)) == 0
+
+    rng = np.random.default_rng(1)
+    F = factor(n, lower, dtype)
+    Fj = torch.from_numpy(junk(F, lower)).cuda()
+    Lbar = rng.standard_normal((BATCH, n, n)).astype(NP[dtype])
+    Abar = la.potrf_backward(Fj, torch.from_numpy(junk(Lbar, lower)).cuda(), lower=lower)
+    assert torch.equal(Abar, Abar.mT)
+    assert rel(Abar, oracle.potrf_backward(F.astype(np.float64), Lbar.astype(np.float64), lower=lower)) <= TOL[dtype]
+
+    buf = Fj.clone()
+    B = la.potri(buf, lower=lower, out=buf)
+    assert torch.equal(B, B.mT)
+    Bref = oracle.potri(F.astype(np.float64), lower=lower)
+    assert rel(B, Bref) <= TOL[dtype]
+
+    B = Bref.astype(NP[dtype])
+    Bbar = rng.standard_normal((BATCH, n, n)).astype(NP[dtype])
+    G = la.potri_backward(Fj, torch.from_numpy(B).cuda(), torch.from_numpy(Bbar).cuda(), lower=lower)
+    assert torch.count_nonzero(G.triu(1) if lower else G.tril(-1)) == 0
+    assert rel(G, oracle.potri_backward(F.astype(np.float64), B.astype(np.float64), Bbar.astype(np.float64), lower=lower)) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("rightside", [False, True])
+@pytest.mark.parametrize("lower,trans", [(True, False), (True, True), (False, False), (False, True)])
+@pytest.mark.parametrize("n,m", [(33, 1), (37, 16), (40, 33), (45, 15), (47, 49), (48, 65), (49, 50), (64, 128)])
+def test_solves(n, m, lower, trans, rightside, dtype):
+    F = factor(n, lower, dtype)
+    rng = np.random.default_rng(2)
+    X = rng.standard_normal((BATCH, m, n) if rightside else (BATCH, n, m)).astype(NP[dtype])
+    M = np.tril(F) if lower else np.triu(F)
+    M = (M.transpose(0, 2, 1) if trans else M).astype(np.float64)
+    if rightside:
+        ref = np.linalg.solve(M.transpose(0, 2, 1), X.transpose(0, 2, 1).astype(np.float64)).transpose(0, 2, 1)
+    else:
+        ref = np.linalg.solve(M, X.astype(np.float64))
+    buf = torch.from_numpy(X).cuda()
+    got = la.trsm(torch.from_numpy(junk(F, lower)).cuda(), buf, lower=lower, trans=trans, rightside=rightside, alpha=-1.5, out=buf)
+    assert rel(got, -1.5 * ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [37, 64])
+def test_first_failing_pivot(n, dtype):
+    A = spd(n, 3, dtype)
+    for k in range(n):
+        A[k, k, k] = -1.0
+    info = torch.zeros(BATCH, dtype=torch.int32, device="cuda")
+    la.potrf(torch.from_numpy(A).cuda(), info=info)
+    assert info[:n].tolist() == list(range(1, n + 1))
+    assert torch.count_nonzero(info[n:]) == 0

@@ -141,7 +141,7 @@ def _compile_isa(name):
         return open(out).read(), ""
 
 
-_ISA_FILES = ["leaf.hip", "tiny.hip", "tiny_ops.hip", "kalman.hip", "trsm_stream.hip", "tiny_rows.hip"]
+_ISA_FILES = ["leaf.hip", "tiny.hip", "tiny_ops.hip", "kalman.hip", "trsm_stream.hip", "tiny_rows.hip", "small_wave.hip"]
 _isa_cache = {}
 
 
@@ -214,4 +214,11 @@ def test_two_rows_per_lane_operator_kernels_respect_dpp_spacing():
     text = _isa_text("tiny_rows.hip")
     hazards, n_dpp = find_hazards(text)
     assert text.count("v_fmac_f32_dpp") >= 1000 and text.count("v_fmac_f64_dpp") >= 1000
+    assert hazards == []
+
+
+def test_one_wavefront_kernels_respect_dpp_spacing():
+    text = _isa_text("small_wave.hip")
+    hazards, n_dpp = find_hazards(text)
+    assert n_dpp > 4000
     assert hazards == []
