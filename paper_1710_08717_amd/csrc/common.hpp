@@ -669,6 +669,20 @@ template <typename T>
 la_status launch_potri_backward_wave(View<const T> Lam, View<const T> B, View<const T> Bbar, View<T> out, int64_t batch, int n,
                                      hipStream_t st);
 
+// as launch_trmm_leaf, launch_symm_leaf and launch_outer_leaf
+template <typename T>
+bool trmm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out);
+bool syrk_wave_takes(int64_t batch, int n, int k);
+template <typename T>
+bool outer_wave_takes(int64_t batch, int n, int m);
+template <typename T>
+la_status launch_trmm_wave(View<const T> Lam, View<const T> Xin, View<T> X, int64_t batch, int n, int m, T alpha, bool fwd,
+                           hipStream_t st);
+template <typename T>
+la_status launch_symm_wave(T alpha, int64_t batch, int n, int k, View<const T> G, View<const T> A, View<T> Out, hipStream_t st);
+template <typename T>
+la_status launch_outer_wave(int tri, T alpha, int64_t batch, int n, int k, View<const T> U, View<const T> V, View<T> C, hipStream_t st);
+
 // Gaussian-process criterion and gradient, one workgroup per matrix (leaf.hip); n <= 128.
 template <typename T>
 la_status launch_gp_leaf16(View<const T> A, const T *y, T *loss, View<T> Abar, int32_t *info, int64_t batch, int n,

@@ -521,6 +521,9 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
     o.triA = fwd ? 1 : 2;  // Lam keeps e >= k, Lam^T keeps e <= k; the same holds for their inverses
     o.reverse = fwd ? 1 : 0;  // heavy tile rows first: the last ones for a lower operand
 
+    if (!solve && Lam.nb2 == 1 && trmm_wave_takes<T>(batch, n, m, Xin, X))  // one wavefront per item, in place too
+        return launch_trmm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
+
     // n <= 64 with at most 16 vectors stored as whole items back to back: G lanes per matrix.  (A solve
     // with 16 < n over a small batch is quicker in the one-workgroup kernel below: 16 matrices of n = 32,
     // fp64: 6.5 against 10.9 us; up to n = 32 the lane-group kernel wins once there are more matrices than
@@ -624,6 +627,8 @@ static la_status syrk_t(int trans, double alpha, int64_t batch, int n, int k, co
         return launch_syrk_tiny<T>(trans != 0, (T)alpha, batch, n, k, (const T *)A, C, st);
     if (outer_rows_takes<T>(n, k, false))  // 16 < n <= 32: 16 lanes per matrix, two rows per lane
         return launch_outer_rows<T>(trans != 0, 0, (T)alpha, batch, n, k, (const T *)A, (const T *)A, C, st);
+    if (syrk_wave_takes(batch, n, k))  // one wavefront per matrix
+        return launch_outer_wave<T>(0, (T)alpha, batch, n, k, Ank, Ank, C, st);
     if (outer_leaf_takes<T>(batch, n, k, false))  // one workgroup per matrix, operands in LDS
         return launch_outer_leaf<T>(0, (T)alpha, batch, n, k, Ank, Ank, C, st);
     GemmOpts o;
@@ -693,6 +698,14 @@ static la_status tri_outer_t(int lower, int trans, int rightside, T scale, int64
             return launch_outer_tiny<T>(rightside != 0, lower ? 1 : 2, scale, batch, n, m, U, V, G, st);
         return launch_outer_rows<T>(rightside != 0, lower ? 1 : 2, scale, batch, n, m, U, V, G, st);
     }
+    if (outer_wave_takes<T>(batch, n, m)) {  // one wavefront per matrix: product, mask and zeros in one launch
+        const T *X1 = trans ? Q : P, *X2 = trans ? P : Q;
+        if (!rightside)
+            return launch_outer_wave<T>(lower ? 1 : 2, scale, batch, n, m, View<const T>{X1, nm, m, 1},
+                                        View<const T>{X2, nm, m, 1}, G, st);
+        return launch_outer_wave<T>(lower ? 1 : 2, scale, batch, n, m, View<const T>{X2, nm, 1, n},
+                                    View<const T>{X1, nm, 1, n}, G, st);
+    }
     if (outer_leaf_takes<T>(batch, n, m, true)) {  // one workgroup per matrix: product, mask and zeros in one launch
         const T *X1 = trans ? Q : P, *X2 = trans ? P : Q;
         if (!rightside)
@@ -753,6 +766,11 @@ static la_status syrk_backward_t(int trans, double alpha, int64_t batch, int n, 
         return launch_symm_tiny<T>(trans != 0, (T)alpha, batch, n, k, G, (const T *)A, (T *)Abar, st);
     if (symm_rows_takes<T>(n, k))  // 16 < n <= 32: 16 lanes per matrix, two rows per lane
         return launch_symm_rows<T>(trans != 0, (T)alpha, batch, n, k, G, (const T *)A, (T *)Abar, st);
+    if (syrk_wave_takes(batch, n, k)) {  // one wavefront per matrix; A and Abar as n x k views
+        if (!trans)
+            return launch_symm_wave<T>((T)alpha, batch, n, k, G, View<const T>{(const T *)A, nk, k, 1}, View<T>{(T *)Abar, nk, k, 1}, st);
+        return launch_symm_wave<T>((T)alpha, batch, n, k, G, View<const T>{(const T *)A, nk, 1, n}, View<T>{(T *)Abar, nk, 1, n}, st);
+    }
     if (symm_leaf_takes<T>(batch, n, k)) {  // one workgroup per matrix, operands in LDS; A and Abar as n x k views
         if (!trans)
             return launch_symm_leaf<T>((T)alpha, batch, n, k, G, View<const T>{(const T *)A, nk, k, 1},

@@ -53,50 +53,80 @@ struct Wave {
         for (int v = 0; v < 4; ++v)
             y[v] = lds[c * PS + 4 * v + g];
     }
-    // element (4 v + g, c) of tile (i, j) as it lies in memory; zero beyond the matrix (read from addresses inside it)
+    // Element (4 v + g, c) of tile (i, j) as it lies in memory; beyond the matrix one of its other elements, until mask() makes it zero.
+    // rin, cin: all rows, columns of the tile exist.
     template <typename M>
-    __device__ __forceinline__ void load_direct(const Mat<M> &m, int i, int j, T (&x)[4]) const
+    __device__ __forceinline__ void raw(const Mat<M> &m, int i, int j, T (&x)[4], bool rin, bool cin) const
     {
-        const int col = LT * j + c, cc = min(col, m.C - 1);
+        const int col = LT * j + c, cc = cin ? col : min(col, m.C - 1);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int row = LT * i + 4 * v + g, rr = min(row, m.R - 1);
-            const T e = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(m.p) +
-                                                     ((unsigned)rr * m.rs + (unsigned)cc * m.cs) * (unsigned)sizeof(T));
-            x[v] = row < m.R && col < m.C ? e : T(0);
+            const int row = LT * i + 4 * v + g, rr = rin ? row : min(row, m.R - 1);
+            x[v] = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(m.p) +
+                                                ((unsigned)rr * m.rs + (unsigned)cc * m.cs) * (unsigned)sizeof(T));
         }
     }
-    __device__ __forceinline__ void store_direct(const Mat<T> &m, int i, int j, const T (&x)[4]) const
+    template <typename M>
+    __device__ __forceinline__ void mask(const Mat<M> &m, int i, int j, T (&x)[4], bool rin, bool cin) const
+    {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            x[v] = (rin || LT * i + 4 * v + g < m.R) && (cin || LT * j + c < m.C) ? x[v] : T(0);
+    }
+    template <typename M>
+    __device__ __forceinline__ void load_direct(const Mat<M> &m, int i, int j, T (&x)[4], bool rin, bool cin) const
+    {
+        raw(m, i, j, x, rin, cin);
+        mask(m, i, j, x, rin, cin);
+    }
+    __device__ __forceinline__ void store_direct(const Mat<T> &m, int i, int j, const T (&x)[4], bool rin, bool cin) const
     {
         const int col = LT * j + c;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = LT * i + 4 * v + g;
-            if (row < m.R && col < m.C)
+            if ((rin || row < m.R) && (cin || col < m.C))
                 *reinterpret_cast<T *>(reinterpret_cast<char *>(m.p) + ((unsigned)row * m.rs + (unsigned)col * m.cs) * (unsigned)sizeof(T)) =
                     x[v];
         }
     }
-    // the same along the direction in which the matrix is contiguous
+    // the same along the direction in which the matrix is contiguous, in two steps: the elements on their way, and in place
     template <typename M>
-    __device__ __forceinline__ void load(const Mat<M> &m, int i, int j, T (&x)[4]) const
+    __device__ __forceinline__ void fetch(const Mat<M> &m, int i, int j, T (&x)[4], bool rin, bool cin) const
+    {
+        if (m.cs == 1 || m.rs != 1)
+            raw(m, i, j, x, rin, cin);
+        else
+            raw(m.t(), j, i, x, cin, rin);
+    }
+    template <typename M>
+    __device__ __forceinline__ void arrange(const Mat<M> &m, int i, int j, T (&in)[4], T (&x)[4], bool rin, bool cin) const
     {
         if (m.cs == 1 || m.rs != 1) {
-            load_direct(m, i, j, x);
+            mask(m, i, j, in, rin, cin);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] = in[v];
         } else {
-            T y[4];
-            load_direct(m.t(), j, i, y);
-            turn(y, x);
+            mask(m.t(), j, i, in, cin, rin);
+            turn(in, x);
         }
     }
-    __device__ __forceinline__ void store(const Mat<T> &m, int i, int j, const T (&x)[4]) const
+    template <typename M>
+    __device__ __forceinline__ void load(const Mat<M> &m, int i, int j, T (&x)[4], bool rin, bool cin) const
+    {
+        T y[4];
+        fetch(m, i, j, y, rin, cin);
+        arrange(m, i, j, y, x, rin, cin);
+    }
+    __device__ __forceinline__ void store(const Mat<T> &m, int i, int j, const T (&x)[4], bool rin, bool cin) const
     {
         if (m.cs == 1 || m.rs != 1) {
-            store_direct(m, i, j, x);
+            store_direct(m, i, j, x, rin, cin);
         } else {
             T y[4];
             turn(x, y);
-            store_direct(m.t(), j, i, y);
+            store_direct(m.t(), j, i, y, cin, rin);
         }
     }
     // lower triangle of a diagonal tile, `pad` on the diagonal beyond row n
@@ -111,7 +141,7 @@ struct Wave {
         }
     }
     // tile (i, j) of a symmetric result and its mirror image
-    __device__ __forceinline__ void store_sym(const Mat<T> &m, int i, int j, T (&x)[4]) const
+    __device__ __forceinline__ void store_sym(const Mat<T> &m, int i, int j, T (&x)[4], bool rin, bool cin) const
     {
         T y[4];
         turn(x, y);
@@ -119,10 +149,10 @@ struct Wave {
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 x[v] = 4 * v + g < c ? y[v] : x[v];
-            store_direct(m, i, i, x);
+            store_direct(m, i, i, x, rin, rin);
         } else {
-            store_direct(m, i, j, x);
-            store_direct(m, j, i, y);
+            store_direct(m, i, j, x, rin, cin);
+            store_direct(m, j, i, y, cin, rin);
         }
     }
     // inverse of a lower-triangular diagonal tile (zeros above the diagonal) and its transpose; in: the tile
@@ -198,7 +228,7 @@ __device__ __forceinline__ void load_lower(const Wave<T> &w, const Mat<const T> 
     for (int i = 0; i < K; ++i)
 #pragma unroll
         for (int j = 0; j <= i; ++j)
-            w.load(m, i, j, l[tri_at(i, j)]);
+            w.load(m, i, j, l[tri_at(i, j)], i < K - 1, j < K - 1);
 #pragma unroll
     for (int i = 0; i < K; ++i)
         w.keep_lower(l[tri_at(i, i)], i, m.R, pad);
@@ -231,6 +261,29 @@ __device__ __forceinline__ void invert_lower(const Wave<T> &w, const T (&l)[K * 
     }
 }
 
+// all tiles of G + G^T
+template <typename T, int K>
+__device__ __forceinline__ void load_sym_sum(const Wave<T> &w, const Mat<const T> &m, T (&s)[K][K][4])
+{
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            w.load_direct(m, i, j, s[i][j], i < K - 1, j < K - 1);
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            T y[4];
+            w.turn(s[j][i], y);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                s[i][j][v] += y[v];
+            if (i != j)
+                w.turn(s[i][j], s[j][i]);
+        }
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------------------
@@ -255,7 +308,7 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_
     for (int i = 0; i < K; ++i)
 #pragma unroll
         for (int j = 0; j <= i; ++j)
-            w.load(Am, i, j, u[tri_at(i, j)]);
+            w.load(Am, i, j, u[tri_at(i, j)], i < K - 1, j < K - 1);
 #pragma unroll
     for (int i = 0; i < K; ++i) {
 #pragma unroll
@@ -315,18 +368,18 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_
                 set<T>(t, acc);
             }
         }
-        w.store(Lm, k, k, dt);
+        w.store(Lm, k, k, dt, k < K - 1, k < K - 1);
     }
     const T zero[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < K; ++i)
 #pragma unroll
         for (int j = 0; j < i; ++j) {
-            w.store(Lm.t(), j, i, u[tri_at(i, j)]);
+            w.store(Lm.t(), j, i, u[tri_at(i, j)], true, i < K - 1);
             if (Lm.cs == 1 || Lm.rs != 1)
-                w.store_direct(Lm, j, i, zero);
+                w.store_direct(Lm, j, i, zero, true, i < K - 1);
             else
-                w.store_direct(Lm.t(), i, j, zero);
+                w.store_direct(Lm.t(), i, j, zero, i < K - 1, true);
         }
     if (info != nullptr && (threadIdx.x & 63) == 0 && fail != 0 && fail <= n)
         if (info[b] == 0)
@@ -338,7 +391,7 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_
 // Abar_ij = 1/2 sum_{k >= i} (Li_ki^T Z_kj + Z_ki^T Li_kj) are products of tiles as they stand.
 // ---------------------------------------------------------------------------------------
 template <typename T, int K>
-__global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : (sizeof(T) * K <= 24 ? 3 : 1)) void k_backward_wave(
+__global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : (sizeof(T) * K <= 24 ? 3 : 2)) void k_backward_wave(
     View<const T> Lam, View<const T> G, View<T> Abar, int64_t batch, int n)
 {
     using W = Wave<T>;
@@ -400,7 +453,7 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : (sizeof(T)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 x[v] = T(0.5) * acc[v];
-            w.store_sym(out, i, j, x);
+            w.store_sym(out, i, j, x, i < K - 1, j < K - 1);
         }
 }
 
@@ -432,7 +485,7 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_
                 acc = frag_mma<T>(li[tri_at(k, i)], li[tri_at(k, j)], acc);
             T x[4];
             set<T>(x, acc);
-            w.store_sym(out, i, j, x);
+            w.store_sym(out, i, j, x, i < K - 1, j < K - 1);
         }
 }
 
@@ -467,11 +520,20 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_
     }
     const Mat<const T> in = item_of<const T>(Xin, b, n, m);
     const Mat<T> out = item_of<T>(X, b, n, m);
+    T next[K][4];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        w.fetch(in, k, 0, next[k], k < K - 1, false);
     for (int ct = 0; ct * LT < m; ++ct) {
         T x[K][4];
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            w.load(in, k, ct, x[k]);
+            w.arrange(in, k, ct, next[k], x[k], k < K - 1, false);
+        if ((ct + 1) * LT < m) {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                w.fetch(in, k, ct + 1, next[k], k < K - 1, false);
+        }
 #pragma unroll
         for (int q = 0; q < K; ++q) {
             const int k = FWD ? q : K - 1 - q;
@@ -490,7 +552,7 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_
         }
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            w.store(out, k, ct, x[k]);
+            w.store(out, k, ct, x[k], k < K - 1, false);
     }
 }
 
@@ -510,28 +572,9 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 12 ? 4 : (sizeof(T)
         return;
     const W w(lds[threadIdx.x >> 6], threadIdx.x & 63);
     T s[K][K][4];
-    {
-        const Mat<const T> m = item_of<const T>(Bbar, b, n, n);
-#pragma unroll
-        for (int i = 0; i < K; ++i)
-#pragma unroll
-            for (int j = 0; j < K; ++j)
-                w.load_direct(m, i, j, s[i][j]);
-    }
+    load_sym_sum<T, K>(w, item_of<const T>(Bbar, b, n, n), s);
     T l[NT][4];  // L_ij^T below the diagonal, L_ii^-T on it
     load_lower<T, K>(w, item_of<const T>(Lam, b, n, n), T(1), l);
-#pragma unroll
-    for (int i = 0; i < K; ++i)
-#pragma unroll
-        for (int j = 0; j <= i; ++j) {
-            T y[4];
-            w.turn(s[j][i], y);
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                s[i][j][v] += y[v];
-            if (i != j)
-                w.turn(s[i][j], s[j][i]);
-        }
 #pragma unroll
     for (int i = 0; i < K; ++i) {
         T li[4], lit[4];
@@ -552,7 +595,7 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 12 ? 4 : (sizeof(T)
         T bt[K][4];
 #pragma unroll
         for (int k = 0; k < K; ++k)
-            w.load(Bm, k, j, bt[k]);
+            w.load(Bm, k, j, bt[k], k < K - 1, j < K - 1);
 #pragma unroll
         for (int i = 0; i <= j; ++i) {
             Acc<T> y = {0, 0, 0, 0}, acc = {0, 0, 0, 0};
@@ -579,12 +622,182 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 12 ? 4 : (sizeof(T)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 e[v] = i == j && 4 * v + w.g > w.c ? T(0) : -q[tri_at(j, i)][v];
-            w.store(out, i, j, e);
+            w.store(out, i, j, e, i < K - 1, j < K - 1);
             if (i != j) {
                 if (out.cs == 1)
-                    w.store_direct(out, j, i, zero);
+                    w.store_direct(out, j, i, zero, j < K - 1, true);
                 else
-                    w.store_direct(out.t(), i, j, zero);
+                    w.store_direct(out.t(), i, j, zero, true, j < K - 1);
+            }
+        }
+}
+
+// ---------------------------------------------------------------------------------------
+// Products of small matrices:  trmm  X = alpha t(L) B,  16 vectors at a time;  the rule of syrk  Out = alpha (G + G^T) A,  16 columns
+// at a time;  U V^T with its triangles treated as in k_outer_leaf16.
+// ---------------------------------------------------------------------------------------
+template <typename T, int K, bool FWD>
+__global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_trmm_wave(View<const T> Lam, View<const T> Xin, View<T> X,
+                                                                                         int64_t batch, int n, int m, T alpha)
+{
+    using W = Wave<T>;
+    constexpr int NT = K * (K + 1) / 2;
+    __shared__ __align__(16) T lds[SW_WAVES][W::TILE];
+    const int64_t b = my_item();
+    if (b >= batch)
+        return;
+    const W w(lds[threadIdx.x >> 6], threadIdx.x & 63);
+    const Mat<const T> in = item_of<const T>(Xin, b, n, m);
+    const Mat<T> out = item_of<T>(X, b, n, m);
+    T l[NT][4], next[K][4];  // L_ij^T (fwd) or L_ij
+    load_lower<T, K>(w, item_of<const T>(Lam, b, n, n), T(0), l);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        w.fetch(in, k, 0, next[k], k < K - 1, false);
+    if constexpr (FWD)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            w.turn(l[t], l[t]);
+    for (int ct = 0; ct * LT < m; ++ct) {
+        T x[K][4];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            w.arrange(in, k, ct, next[k], x[k], k < K - 1, false);
+        if ((ct + 1) * LT < m) {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                w.fetch(in, k, ct + 1, next[k], k < K - 1, false);
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            Acc<T> acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+                if (FWD ? j <= i : j >= i)
+                    acc = frag_mma<T>(l[FWD ? tri_at(i, j) : tri_at(j, i)], x[j], acc);
+            T y[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                y[v] = alpha * acc[v];
+            w.store(out, i, ct, y, i < K - 1, false);
+        }
+    }
+}
+
+template <typename T, int K>
+__global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 12 ? 4 : 2) void k_symm_wave(View<const T> G, View<const T> A, View<T> Out,
+                                                                                         int64_t batch, int n, int k, T alpha)
+{
+    using W = Wave<T>;
+    __shared__ __align__(16) T lds[SW_WAVES][W::TILE];
+    const int64_t b = my_item();
+    if (b >= batch)
+        return;
+    const W w(lds[threadIdx.x >> 6], threadIdx.x & 63);
+    const Mat<const T> in = item_of<const T>(A, b, n, k);
+    const Mat<T> out = item_of<T>(Out, b, n, k);
+    T s[K][K][4], next[K][4];
+    load_sym_sum<T, K>(w, item_of<const T>(G, b, n, n), s);
+#pragma unroll
+    for (int q = 0; q < K; ++q)
+        w.fetch(in, q, 0, next[q], q < K - 1, false);
+    for (int ct = 0; ct * LT < k; ++ct) {
+        T x[K][4];
+#pragma unroll
+        for (int q = 0; q < K; ++q)
+            w.arrange(in, q, ct, next[q], x[q], q < K - 1, false);
+        if ((ct + 1) * LT < k) {
+#pragma unroll
+            for (int q = 0; q < K; ++q)
+                w.fetch(in, q, ct + 1, next[q], q < K - 1, false);
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            Acc<T> acc = {0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < K; ++q)
+                acc = frag_mma<T>(s[q][i], x[q], acc);
+            T y[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                y[v] = alpha * acc[v];
+            w.store(out, i, ct, y, i < K - 1, false);
+        }
+    }
+}
+
+template <typename T, int K, int TRI>
+__global__ __launch_bounds__(SW_WAVES * 64, TRI != 0 ? (sizeof(T) * K <= 12 ? 3 : (sizeof(T) * K <= 24 ? 2 : 1)) : (sizeof(T) * K <= 16 ? 4 : 2)) void k_outer_wave(View<const T> U, View<const T> V, View<T> Cv,
+                                                                                          int64_t batch, int n, int k, T alpha)
+{
+    using W = Wave<T>;
+    constexpr int NT = K * (K + 1) / 2;
+    __shared__ __align__(16) T lds[SW_WAVES][W::TILE];
+    const int64_t b = my_item();
+    if (b >= batch)
+        return;
+    const W w(lds[threadIdx.x >> 6], threadIdx.x & 63);
+    const Mat<const T> um = item_of<const T>(U, b, n, k).t(), vm = item_of<const T>(V, b, n, k).t();
+    T nu[K][4], nv[TRI ? K : 1][4];
+    Acc<T> acc[NT];  // tile (i, j) of C on or below the diagonal; with TRI 2 the transpose of tile (j, i)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+        acc[t] = Acc<T>{0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        w.fetch(um, 0, i, nu[i], false, i < K - 1);
+        if constexpr (TRI != 0)
+            w.fetch(vm, 0, i, nv[i], false, i < K - 1);
+    }
+    for (int kk = 0; kk * LT < k; ++kk) {
+        T u[K][4], v[TRI ? K : 1][4];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            w.arrange(um, kk, i, nu[i], u[i], false, i < K - 1);
+            if constexpr (TRI != 0)
+                w.arrange(vm, kk, i, nv[i], v[i], false, i < K - 1);
+        }
+        if ((kk + 1) * LT < k) {
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                w.fetch(um, kk + 1, i, nu[i], false, i < K - 1);
+                if constexpr (TRI != 0)
+                    w.fetch(vm, kk + 1, i, nv[i], false, i < K - 1);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+#pragma unroll
+            for (int j = 0; j <= i; ++j) {
+                if constexpr (TRI == 0)
+                    acc[tri_at(i, j)] = frag_mma<T>(u[i], u[j], acc[tri_at(i, j)]);
+                else if constexpr (TRI == 1)
+                    acc[tri_at(i, j)] = frag_mma<T>(u[i], v[j], acc[tri_at(i, j)]);
+                else  // tile (j, i)
+                    acc[tri_at(i, j)] = frag_mma<T>(u[j], v[i], acc[tri_at(i, j)]);
+            }
+    }
+    const Mat<T> out = item_of<T>(Cv, b, n, n);
+    const T zero[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            T x[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] = alpha * acc[tri_at(i, j)][v];
+            if constexpr (TRI == 0) {
+                w.store_sym(out, i, j, x, i < K - 1, j < K - 1);
+            } else {
+                if (i == j) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        x[v] = (TRI == 1 ? 4 * v + w.g < w.c : 4 * v + w.g > w.c) ? T(0) : x[v];
+                }
+                w.store_direct(out, TRI == 1 ? i : j, TRI == 1 ? j : i, x, (TRI == 1 ? i : j) < K - 1, (TRI == 1 ? j : i) < K - 1);
+                if (i != j)
+                    w.store_direct(out, TRI == 1 ? j : i, TRI == 1 ? i : j, zero, (TRI == 1 ? j : i) < K - 1, (TRI == 1 ? i : j) < K - 1);
             }
         }
 }
@@ -592,6 +805,14 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 12 ? 4 : (sizeof(T)
 // ---------------------------------------------------------------------------------------
 // launches: 32 < n <= 64, three or four tile rows
 // ---------------------------------------------------------------------------------------
+static bool wave_range(int64_t batch, int n) { return n > 2 * LT && n <= 4 * LT && batch > 1024 && batch <= 0x7fffffffll; }
+// the kernels address an item by 32-bit byte offsets
+template <typename T>
+static bool offsets_fit(int64_t rows, int64_t cols, int64_t rs, int64_t cs, int nb2)
+{
+    return nb2 == 1 && rs >= 0 && cs >= 0 && ((rows - 1) * rs + (cols - 1) * cs + 1) * (int64_t)sizeof(T) <= 0xffffffffll;
+}
+
 // Against the four-wavefront kernels (1025 matrices or more; us, fp32 / fp64):
 //   12255 of n = 37: potrf 88 -> 41 / 140 -> 69, backward 142 -> 77 / 214 -> 162, potri 73 -> 39 / 96 -> 65, its backward rule
 //   207 -> 99 / 370 -> 288, trsm of 16 vectors 59 -> 40 / 79 -> 56, of 37 85 -> 79 / 176 -> 142;
@@ -604,7 +825,7 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 12 ? 4 : (sizeof(T)
 template <typename T>
 bool small_wave_takes(SmallWaveOp op, int64_t batch, int n)
 {
-    if (n <= 2 * LT || n > 4 * LT || batch <= 1024 || batch > 0x7fffffffll)
+    if (!wave_range(batch, n))
         return false;
     if (op == SmallWaveOp::potri_backward)
         return true;
@@ -625,18 +846,46 @@ template bool small_wave_takes<double>(SmallWaveOp, int64_t, int);
 template <typename T>
 bool trsm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out)
 {
-    if (n <= 2 * LT || n > 4 * LT || batch <= 1024 || batch > 0x7fffffffll)
+    if (!wave_range(batch, n) || !offsets_fit<T>(n, m, in.rs, in.cs, in.nb2) || !offsets_fit<T>(n, m, out.rs, out.cs, out.nb2))
         return false;
     if (m <= 3 * LT && (n >= 3 * LT || (n > 40 && (m > LT || batch <= 1536))))
         return false;
-    if (m > 8 * LT && batch <= 3072)
-        return false;
-    auto fits = [&](int64_t rs, int64_t cs) { return ((n - 1) * rs + (m - 1) * cs + 1) * (int64_t)sizeof(T) <= 0xffffffffll; };
-    return in.nb2 == 1 && out.nb2 == 1 && in.rs >= 0 && in.cs >= 0 && out.rs >= 0 && out.cs >= 0 && fits(in.rs, in.cs) &&
-           fits(out.rs, out.cs);
+    return m <= 8 * LT || batch > 3072;
 }
 template bool trsm_wave_takes<float>(int64_t, int, int, const View<const float> &, const View<float> &);
 template bool trsm_wave_takes<double>(int64_t, int, int, const View<const double> &, const View<double> &);
+
+// Against one workgroup per matrix or the general product, us, fp32 / fp64, 12255 of n = 37: trmm of 16 vectors 52 -> 23 / 61 -> 38, of 40
+// 81 -> 46 / 123 -> 94; 16384 of n = 64 75 -> 66 / 111 -> 110.  The general product wins where it fills its tiles: 5000 of n = 48 with
+// 300 vectors, fp32, 202 -> 258, 1100 of n = 64 in fp64 105 -> 128 (5000 of n = 61 630 -> 514).
+template <typename T>
+bool trmm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out)
+{
+    if (!wave_range(batch, n) || !offsets_fit<T>(n, m, in.rs, in.cs, in.nb2) || !offsets_fit<T>(n, m, out.rs, out.cs, out.nb2))
+        return false;
+    return m <= 4 * LT || (sizeof(T) == 8 && (n <= 3 * LT || batch > 3072));
+}
+template bool trmm_wave_takes<float>(int64_t, int, int, const View<const float> &, const View<float> &);
+template bool trmm_wave_takes<double>(int64_t, int, int, const View<const double> &, const View<double> &);
+
+// syrk and its rule, any k: 12255 of n = 37 with k = 32 syrk 51 -> 28 / 67 -> 44, its rule 66 -> 37 / 115 -> 71, with k = 64 66 -> 38 /
+// 129 -> 79 and 130 -> 81 / 188 -> 117; 5000 of n = 61 with k = 300 184 -> 128 / 377 -> 243 and 683 -> 340 / 1425 -> 524.
+bool syrk_wave_takes(int64_t batch, int n, int k) { return wave_range(batch, n) && k >= 1; }
+
+// The gradients of triangular operands, U V^T with one triangle kept: the rule of trmm on 12255 of n = 37 with 16 vectors 97 -> 46 /
+// 128 -> 96, with 40 205 -> 100 / 345 -> 181.  With four tile rows the ten sums leave few wavefronts on a compute unit: 8000 of n = 60
+// with 16 vectors, fp64, 79 -> 102 for this product alone (40 vectors: 181 -> 132), 1100 of n = 64 with 300 44 -> 56 / 74 -> 120.
+template <typename T>
+bool outer_wave_takes(int64_t batch, int n, int m)
+{
+    if (!wave_range(batch, n) || m < 1)
+        return false;
+    if (n <= 3 * LT)
+        return true;
+    return (sizeof(T) == 4 || m > LT) && (m <= 4 * LT || (m <= 32 * LT && batch > 3072));
+}
+template bool outer_wave_takes<float>(int64_t, int, int);
+template bool outer_wave_takes<double>(int64_t, int, int);
 
 #define LA_GO_WAVE(KERNEL, ...)                                                                                                  \
     do {                                                                                                                         \
@@ -694,13 +943,54 @@ la_status launch_potri_backward_wave(View<const T> Lam, View<const T> B, View<co
 #undef LA_K
     return launch_check("potri_backward_wave");
 }
+template <typename T>
+la_status launch_trmm_wave(View<const T> Lam, View<const T> Xin, View<T> X, int64_t batch, int n, int m, T alpha, bool fwd, hipStream_t st)
+{
+#define LA_K(K_) k_trmm_wave<T, K_, true>
+#define LA_K2(K_) k_trmm_wave<T, K_, false>
+    if (fwd)
+        LA_GO_WAVE(LA_K, Lam, Xin, X, batch, n, m, alpha);
+    else
+        LA_GO_WAVE(LA_K2, Lam, Xin, X, batch, n, m, alpha);
+#undef LA_K
+#undef LA_K2
+    return launch_check("trmm_wave");
+}
+template <typename T>
+la_status launch_symm_wave(T alpha, int64_t batch, int n, int k, View<const T> G, View<const T> A, View<T> Out, hipStream_t st)
+{
+#define LA_K(K_) k_symm_wave<T, K_>
+    LA_GO_WAVE(LA_K, G, A, Out, batch, n, k, alpha);
+#undef LA_K
+    return launch_check("symm_wave");
+}
+template <typename T>
+la_status launch_outer_wave(int tri, T alpha, int64_t batch, int n, int k, View<const T> U, View<const T> V, View<T> C, hipStream_t st)
+{
+#define LA_K0(K_) k_outer_wave<T, K_, 0>
+#define LA_K1(K_) k_outer_wave<T, K_, 1>
+#define LA_K2(K_) k_outer_wave<T, K_, 2>
+    if (tri == 0)
+        LA_GO_WAVE(LA_K0, U, V, C, batch, n, k, alpha);
+    else if (tri == 1)
+        LA_GO_WAVE(LA_K1, U, V, C, batch, n, k, alpha);
+    else
+        LA_GO_WAVE(LA_K2, U, V, C, batch, n, k, alpha);
+#undef LA_K0
+#undef LA_K1
+#undef LA_K2
+    return launch_check("outer_wave");
+}
 #define LA_INST(T)                                                                                                               \
     template la_status launch_potrf_wave<T>(View<const T>, View<T>, int32_t *, int64_t, int, hipStream_t);                       \
     template la_status launch_backward_wave<T>(View<const T>, View<const T>, View<T>, int64_t, int, hipStream_t);                \
     template la_status launch_potri_wave<T>(View<const T>, View<T>, int64_t, int, hipStream_t);                                  \
     template la_status launch_trsm_wave<T>(View<const T>, View<const T>, View<T>, int64_t, int, int, T, bool, hipStream_t);      \
     template la_status launch_potri_backward_wave<T>(View<const T>, View<const T>, View<const T>, View<T>, int64_t, int,         \
-                                                     hipStream_t);
+                                                     hipStream_t);                                                               \
+    template la_status launch_trmm_wave<T>(View<const T>, View<const T>, View<T>, int64_t, int, int, T, bool, hipStream_t);      \
+    template la_status launch_symm_wave<T>(T, int64_t, int, int, View<const T>, View<const T>, View<T>, hipStream_t);            \
+    template la_status launch_outer_wave<T>(int, T, int64_t, int, int, View<const T>, View<const T>, View<T>, hipStream_t);
 LA_INST(float)
 LA_INST(double)
 #undef LA_INST

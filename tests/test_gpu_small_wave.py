@@ -100,3 +100,37 @@ def test_first_failing_pivot(n, dtype):
     la.potrf(torch.from_numpy(A).cuda(), info=info)
     assert info[:n].tolist() == list(range(1, n + 1))
     assert torch.count_nonzero(info[n:]) == 0
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("lower,trans,rightside", [(True, False, False), (True, True, True), (False, False, True), (False, True, False)])
+@pytest.mark.parametrize("n,m", [(33, 1), (37, 16), (48, 17), (49, 33), (63, 48), (64, 65)])
+def test_products(n, m, lower, trans, rightside, dtype):
+    """trmm (in place), its rule, syrk and its rule, against the definitions in 64 bits"""
+    F = factor(n, lower, dtype)
+    rng = np.random.default_rng(4)
+    shape = (BATCH, m, n) if rightside else (BATCH, n, m)
+    X, Xbar = (rng.standard_normal(shape).astype(NP[dtype]) for _ in range(2))
+    Fj = torch.from_numpy(junk(F, lower)).cuda()
+    M = (np.tril(F) if lower else np.triu(F)).astype(np.float64)
+    t = (lambda x: x.transpose(0, 2, 1))
+    Mt, X64, Xb64 = (t(M) if trans else M), X.astype(np.float64), Xbar.astype(np.float64)
+    buf = torch.from_numpy(X).cuda()
+    got = la.trmm(Fj, buf, lower=lower, trans=trans, rightside=rightside, alpha=0.5, out=buf)
+    assert rel(got, 0.5 * (X64 @ Mt if rightside else Mt @ X64)) <= TOL[dtype]
+
+    Abar, Lbar = la.trmm_backward(Fj, torch.from_numpy(X).cuda(), torch.from_numpy(Xbar).cuda(), lower=lower, trans=trans,
+                                  rightside=rightside)
+    assert rel(Abar, Xb64 @ t(Mt) if rightside else t(Mt) @ Xb64) <= TOL[dtype]
+    G = t(X64) @ Xb64 if rightside else Xb64 @ t(X64)  # gradient of t(M)
+    G = t(G) if trans else G
+    assert rel(Lbar, np.tril(G) if lower else np.triu(G)) <= TOL[dtype]
+    assert torch.count_nonzero(Lbar.triu(1) if lower else Lbar.tril(-1)) == 0
+
+    S = la.syrk(torch.from_numpy(X).cuda(), trans=rightside, alpha=-2.0)  # n x n from n x m, or from m x n transposed
+    assert torch.equal(S, S.mT)
+    assert rel(S, -2.0 * (t(X64) @ X64 if rightside else X64 @ t(X64))) <= TOL[dtype]
+    B = rng.standard_normal((BATCH, n, n)).astype(NP[dtype])
+    B64 = B.astype(np.float64) + t(B.astype(np.float64))
+    got = la.syrk_backward(torch.from_numpy(X).cuda(), torch.from_numpy(B).cuda(), trans=rightside)
+    assert rel(got, X64 @ B64 if rightside else B64 @ X64) <= TOL[dtype]
