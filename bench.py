@@ -33,28 +33,26 @@ def log(*a):
 
 
 def backward_flops(n, batch, elem_size):
-    """Flops per matrix of the backward pass as the library runs it.  Up to a block size that
-    depends on the batch it evaluates the closed expression, counted as 2 n^3 (lower triangle of
-    L^T Lbar, L^-T applied to n columns, lower triangle of the product with L^-1).  Above it, it
-    sweeps the blocked factorisation in reverse, which needs fewer flops: a level that splits n
-    into n1 + n2 costs 2 n2^2 n1 (symmetric block times panel) + n1^2 n2 (panel solve) +
-    n1^2 n2 (lower triangle of the panel product) = 2 n1 n2 n, and the blocks at the bottom cost
-    2 n0^3 each.  The rule for the block size and the split mirror the library's."""
-    budget = (16.0 if elem_size == 4 else 8.0) * 1048576.0
-    base = 2048
-    while base > 256 and float(base) * base * batch > budget:
-        base //= 2
-
-    def rec(k):
-        if k <= base:
-            return 2.0 * k ** 3
-        q = k // 2048
-        halves_fit = k % 2048 == 0 and q & (q - 1) == 0
-        k1 = 2048 if (k > 4096 and not halves_fit) else (k // 2 + 127) // 128 * 128
-        k2 = k - k1
-        return 2.0 * k1 * k2 * k + rec(k1) + rec(k2)
-
-    return rec(n)
+    """Flops per matrix of the backward pass as the library runs it.  Small problems evaluate the closed
+    expression, counted as 2 n^3 (lower triangle of L^T Lbar, L^-T applied to n columns, lower triangle of
+    the product with L^-1).  Others sweep the blocked factorisation in reverse, which needs fewer flops: a
+    block column of k columns with r rows below costs 2 r^2 k (symmetric block times panel) + r k^2 (panel
+    solve) + r k^2 (lower triangle of the panel product) and its diagonal block 2 k^3.  The rule for the
+    block size mirrors the library's."""
+    mi = 1048576.0
+    if n <= 128 or float(batch) * n * n < (8.0 if elem_size == 4 else 4.0) * mi:
+        return 2.0 * n ** 3
+    base = 128
+    while base < 1024 and 2.0 * base <= 0.6 * n and 4.0 * base * base * batch <= 4.0 * mi:
+        base *= 2
+    if base > 0.6 * n:
+        return 2.0 * n ** 3
+    total = 0.0
+    for o in range(0, n, base):
+        k = min(base, n - o)
+        r = n - o - k
+        total += 2.0 * r * r * k + 2.0 * r * k * k + 2.0 * k ** 3
+    return total
 
 
 def flops_model(name, n, m, batch=1, elem_size=8):

@@ -747,6 +747,10 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
         const int64_t wg128 = wgs(128), wg64 = wgs(64);
         // K slabs of 64: the whole range in such slabs, or (ragged) little of the last one empty
         const bool k64 = f.rag ? (K >= 128 || (K & 63) == 0 || (K & 63) > 32) : K % 64 == 0;
+        // quarter tiles, which exist with slabs of 64 only: aligned operands with another K take the ragged form, whose last slab ends where K
+        // does (us, tiles of 64 in slabs of 16 -> quarter tiles, fp64 / fp32: gradient of the factorisation 1 x 2000^2 819 -> 492 / 553 -> 315,
+        // 16 x 336^2 147 -> 112 / 107 -> 77, trmm 1 x 2000^2 with 48 vectors 123 -> 58 / 81 -> 37)
+        const bool quarters = k64 || K >= 128;
         if (!o.triA && !o.triB && !o.min_tile64 && !o.ksplit && !o.symsum && wg64 <= 128 && K >= 2048 && A.nb2 == 1 && B.nb2 == 1 &&
             C.nb2 == 1) {
             int splits = (int)std::min<int64_t>(512 / wg64, K / 256);
@@ -782,7 +786,7 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             // Triangular operands make the K range, hence the time, of a tile vary along the tile
             // list (heaviest first): the 512 workgroup slots only fill evenly if there are several
             // rounds of tiles, so take the largest tile that still gives 1024 workgroups.
-            e = wg128 >= 1024 && !padded ? 128 : ((wg64 >= 1024 || !k64 || o.min_tile64) ? 64 : 32);
+            e = wg128 >= 1024 && !padded ? 128 : ((wg64 >= 1024 || !quarters || o.min_tile64) ? 64 : 32);
         } else {
             // Equal tiles: big tiles once they (nearly) fill the 512 workgroup slots (496 tiles, 3952 x 2048 x 2000, fp64 598 -> 555
             // us and fp32 310 -> 296 against 64 x 64 tiles, 480 the same, 448 262 -> 291; a compute unit with one workgroup waits for
@@ -807,9 +811,9 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             // per load, and the quarters save no padding (b items of 61 x 174, K = 147, us, 32 x 32 -> 64 x 64: b = 331, 993 tiles, fp64
             // 60 -> 44, fp32 29 -> 22; with one round and a half the products of potri's backward rule, 30 x 297 x 297, 220 -> 232; 26 x 2478 x 22, 1014
             // tiles that the quarters halve, fp32 36 -> 54).
-            const bool two_rounds = f.rag && !o.maskC && !o.symsum && wg64 >= 960 &&
+            const bool two_rounds = (f.rag || !k64) && !o.maskC && !o.symsum && wg64 >= 960 &&
                                     (int64_t)((M + 63) / 64) * ((N + 63) / 64) * 4 == (int64_t)((M + 31) / 32) * ((N + 31) / 32);
-            e = ((t128 >= (o.maskC ? 512 : 480) || one_round) && big && !padded) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64 && !two_rounds) ? 32 : 64);
+            e = ((t128 >= (o.maskC ? 512 : 480) || one_round) && big && !padded) ? 128 : ((wg64 < 1024 && quarters && !o.min_tile64 && !two_rounds) ? 32 : 64);
         }
         if (o.symsum && e == 128)  // (the form that stores both triangles has tiles up to 64 only)
             e = 64;
@@ -837,6 +841,8 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
                                       C.level2((int64_t)e * (C.rs + C.cs), (int)Tt), batch * Tt, e, e, K, alpha, beta, o, st);
             }
         }
+        if (e == 32 && !k64)
+            f.rag = true;
         if (e == 128)
             launch_tiles<T, 128, 128, 16, 2>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
         else if (e == 32)

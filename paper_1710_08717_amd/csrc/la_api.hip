@@ -258,20 +258,26 @@ static la_status potrf_rec(View<T> Wk, View<T> L, int32_t *info, int off, int64_
 //   Z = P Li                       lower x lower = lower
 //   Abar = 1/2 (W + W^T), W = Li^T Z (upper x lower = full): the lower tiles of Li^T Z + Z^T Li, mirrored
 template <typename T>
-static la_status backward_blocked(View<const T> Lam, View<const T> G, View<T> W, int64_t batch, int n, bool aliased,
-                                  hipStream_t st);
+static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, int64_t batch, int n, int n0, bool aliased,
+                                hipStream_t st);
 
-// Largest block the inverse-based expression is used on.  Its 5 n^3 / 3 flops run in a few large
-// products; the blocked sweep needs 2 n^3 / 3 but in many smaller, dependent ones, so it pays once
-// the products of a block fill the chip: from about 8 M (fp64; 16 M fp32) matrix elements per
-// level over the whole batch (measured: 2048 for one matrix, 1024 for 4 to 8, 256 for 256).
-static int bwd_base(int64_t batch, size_t elem)
+// Block columns of the reverse sweep, 0 where the inverse-based expression takes the whole matrix.  The expression's 5 n^3 / 3 flops run
+// in a few large products, the sweep's 2 n^3 / 3 and n0^3 per block in many smaller, dependent ones: it pays from about 4 Mi matrix
+// elements over the whole batch (fp32: 8 Mi), in block columns that leave up to 4 Mi to one block's products.  Expression -> sweep, us:
+// fp64 18 x 512^2 226 -> 195, 32 x 512^2 294 -> 240, 4 x 1024^2 279 -> 259 (3: 224 -> 229), 100 x 256^2 175 -> 170, 60 x 333^2 252 -> 258,
+// 1 x 1800^2 411 -> 425; fp32 32 x 512^2 178 -> 153, 18 131 -> 131, 8 x 1024^2 278 -> 218, 4 161 -> 175, 100 x 256^2 100 -> 109.
+// n0 = 256 / 512 / 1024: fp64 8 x 1024^2 401 / 343 / -, 4 x 2048^2 1146 / 941 / 966, 1 x 3001^2 1509 / 1082 / 898 (2048: 909),
+// 30 x 640^2 391 / 450 / -.  Blocks of 2048 would be 4 to 6 % faster above n = 5000 (1 x 8192^2 fp64 8339 -> 7982, fp32 4481 -> 4210), but
+// the errors grow with the blocks' inverses: fp32 7.5e-7 -> 1.05e-6 there (halving with substitutions: 9.0e-7).
+static int sweep_block(int64_t batch, int n, size_t elem)
 {
-    const double budget = (elem == 4 ? 16.0 : 8.0) * 1048576.0;
-    int b = 2048;
-    while (b > 256 && (double)b * b * (double)batch > budget)
-        b /= 2;
-    return b;
+    const double mi = 1048576.0, elements = (double)batch * n * n;
+    if (elements < (elem == 4 ? 8.0 : 4.0) * mi)
+        return 0;
+    int b = 128;
+    while (b < 1024 && 2.0 * b <= 0.6 * n && 4.0 * b * b * (double)batch <= 4.0 * mi)
+        b *= 2;
+    return b <= 0.6 * n ? b : 0;
 }
 
 // W = 1/2 (Li^T (P + P^T) Li) for lower triangular Li and P (what lies above their diagonals is not read), both triangles
@@ -298,8 +304,6 @@ template <typename T>
 static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, int64_t batch, int n, bool aliased,
                                hipStream_t st)
 {
-    if (n > bwd_base(batch, sizeof(T)))
-        return backward_blocked<T>(Lam, G, W, batch, n, aliased, st);
     // n <= 16: 16 lanes per matrix, HBM bound.  16 < n <= 32: the register kernel has the higher
     // throughput (11 against 16 ns per fp32 matrix), the one-workgroup kernel the shorter latency
     // (25 against 37 us), so the batch size decides.
@@ -309,6 +313,8 @@ static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, in
         return launch_backward_wave<T>(Lam, G, W, batch, n, st);
     if (n <= backward_leaf16_max_n<T>())  // one workgroup per matrix, everything in LDS, no scratch
         return launch_backward_leaf16<T>(Lam, G, W, batch, n, st);
+    if (const int n0 = sweep_block(batch, n, sizeof(T)))
+        return backward_sweep<T>(Lam, G, W, batch, n, n0, aliased, st);
     ArenaFrame frame;
     View<T> sc[2];
     LA_TRY(scratch_views<T>(batch, n, 2, sc));
@@ -333,55 +339,64 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
                              View<const T> Xin, View<T> X, bool inplace, hipStream_t st);
 
 // ---------------------------------------------------------------------------------
-// Large n: reverse sweep over the blocked factorisation (section 4.2 names differentiating the
-// blocked algorithm itself as the cheaper route).  For the split
+// Reverse sweep over the blocked factorisation (section 4.2 names differentiating the blocked algorithm itself as the cheaper
+// route), block column by block column of n0 columns.  For the split
 //   L11 = chol(A11),  L21 = A21 L11^-T,  S = A22 - L21 L21^T,  L22 = chol(S)
-// the adjoints follow in reverse order (W holds Lbar's lower triangle on entry and the symmetric
-// Abar on return, block by block, in place):
-//   W22 <- backward(L22, W22)                       symmetric, both triangles
+// the adjoints follow in reverse order (W holds Lbar's lower triangle on entry and the symmetric Abar on return, block by
+// block, in place; W22 is finished when its turn to the left comes):
 //   W21 <- W21 - 2 W22 L21                          adjoint of the update S
 //   W21 <- 1/2 W21 L11^-1                           adjoint of the panel solve, halved because A21
 //                                                   enters the symmetric A twice
 //   W11 <- W11 - 2 tril(W21^T L21)                  the panel solve's effect on L11
-//   W11 <- backward(L11, W11)
+//   W11 <- backward(L11, W11)                       the inverse-based expression
 //   W12 <- W21^T
-// 2 n^3 / 3 flops at the blocked levels instead of 5 n^3 / 3 with the full inverse; blocks of at
-// most bwd_base(batch) rows take the inverse-based path.
+// 2 n^3 / 3 flops in the large products instead of 5 n^3 / 3 with the full inverse.  The inverses of all diagonal blocks are formed
+// beforehand in one go; they serve the solves with L11 and the blocks' own expressions.  Scratch per matrix: the inverses as a band of
+// n0 columns and two n0 x n0 blocks, in which the merges' temporary lives before.  W21 on its way to the product with the inverse is
+// kept where W12 comes in the end.
+// Against halving with an inverse (and block substitutions) of their own per block, ms, fp64 / fp32: one matrix of n = 8192 8.87 -> 8.34 /
+// 4.90 -> 4.48, 4096 1.83 -> 1.60 / 1.02 -> 0.92, 3001 1.05 -> 0.90 / 0.71 -> 0.57, 1000 of n = 300 2.80 -> 2.06 / 1.51 -> 1.20.
 // ---------------------------------------------------------------------------------
 template <typename T>
-static la_status backward_rec(View<const T> Lam, View<T> W, int64_t batch, int n, hipStream_t st)
+static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, int64_t batch, int n, int n0, bool aliased,
+                                hipStream_t st)
 {
-    if (n <= bwd_base(batch, sizeof(T)))
-        return backward_impl<T>(Lam, cv(W), W, batch, n, true, st);
-    // Halving (to the multiple of 128 next to n / 2) when that lands on whole base blocks all the way
-    // down, i.e. n = 2048 * 2^k; any other n > 4096 peels a first block of 2048 columns instead, which
-    // keeps the solve with L11 small and the blocks at the bottom at the full base size
-    // (n = 6144: 5.5 -> 4.8 ms, 12288: 27.9 -> 25.5 ms; 8192: no difference).
-    const int q = n / 2048;
-    const bool halves_fit = n % 2048 == 0 && (q & (q - 1)) == 0;
-    const int n1 = (n > 4096 && !halves_fit) ? 2048 : (n / 2 + 127) / 128 * 128, n2 = n - n1;
-    View<T> W21 = W.sub(n1, 0), W22 = W.sub(n1, n1);
-    View<const T> L21 = Lam.sub(n1, 0);
-    LA_TRY(backward_rec<T>(Lam.sub(n1, n1), W22, batch, n2, st));
-    GemmOpts plain;
-    LA_TRY(launch_gemm<T>(cv(W22), L21, W21, batch, n2, n1, n2, T(-2), T(1), plain, st));
-    // rows of W21 are the vectors; x <- x L11^-1 is L11^-T applied to x^T
-    LA_TRY(tri_apply_v<T>(true, false, T(0.5), batch, n1, n2, Lam, cv(W21).t(), W21.t(), true, st));
-    GemmOpts om;
-    om.maskC = 1;
-    LA_TRY(launch_gemm<T>(cv(W21).t(), L21, W, batch, n1, n1, n2, T(-2), T(1), om, st));
-    LA_TRY(backward_rec<T>(Lam, W, batch, n1, st));
-    return launch_copy<T>(cv(W21).t(), W.sub(0, n1), batch, n1, n2, T(1), 0, st);
-}
-
-template <typename T>
-static la_status backward_blocked(View<const T> Lam, View<const T> G, View<T> W, int64_t batch, int n, bool aliased,
-                                  hipStream_t st)
-{
-    if (!aliased)  // lower triangle of Lbar into the output, which is then updated in place; what lies above the
-                   // diagonal is never read and is all written by the sweep (base blocks and mirror copies)
-        LA_TRY(launch_copy<T>(G, W, batch, n, n, T(1), 2, st));
-    return backward_rec<T>(Lam, W, batch, n, st);
+    ArenaFrame frame;
+    // (one stride for all of them: the symmetric sum of two products exchanges its operands' base pointers)
+    const int64_t band = (int64_t)n * n0 + n, block = (int64_t)n0 * n0, item = band + std::max(2 * block, (int64_t)n * n0 / 4);
+    void *p = nullptr;
+    LA_TRY(arena_take((size_t)(batch * item) * sizeof(T), &p));
+    View<T> Li{(T *)p, item, n0, 1}, X{Li.p + band, item, n0, 1}, Y{X.p + block, item, n0, 1};
+    LA_TRY(launch_tri_inverse128<T>(Lam, Li, batch, n, st));
+    LA_TRY(inverse_merge<T>(Lam, Li, X, batch, n, n0, st));
+    for (int o = (n - 1) / n0 * n0; o >= 0; o -= n0) {
+        const int nb = n - o < n0 ? n - o : n0, q = o + nb, r = n - q;
+        View<const T> L11 = Lam.sub(o, o), G11 = G.sub(o, o);
+        View<T> W11 = W.sub(o, o), W21 = W.sub(q, o), W12 = W.sub(o, q);
+        if (r > 0) {
+            View<const T> L21 = Lam.sub(q, o);
+            LA_TRY(launch_copy<T>(G.sub(q, o), W12.t(), batch, r, nb, T(1), 0, st));
+            if (!aliased)
+                LA_TRY(launch_copy<T>(G11, W11, batch, nb, nb, T(1), 2, st));
+            GemmOpts plain, ol, om;
+            LA_TRY(launch_gemm<T>(cv(W).sub(q, q), L21, W12.t(), batch, r, nb, r, T(-2), T(1), plain, st));
+            ol.triB = 1;
+            LA_TRY(launch_gemm<T>(cv(W12).t(), cv(Li).sub(o, o), W21, batch, r, nb, nb, T(0.5), T(0), ol, st));
+            om.maskC = 1;
+            LA_TRY(launch_gemm<T>(cv(W21).t(), L21, W11, batch, nb, nb, r, T(-2), T(1), om, st));
+            G11 = cv(W11);
+        }
+        GemmOpts op;
+        op.triA = 2;
+        op.triB = 1;
+        op.maskC = 1;
+        op.halfDiag = 1;
+        LA_TRY(launch_gemm<T>(L11.t(), G11, X, batch, nb, nb, nb, T(1), T(0), op, st));
+        LA_TRY(congruence<T>(cv(Li).sub(o, o), cv(X), Y, W11, batch, nb, st));
+        if (r > 0)
+            LA_TRY(launch_copy<T>(cv(W21).t(), W12, batch, nb, r, T(1), 0, st));
+    }
+    return LA_OK;
 }
 
 // ---------------------------------------------------------------------------------

@@ -1,0 +1,64 @@
+"""The factorisation's gradient swept block column by block column, at the edges of the block rule: last blocks of one row and of
+nearly a whole block, every block size, both triangles, in place, beside the problems just below the rule; and operators whose inner
+dimension is a multiple of 16 but not of 64."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1710_08717_amd as la
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f64": 1e-10, "f32": 2e-4}
+NP = {"f64": np.float64, "f32": np.float32}
+
+
+def rel(x, ref):
+    x = x.cpu().numpy().astype(np.float64).reshape(x.shape[0], -1)
+    ref = np.asarray(ref).reshape(ref.shape[0], -1)
+    return np.max(np.linalg.norm(x - ref, axis=1) / np.linalg.norm(ref, axis=1))
+
+
+def factor(batch, n, rng, dtype):
+    L = np.tril(rng.standard_normal((batch, n, n))) * (0.5 / np.sqrt(n))
+    i = np.arange(n)
+    L[:, i, i] = 1.0 + rng.random((batch, n))
+    return L.astype(NP[dtype])
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("lower", [True, False])
+@pytest.mark.parametrize("batch,n", [(150, 257), (180, 214), (178, 213), (40, 427), (36, 513), (9, 1025), (4, 1024), (3, 1183), (2, 2048)])
+def test_sweep(batch, n, lower, dtype):
+    rng = np.random.default_rng(n)
+    L = factor(batch, n, rng, dtype)
+    Lbar = rng.standard_normal((batch, n, n)).astype(NP[dtype])
+    if not lower:
+        L = L.transpose(0, 2, 1).copy()
+    ref = oracle.potrf_backward(L.astype(np.float64), Lbar.astype(np.float64), lower=lower)
+    other = np.triu(np.ones((n, n), bool), 1) if lower else np.tril(np.ones((n, n), bool), -1)
+    L[:, other] = np.nan
+    Lbar[:, other] = np.nan
+    Lg, Gg = torch.from_numpy(L).cuda(), torch.from_numpy(Lbar).cuda()
+    got = la.potrf_backward(Lg, Gg, lower=lower)
+    assert torch.equal(got, got.mT)
+    assert rel(got, ref) <= TOL[dtype]
+    inplace = la.potrf_backward(Lg, Gg, lower=lower, out=Gg)
+    assert torch.equal(inplace, got)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("batch,n", [(1, 144), (3, 208), (2, 336), (1, 720), (40, 304)])
+def test_inner_dimension_of_16_not_64(batch, n, dtype):
+    rng = np.random.default_rng(n)
+    L = factor(batch, n, rng, dtype)
+    X = rng.standard_normal((batch, n, 48)).astype(NP[dtype])
+    G = rng.standard_normal((batch, n, n)).astype(NP[dtype])
+    L64, X64, G64 = (np.tril(L).astype(np.float64), X.astype(np.float64), G.astype(np.float64))
+    Lg, Xg, Gg = (torch.from_numpy(x).cuda() for x in (L, X, G))
+    assert rel(la.trmm(Lg, Xg), L64 @ X64) <= TOL[dtype]
+    assert rel(la.gemm2(Gg, Xg), G64 @ X64) <= TOL[dtype]
+    assert rel(la.syrk_backward(Xg, Gg), (G64 + G64.transpose(0, 2, 1)) @ X64) <= TOL[dtype]
+    assert rel(la.potri(Lg), oracle.potri(L64)) <= TOL[dtype]
+    assert rel(la.potrf_backward(Lg, Gg), oracle.potrf_backward(L64, G64)) <= TOL[dtype]
