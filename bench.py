@@ -39,13 +39,14 @@ def backward_flops(n, batch, elem_size):
     block column of k columns with r rows below costs 2 r^2 k (symmetric block times panel) + r k^2 (panel
     solve) + r k^2 (lower triangle of the panel product) and its diagonal block 2 k^3.  The rule for the
     block size mirrors the library's."""
-    mi = 1048576.0
-    if n <= 128 or float(batch) * n * n < (8.0 if elem_size == 4 else 4.0) * mi:
-        return 2.0 * n ** 3
-    base = 128
-    while base < 1024 and 2.0 * base <= 0.6 * n and 4.0 * base * base * batch <= 4.0 * mi:
-        base *= 2
-    if base > 0.6 * n:
+    elements, scale = float(batch) * n * n / 1048576.0, 2.0 if elem_size == 4 else 1.0
+    if n >= 400 and batch <= 128 and elements >= 4.0 * scale:
+        base = 256
+        while base < 1024 and 2.0 * base <= 0.6 * n and 4.0 * base * base * batch <= 4.0 * 1048576.0:
+            base *= 2
+    elif n >= 214 and elements >= 12.0 * scale:
+        base = 128
+    else:
         return 2.0 * n ** 3
     total = 0.0
     for o in range(0, n, base):

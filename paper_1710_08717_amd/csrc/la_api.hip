@@ -262,22 +262,25 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
                                 hipStream_t st);
 
 // Block columns of the reverse sweep, 0 where the inverse-based expression takes the whole matrix.  The expression's 5 n^3 / 3 flops run
-// in a few large products, the sweep's 2 n^3 / 3 and n0^3 per block in many smaller, dependent ones: it pays from about 4 Mi matrix
-// elements over the whole batch (fp32: 8 Mi), in block columns that leave up to 4 Mi to one block's products.  Expression -> sweep, us:
-// fp64 18 x 512^2 226 -> 195, 32 x 512^2 294 -> 240, 4 x 1024^2 279 -> 259 (3: 224 -> 229), 100 x 256^2 175 -> 170, 60 x 333^2 252 -> 258,
-// 1 x 1800^2 411 -> 425; fp32 32 x 512^2 178 -> 153, 18 131 -> 131, 8 x 1024^2 278 -> 218, 4 161 -> 175, 100 x 256^2 100 -> 109.
-// n0 = 256 / 512 / 1024: fp64 8 x 1024^2 401 / 343 / -, 4 x 2048^2 1146 / 941 / 966, 1 x 3001^2 1509 / 1082 / 898 (2048: 909),
-// 30 x 640^2 391 / 450 / -.  Blocks of 2048 would be 4 to 6 % faster above n = 5000 (1 x 8192^2 fp64 8339 -> 7982, fp32 4481 -> 4210), but
-// the errors grow with the blocks' inverses: fp32 7.5e-7 -> 1.05e-6 there (halving with substitutions: 9.0e-7).
+// in a few large products, the sweep's 2 n^3 / 3 and n0^3 per block in many smaller, dependent ones: with columns of 256 and more it pays
+// from about 4 Mi matrix elements over the whole batch (fp32: 8 Mi), with columns of 128 from 12 Mi (24 Mi).  Expression -> sweep, us:
+// 256, fp64 18 x 512^2 226 -> 195, 32 x 512^2 294 -> 240, 13 x 512^2 170 -> 166, 100 x 400^2 494 -> 482, 60 x 333^2 252 -> 252, fp32 32 x 512^2
+// 178 -> 153, 18 131 -> 131, 100 x 400^2 276 -> 270; 512, fp64 4 x 1024^2 279 -> 259 (3: 224 -> 229), fp32 8 x 1024^2 278 -> 218, 4 161 -> 175;
+// 128, fp64 300 x 222^2 420 -> 398, 200 x 250^2 345 -> 342, 80 x 333^2 292 -> 306, fp32 400 x 256^2 358 -> 292, 300 x 222^2 225 -> 238,
+// 150 x 333^2 292 -> 280.  n0 = 256 / 512 / 1024: fp64 8 x 1024^2 401 / 343 / -, 4 x 2048^2 1146 / 941 / 966, 1 x 3001^2 1509 / 1082 / 898
+// (2048: 909), 30 x 640^2 391 / 450 / -; 128 / 256: 70 x 480^2 496 / 475 and fp32 309 / 267.  Blocks of 2048 would be 4 to 6 % faster above
+// n = 5000 (1 x 8192^2 fp64 8339 -> 7982, fp32 4481 -> 4210), but the errors grow with the blocks' inverses: fp32 7.5e-7 -> 1.05e-6 there
+// (halving with substitutions: 9.0e-7).
 static int sweep_block(int64_t batch, int n, size_t elem)
 {
-    const double mi = 1048576.0, elements = (double)batch * n * n;
-    if (elements < (elem == 4 ? 8.0 : 4.0) * mi)
-        return 0;
-    int b = 128;
-    while (b < 1024 && 2.0 * b <= 0.6 * n && 4.0 * b * b * (double)batch <= 4.0 * mi)
-        b *= 2;
-    return b <= 0.6 * n ? b : 0;
+    const double mi = 1048576.0, b = (double)batch, elements = b * n * n, scale = elem == 4 ? 2.0 : 1.0;
+    if (n >= 400 && b <= 128.0 && elements >= 4.0 * scale * mi) {
+        int n0 = 256;
+        while (n0 < 1024 && 2.0 * n0 <= 0.6 * n && 4.0 * n0 * n0 * b <= 4.0 * mi)
+            n0 *= 2;
+        return n0;
+    }
+    return n >= 214 && elements >= 12.0 * scale * mi ? 128 : 0;
 }
 
 // W = 1/2 (Li^T (P + P^T) Li) for lower triangular Li and P (what lies above their diagonals is not read), both triangles
