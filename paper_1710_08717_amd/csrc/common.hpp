@@ -604,6 +604,9 @@ la_status launch_zero_strict_upper(View<T> X, int64_t batch, int n, hipStream_t 
 // X <- scale * (X + X^T) on n x n (exactly symmetric result).
 template <typename T>
 la_status launch_symmetrize(View<T> X, int64_t batch, int n, T scale, hipStream_t st);
+// X <- S + S^T for a matrix S with X's strides (exactly symmetric result)
+template <typename T>
+la_status launch_sym_sum(const T *S, View<T> X, int64_t batch, int n, hipStream_t st);
 // X(i,j) <- X(j,i) for i < j (copy the lower triangle over the upper).
 template <typename T>
 la_status launch_mirror_lower(View<T> X, int64_t batch, int n, hipStream_t st);

@@ -141,11 +141,11 @@ la_status launch_zero_strict_upper(View<T> X, int64_t batch, int n, hipStream_t 
     return launch_check("zero_strict_upper");
 }
 
-// mode 0: X <- scale * (X + X^T).   mode 1: X(i,j) <- X(j,i) for i < j (lower copied to upper).
+// mode 0: X <- scale * (S + S^T), S a matrix with X's strides, or X itself.   mode 1 (S is X): X(i,j) <- X(j,i) for i < j (lower copied to upper).
 // One block per tile pair (ti >= tj); both tiles pass through LDS so every global access is
 // along the contiguous direction.
 template <typename T>
-__global__ __launch_bounds__(256) void k_sym(View<T> X, int64_t batch, int n, T scale, int mode, int nt)
+__global__ __launch_bounds__(256) void k_sym(const T *S, View<T> X, int64_t batch, int n, T scale, int mode, int nt)
 {
     __shared__ T sa[ET][ET + 1];
     __shared__ T sb[ET][ET + 1];
@@ -156,14 +156,15 @@ __global__ __launch_bounds__(256) void k_sym(View<T> X, int64_t batch, int n, T 
     if (tj > ti)
         return;
     T *xp = X.p + b * X.bs;
+    const T *sp = S + b * X.bs;
     // treat the matrix in memory order: for a symmetric operation the orientation is immaterial
     const bool tr = (X.cs != 1);
     const int64_t ld = tr ? X.cs : X.rs;
     const int r0 = ti * ET, c0 = tj * ET;
     for (int t = threadIdx.x; t < ET * ET; t += 256) {
         const int u = t / ET, w = t % ET;
-        sa[u][w] = (r0 + u < n && c0 + w < n) ? xp[(int64_t)(r0 + u) * ld + c0 + w] : T(0);  // tile (ti,tj)
-        sb[u][w] = (c0 + u < n && r0 + w < n) ? xp[(int64_t)(c0 + u) * ld + r0 + w] : T(0);  // tile (tj,ti)
+        sa[u][w] = (r0 + u < n && c0 + w < n) ? sp[(int64_t)(r0 + u) * ld + c0 + w] : T(0);  // tile (ti,tj)
+        sb[u][w] = (c0 + u < n && r0 + w < n) ? sp[(int64_t)(c0 + u) * ld + r0 + w] : T(0);  // tile (tj,ti)
     }
     __syncthreads();
     // In memory order "lower" means row >= column; when the view is transposed the logical
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(256) void k_sym(View<T> X, int64_t batch, int n, T 
 }
 
 template <typename T>
-static la_status launch_sym(View<T> X, int64_t batch, int n, T scale, int mode, hipStream_t st)
+static la_status launch_sym(const T *S, View<T> X, int64_t batch, int n, T scale, int mode, hipStream_t st)
 {
     if (batch <= 0 || n <= 0)
         return LA_OK;
@@ -211,18 +212,23 @@ static la_status launch_sym(View<T> X, int64_t batch, int n, T scale, int mode, 
     const int64_t blocks = (int64_t)nt * nt * batch;
     if (blocks > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
-    LA_LAUNCH((k_sym<T>), dim3((unsigned)blocks), dim3(256), 0, st, X, batch, n, scale, mode, nt);
+    LA_LAUNCH((k_sym<T>), dim3((unsigned)blocks), dim3(256), 0, st, S, X, batch, n, scale, mode, nt);
     return launch_check("sym");
 }
 template <typename T>
 la_status launch_symmetrize(View<T> X, int64_t batch, int n, T scale, hipStream_t st)
 {
-    return launch_sym<T>(X, batch, n, scale, 0, st);
+    return launch_sym<T>(X.p, X, batch, n, scale, 0, st);
+}
+template <typename T>
+la_status launch_sym_sum(const T *S, View<T> X, int64_t batch, int n, hipStream_t st)
+{
+    return launch_sym<T>(S, X, batch, n, T(1), 0, st);
 }
 template <typename T>
 la_status launch_mirror_lower(View<T> X, int64_t batch, int n, hipStream_t st)
 {
-    return launch_sym<T>(X, batch, n, T(1), 1, st);
+    return launch_sym<T>(X.p, X, batch, n, T(1), 1, st);
 }
 
 // One wavefront per matrix: out[b] = sum_i log L[b,i,i].
@@ -523,6 +529,7 @@ la_status launch_fill_i32(int32_t *p, int64_t count, int32_t v, hipStream_t st)
     template la_status launch_tril_split<T>(View<const T>, View<T>, View<T>, int64_t, int, hipStream_t);        \
     template la_status launch_zero_strict_upper<T>(View<T>, int64_t, int, hipStream_t);                         \
     template la_status launch_symmetrize<T>(View<T>, int64_t, int, T, hipStream_t);                             \
+    template la_status launch_sym_sum<T>(const T *, View<T>, int64_t, int, hipStream_t);                        \
     template la_status launch_mirror_lower<T>(View<T>, int64_t, int, hipStream_t);                              \
     template la_status launch_sumlogdiag<T>(const T *, T *, int64_t, int, hipStream_t);                         \
     template la_status launch_partial_sums<T>(const SumList<T> &, int, double *, hipStream_t); \

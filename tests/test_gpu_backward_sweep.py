@@ -62,3 +62,23 @@ def test_inner_dimension_of_16_not_64(batch, n, dtype):
     assert rel(la.syrk_backward(Xg, Gg), (G64 + G64.transpose(0, 2, 1)) @ X64) <= TOL[dtype]
     assert rel(la.potri(Lg), oracle.potri(L64)) <= TOL[dtype]
     assert rel(la.potrf_backward(Lg, Gg), oracle.potrf_backward(L64, G64)) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("lower", [True, False])
+@pytest.mark.parametrize("batch,n,k", [(64, 128, 128), (63, 129, 131), (64, 127, 128), (5, 517, 127), (5, 517, 160)])
+def test_rules_on_the_symmetric_sum(batch, n, k, lower, dtype):
+    """potri's and syrk's backward rules on both sides of the sizes from which G + G^T is formed"""
+    rng = np.random.default_rng(n + k)
+    L = factor(batch, n, rng, dtype)
+    G = rng.standard_normal((batch, n, n)).astype(NP[dtype])
+    A = rng.standard_normal((batch, n, k) if lower else (batch, k, n)).astype(NP[dtype])
+    if not lower:
+        L = L.transpose(0, 2, 1).copy()
+    B = oracle.potri(L.astype(np.float64), lower=lower).astype(NP[dtype])
+    Lg, Gg, Ag, Bg = (torch.from_numpy(x).cuda() for x in (L, G, A, B))
+    ref = oracle.potri_backward(L.astype(np.float64), B.astype(np.float64), G.astype(np.float64), lower=lower)
+    assert rel(la.potri_backward(Lg, Bg, Gg, lower=lower), ref) <= TOL[dtype]
+    S = G.astype(np.float64) + G.transpose(0, 2, 1).astype(np.float64)
+    ref = S @ A.astype(np.float64) if lower else A.astype(np.float64) @ S
+    assert rel(la.syrk_backward(Ag, Gg, trans=not lower), ref) <= TOL[dtype]
