@@ -366,7 +366,12 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
 {
     ArenaFrame frame;
     // (one stride for all of them: the symmetric sum of two products exchanges its operands' base pointers)
-    const int64_t band = (int64_t)n * n0 + n, block = (int64_t)n0 * n0, item = band + std::max(2 * block, (int64_t)n * n0 / 4);
+    const int64_t band = (int64_t)n * n0 + n, block = (int64_t)n0 * n0;
+    int64_t item = band + std::max(2 * block, (int64_t)n * n0 / 4);
+    // up to 8 Mi elements (fp32: 16 Mi) a call takes no less than the two squares of the inverse-based expression: its size does not
+    // depend on which of the two forms runs
+    if ((double)batch * n * n <= (sizeof(T) == 4 ? 16.0 : 8.0) * 1048576.0)
+        item = std::max(item, 2 * (int64_t)n * n);
     void *p = nullptr;
     LA_TRY(arena_take((size_t)(batch * item) * sizeof(T), &p));
     View<T> Li{(T *)p, item, n0, 1}, X{Li.p + band, item, n0, 1}, Y{X.p + block, item, n0, 1};
