@@ -41,8 +41,9 @@
  *    The plain form of an entry point is its _ws form without a workspace: it returns
  *    LA_ERR_WORKSPACE (and launches nothing) when the call needs one.  A product over a long
  *    inner dimension whose sizes or addresses are off the 16-byte grid is split only where the
- *    workspace has room for it: la_workspace_bytes() counts that room, but the call also runs
- *    without it (slower).
+ *    workspace has room for it, and the backward rules of syrk and potri form Bbar + Bbar^T once
+ *    where it has room for that beside what the product with it takes: la_workspace_bytes() counts
+ *    that room, but the call also runs without it (slower).
  *    A workspace is device memory, 256-byte aligned, disjoint from every operand; its
  *    contents are undefined after the call; it may be reused by the next call on the
  *    same stream and must not be shared by calls that may run at the same time.

@@ -62,6 +62,22 @@ bool arena_room(size_t bytes)
     return a->used + ((bytes + 255) & ~(size_t)255) <= a->cap;
 }
 
+// The most scratch that `op` takes at a time, found by a run that launches nothing; needed_only: without what arena_room offers.
+template <class F>
+static la_status sizing_pass(F &&op, size_t *peak, bool needed_only = false)
+{
+    Arena a;
+    a.dry = true;
+    a.needed_only = needed_only;
+    a.base = reinterpret_cast<char *>((uintptr_t)1 << 46);  // never dereferenced
+    Arena *prev = current_arena();
+    current_arena() = &a;
+    const la_status s = op();
+    current_arena() = prev;
+    *peak = a.peak;
+    return s;
+}
+
 template <typename T>
 static la_status scratch_views(int64_t batch, int n, int count, View<T> *out)
 {
@@ -777,18 +793,33 @@ static la_status trsm_backward_t(int lower, int trans, int rightside, double alp
     return LA_OK;
 }
 
-// S = G + G^T in scratch, where the call's workspace has room for it and one product with S instead of two with G and G^T pays for the pass
-// (`cols` columns of the product; S.p stays null otherwise).  us, fp64 / fp32: potri's rule on 64 x 200^2 153 -> 110 / 87 -> 71, 64 x 128^2
+// C = alpha (G + G^T) A, resp. (right) alpha A (G + G^T), as one product with S = G + G^T in scratch (`cols` rows or columns beside S).
+// Only where the workspace has room for S and for what that product takes itself, a split inner dimension, and where the product it saves
+// pays for the pass over G; *done stays false otherwise.  us, fp64 / fp32: potri's rule on 64 x 200^2 153 -> 110 / 87 -> 71, 64 x 128^2
 // 62 -> 58 / 43 -> 41, 2000^2 1051 -> 703 / 613 -> 427, syrk's rule on 64 x 200^2 with 128 columns 62 -> 41 / 34 -> 25.
 template <typename T>
-static la_status sym_sum_scratch(const T *G, int64_t batch, int n, int cols, View<T> *S, hipStream_t st)
+static la_status symm_product(const T *G, View<const T> A, View<T> C, int64_t batch, int n, int cols, bool right, T alpha, bool *done,
+                              hipStream_t st)
 {
     const int64_t nn = (int64_t)n * n;
-    *S = View<T>{nullptr, nn, n, 1};
-    if (n < 128 || cols < 128 || (double)batch * nn < 1048576.0 || !arena_room((size_t)batch * nn * sizeof(T)))
+    *done = false;
+    if (n < 128 || cols < 128 || (double)batch * nn < 1048576.0)
         return LA_OK;
-    LA_TRY(scratch_views<T>(batch, n, 1, S));
-    return launch_sym_sum<T>(G, *S, batch, n, st);
+    ArenaFrame frame;
+    View<T> S;
+    auto product = [&]() {
+        LA_TRY(scratch_views<T>(batch, n, 1, &S));
+        LA_TRY(launch_sym_sum<T>(G, S, batch, n, st));
+        GemmOpts o;
+        return right ? launch_gemm<T>(A, cv(S), C, batch, cols, n, n, alpha, T(0), o, st)
+                     : launch_gemm<T>(cv(S), A, C, batch, n, cols, n, alpha, T(0), o, st);
+    };
+    size_t bytes = 0;
+    LA_TRY(sizing_pass(product, &bytes));
+    if (!arena_room(bytes))
+        return LA_OK;
+    *done = true;
+    return product();
 }
 
 // syrk backward (section 4.2 "syrk"): Abar = alpha (Bbar + Bbar^T) A  resp.  alpha A (Bbar + Bbar^T),
@@ -816,21 +847,16 @@ static la_status syrk_backward_t(int trans, double alpha, int64_t batch, int n, 
                                    View<T>{(T *)Abar, nk, 1, n}, st);
     }
     GemmOpts o;
-    ArenaFrame frame;
-    View<T> S;
-    LA_TRY(sym_sum_scratch<T>(G.p, batch, n, k, &S, st));
+    View<const T> Av{(const T *)A, nk, trans ? n : k, 1};
+    View<T> Ov{(T *)Abar, nk, trans ? n : k, 1};
+    bool done;
+    LA_TRY(symm_product<T>(G.p, Av, Ov, batch, n, k, trans != 0, (T)alpha, &done, st));
+    if (done)
+        return LA_OK;
     if (!trans) {
-        View<const T> Av{(const T *)A, nk, k, 1};
-        View<T> Ov{(T *)Abar, nk, k, 1};
-        if (S.p)
-            return launch_gemm<T>(cv(S), Av, Ov, batch, n, k, n, (T)alpha, T(0), o, st);
         LA_TRY(launch_gemm<T>(G, Av, Ov, batch, n, k, n, (T)alpha, T(0), o, st));
         return launch_gemm<T>(G.t(), Av, Ov, batch, n, k, n, (T)alpha, T(1), o, st);
     }
-    View<const T> Av{(const T *)A, nk, n, 1};
-    View<T> Ov{(T *)Abar, nk, n, 1};
-    if (S.p)
-        return launch_gemm<T>(Av, cv(S), Ov, batch, k, n, n, (T)alpha, T(0), o, st);
     LA_TRY(launch_gemm<T>(Av, G, Ov, batch, k, n, n, (T)alpha, T(0), o, st));
     return launch_gemm<T>(Av, G.t(), Ov, batch, k, n, n, (T)alpha, T(1), o, st);
 }
@@ -916,15 +942,8 @@ static la_status potri_backward_t(int lower, int64_t batch, int n, const void *L
     // 40 215 -> 144 and 433 -> 251; 4096 of n = 48 118 -> 90 and 198 -> 146); at n = 64 the tiles of the general product are
     // full (298 -> 313 us).
     const bool leaf = n <= 48 && symm_leaf_takes<T>(batch, n, n);
-    bool summed = false;
-    {
-        ArenaFrame frame;
-        View<T> S;
-        LA_TRY(sym_sum_scratch<T>(G.p, batch, n, n, &S, st));
-        summed = S.p != nullptr;
-        if (summed)
-            LA_TRY(launch_gemm<T>(lower ? Bv : cv(S), lower ? cv(S) : Bv, X, batch, n, n, n, T(1), T(0), o, st));
-    }
+    bool summed;
+    LA_TRY(symm_product<T>(G.p, Bv, X, batch, n, n, lower != 0, T(1), &summed, st));
     if (lower) {
         if (leaf) {  // (B S)^T = S B^T
             LA_TRY(launch_symm_leaf<T>(T(1), batch, n, n, G, Bv.t(), X.t(), st));
@@ -1093,21 +1112,6 @@ static la_status gp_t(int64_t batch, int n, const void *A, const void *y, void *
 // What the body can also use (arena_room) is in the answer of la_workspace_bytes, but nothing is
 // refused for the lack of it.
 // ---------------------------------------------------------------------------------
-template <class F>
-static la_status sizing_pass(F &&op, size_t *peak, bool needed_only = false)
-{
-    Arena a;
-    a.dry = true;
-    a.needed_only = needed_only;
-    a.base = reinterpret_cast<char *>((uintptr_t)1 << 46);  // never dereferenced
-    Arena *prev = current_arena();
-    current_arena() = &a;
-    const la_status s = op();
-    current_arena() = prev;
-    *peak = a.peak;
-    return s;
-}
-
 template <class F>
 static la_status with_workspace(void *ws, size_t ws_bytes, F &&op)
 {

@@ -249,3 +249,30 @@ def test_products_of_odd_sizes_run_without_a_workspace(la, dtype):
     # aligned sizes: the scratch is needed, as before
     A, B, C = R(64, 4096), R(4096, 64), R(64, 64)
     assert lib.la_gemm2_batched(code, 0, 0, 1.0, 1, 64, 64, 4096, p(A), p(B), p(C), st) == 4
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("trans", [False, True])
+def test_syrk_rule_on_every_workspace_from_the_least_to_the_full_one(la, trans, dtype):
+    """Its product is split along the long inner dimension (which it needs scratch for) and formed with Bbar + Bbar^T where there is room
+    for both: between the two sizes it runs as two products, and nothing behind the workspace is touched."""
+    import torch
+
+    from paper_1710_08717_amd import binding
+
+    dt = torch.float64 if dtype == "f64" else torch.float32
+    tol = {"f32": 2e-4, "f64": 1e-10}[dtype]
+    g = torch.Generator(device="cuda").manual_seed(9)
+    n, k = 2048, 256
+    A = torch.randn((k, n) if trans else (n, k), generator=g, device="cuda", dtype=dt)
+    B = torch.randn(n, n, generator=g, device="cuda", dtype=dt)
+    S = B.double() + B.double().t()
+    ref = A.double() @ S if trans else S @ A.double()
+    full = la.workspace_bytes(binding.OP_SYRK_BACKWARD, A, 1, n, k=k)
+    square = n * n * B.element_size()
+    assert full > square
+    for need in (full - square, square, (square + full) // 2 // 256 * 256, full):
+        buf = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        got = la.syrk_backward(A, B, trans=trans, workspace=buf[:need])
+        assert float((got.double() - ref).norm() / ref.norm()) <= tol, need
+        assert (buf[need:] == 0xA5).all(), need

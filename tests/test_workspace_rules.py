@@ -1,0 +1,102 @@
+"""What a call does on workspaces of other sizes than la_workspace_bytes names, without a GPU: the library runs in a process of its own
+in which the HIP calls of the launch path are replaced by ones that only count the launches."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+SHIM = """
+long la_launches;
+int hipLaunchKernel(const void *f) { ++la_launches; return 0; }
+int hipGetLastError(void) { return 0; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipFuncSetAttribute(const void *f, int a, int v) { return 0; }
+int __hipPushCallConfiguration(void) { return 0; }
+int __hipPopCallConfiguration(void *a, void *b, void *c, void *d) { return 0; }
+"""
+
+# [op, dt, batch, n, m, k, flags, bytes] -> [status, launches]; bytes null: -> what la_workspace_bytes answers
+WORKER = """
+import ctypes, json, sys
+from ctypes import c_double as d, c_int as i, c_int64 as I, c_size_t as sz, c_void_p as vp
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+launches = ctypes.c_long.in_dll(shim, "la_launches")
+lib.la_workspace_bytes.restype = sz
+p = [vp((q + 1) << 44) for q in range(5)]  # operands, far apart and never dereferenced
+
+def call(op, dt, batch, n, m, k, flags, w):
+    if w is None:
+        return lib.la_workspace_bytes(i(op), i(dt), I(batch), i(n), i(m), i(k))
+    lower, trans, right = map(i, flags)
+    b, n, m, k, dt = I(batch), i(n), i(m), i(k), i(dt)
+    ws = (vp(1 << 50 if w else 0), sz(w), vp(0))
+    before = launches.value
+    tri = (dt, lower, trans, right, d(1), b, n, m)
+    s = {
+        0: lambda: lib.la_potrf_batched_ws(dt, lower, b, n, p[0], p[1], vp(0), *ws),
+        1: lambda: lib.la_potrf_backward_ws(dt, lower, b, n, p[0], p[1], p[2], *ws),
+        2: lambda: lib.la_trsm_batched_ws(*tri, p[0], p[1], p[2], *ws),
+        3: lambda: lib.la_trmm_batched_ws(*tri, p[0], p[1], p[1], *ws),
+        4: lambda: lib.la_syrk_batched_ws(dt, trans, d(1), b, n, k, p[0], p[1], *ws),
+        5: lambda: lib.la_gemm2_batched_ws(dt, trans, right, d(1), b, m, n, k, p[0], p[1], p[2], *ws),
+        6: lambda: lib.la_trsm_backward_ws(*tri, *p, *ws),
+        7: lambda: lib.la_trmm_backward_ws(*tri, *p, *ws),
+        8: lambda: lib.la_syrk_backward_ws(dt, trans, d(1), b, n, k, p[0], p[1], p[2], *ws),
+        10: lambda: lib.la_potri_ws(dt, lower, b, n, p[0], p[1], *ws),
+        11: lambda: lib.la_potri_backward_ws(dt, lower, b, n, p[0], p[1], p[2], p[3], *ws),
+    }[op]()
+    return [s, launches.value - before]
+
+print(json.dumps([call(*q) for q in json.load(sys.stdin)]))
+"""
+
+POTRF, BACKWARD, TRSM, TRMM, SYRK, GEMM2, TRSM_B, TRMM_B, SYRK_B, POTRI, POTRI_B = 0, 1, 2, 3, 4, 5, 6, 7, 8, 10, 11
+OPS = (POTRF, BACKWARD, TRSM, TRMM, SYRK, GEMM2, TRSM_B, TRMM_B, SYRK_B, POTRI, POTRI_B)
+OK, WORKSPACE = 0, 4
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    from paper_1710_08717_amd import binding, build
+
+    if not os.path.exists(binding.lib_path()):
+        build.build(force=False)
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None:
+        pytest.skip("no C compiler")
+    tmp = tmp_path_factory.mktemp("shim")
+    (tmp / "shim.c").write_text(SHIM)
+    subprocess.run([cc, "-shared", "-fPIC", "-w", "-o", str(tmp / "shim.so"), str(tmp / "shim.c")], check=True)
+
+    def run(queries):
+        r = subprocess.run([sys.executable, "-c", WORKER, str(tmp / "shim.so"), binding.lib_path()], input=json.dumps(queries),
+                           capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return json.loads(r.stdout)
+
+    return run
+
+
+def test_more_workspace_is_never_refused_and_a_refused_call_launches_nothing(ask):
+    """in steps of a sixteenth of what la_workspace_bytes names, among them products whose long inner dimension is split beside G + G^T"""
+    sizes = [(1, 2048, 256, 256), (1, 4096, 128, 128), (2, 2048, 256, 128), (1, 2050, 256, 256), (1, 512, 64, 64), (128, 512, 64, 64),
+             (4, 1024, 64, 64), (3, 700, 24, 24), (100, 200, 200, 200), (20, 51, 51, 51), (1, 129, 4099, 4099), (1, 64, 64, 4096)]
+    cases = [(op, dt, *s, fl) for op in OPS for dt in (0, 1) for s in sizes for fl in ((1, 0, 0), (0, 1, 1))]
+    full = ask([[*c, None] for c in cases])
+    steps = [[w * q // 16 // 256 * 256 for q in range(17)] for w in full]
+    got = iter(ask([[*c, w] for c, ws in zip(cases, steps) for w in ws]))
+    wrong = []
+    for c, ws in zip(cases, steps):
+        accepted = False
+        for w in ws:
+            status, launches = next(got)
+            if status not in (OK, WORKSPACE) or (status == WORKSPACE and (launches or accepted)) or (status == OK and not launches):
+                wrong.append((c, w, status, launches))
+            accepted = accepted or status == OK
+        if not accepted:
+            wrong.append((c, "the full size"))
+    assert wrong == []
