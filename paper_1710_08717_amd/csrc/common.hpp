@@ -582,6 +582,7 @@ struct GemmOpts {
                          // A^T B's, so the second pass only swaps the two base pointers -- and store every entry with its
                          // mirror image.  2: C = alpha A B + beta C for an A B that is symmetric (same strides) and a C of
                          // which the lower triangle is read: one pass, stored in the same way.  maskC is not used.
+    int split_if_room = 0;  // 1: a long inner dimension is split only where the workspace has room for the partial sums
 };
 template <typename T>
 la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N, int K, T alpha,

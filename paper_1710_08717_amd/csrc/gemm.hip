@@ -723,6 +723,7 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
         t.reverse = o.reverse;
         t.shells = o.shells;
         t.min_tile64 = o.min_tile64;
+        t.split_if_room = o.split_if_room;
         return launch_gemm<T>(B.t(), A.t(), C.t(), batch, N, M, K, alpha, beta, t, st);
     }
     constexpr int VW = Mfma<T>::VW;
@@ -758,7 +759,7 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             splits = (K + Kc - 1) / Kc;
             const size_t bytes = (size_t)batch * splits * M * N * sizeof(T);
             // (an unaligned or odd-sized product goes without the split where the caller gave no memory for it)
-            if (splits >= 2 && bytes <= SPLITK_MAX_BYTES && (!f.rag || arena_room(bytes))) {
+            if (splits >= 2 && bytes <= SPLITK_MAX_BYTES && ((!f.rag && !o.split_if_room) || arena_room(bytes))) {
                 ArenaFrame frame;
                 void *buf = nullptr;
                 LA_TRY(arena_take(bytes, &buf));

@@ -287,6 +287,7 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
 // (2048: 909), 30 x 640^2 391 / 450 / -; 128 / 256: 70 x 480^2 496 / 475 and fp32 309 / 267.  Blocks of 2048 would be 4 to 6 % faster above
 // n = 5000 (1 x 8192^2 fp64 8339 -> 7982, fp32 4481 -> 4210), but the errors grow with the blocks' inverses: fp32 7.5e-7 -> 1.05e-6 there
 // (halving with substitutions: 9.0e-7).
+constexpr int SWEEP_MIN_N = 214;
 static int sweep_block(int64_t batch, int n, size_t elem)
 {
     const double mi = 1048576.0, b = (double)batch, elements = b * n * n, scale = elem == 4 ? 2.0 : 1.0;
@@ -296,7 +297,14 @@ static int sweep_block(int64_t batch, int n, size_t elem)
             n0 *= 2;
         return n0;
     }
-    return n >= 214 && elements >= 12.0 * scale * mi ? 128 : 0;
+    return n >= SWEEP_MIN_N && elements >= 12.0 * scale * mi ? 128 : 0;
+}
+
+// Elements of scratch per matrix of a sweep that keeps the inverses of `cols` columns at a time: those as a band of n0 columns, and two
+// n0 x n0 blocks, in which the merges' temporary lives before.
+static int64_t sweep_scratch(int n0, int64_t cols)
+{
+    return cols * n0 + cols + std::max(2 * (int64_t)n0 * n0, cols * n0 / 4);
 }
 
 // W = 1/2 (Li^T (P + P^T) Li) for lower triangular Li and P (what lies above their diagonals is not read), both triangles
@@ -332,8 +340,10 @@ static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, in
         return launch_backward_wave<T>(Lam, G, W, batch, n, st);
     if (n <= backward_leaf16_max_n<T>())  // one workgroup per matrix, everything in LDS, no scratch
         return launch_backward_leaf16<T>(Lam, G, W, batch, n, st);
-    if (const int n0 = sweep_block(batch, n, sizeof(T)))
-        return backward_sweep<T>(Lam, G, W, batch, n, n0, aliased, st);
+    // (the expression takes two squares; where the workspace has no room for them the sweep does with less)
+    const int n0 = sweep_block(batch, n, sizeof(T));
+    if (n0 > 0 || (n >= SWEEP_MIN_N && !arena_room((size_t)(2 * batch * n * n) * sizeof(T))))
+        return backward_sweep<T>(Lam, G, W, batch, n, n0 > 0 ? n0 : 256, aliased, st);
     ArenaFrame frame;
     View<T> sc[2];
     LA_TRY(scratch_views<T>(batch, n, 2, sc));
@@ -370,9 +380,10 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
 //   W11 <- backward(L11, W11)                       the inverse-based expression
 //   W12 <- W21^T
 // 2 n^3 / 3 flops in the large products instead of 5 n^3 / 3 with the full inverse.  The inverses of all diagonal blocks are formed
-// beforehand in one go; they serve the solves with L11 and the blocks' own expressions.  Scratch per matrix: the inverses as a band of
-// n0 columns and two n0 x n0 blocks, in which the merges' temporary lives before.  W21 on its way to the product with the inverse is
+// beforehand in one go; they serve the solves with L11 and the blocks' own expressions.  W21 on its way to the product with the inverse is
 // kept where W12 comes in the end.
+// Where the workspace is short the inverses are formed for fewer columns at a time, down to one block's, and with smaller blocks: what a call
+// cannot do without grows with the batch alone, so a workspace that was sized for a larger batch serves every smaller one.
 // Against halving with an inverse (and block substitutions) of their own per block, ms, fp64 / fp32: one matrix of n = 8192 8.87 -> 8.34 /
 // 4.90 -> 4.48, 4096 1.83 -> 1.60 / 1.02 -> 0.92, 3001 1.05 -> 0.90 / 0.71 -> 0.57, 1000 of n = 300 2.80 -> 2.06 / 1.51 -> 1.20.
 // ---------------------------------------------------------------------------------
@@ -381,20 +392,30 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
                                 hipStream_t st)
 {
     ArenaFrame frame;
+    int cols = n;  // whole blocks, or all of them
+    while (!arena_room((size_t)(batch * sweep_scratch(n0, cols)) * sizeof(T)) && (cols > n0 || n0 > 2 * NB)) {
+        if (cols > n0) {
+            cols = (cols / 2 + n0 - 1) / n0 * n0;
+        } else {
+            n0 /= 2;
+            cols = n;
+        }
+    }
     // (one stride for all of them: the symmetric sum of two products exchanges its operands' base pointers)
-    const int64_t band = (int64_t)n * n0 + n, block = (int64_t)n0 * n0;
-    int64_t item = band + std::max(2 * block, (int64_t)n * n0 / 4);
-    // up to 8 Mi elements (fp32: 16 Mi) a call takes no less than the two squares of the inverse-based expression: its size does not
-    // depend on which of the two forms runs
-    if ((double)batch * n * n <= (sizeof(T) == 4 ? 16.0 : 8.0) * 1048576.0)
-        item = std::max(item, 2 * (int64_t)n * n);
+    const int64_t item = sweep_scratch(n0, cols);
     void *p = nullptr;
     LA_TRY(arena_take((size_t)(batch * item) * sizeof(T), &p));
-    View<T> Li{(T *)p, item, n0, 1}, X{Li.p + band, item, n0, 1}, Y{X.p + block, item, n0, 1};
-    LA_TRY(launch_tri_inverse128<T>(Lam, Li, batch, n, st));
-    LA_TRY(inverse_merge<T>(Lam, Li, X, batch, n, n0, st));
+    if (!arena_room(0))  // (a sizing pass for the least: the products below take none they need)
+        return LA_OK;
+    View<T> Li{(T *)p, item, n0, 1}, X{Li.p + (int64_t)cols * n0 + cols, item, n0, 1}, Y{X.p + (int64_t)n0 * n0, item, n0, 1};
     for (int o = (n - 1) / n0 * n0; o >= 0; o -= n0) {
         const int nb = n - o < n0 ? n - o : n0, q = o + nb, r = n - q;
+        const int c0 = o / cols * cols, cc = n - c0 < cols ? n - c0 : cols;  // the columns whose inverses are there
+        if (q == c0 + cc) {
+            LA_TRY(launch_tri_inverse128<T>(Lam.sub(c0, c0), Li, batch, cc, st));
+            LA_TRY(inverse_merge<T>(Lam.sub(c0, c0), Li, X, batch, cc, n0, st));
+        }
+        const View<const T> Lio = cv(Li).sub(o - c0, o - c0);
         View<const T> L11 = Lam.sub(o, o), G11 = G.sub(o, o);
         View<T> W11 = W.sub(o, o), W21 = W.sub(q, o), W12 = W.sub(o, q);
         if (r > 0) {
@@ -403,9 +424,10 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
             if (!aliased)
                 LA_TRY(launch_copy<T>(G11, W11, batch, nb, nb, T(1), 2, st));
             GemmOpts plain, ol, om;
+            plain.split_if_room = om.split_if_room = 1;  // (the inverses had the first pick of the workspace)
             LA_TRY(launch_gemm<T>(cv(W).sub(q, q), L21, W12.t(), batch, r, nb, r, T(-2), T(1), plain, st));
             ol.triB = 1;
-            LA_TRY(launch_gemm<T>(cv(W12).t(), cv(Li).sub(o, o), W21, batch, r, nb, nb, T(0.5), T(0), ol, st));
+            LA_TRY(launch_gemm<T>(cv(W12).t(), Lio, W21, batch, r, nb, nb, T(0.5), T(0), ol, st));
             om.maskC = 1;
             LA_TRY(launch_gemm<T>(cv(W21).t(), L21, W11, batch, nb, nb, r, T(-2), T(1), om, st));
             G11 = cv(W11);
@@ -416,7 +438,7 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
         op.maskC = 1;
         op.halfDiag = 1;
         LA_TRY(launch_gemm<T>(L11.t(), G11, X, batch, nb, nb, nb, T(1), T(0), op, st));
-        LA_TRY(congruence<T>(cv(Li).sub(o, o), cv(X), Y, W11, batch, nb, st));
+        LA_TRY(congruence<T>(Lio, cv(X), Y, W11, batch, nb, st));
         if (r > 0)
             LA_TRY(launch_copy<T>(cv(W21).t(), W12, batch, nb, r, T(1), 0, st));
     }

@@ -7,6 +7,7 @@ import torch
 
 import oracle
 import paper_1710_08717_amd as la
+from paper_1710_08717_amd import binding
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +83,33 @@ def test_rules_on_the_symmetric_sum(batch, n, k, lower, dtype):
     S = G.astype(np.float64) + G.transpose(0, 2, 1).astype(np.float64)
     ref = S @ A.astype(np.float64) if lower else A.astype(np.float64) @ S
     assert rel(la.syrk_backward(Ag, Gg, trans=not lower), ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("lower", [True, False])
+@pytest.mark.parametrize("batch,n", [(3, 214), (2, 300), (3, 513), (70, 500), (5, 1025), (2, 1183), (1, 2300)])
+def test_sweep_on_short_workspaces(batch, n, lower, dtype):
+    """fewer inverses at a time and smaller blocks: from the full workspace down to the least, in place and not, nothing behind it touched"""
+    rng = np.random.default_rng(n)
+    L = factor(batch, n, rng, dtype)
+    Lbar = rng.standard_normal((batch, n, n)).astype(NP[dtype])
+    if not lower:
+        L = L.transpose(0, 2, 1).copy()
+    ref = oracle.potrf_backward(L.astype(np.float64), Lbar.astype(np.float64), lower=lower)
+    other = np.triu(np.ones((n, n), bool), 1) if lower else np.tril(np.ones((n, n), bool), -1)
+    L[:, other] = np.nan
+    Lbar[:, other] = np.nan
+    Lg, Gg = torch.from_numpy(L).cuda(), torch.from_numpy(Lbar).cuda()
+    full = la.workspace_bytes(binding.OP_POTRF_BACKWARD, Lg, batch, n)
+    least = batch * (3 * 128 * 128 + 128) * Lg.element_size()
+    assert least < full
+    for need in sorted({least, full} | {least + (full - least) * q // 8 // 256 * 256 for q in range(8)}):
+        buf = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        got = la.potrf_backward(Lg, Gg, lower=lower, workspace=buf[:need])
+        assert torch.equal(got, got.mT), need
+        assert rel(got, ref) <= TOL[dtype], need
+        inplace = Gg.clone()
+        assert torch.equal(la.potrf_backward(Lg, inplace, lower=lower, out=inplace, workspace=buf[:need]), got), need
+        assert (buf[need:] == 0xA5).all(), need
+    with pytest.raises(la.LaError):
+        la.potrf_backward(Lg, Gg, lower=lower, workspace=buf[:least - 256])

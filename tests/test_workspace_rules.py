@@ -100,3 +100,14 @@ def test_more_workspace_is_never_refused_and_a_refused_call_launches_nothing(ask
         if not accepted:
             wrong.append((c, "the full size"))
     assert wrong == []
+
+
+@pytest.mark.parametrize("dt", [0, 1])
+@pytest.mark.parametrize("n", [129, 213, 214, 222, 300, 400, 512, 600, 1024, 1183, 2048, 3001])
+def test_gradient_of_the_factorisation_runs_smaller_batches_on_a_larger_ones_workspace(ask, n, dt):
+    """across the batches at which its block columns get narrower (128 | 129 among them) and its two forms change places"""
+    batches = [b for b in (1, 2, 3, 4, 5, 8, 12, 15, 16, 17, 31, 32, 33, 63, 64, 65, 100, 127, 128, 129, 150, 256, 300, 600) if b * n * n < 2e8]
+    full = ask([[BACKWARD, dt, b, n, 0, 0, (1, 0, 0), None] for b in batches])
+    pairs = [(b, w, big) for w, big in zip(full, batches) for b in batches if b <= big]
+    got = ask([[BACKWARD, dt, b, n, 0, 0, (1, 0, 0), w] for b, w, _ in pairs])
+    assert [(b, big) for (b, w, big), (status, _) in zip(pairs, got) if status != OK] == []
