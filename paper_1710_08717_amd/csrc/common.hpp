@@ -656,6 +656,9 @@ la_status launch_sgp_scalars(const double *sums, double lam, int n, T *phi, T *n
 enum class SmallWaveOp { potrf, backward, potri, potri_backward };
 template <typename T>
 bool small_wave_takes(SmallWaveOp op, int64_t batch, int n);
+// can launch_trsm_wave and launch_trmm_wave take these operands, and are they the faster ones for them
+template <typename T>
+bool tri_wave_can(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out);
 template <typename T>
 bool trsm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out);
 template <typename T>

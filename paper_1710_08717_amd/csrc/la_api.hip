@@ -383,7 +383,8 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
 // beforehand in one go; they serve the solves with L11 and the blocks' own expressions.  W21 on its way to the product with the inverse is
 // kept where W12 comes in the end.
 // Where the workspace is short the inverses are formed for fewer columns at a time, down to one block's, and with smaller blocks: what a call
-// cannot do without grows with the batch alone, so a workspace that was sized for a larger batch serves every smaller one.
+// cannot do without grows with the batch alone, so a workspace that was sized for a larger batch serves every smaller one (full size, three
+// quarters, half, least; us, fp64: 128 x 512^2 769, 791, 735, 768, 32 x 512^2 243, 258, 279, 324, 1 x 4096^2 1606, 1669, 1808, 4656).
 // Against halving with an inverse (and block substitutions) of their own per block, ms, fp64 / fp32: one matrix of n = 8192 8.87 -> 8.34 /
 // 4.90 -> 4.48, 4096 1.83 -> 1.60 / 1.02 -> 0.92, 3001 1.05 -> 0.90 / 0.71 -> 0.57, 1000 of n = 300 2.80 -> 2.06 / 1.51 -> 1.20.
 // ---------------------------------------------------------------------------------
@@ -621,6 +622,14 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
             return s;
     }
 
+    // Many items of 32 < n <= 64 went to the kernels of one wavefront per item, which take no scratch.  Fewer go through the inverse or a
+    // panel, which do; those kernels take them, too, where the workspace has no room, so that one sized for many items serves a few (with
+    // scratch -> without, us, fp64 / fp32: trmm, 500 of n = 64 with 300 vectors 50 -> 51 / 25 -> 40, 1000 of n = 48 with 100 31 -> 20 /
+    // 18 -> 18; trsm of the same 92 -> 55 / 54 -> 42 and 72 -> 22 / 46 -> 16).
+    if (Lam.nb2 == 1 && tri_wave_can<T>(batch, n, m, Xin, X) && !arena_room((size_t)batch * (solve ? nn : nm) * sizeof(T)))
+        return solve ? launch_trsm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st)
+                     : launch_trmm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
+
     ArenaFrame frame;
     if (solve && n <= NB) {  // inverse of the single block, then one product in place
         if (!inplace || alpha != T(1))
@@ -778,6 +787,7 @@ static la_status tri_outer_t(int lower, int trans, int rightside, T scale, int64
     LA_TRY(launch_zero_strict_upper<T>(lower ? G : G.t(), batch, n, st));  // the other triangle of the result
     GemmOpts o;
     o.maskC = lower ? 1 : 2;
+    o.split_if_room = n <= NB;  // (as the solve or product of the same call: tri_apply_v)
     if (m == 0)  // empty product: the kept triangle is zero too (written without reading what the buffer held)
         return launch_fill_i32((int32_t *)out, batch * nn * (int64_t)(sizeof(T) / 4), 0, st);
     const T *X1 = trans ? Q : P, *X2 = trans ? P : Q;

@@ -839,6 +839,16 @@ bool small_wave_takes(SmallWaveOp op, int64_t batch, int n)
 template bool small_wave_takes<float>(SmallWaveOp, int64_t, int);
 template bool small_wave_takes<double>(SmallWaveOp, int64_t, int);
 
+// any batch: what is not ahead of the paths with scratch stands in for them where there is none
+template <typename T>
+bool tri_wave_can(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out)
+{
+    return n > 2 * LT && n <= 4 * LT && batch <= 0x7fffffffll && offsets_fit<T>(n, m, in.rs, in.cs, in.nb2) &&
+           offsets_fit<T>(n, m, out.rs, out.cs, out.nb2);
+}
+template bool tri_wave_can<float>(int64_t, int, int, const View<const float> &, const View<float> &);
+template bool tri_wave_can<double>(int64_t, int, int, const View<const double> &, const View<double> &);
+
 // More than 48 vectors went through the inverse and a product before: 5001 of n = 51 with 51 vectors 167 -> 81 / 317 -> 167.  Up to
 // 48 the other kernel gives every tile of vectors a wavefront of its own: 9000 of n = 45 with 45 vectors, fp32, 70 -> 79 (with 16
 // 46 -> 36; of n = 40 with 40 75 -> 66), 8000 of n = 60 with 16, fp64, 93 -> 133.  Many vectors of few items are left to the product, too (fp32: 1500 of
@@ -846,7 +856,7 @@ template bool small_wave_takes<double>(SmallWaveOp, int64_t, int);
 template <typename T>
 bool trsm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out)
 {
-    if (!wave_range(batch, n) || !offsets_fit<T>(n, m, in.rs, in.cs, in.nb2) || !offsets_fit<T>(n, m, out.rs, out.cs, out.nb2))
+    if (!wave_range(batch, n) || !tri_wave_can<T>(batch, n, m, in, out))
         return false;
     if (m <= 3 * LT && (n >= 3 * LT || (n > 40 && (m > LT || batch <= 1536))))
         return false;
@@ -861,7 +871,7 @@ template bool trsm_wave_takes<double>(int64_t, int, int, const View<const double
 template <typename T>
 bool trmm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out)
 {
-    if (!wave_range(batch, n) || !offsets_fit<T>(n, m, in.rs, in.cs, in.nb2) || !offsets_fit<T>(n, m, out.rs, out.cs, out.nb2))
+    if (!wave_range(batch, n) || !tri_wave_can<T>(batch, n, m, in, out))
         return false;
     return m <= 4 * LT || (sizeof(T) == 8 && (n <= 3 * LT || batch > 3072));
 }

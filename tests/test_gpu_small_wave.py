@@ -134,3 +134,32 @@ def test_products(n, m, lower, trans, rightside, dtype):
     B64 = B.astype(np.float64) + t(B.astype(np.float64))
     got = la.syrk_backward(torch.from_numpy(X).cuda(), torch.from_numpy(B).cuda(), trans=rightside)
     assert rel(got, X64 @ B64 if rightside else B64 @ X64) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("lower", [True, False])
+@pytest.mark.parametrize("batch,n,m", [(1, 33, 49), (5, 48, 65), (6, 49, 300), (3, 64, 64)])
+def test_few_matrices_without_a_workspace(batch, n, m, lower, dtype):
+    """the operators that take scratch for small batches of these sizes, on none"""
+    rng = np.random.default_rng(6)
+    F = factor(n, lower, dtype)[:batch]
+    X, Xbar = (rng.standard_normal((batch, n, m)).astype(NP[dtype]) for _ in range(2))
+    Bbar = rng.standard_normal((batch, n, n)).astype(NP[dtype])
+    M = (np.tril(F) if lower else np.triu(F)).astype(np.float64)
+    t = (lambda x: x.transpose(0, 2, 1))
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    Fj = torch.from_numpy(junk(F, lower)).cuda()
+    Xg, Xbg = torch.from_numpy(X).cuda(), torch.from_numpy(Xbar).cuda()
+    ref = np.linalg.solve(M, X.astype(np.float64))
+    assert rel(la.trsm(Fj, Xg, lower=lower, workspace=none), ref) <= TOL[dtype]
+    assert rel(la.trmm(Fj, Xg, lower=lower, workspace=none), M @ X.astype(np.float64)) <= TOL[dtype]
+    buf = Xg.clone()
+    assert rel(la.trmm(Fj, buf, lower=lower, trans=True, out=buf, workspace=none), t(M) @ X.astype(np.float64)) <= TOL[dtype]
+    Y, Lbar = la.trsm_backward(Fj, torch.from_numpy(ref.astype(NP[dtype])).cuda(), Xbg, lower=lower, workspace=none)
+    Yref = np.linalg.solve(t(M), Xbar.astype(np.float64))
+    assert rel(Y, Yref) <= TOL[dtype]
+    G = -Yref @ t(ref)
+    assert rel(Lbar, np.tril(G) if lower else np.triu(G)) <= TOL[dtype]
+    B = oracle.potri(F.astype(np.float64), lower=lower).astype(NP[dtype])
+    got = la.potri_backward(Fj, torch.from_numpy(B).cuda(), torch.from_numpy(Bbar).cuda(), lower=lower, workspace=none)
+    assert rel(got, oracle.potri_backward(F.astype(np.float64), B.astype(np.float64), Bbar.astype(np.float64), lower=lower)) <= TOL[dtype]

@@ -111,3 +111,14 @@ def test_gradient_of_the_factorisation_runs_smaller_batches_on_a_larger_ones_wor
     pairs = [(b, w, big) for w, big in zip(full, batches) for b in batches if b <= big]
     got = ask([[BACKWARD, dt, b, n, 0, 0, (1, 0, 0), w] for b, w, _ in pairs])
     assert [(b, big) for (b, w, big), (status, _) in zip(pairs, got) if status != OK] == []
+
+
+@pytest.mark.parametrize("dt", [0, 1])
+@pytest.mark.parametrize("op", [TRSM, TRMM, TRSM_B, TRMM_B, POTRI_B])
+def test_matrices_of_33_to_64_rows_run_smaller_batches_on_a_larger_ones_workspace(ask, op, dt):
+    """across the 1024 matrices from which one wavefront each does the operator without scratch"""
+    batches = (1, 5, 100, 1000, 1024, 1025, 1536, 1537, 3072, 3073, 5000)
+    for n, m in ((33, 49), (40, 60), (48, 80), (51, 51), (64, 100), (64, 300), (37, 700), (48, 2048), (64, 4096)):
+        full = ask([[op, dt, b, n, m, 0, (1, 0, 0), None] for b in batches])
+        queries = [[op, dt, b, n, m, 0, fl, w] for w, big in zip(full, batches) for b in batches if b <= big for fl in ((1, 0, 0), (0, 1, 1))]
+        assert [q for q, (status, _) in zip(queries, ask(queries)) if status != OK] == []
