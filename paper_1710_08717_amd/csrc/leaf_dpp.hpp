@@ -75,6 +75,15 @@ __device__ __forceinline__ void settle(T &v)
     asm volatile("s_nop 1" : "+v"(v));
 }
 
+// what one lane of the wavefront wrote to LDS is there for the others: the barrier alone keeps the lanes together but lets the compiler move
+// accesses across it whose addresses it can tell apart
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ float rcp_newton(float x) { return __builtin_amdgcn_rcpf(x); }
 // seed good to 2^-24, one third-order step r (1 + e + e^2), e = 1 - x r: three dependent multiply-adds
 __device__ __forceinline__ double rcp_newton(double x)
@@ -245,7 +254,7 @@ __device__ __forceinline__ void chain_diag(T (&S)[4], T *row, T &d, T (&X)[4], i
         constexpr int p = decltype(pc)::value;
         T c[4];
         row[4 * p + g] = S[p];
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
 #pragma unroll
         for (int h = 0; h < 4; h += VW) {
             const V w = *reinterpret_cast<const V *>(row + 4 * p + h);
@@ -256,7 +265,7 @@ __device__ __forceinline__ void chain_diag(T (&S)[4], T *row, T &d, T (&X)[4], i
                 c[3] = w.w;
             }
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         T rinv = rcp_newton(c[0]);  // meaningful in the pivot's lane only
         static_for<0, 4>([&](auto qc) {
             constexpr int q = decltype(qc)::value, k = 4 * p + q, K = chain_nat<T>(k);
@@ -289,7 +298,7 @@ __device__ __forceinline__ void chain_diag(T (&S)[4], T *row, T &d, T (&X)[4], i
             *reinterpret_cast<V *>(row + 4 * p + h) = w;
         }
     });
-    __builtin_amdgcn_wave_barrier();
+    wave_sync();
     d = row[r];
 }
 

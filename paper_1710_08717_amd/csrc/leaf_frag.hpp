@@ -285,7 +285,7 @@ __device__ __forceinline__ int leaf_factor(const FactorLds<T> &m, const TileIO<T
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             tile[in.lds(v)] = a[v];
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         F::load(tile, fo, b);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -396,7 +396,7 @@ __device__ __forceinline__ int leaf_factor(const FactorLds<T> &m, const TileIO<T
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     tile[in.lds(v)] = a[s][v];
-                __builtin_amdgcn_wave_barrier();
+                wave_sync();
                 F::load(tile, fo, b);
             }
             N[s] = acc_t{-b[0], -b[1], -b[2], -b[3]};

@@ -16,14 +16,6 @@ constexpr int SW_WAVES = 4;  // matrices per workgroup
 
 constexpr __host__ __device__ int tri_at(int i, int j) { return i * (i + 1) / 2 + j; }  // tile (i, j), i >= j
 
-// order the wavefront's own LDS accesses
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // One matrix in memory, R x C elements, any strides.
 template <typename T>
 struct Mat {

@@ -222,3 +222,21 @@ def test_one_wavefront_kernels_respect_dpp_spacing():
     hazards, n_dpp = find_hazards(text)
     assert n_dpp > 4000
     assert hazards == []
+
+
+def test_wave_barriers_stand_between_fences():
+    """The barrier keeps a wavefront's lanes together but orders no memory: LDS that one lane writes and another reads needs the fences"""
+    from paper_1710_08717_amd import build
+
+    barrier = "__builtin_amdgcn_wave_barrier();"
+    fence = '__builtin_amdgcn_fence(__ATOMIC_%s, "wavefront");'
+    wrong, seen = [], 0
+    for name in sorted(os.listdir(build.CSRC)):
+        with open(os.path.join(build.CSRC, name)) as f:
+            lines = [line.strip() for line in f]
+        for i, line in enumerate(lines):
+            if line.startswith(barrier):
+                seen += 1
+                if lines[i - 1] != fence % "RELEASE" or lines[i + 1] != fence % "ACQUIRE":
+                    wrong.append(f"{name}:{i + 1}")
+    assert seen > 0 and wrong == []
