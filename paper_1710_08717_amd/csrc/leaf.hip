@@ -163,6 +163,14 @@ __device__ __forceinline__ int leaf_diag(const LeafLds<T> &m, int k, int lane)
         for (int c = 0; c < LT; ++c)
             dk[c] = (c <= r) ? a[c] : T(0);
     }
+    if (__builtin_expect(f != 0, 0)) {
+        wave_sync();
+        const T p = dk[r];
+        inverse_before<T>(dk, p, x, r, g, f - 1, [](int q) { return q; });
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            x[j] = r < f - 1 ? x[j] / p : x[j];
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j)
         xk[4 * j + g] = (4 * j + g <= r) ? x[j] : T(0);

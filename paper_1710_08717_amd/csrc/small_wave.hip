@@ -322,13 +322,9 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : 2) void k_
     for (int k = 0; k < K; ++k) {
         T d, x[4];
         wave_sync();
-        chain_diag<T>(u[tri_at(k, k)], w.lds + w.c * W::PS, d, x, w.c, w.g);
-        const unsigned bad = (unsigned)(__ballot(!(d > T(0))) & 0xffffu);
-        if (bad && fail == 0) {
-#pragma unroll
-            for (int q = LT - 1; q >= 0; --q)
-                fail = (bad >> chain_nat<T>(q)) & 1 ? LT * k + q + 1 : fail;
-        }
+        const unsigned bad = chain_diag<T>(u[tri_at(k, k)], w.lds + w.c * W::PS, d, x, w.c, w.g);
+        if (bad && fail == 0)
+            fail = LT * k + first_row<T>(bad) + 1;
         const T rs = rsqrt_acc(d);
 #pragma unroll
         for (int v = 0; v < 4; ++v)

@@ -62,6 +62,28 @@ def test_first_failing_pivot(n, dtype):
     assert rel(L[-1:], oracle.potrf(A[-1:].astype(np.float64))) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("lower", [True, False])
+@pytest.mark.parametrize("pivot", [0.0, -1.0, float("nan")])
+@pytest.mark.parametrize("batch,n", [(20, 66), (20, 100), (20, 128), (20, 300), (1539, 37), (1539, 64), (1100, 48), (1100, 64)])
+def test_columns_before_a_failing_pivot(batch, n, pivot, lower, dtype):
+    """the factor is unspecified from the failing column on, and right before it: in the failing tile, below it and in later blocks"""
+    bad = sorted({1, 2, 3, 5, 8, 12, 15, 17, 24, 31, 33, 36, 40, 47, 63, 65, 80, 99, 127, 128, 131, 200, 257, n - 1})
+    bad = [k for k in bad if k < n]
+    A = np.repeat(spd(1, n, 11, "f64"), max(batch, len(bad)), axis=0)
+    for b, k in enumerate(bad):
+        A[b, k, :] = A[b, :, k] = 0.0
+        A[b, k, k] = pivot
+    info = torch.zeros(len(A), dtype=torch.int32, device="cuda")
+    L = la.potrf(torch.from_numpy(A.astype(NP[dtype])).cuda(), lower=lower, info=info).cpu().numpy().astype(np.float64)
+    L = L if lower else L.transpose(0, 2, 1)
+    assert info[: len(bad)].tolist() == [k + 1 for k in bad] and not info[len(bad) :].any()
+    for b, k in enumerate(bad):
+        lead = np.linalg.cholesky(A[b, :k, :k])
+        ref = np.vstack([lead, np.linalg.solve(lead, A[b, k:, :k].T).T])
+        assert np.linalg.norm(L[b, :, :k] - ref) <= TOL[dtype] * np.linalg.norm(ref), k
+
+
 @pytest.mark.parametrize("exponent", [-480, 480])
 def test_scales_far_from_one(exponent):
     """the factor of 4^e A is 2^e times that of A, down to pivots of 2^-960"""
