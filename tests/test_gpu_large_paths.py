@@ -1,9 +1,9 @@
 """Element-by-element parity with the CPU oracle on the code paths only a large single matrix takes
 (section 4.2: potrf and its backward expression): potrf right-looking over panels of 2048 columns
-(one matrix of n >= 4096), the backward pass as the closed expression on a 2048 x 2048 block with
-every merge level of the explicit inverse, and the reverse sweep over the blocked factorisation
-with 2048-row base blocks (n = 4096: halving; n = 5376: a first block of 2048 peeled off, ragged
-remainder).  Spec tolerances, relative Frobenius error of the whole matrix."""
+(one matrix of n >= 4096), the backward pass as the closed expression with every merge level of the
+explicit inverse (n = 2048 in fp32, 2047 in fp64) and as the reverse sweep over the blocked factorisation
+by block columns of 1024 (fp64 from n = 2048 on, fp32 at 4096; n = 5376: a ragged last block of 256).  The
+tolerances of the operators, relative Frobenius error of the whole matrix."""
 import sys
 import time
 
@@ -98,17 +98,18 @@ def test_trsm_block_substitution_n4096_full_compare(la, orc, dtype):
         assert relerr(X, orc.trsm(Lr, R, **kw)) <= TOL[dtype], kw
 
 
-@pytest.mark.parametrize("dtype", ["f64", "f32"])
-def test_backward_closed_expression_n2048_full_compare(la, orc, dtype):
-    w = problem(2048, dtype)
+@pytest.mark.parametrize("n,dtype", [(2047, "f64"), (2048, "f64"), (2048, "f32")])
+def test_backward_closed_expression_n2048_full_compare(la, orc, n, dtype):
+    """the largest sizes of the closed expression, and in fp64 the first of the sweep: one matrix of 4 Mi elements"""
+    w = problem(n, dtype)
     Lr = w["L_oracle"].astype(workloads.np_dtype(dtype))
     t = time.time()
     ref = orc.potrf_backward(Lr, w["Lbar"])
-    note(f"oracle backward n=2048 {dtype}: {time.time() - t:.1f} s")
+    note(f"oracle backward n={n} {dtype}: {time.time() - t:.1f} s")
     Abar = host(la.potrf_backward(dev(Lr), dev(w["Lbar"])))
     assert np.array_equal(Abar[0], Abar[0].T)
     assert relerr(Abar, ref) <= TOL[dtype]
-    # in place (Abar over Lbar) takes the same path with one more copy
+    # in place (Abar over Lbar) takes the same path, the closed expression with one more copy
     G = dev(w["Lbar"])
     la.potrf_backward(dev(Lr), G, out=G)
     assert relerr(host(G), ref) <= TOL[dtype]
@@ -127,8 +128,8 @@ def test_backward_sweep_n4096_full_compare(la, orc, dtype):
 
 
 def test_potrf_and_backward_sweep_ragged_n5376_full_compare(la, orc):
-    """n = 5376 = 2048 + 2048 + 1280: three potrf panels with a ragged last one; the sweep peels a first
-    block of 2048 columns and halves the remaining 3328 into base blocks of 1664."""
+    """n = 5376 = 2048 + 2048 + 1280: three potrf panels with a ragged last one; the sweep goes by five block columns of
+    1024 and a last one of 256."""
     dtype = "f64"
     w = problem(5376, dtype)
     L = host(la.potrf(dev(w["A"])))
