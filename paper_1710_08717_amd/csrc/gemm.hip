@@ -748,10 +748,36 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
         const int64_t wg128 = wgs(128), wg64 = wgs(64);
         // K slabs of 64: the whole range in such slabs, or (ragged) little of the last one empty
         const bool k64 = f.rag ? (K >= 128 || (K & 63) == 0 || (K & 63) > 32) : K % 64 == 0;
-        // quarter tiles, which exist with slabs of 64 only: aligned operands with another K take the ragged form, whose last slab ends where K
-        // does (us, tiles of 64 in slabs of 16 -> quarter tiles, fp64 / fp32: gradient of the factorisation 1 x 2000^2 819 -> 492 / 553 -> 315,
-        // 16 x 336^2 147 -> 112 / 107 -> 77, trmm 1 x 2000^2 with 48 vectors 123 -> 58 / 81 -> 37)
-        const bool quarters = k64 || K >= 128;
+        // Quarter tiles exist with slabs of 64 only; aligned operands with another K take them in the ragged form, whose last slab ends where K
+        // does and whose loads cost address arithmetic, instead of 64 x 64 tiles in slabs of 16.  Two things decide: how many tiles of 64 there
+        // are, `work` (a last slab counts whole), against the 512 slots, and `share`, the quarter tiles' area as a part of theirs.  Gain, mean of
+        // 2700 products of 128 <= K <= 2000, by work (300 to 420 / 420 to 520 / 520 to 640 / 640 to 720 / 720 to 820 / above):
+        //   uniform, fp64, share above 1 (K far from the end of a slab) 1.07 / 0.88 / 0.90 / 0.79 / 0.76 / 0.79, 0.88 to 1 1.16 / 0.96 / 1.04 / 0.91 / 0.96 /
+        //   0.88, 0.75 to 0.88 1.28 / 1.09 / 1.10 / 0.95 / 0.96 / 0.96, below 1.68 / 1.48 / 1.44 / 1.46 / 1.31 / 1.34;
+        //   uniform, fp32, above 1 1.23 / 1.01 / 0.99 / 0.91 / 0.88 / 0.89, 0.88 to 1 1.29 / 1.08 / 1.11 / 1.03 / 1.00 / 1.01;
+        //   triangular operands, fp64, above 1 1.35 / 1.23 / 1.09 / 1.10 / 1.01 / 0.94, 0.88 to 1 1.47 / 1.29 / 1.23 / 1.22 / 1.11 / 1.02; fp32, above 1
+        //   1.63 / 1.46 / 1.26 / 1.18 / 1.08 / 1.07;
+        //   symmetric results, fp64, above 1 1.13 / 1.05 / 1.07 / 1.03 / 0.94 / 0.92, 0.88 to 1 1.26 / 1.12 / 1.15 / 1.02 / 1.00 / 0.99, 0.75 to 0.88 1.37 /
+        //   1.13 / 1.16 / 1.13 / 1.08 / 1.02; fp32, above 1 1.15 / 1.11 / 1.13 / 1.00 / 0.99 / 0.99.
+        // Within 513 to 560 tiles the last round of 64 x 64 ones runs nearly empty (uniform, fp64, share 0.88 to 1: 1.09).  Up to K = 192 the last of two
+        // or three slabs is too much of the work: share above 0.88, fp64 0.84 to 0.97, uniform, and 0.79 to 1.07, triangular
+        // (0.83: 138 x 144^2 with 80 vectors 0.90).  Of the 2700, 47 are
+        // 4 % or more slower than with tiles of 64, ten of them 10 to 22 % (7 x (720 x 300 x 1824) and 237 x (122 x 80 x 1200), fp32).
+        const bool f32 = sizeof(T) == 4, tri = (o.triA | o.triB) != 0, uniform = !tri && !o.symsum;
+        const double slabs = (double)((K + 63) / 64 * 64) / K, work = (double)wg64 * slabs;
+        const double share = 0.25 * (double)wgs(32) / (double)wg64 * slabs;
+        double most = f32 ? 1.0 : 0.875;  // share up to which the quarter tiles are taken
+        if (work < (uniform && f32 ? 448.0 : 416.0))
+            most = 2.0;
+        else if (uniform)
+            most = f32 || (wg64 > 512 && wg64 <= 560) ? 1.0 : (work < 640.0 ? 0.875 : 0.74);
+        else if (work < 720.0)
+            most = 1.05;
+        else if (tri)
+            most = f32 ? (work < 1100.0 ? 1.1 : 1.0) : 0.93;
+        if (K <= 192 && work >= 400.0)
+            most = std::min(most, 0.8);
+        const bool quarters = k64 || (K >= 128 && share <= most);
         if (!o.triA && !o.triB && !o.min_tile64 && !o.ksplit && !o.symsum && wg64 <= 128 && K >= 2048 && A.nb2 == 1 && B.nb2 == 1 &&
             C.nb2 == 1) {
             int splits = (int)std::min<int64_t>(512 / wg64, K / 256);
@@ -812,7 +838,7 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             // per load, and the quarters save no padding (b items of 61 x 174, K = 147, us, 32 x 32 -> 64 x 64: b = 331, 993 tiles, fp64
             // 60 -> 44, fp32 29 -> 22; with one round and a half the products of potri's backward rule, 30 x 297 x 297, 220 -> 232; 26 x 2478 x 22, 1014
             // tiles that the quarters halve, fp32 36 -> 54).
-            const bool two_rounds = (f.rag || !k64) && !o.maskC && !o.symsum && wg64 >= 960 &&
+            const bool two_rounds = f.rag && !o.maskC && !o.symsum && wg64 >= 960 &&
                                     (int64_t)((M + 63) / 64) * ((N + 63) / 64) * 4 == (int64_t)((M + 31) / 32) * ((N + 31) / 32);
             e = ((t128 >= (o.maskC ? 512 : 480) || one_round) && big && !padded) ? 128 : ((wg64 < 1024 && quarters && !o.min_tile64 && !two_rounds) ? 32 : 64);
         }

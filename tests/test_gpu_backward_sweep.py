@@ -113,3 +113,24 @@ def test_sweep_on_short_workspaces(batch, n, lower, dtype):
         assert (buf[need:] == 0xA5).all(), need
     with pytest.raises(la.LaError):
         la.potrf_backward(Lg, Gg, lower=lower, workspace=buf[:least - 256])
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("batch,m,n,k", [(25, 256, 256, 144), (28, 256, 256, 208), (103, 128, 128, 400), (112, 128, 128, 400), (513, 64, 64, 272),
+                                         (150, 64, 256, 336), (137, 80, 160, 176), (255, 128, 128, 144), (64, 96, 300, 1040)])
+def test_products_on_both_sides_of_the_tile_rule(batch, m, n, k, dtype):
+    """aligned operands, inner dimension a multiple of 16 but not of 64: tiles of 64 and quarter tiles, uniform, triangular and symmetric"""
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    dt = torch.float64 if dtype == "f64" else torch.float32
+    R = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=dt)
+    err = lambda x, r: float((x.double() - r).norm() / r.norm())
+    A, B = R(batch, m, k), R(batch, k, n)
+    At, Bt = A.mT.contiguous(), B.mT.contiguous()
+    ref = torch.bmm(A.double(), B.double())
+    for ta in (False, True):
+        for tb in (False, True):
+            assert err(la.gemm2(At if ta else A, Bt if tb else B, ta=ta, tb=tb), ref) <= TOL[dtype]
+    assert err(la.syrk(A), torch.bmm(A.double(), At.double())) <= TOL[dtype]
+    L = R(batch, k, k).tril_()
+    assert err(la.trmm(L, B), torch.bmm(L.double(), B.double())) <= TOL[dtype]
+    assert err(la.trmm(L, A, rightside=True), torch.bmm(A.double(), L.double())) <= TOL[dtype]
