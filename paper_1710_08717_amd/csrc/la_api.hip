@@ -388,6 +388,59 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
 // Against halving with an inverse (and block substitutions) of their own per block, ms, fp64 / fp32: one matrix of n = 8192 8.87 -> 8.34 /
 // 4.90 -> 4.48, 4096 1.83 -> 1.60 / 1.02 -> 0.92, 3001 1.05 -> 0.90 / 0.71 -> 0.57, 1000 of n = 300 2.80 -> 2.06 / 1.51 -> 1.20.
 // ---------------------------------------------------------------------------------
+// Columns [o, q) of the rows [o, end); `inv` holds the inverses of the diagonal blocks of n0 from row c0 on.  A column wider than n0 has its panel
+// solved block by block, from the right, and its diagonal block swept in turn.
+template <typename T>
+static la_status sweep_column(View<const T> Lam, View<const T> inv, int c0, View<const T> G, View<T> W, View<T> X, View<T> Y, int64_t batch,
+                              int o, int q, int end, int n0, bool aliased, hipStream_t st)
+{
+    const int w = q - o, r = end - q;
+    View<const T> L11 = Lam.sub(o, o), G11 = G.sub(o, o);
+    View<T> W11 = W.sub(o, o), W21 = W.sub(q, o), W12 = W.sub(o, q);
+    if (r > 0) {
+        View<const T> L21 = Lam.sub(q, o);
+        LA_TRY(launch_copy<T>(G.sub(q, o), W12.t(), batch, r, w, T(1), 0, st));
+        if (!aliased)
+            LA_TRY(launch_copy<T>(G11, W11, batch, w, w, T(1), 2, st));
+        GemmOpts plain, ol, om;
+        plain.split_if_room = om.split_if_room = 1;  // (the inverses had the first pick of the workspace)
+        LA_TRY(launch_gemm<T>(cv(W).sub(q, q), L21, W12.t(), batch, r, w, r, T(-2), T(1), plain, st));
+        ol.triB = 1;
+        for (int b = (w - 1) / n0 * n0; b >= 0; b -= n0) {
+            const int nb = w - b < n0 ? w - b : n0, e = b + nb;
+            if (e < w)  // what the blocks to the right take off (W21 holds half of their x)
+                LA_TRY(launch_gemm<T>(cv(W21).sub(0, e), L11.sub(e, b), W12.t().sub(0, b), batch, r, nb, w - e, T(-2), T(1), plain, st));
+            LA_TRY(launch_gemm<T>(cv(W12).t().sub(0, b), inv.sub(o + b - c0, o + b - c0), W21.sub(0, b), batch, r, nb, nb, T(0.5), T(0), ol,
+                                  st));
+        }
+        om.maskC = 1;
+        LA_TRY(launch_gemm<T>(cv(W21).t(), L21, W11, batch, w, w, r, T(-2), T(1), om, st));
+        G = cv(W);
+        G11 = cv(W11);
+        aliased = true;
+    }
+    if (w > n0) {
+        for (int b = (w - 1) / n0 * n0; b >= 0; b -= n0)
+            LA_TRY(sweep_column<T>(Lam, inv, c0, G, W, X, Y, batch, o + b, w - b < n0 ? q : o + b + n0, q, n0, aliased, st));
+    } else {
+        GemmOpts op;
+        op.triA = 2;
+        op.triB = 1;
+        op.maskC = 1;
+        op.halfDiag = 1;
+        LA_TRY(launch_gemm<T>(L11.t(), G11, X, batch, w, w, w, T(1), T(0), op, st));
+        LA_TRY(congruence<T>(inv.sub(o - c0, o - c0), cv(X), Y, W11, batch, w, st));
+    }
+    return r > 0 ? launch_copy<T>(cv(W21).t(), W12, batch, w, r, T(1), 0, st) : LA_OK;
+}
+
+// From n = 10000 on a column of two blocks: the products with W22 and the panel's with itself get twice the columns, where those of 1024 make too few
+// tiles for the chip, and the blocks' inverses, which the errors grow with, stay as they are.  One matrix, ms, fp64 / fp32, halving with
+// blocks of 2048 -> columns of one block -> of two: 8192 8.87 -> 8.22 -> 8.11 / 4.90 -> 4.47 -> 4.36, 9000 12.3 -> 11.0 -> 11.7 / 6.83 -> 6.12 -> 6.41, 10000
+// 16.4 -> 15.3 -> 14.1 / 9.26 -> 8.41 -> 7.67, 12288 25.3 -> 26.1 -> 24.0 / 13.5 -> 13.8 -> 12.7, 16384 55.3 -> 58.2 -> 53.3 / 28.9 -> 30.9 -> 27.9, 24000 170 ->
+// 177 -> 164 / 86.6 -> 93.1 -> 84.8 (four blocks: 16384 52.4 / 27.9, 10000 14.1 / 7.7); three 12288 70.2 -> 69.8 -> 66.3, four 94.1 -> 88.4 -> 90.4.  Errors, fp32:
+// 12288 8.7e-7 -> 7.6e-7 -> 7.4e-7, 24000 9.0e-7 -> 8.6e-7 -> 8.5e-7.
+constexpr int SWEEP_WIDE_N = 10000, SWEEP_WIDE_BATCH = 3;
 template <typename T>
 static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, int64_t batch, int n, int n0, bool aliased,
                                 hipStream_t st)
@@ -409,39 +462,15 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
     if (!arena_room(0))  // (a sizing pass for the least: the products below take none they need)
         return LA_OK;
     View<T> Li{(T *)p, item, n0, 1}, X{Li.p + (int64_t)cols * n0 + cols, item, n0, 1}, Y{X.p + (int64_t)n0 * n0, item, n0, 1};
-    for (int o = (n - 1) / n0 * n0; o >= 0; o -= n0) {
-        const int nb = n - o < n0 ? n - o : n0, q = o + nb, r = n - q;
+    const int wide = n >= SWEEP_WIDE_N && batch <= SWEEP_WIDE_BATCH && cols == n ? 2 * n0 : n0;
+    for (int o = (n - 1) / wide * wide; o >= 0; o -= wide) {
+        const int q = n - o < wide ? n : o + wide;
         const int c0 = o / cols * cols, cc = n - c0 < cols ? n - c0 : cols;  // the columns whose inverses are there
         if (q == c0 + cc) {
             LA_TRY(launch_tri_inverse128<T>(Lam.sub(c0, c0), Li, batch, cc, st));
             LA_TRY(inverse_merge<T>(Lam.sub(c0, c0), Li, X, batch, cc, n0, st));
         }
-        const View<const T> Lio = cv(Li).sub(o - c0, o - c0);
-        View<const T> L11 = Lam.sub(o, o), G11 = G.sub(o, o);
-        View<T> W11 = W.sub(o, o), W21 = W.sub(q, o), W12 = W.sub(o, q);
-        if (r > 0) {
-            View<const T> L21 = Lam.sub(q, o);
-            LA_TRY(launch_copy<T>(G.sub(q, o), W12.t(), batch, r, nb, T(1), 0, st));
-            if (!aliased)
-                LA_TRY(launch_copy<T>(G11, W11, batch, nb, nb, T(1), 2, st));
-            GemmOpts plain, ol, om;
-            plain.split_if_room = om.split_if_room = 1;  // (the inverses had the first pick of the workspace)
-            LA_TRY(launch_gemm<T>(cv(W).sub(q, q), L21, W12.t(), batch, r, nb, r, T(-2), T(1), plain, st));
-            ol.triB = 1;
-            LA_TRY(launch_gemm<T>(cv(W12).t(), Lio, W21, batch, r, nb, nb, T(0.5), T(0), ol, st));
-            om.maskC = 1;
-            LA_TRY(launch_gemm<T>(cv(W21).t(), L21, W11, batch, nb, nb, r, T(-2), T(1), om, st));
-            G11 = cv(W11);
-        }
-        GemmOpts op;
-        op.triA = 2;
-        op.triB = 1;
-        op.maskC = 1;
-        op.halfDiag = 1;
-        LA_TRY(launch_gemm<T>(L11.t(), G11, X, batch, nb, nb, nb, T(1), T(0), op, st));
-        LA_TRY(congruence<T>(Lio, cv(X), Y, W11, batch, nb, st));
-        if (r > 0)
-            LA_TRY(launch_copy<T>(cv(W21).t(), W12, batch, nb, r, T(1), 0, st));
+        LA_TRY(sweep_column<T>(Lam, cv(Li), c0, G, W, X, Y, batch, o, q, n, n0, aliased, st));
     }
     return LA_OK;
 }

@@ -140,3 +140,30 @@ def test_potrf_and_backward_sweep_ragged_n5376_full_compare(la, orc):
     Abar = host(la.potrf_backward(dev(w["L_oracle"]), dev(w["Lbar"])))
     assert np.array_equal(Abar[0], Abar[0].T)
     assert relerr(Abar, ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("batch,n,dtype,lower", [(1, 10000, "f32", True), (1, 10241, "f64", False), (2, 10000, "f64", True)])
+def test_backward_sweep_by_columns_of_two_blocks(la, batch, n, dtype, lower):
+    """n >= 10000, up to three matrices: the rule's own expression, multiplied out in 64 bits (the factors have condition numbers of
+    about three, so that the errors of Abar are seen at their own size); in place too"""
+    import torch
+
+    dt = torch.float64 if dtype == "f64" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(n)
+    L = torch.randn(batch, n, n, generator=g, device="cuda", dtype=dt).tril_().mul_(0.5 / n**0.5)
+    L.diagonal(dim1=1, dim2=2).copy_(1 + torch.rand(batch, n, generator=g, device="cuda", dtype=dt))
+    G = torch.randn(batch, n, n, generator=g, device="cuda", dtype=dt).tril_()
+    if not lower:
+        L, G = L.mT.contiguous(), G.mT.contiguous()
+    got = la.potrf_backward(L, G, lower=lower)
+    inplace = G.clone()
+    la.potrf_backward(L, inplace, lower=lower, out=inplace)
+    assert torch.equal(inplace, got)
+    del inplace
+    for b in range(batch):
+        assert torch.equal(got[b], got[b].mT)
+        F, D = (L[b].double(), G[b].double()) if lower else (L[b].double().mT.contiguous(), G[b].double().mT.contiguous())
+        P = (F.mT.contiguous() @ D).tril_()  # 2 L^T Abar L = Phi(L^T Lbar) + its transpose
+        P.diagonal().mul_(0.5)
+        P = P + P.mT
+        assert float((2.0 * (F.mT.contiguous() @ got[b].double() @ F) - P).norm() / P.norm()) <= TOL[dtype]
