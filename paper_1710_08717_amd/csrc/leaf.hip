@@ -1273,14 +1273,15 @@ __global__ __launch_bounds__(NW * 64) void k_gp_leaf16(View<const T> A, const T 
     __syncthreads();
     // ---- alpha = Li^T z, a wavefront per tile column ------------------------------------------------
     if (wave < K) {
-        T part = T(0);
+        T sum[4] = {};  // (four short sums: with one of 32 terms the gradient's error is 3 % larger)
         for (int k = wave; k < K; ++k) {
             T x[4];
             F::load(m.x(k, wave), fo, x);
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                part = fma(x[v], sz[k * LT + 4 * v + g], part);
+                sum[v] = fma(x[v], sz[k * LT + 4 * v + g], sum[v]);
         }
+        T part = (sum[0] + sum[1]) + (sum[2] + sum[3]);
         part += __shfl_xor(part, 16, WAVE);
         part += __shfl_xor(part, 32, WAVE);
         if (lane < LT)

@@ -162,3 +162,21 @@ def test_gp_gradient_is_as_accurate_as_the_operators(la, n, dim, noise, width):
         errs += [rel(la.gp_criterion(a, yy)[1][0].cpu().numpy(), ref), rel(la.potrf_backward(L, Lbar)[0].cpu().numpy(), ref)]
     sys.stderr.write(f"criterion / operators {errs[0] / errs[1]:.3f}\n")
     assert errs[0] <= 1.1 * errs[1]
+
+
+def test_gradient_error_in_fp32(la):
+    """alpha is summed in short pieces: over these matrices the gradient's error is 4.55e-7 (with one sum of 32 terms per lane 4.71e-7)"""
+    import torch
+
+    n, errors = 128, []
+    for seed in range(8):
+        rng = np.random.default_rng(seed)
+        P = rng.uniform(-2.0, 2.0, (64, n, 8))
+        A = np.exp(-0.5 * ((P[:, :, None] - P[:, None]) ** 2).sum(-1)) + 0.1 * np.eye(n)
+        A = torch.from_numpy(A.astype(np.float32)).cuda()
+        y = torch.from_numpy(rng.standard_normal((64, n)).astype(np.float32)).cuda()
+        grad = la.gp_criterion(A, y)[1]
+        Ai = np.linalg.inv(A.cpu().numpy().astype(np.float64))
+        a = np.einsum("bij,bj->bi", Ai, y.cpu().numpy().astype(np.float64))
+        errors.append(rel(grad.cpu().numpy(), 0.5 * (Ai - a[:, :, None] * a[:, None, :])))
+    assert np.mean(errors) <= 4.63e-7
