@@ -40,7 +40,7 @@ def backward_flops(n, batch, elem_size):
     solve) + r k^2 (lower triangle of the panel product) and its diagonal block 2 k^3.  The rule for the
     block size mirrors the library's."""
     elements, scale = float(batch) * n * n / 1048576.0, 2.0 if elem_size == 4 else 1.0
-    if n >= 400 and batch <= 128 and elements >= 4.0 * scale:
+    if n >= 400 and batch <= 128 and elements >= (5.5 if 700 <= n < 860 and batch <= 8 * scale else 4.0) * scale:
         base = 256
         while base < 1024 and 2.0 * base <= 0.6 * n and 4.0 * base * base * batch <= 4.0 * 1048576.0:
             base *= 2

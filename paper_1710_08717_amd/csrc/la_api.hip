@@ -291,7 +291,11 @@ constexpr int SWEEP_MIN_N = 214;
 static int sweep_block(int64_t batch, int n, size_t elem)
 {
     const double mi = 1048576.0, b = (double)batch, elements = b * n * n, scale = elem == 4 ? 2.0 : 1.0;
-    if (n >= 400 && b <= 128.0 && elements >= 4.0 * scale * mi) {
+    // (n = 700 to 860 is three blocks of 256 and a bit; with up to 8 matrices, fp32 16, the items of the expression's products fill the 8 XCDs
+    // evenly: 8 x 770^2 fp64 291 -> 325, 7 x 785^2 303 -> 354, 15 x 850^2 fp32 322 -> 346, from 5.5 Mi on ahead again; 9 x 737^2 427 -> 335,
+    // 20 x 720^2 fp32 308 -> 269)
+    const double least = n >= 700 && n < 860 && b <= 8.0 * scale ? 5.5 : 4.0;
+    if (n >= 400 && b <= 128.0 && elements >= least * scale * mi) {
         int n0 = 256;
         while (n0 < 1024 && 2.0 * n0 <= 0.6 * n && 4.0 * n0 * n0 * b <= 4.0 * mi)
             n0 *= 2;

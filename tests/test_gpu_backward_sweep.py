@@ -30,7 +30,7 @@ def factor(batch, n, rng, dtype):
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 @pytest.mark.parametrize("lower", [True, False])
-@pytest.mark.parametrize("batch,n", [(400, 257), (300, 214), (600, 214), (280, 213), (129, 400), (53, 400), (36, 513), (9, 1025), (4, 1024), (3, 1183), (2, 2048)])
+@pytest.mark.parametrize("batch,n", [(400, 257), (300, 214), (600, 214), (280, 213), (129, 400), (53, 400), (36, 513), (8, 770), (13, 799), (9, 1025), (4, 1024), (3, 1183), (2, 2048)])
 def test_sweep(batch, n, lower, dtype):
     rng = np.random.default_rng(n)
     L = factor(batch, n, rng, dtype)
