@@ -809,7 +809,8 @@ static bool offsets_fit(int64_t rows, int64_t cols, int64_t rs, int64_t cs, int 
 // 1100 of n = 37: 14 -> 10, 22 -> 15), hence the second line.  Where nothing is ragged the four-wavefront kernels move
 // 16-byte pieces, and from memory (not the last-level cache) they are then the faster ones: 16384 of n = 64, fp32, potrf 141 -> 180,
 // 4096 37 -> 30; 20000 of n = 48 109 -> 120, 7281 42 -> 33; backward 7281 of n = 48, fp64, 121 -> 138, 2048 39 -> 34.
-// potrf in fp64 with four tile rows is equal there: 8000 of n = 60 133 -> 142, 5001 of n = 51 83 -> 56.
+// potrf in fp64 with four tile rows is equal there: 8000 of n = 60 133 -> 142, 5001 of n = 51 83 -> 56; so is potri with nearly three whole
+// ones: 24618 of n = 47 202 -> 231, 12169 102 -> 110, 9000 to 11000 (160 MiB) 1.04 to 1.2 times as fast.
 template <typename T>
 bool small_wave_takes(SmallWaveOp op, int64_t batch, int n)
 {
@@ -822,7 +823,9 @@ bool small_wave_takes(SmallWaveOp op, int64_t batch, int n)
     const double mib = (double)batch * n * n * sizeof(T) / 1048576.0;
     if (n % LT == 0)
         return mib <= 64.0;
-    return !(op == SmallWaveOp::potrf && sizeof(T) == 8 && n > 3 * LT && mib > 128.0);
+    if (sizeof(T) == 4)
+        return true;
+    return !(op == SmallWaveOp::potrf && n > 3 * LT && mib > 128.0) && !(op == SmallWaveOp::potri && n > 44 && n < 3 * LT && mib > 192.0);
 }
 template bool small_wave_takes<float>(SmallWaveOp, int64_t, int);
 template bool small_wave_takes<double>(SmallWaveOp, int64_t, int);
@@ -860,6 +863,12 @@ template <typename T>
 bool trmm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out)
 {
     if (!wave_range(batch, n) || !tri_wave_can<T>(batch, n, m, in, out))
+        return false;
+    // 33 to 47 vectors side by side, in rows of no whole 64 bytes, from memory, fp64: the one-workgroup kernel is the faster one (10463 of n = 44
+    // with 47 120 -> 150, 23423 of n = 46 with 41 241 -> 317, 24411 of n = 39 with 47 246 -> 294; 3956 of n = 46 with 45, 64 MiB, 46 -> 42, 11077 of
+    // n = 46 with 40 120 -> 113, 44560 of n = 34 with 37 412 -> 366, as rows of n 20618 of n = 42 with 45 215 -> 178)
+    if (sizeof(T) == 8 && in.cs == 1 && n > (m > 40 ? 36 : 41) && n <= 3 * LT && m > 2 * LT && m < 3 * LT && m % 8 != 0 &&
+        (double)batch * n * n * sizeof(T) > 128.0 * 1048576.0)
         return false;
     return m <= 4 * LT || (sizeof(T) == 8 && (n <= 3 * LT || batch > 3072));
 }

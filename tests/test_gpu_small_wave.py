@@ -163,3 +163,20 @@ def test_few_matrices_without_a_workspace(batch, n, m, lower, dtype):
     B = oracle.potri(F.astype(np.float64), lower=lower).astype(NP[dtype])
     got = la.potri_backward(Fj, torch.from_numpy(B).cuda(), torch.from_numpy(Bbar).cuda(), lower=lower, workspace=none)
     assert rel(got, oracle.potri_backward(F.astype(np.float64), B.astype(np.float64), Bbar.astype(np.float64), lower=lower)) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("batch,n,m", [(11700, 47, 8), (10700, 46, 45), (10700, 46, 40)])
+def test_sizes_from_memory(batch, n, m):
+    """potri of nearly whole tiles and products with rows of an odd number of vectors, beyond 128 (192) MiB in fp64"""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    L = torch.randn(batch, n, n, generator=g, device="cuda", dtype=torch.float64).tril_().mul_(0.5 / n**0.5)
+    L.diagonal(dim1=1, dim2=2).copy_(1 + torch.rand(batch, n, generator=g, device="cuda", dtype=torch.float64))
+    X = torch.randn(batch, n, m, generator=g, device="cuda", dtype=torch.float64)
+    ref = torch.bmm(L, X)
+    assert float((la.trmm(L, X) - ref).norm() / ref.norm()) <= TOL["f64"]
+    buf = X.clone()
+    assert float((la.trmm(L, buf, out=buf) - ref).norm() / ref.norm()) <= TOL["f64"]
+    B = la.potri(L)
+    assert torch.equal(B, B.mT)
+    one = torch.bmm(L.mT.contiguous(), torch.bmm(B, L))
+    assert float((one - torch.eye(n, device="cuda", dtype=torch.float64)).norm() / (batch * n) ** 0.5) <= TOL["f64"]
