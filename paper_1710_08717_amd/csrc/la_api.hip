@@ -861,7 +861,10 @@ static la_status trsm_backward_t(int lower, int trans, int rightside, double alp
 // C = alpha (G + G^T) A, resp. (right) alpha A (G + G^T), as one product with S = G + G^T in scratch (`cols` rows or columns beside S).
 // Only where the workspace has room for S and for what that product takes itself, a split inner dimension, and where the product it saves
 // pays for the pass over G; *done stays false otherwise.  us, fp64 / fp32: potri's rule on 64 x 200^2 153 -> 110 / 87 -> 71, 64 x 128^2
-// 62 -> 58 / 43 -> 41, 2000^2 1051 -> 703 / 613 -> 427, syrk's rule on 64 x 200^2 with 128 columns 62 -> 41 / 34 -> 25.
+// 62 -> 58 / 43 -> 41, 2000^2 1051 -> 703 / 613 -> 427, syrk's rule on 64 x 200^2 with 128 columns 62 -> 41 / 34 -> 25, with 32 22 -> 22 / 16 -> 19; on
+// 32 x 512^2 with 128 106 -> 80 / 61 -> 53, with 96 83 -> 68 / 45 -> 45, with 32 37 -> 46 / 24 -> 35; on 300 x 128^2 with 128 87 -> 60 / 42 -> 36, with 32
+// 34 -> 37 / 18 -> 26.  Single matrices would gain from fewer columns (2000^2 with 32 96 -> 58 / 62 -> 43) and fewer elements (700^2 with 128 37 -> 25 /
+// 25 -> 18).
 template <typename T>
 static la_status symm_product(const T *G, View<const T> A, View<T> C, int64_t batch, int n, int cols, bool right, T alpha, bool *done,
                               hipStream_t st)

@@ -224,7 +224,8 @@ __host__ __device__ constexpr int chain_nat(int l)
 
 // The inverse of a tile with a pivot that is not > 0, once more for the rows before it.  A zero or NaN there has reached their x as
 // 0 * inf or 0 * NaN, and the columns of the factor before that pivot are still asked for.  Out of line of the chain of pivots: only such a tile
-// comes here (the question after the last pivot: potrf of 32 x 128^2 12.5 -> 12.6 us in fp32, 16.5 -> 16.4 in fp64).  row = row r of the tile in LDS, its columns before `first` final and divided by anything that is the same down a
+// comes here (the question after the last pivot: potrf of 32 x 128^2 12.5 -> 12.6 us in fp32, 16.5 -> 16.4 in fp64).
+// row = row r of the tile in LDS, its columns before `first` final and divided by anything that is the same down a
 // column; p = element r of that row; x as elsewhere, scaled so that its diagonal is one.  at(k) = the lane (of 16) that has row k.
 template <typename T, typename F>
 __device__ __forceinline__ void inverse_before(const T *row, T p, T (&x)[4], int r, int g, int first, F &&at)

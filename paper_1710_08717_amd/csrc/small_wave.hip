@@ -6,6 +6,9 @@
 // leaf_frag.hpp: lane (g, p) has the rows 4 v + g of column nat(p)), and that is the first operand of A^T B and the second of
 // A B.  Every operator is therefore phrased in products  X^T Y  of tiles as they stand, some of them kept transposed; LDS
 // only turns a tile where its transpose is wanted, too, or where memory runs the other way.
+// What bounds them is registers: 56 to 210 with three tile rows, 76 to 250 with four, so 8 to 2 wavefronts per SIMD, and one only for
+// k_potri_backward_wave and k_outer_wave with a triangle, fp64, four tile rows (364 to 367 of the 512 a wavefront can have), where nothing hides a load; the launch bounds
+// ask for what each has.
 #include "leaf_frag.hpp"
 
 namespace la {
@@ -793,6 +796,10 @@ __global__ __launch_bounds__(SW_WAVES * 64, TRI != 0 ? (sizeof(T) * K <= 12 ? 3 
 // ---------------------------------------------------------------------------------------
 // launches: 32 < n <= 64, three or four tile rows
 // ---------------------------------------------------------------------------------------
+// The edge is that of the four-wavefront kernels these stand beside; it does not lie where these stop paying.  In a graph, us, 1024 matrices, fp32 /
+// fp64: potrf of n = 37 33 -> 7.3 / 42 -> 9.6, of n = 60 28 -> 11 / 38 -> 17, backward 30 -> 8.7 / 36 -> 14 and 39 -> 16 / 47 -> 27, potri 19 -> 6.1 /
+// 22 -> 8.7 and 24 -> 10 / 29 -> 16; 128 matrices of n = 37: 33 -> 6.5 / 41 -> 8.1, 12 -> 8.0 / 13 -> 12, 7.4 -> 5.3 / 8.2 -> 7.1.  Behind they are with
+// 256 and fewer of n > 48 in fp64: backward 17 -> 20, syrk's rule 6.4 -> 8.0 (n = 64 also trmm 5.0 -> 6.7, potri 9.5 -> 12).  Left where it was.
 static bool wave_range(int64_t batch, int n) { return n > 2 * LT && n <= 4 * LT && batch > 1024 && batch <= 0x7fffffffll; }
 // the kernels address an item by 32-bit byte offsets
 template <typename T>
