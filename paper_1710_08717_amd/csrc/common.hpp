@@ -392,7 +392,7 @@ struct Mfma<double> {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
     // accumulator register v of lane l holds D[row][l % 16]
-    static __device__ __forceinline__ int row(int l, int v) { return (l >> 4) + 4 * v; }
+    static __device__ __host__ __forceinline__ constexpr int row(int l, int v) { return (l >> 4) + 4 * v; }
 };
 template <>
 struct Mfma<float> {
@@ -403,7 +403,7 @@ struct Mfma<float> {
     {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
-    static __device__ __forceinline__ int row(int l, int v) { return 4 * (l >> 4) + v; }
+    static __device__ __host__ __forceinline__ constexpr int row(int l, int v) { return 4 * (l >> 4) + v; }
 };
 
 // a 16-byte chunk that starts anywhere an element may start (global loads need dword alignment only)

@@ -6,26 +6,32 @@
 //   C(i,j) = beta * C(i,j) + alpha * sum_k A(i,k) B(k,j)
 //
 // Operands are strided views (either index may be the contiguous one), so transposes and
-// upper/lower variants never copy.  Triangular operands are masked while they are staged
-// in LDS and their structurally-zero K range is skipped.
+// upper/lower variants never copy.  Triangular operands are masked between LDS and the matrix cores
+// and their structurally-zero K range is skipped.
 //
-// k_gemm: 16-byte vector loads, register prefetch of the next K slab while the current one is
-// multiplied out of LDS, 128x128 (K slabs of 16, double-buffered LDS, one barrier per slab),
-// 64x64 (K slabs of 32) or 32x32 workgroup tiles (K slabs of 64, for the small, latency-bound
-// grids of the recursion's lower levels), four
-// wavefronts in a 2 x 2 arrangement, 16x16x4 MFMA (v_mfma_f64_16x16x4_f64 /
-// v_mfma_f32_16x16x4_f32).  Two forms: with 16-byte aligned operands and K a multiple of 16 every
-// chunk is one aligned load; otherwise (odd sizes and leading dimensions) the chunks are loaded
-// with the alignment of one element and the ones that cross the end of the operand element by
-// element, zeros behind it.  The second form keeps the pipeline of the first and issues the same
-// number of loads; a chunk then spans two cache lines more often.  (Staging such operands element by element without prefetch, as an earlier kernel
-// did, was bound by its load instructions and address arithmetic: factor + gradient of one
-// fp64 matrix of n = 3001 8.83 ms, now 2.77; 24 fp32 matrices of n = 333 0.70 ms, now 0.23.)
+// k_gemm: operands whose rows are 16-byte aligned.  Slabs of K go straight from memory to LDS (global_load_lds_dwordx4), slab s + 1 while slab
+// s is multiplied; 128 x 128, 64 x 64 and 32 x 32 workgroup tiles, four wavefronts in a 2 x 2 arrangement, 16x16x4 MFMA
+// (v_mfma_f64_16x16x4_f64 / v_mfma_f32_16x16x4_f32).  Bound by the matrix cores, and by what else is issued beside them: a vector instruction
+// waits for the matrix instruction under way on its SIMD, so the loop has next to none (4 to 9 per 64 to 128 matrix instructions on 128 x 128 tiles, for
+// 100 to 150 when slabs passed through registers with their addresses added up and their triangles masked on the way).
+// us, slabs through registers -> to LDS: 4096^3 fp64 2240 -> 1965 (70 TFLOP/s), fp32 1170 -> 995 (138); 6144^2 x 1024 1355 -> 1158 and 655 -> 580; 32 x 512^3
+// 153 -> 132 and 84 -> 70; 32 x 256^3 29.5 -> 23.5 and 17.4 -> 13.6; 64 x 200^3 49 -> 34 and 25 -> 24; 4096 x 512 x 512 51 -> 41 and 29 -> 22.5.
+// k_gemm_staged: ragged operands (odd sizes and leading dimensions), whose chunks are loaded with the alignment of one element.
 #include <algorithm>
 
 #include "common.hpp"
 
 namespace la {
+
+// One 16-byte chunk per lane from memory to LDS: lane l's goes to `lds` (uniform) + 16 l.  Written as assembly because the compiler waits for all
+// of these before it reads LDS, whichever part, and adds up the addresses in vector registers; wait_loads is where a reader waits.
+__device__ __forceinline__ void load_lds16(const char *base, uint32_t off, void *lds)
+{
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
+}
+// until this wavefront's loads have landed
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ---------------------------------------------------------------------------------------
 // Workgroup -> work slot mapping.  Consecutive workgroups are dealt round-robin to the 8 XCDs
@@ -156,13 +162,423 @@ __device__ __forceinline__ void store_c(T *Cp, int64_t rs, int64_t cs, int i, in
 // ---------------------------------------------------------------------------------------
 // Tile kernel.  AKF: A(i,k) has k contiguous (A.cs == 1), else i contiguous (A.rs == 1).
 // BKF: B(k,j) has k contiguous (B.rs == 1), else j contiguous (B.cs == 1).
-// LDS slab layouts (chosen so that global->LDS stores are 16-byte vectors and the MFMA
-// fragment reads are bank-conflict free):
+//
+// A slab is BK values of k of one operand, BKB = BK * sizeof(T) bytes, kept in LDS as 16-byte chunks in the order of memory:
+//   k contiguous:     row o holds BKB / 16 chunks, chunk c of it at position c ^ (o & 7)
+//   outer contiguous: row k holds OUT / VW chunks in their order
+// (the exchange of chunks spreads the 16 rows that a fragment read touches over all banks).  A lane reads whole chunks: VW consecutive k
+// of its row, or (outer contiguous) one k of G neighbouring rows, which are then the rows of G different 16 x 16 tiles.  So the
+// contraction index k = (4 s + lane / 16) VW + u belongs to step (s, u), and tile x's row r is row map(x, r) of the wavefront's part.
+// ---------------------------------------------------------------------------------------
+template <typename T, int OUT, int BKB, bool KF>
+struct Slab {
+    static constexpr int VW = Mfma<T>::VW;
+    static constexpr int BK = BKB / (int)sizeof(T);
+    static constexpr int ELEMS = OUT * BK;
+    static constexpr int NCH = OUT * BKB / 16 / 256;          // chunks per thread
+    static constexpr int RC = KF ? BKB / 16 : OUT / VW;       // chunks per row of the slab
+    static constexpr int TILES = OUT / 32;                    // 16-wide tiles of a wavefront (two of them share OUT)
+    static constexpr int G = KF ? 1 : (VW < TILES ? VW : TILES);
+    static_assert(NCH >= 1 && BKB >= 128, "slab too small for 256 threads");
+
+    // outer index and k of the chunk that thread (w, lane) copies in its i-th turn to position (i * 4 + w) * 64 + lane
+    static __device__ __forceinline__ void coords(int i, int w, int lane, int &o, int &k)
+    {
+        const int p = (i * 4 + w) * 64 + lane, row = p / RC, c = p % RC;
+        o = KF ? row : c * VW;
+        k = KF ? (c ^ (row & 7)) * VW : row;
+    }
+    static __device__ __forceinline__ int map(int x, int r) { return KF ? 16 * x + r : 16 * G * (x / G) + G * r + x % G; }
+};
+
+// Copies slabs of one operand straight from memory to LDS, in 16-byte chunks: no registers and no vector arithmetic on the way (on this chip a
+// vector instruction waits for the matrix instruction under way on its SIMD).  No address lies outside the operand: rows past its end repeat the
+// last one (nothing that is kept comes from them), and so does a k past its end (the reader masks it).
+template <typename T, int OUT, int BKB, bool KF>
+struct Copier {
+    using S = Slab<T, OUT, BKB, KF>;
+    static constexpr int VW = S::VW;
+    uint32_t off[S::NCH];  // bytes from the slab's first element
+    const char *next;      // the next slab's first element
+    int64_t step;
+
+    // src: the operand's item
+    __device__ __forceinline__ void start(const T *src, int64_t so, int64_t sk, int o0, int k0)
+    {
+        next = reinterpret_cast<const char *>(src + o0 * so + k0 * sk);
+        step = S::BK * sk * (int64_t)sizeof(T);
+    }
+    // no: rows of the operand, a multiple of VW where those are contiguous, as is every o0
+    __device__ __forceinline__ void init(int64_t so, int64_t sk, int o0, int no, int w, int lane)
+    {
+#pragma unroll
+        for (int i = 0; i < S::NCH; ++i) {
+            int o, k;
+            S::coords(i, w, lane, o, k);
+            off[i] = (uint32_t)(min(o, (KF ? no - 1 : no - VW) - o0) * so + k * sk) * (uint32_t)sizeof(T);
+        }
+    }
+    // k0, nk: the slab's first k and the operand's end, both multiples of VW where k is contiguous
+    __device__ __forceinline__ void fetch(T *lds, int64_t sk, int k0, int nk, int w, int lane)
+    {
+        const char *base = next;
+        next += step;
+        if (k0 + S::BK <= nk) {
+#pragma unroll
+            for (int i = 0; i < S::NCH; ++i)
+                load_lds16(base, off[i], lds + (i * 4 + w) * 64 * VW);
+        } else {
+#pragma unroll
+            for (int i = 0; i < S::NCH; ++i) {
+                int o, k;
+                S::coords(i, w, lane, o, k);
+                const int back = max(k - (nk - (KF ? VW : 1) - k0), 0);
+                load_lds16(base, off[i] - (uint32_t)(back * sk) * (uint32_t)sizeof(T), lds + (i * 4 + w) * 64 * VW);
+            }
+        }
+    }
+};
+
+// A wavefront's operand values of NS groups of steps of a slab: value(x, s, u), x the 16-wide tile, step (s, u).
+template <typename T, int OUT, int BKB, bool KF, int NS>
+struct Fragments {
+    using S = Slab<T, OUT, BKB, KF>;
+    static constexpr int VW = S::VW, TILES = S::TILES, G = S::G, W = KF ? VW : G, PER = KF ? NS : NS * VW;
+    typedef T vec __attribute__((ext_vector_type(W)));
+    vec f[PER][TILES / G];  // KF: [s][x], elements u; else [(s, u)][x / G], elements x % G
+
+    __device__ __forceinline__ T value(int x, int s, int u) const
+    {
+        if constexpr (KF)
+            return f[s][x][u];
+        else if constexpr (G == 1)
+            return f[s * VW + u][x][0];
+        else
+            return f[s * VW + u][x / G][x % G];
+    }
+    __device__ __forceinline__ void read(const T *lds, int first, int wo, int lane)
+    {
+        const int l16 = lane & 15, lk = lane >> 4;
+        if constexpr (KF) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const T *p = lds + (wo + l16) * S::BK + ((4 * (first + s) + lk) ^ (l16 & 7)) * VW;
+#pragma unroll
+                for (int x = 0; x < TILES; ++x)
+                    f[s][x] = *reinterpret_cast<const vec *>(p + 16 * x * S::BK);
+            }
+        } else {
+            const T *p = lds + (4 * first + lk) * VW * OUT + wo + G * l16;
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+#pragma unroll
+                for (int u = 0; u < VW; ++u)
+#pragma unroll
+                    for (int g = 0; g < TILES / G; ++g)
+                        f[s * VW + u][g] = *reinterpret_cast<const vec *>(p + (4 * s * VW + u) * OUT + 16 * G * g);
+        }
+    }
+    // zeros from k = nk on; k0: first k of these steps
+    __device__ __forceinline__ void mask_end(int k0, int nk, int lane)
+    {
+        asm volatile("" : "+s"(k0));  // (or the compiler keeps one running index per value through the whole loop)
+        const int lk = lane >> 4;
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int u = 0; u < VW; ++u) {
+                const bool drop = k0 + (4 * s + lk) * VW + u >= nk;
+#pragma unroll
+                for (int x = 0; x < TILES; ++x)
+                    element(x, s, u, drop);
+            }
+    }
+    // zeros on the far side of a triangle: tri 1 keeps outer >= k, 2 outer <= k; o0, k0: first row and k of these steps
+    __device__ __forceinline__ void mask_tri(int o0, int k0, int tri, int lane)
+    {
+        asm volatile("" : "+s"(k0));
+        const int l16 = lane & 15, lk = lane >> 4, sgn = tri == 2 ? -1 : 1;
+        const int d0 = sgn * (o0 + (KF ? 1 : G) * l16 - k0 - lk * VW);  // sign of (row - k) at x, s, u = 0
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int u = 0; u < VW; ++u)
+#pragma unroll
+                for (int x = 0; x < TILES; ++x)
+                    element(x, s, u, d0 < -sgn * (S::map(x, 0) - 4 * s * VW - u));
+    }
+    __device__ __forceinline__ void element(int x, int s, int u, bool drop)
+    {
+        if constexpr (KF)
+            f[s][x][u] = drop ? T(0) : f[s][x][u];
+        else
+            f[s * VW + u][x / G][x % G] = drop ? T(0) : f[s * VW + u][x / G][x % G];
+    }
+};
+
+template <typename T, int BM, int BN, int BKB, int NB, bool AKF, bool BKF, bool SYM>
+__global__ __launch_bounds__(256, BM * BN >= 128 * 128 ? 2 : (sizeof(T) == 4 ? 6 : 4)) void k_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M,
+                                                 int N, int K, T alpha, T beta, GemmOpts o, int tiles_m, int tiles_n)
+{
+    using MF = Mfma<T>;
+    using acc_t = typename MF::acc_t;
+    using SA = Slab<T, BM, BKB, AKF>;
+    using SB = Slab<T, BN, BKB, BKF>;
+    constexpr int BK = SA::BK, VW = SA::VW;
+    constexpr int WM = BM / 2, WN = BN / 2;
+    constexpr int TM = WM / 16, TN = WN / 16;
+    constexpr int PARTS = BM * BN >= 128 * 128 ? 2 : 1;  // of a slab whose operand values are in registers at a time
+    constexpr int PART = WM * (WN + 1);  // a wavefront's part of a symmetric result
+    extern __shared__ __align__(16) char lds_bytes[];  // gemm_lds
+    T *lds = reinterpret_cast<T *>(lds_bytes);
+
+    const int64_t per = tile_count_dev(o.order, tiles_m, tiles_n);
+    int64_t b;
+    int tile;
+    if (o.xcd_batch) {
+        // Batched launch: XCD x (workgroups x, x + 8, ...) owns the items b = x, x + 8, ... and
+        // goes through the tile list once for all of them, tile by tile.  The tile lists are
+        // heaviest-first, so the uneven tiles of triangular problems pack well over the
+        // workgroup slots, and the tiles of one item still meet in one L2.
+        const int x = (int)(blockIdx.x & 7);
+        const int64_t q = blockIdx.x >> 3, mpx = (batch + 7) >> 3;
+        tile = (int)(q / mpx);
+        b = (q % mpx) * 8 + x;
+        if (b >= batch)
+            return;
+    } else {
+        // a few items: tile-major too (tile t of every item, then tile t + 1, ...)
+        const int64_t slot = xcd_slot(blockIdx.x, per * batch, o.order == 5 ? 8 : 16);
+        tile = (int)(slot / batch);
+        b = slot % batch;
+    }
+    if (o.reverse && o.order != 5)
+        tile = (int)per - 1 - tile;  // heaviest tiles first when the work grows along the tile list
+    int tm, tn;
+    decode_tile(o.order, tile, tiles_m, tiles_n, tm, tn);
+    const int i0 = tm * BM, j0 = tn * BN;
+    if ((o.maskC == 1 && j0 > i0 + BM - 1) || (o.maskC == 2 && i0 > j0 + BN - 1))
+        return;
+
+    int Kl = K;  // slice s of a split K range: K elements from s * K on, fewer for the last slice
+    if (o.ksplit > 1)
+        Kl = min(K, o.ktotal - (int)(b % o.ksplit) * K);
+    int kbeg, kend;  // (kbeg is a tile's first row or column: whole chunks start there)
+    k_range(o, i0, j0, BM, BN, Kl, kbeg, kend);
+
+    T *Cp = C.item(b);
+    const int triB_o = o.triB == 1 ? 2 : (o.triB == 2 ? 1 : 0);
+
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = (w >> 1) * WM, wn = (w & 1) * WN;
+
+    acc_t acc[TM][TN];
+#pragma unroll
+    for (int x = 0; x < TM; ++x)
+#pragma unroll
+        for (int y = 0; y < TN; ++y)
+            acc[x][y] = acc_t{0, 0, 0, 0};
+
+    // Software pipeline over slabs in two LDS buffers: slab s + 1 is requested as soon as every wavefront has read slab s - 1 (the barrier) and its
+    // own part of slab s, and is waited for most of a slab of matrix instructions later.  One buffer (NB = 1): requested once everybody has slab
+    // s in registers, a second barrier, but more workgroups a compute unit.  (Three and four buffers: 5 to 15 % slower, fewer workgroups.)
+    // SYM (GemmOpts::symsum): with 1 a second pass over the same range adds B^T A^T -- same strides, the base pointers change places.
+    if (kbeg < kend) {
+        const T *pa = A.item(b), *pb = B.item(b);
+        const int ns = (kend - kbeg + BK - 1) / BK, total = SYM && o.symsum == 1 ? 2 * ns : ns;
+        Copier<T, BM, BKB, AKF> ca;
+        Copier<T, BN, BKB, BKF> cb;
+        ca.init(A.rs, A.cs, i0, M, w, lane);
+        cb.init(B.cs, B.rs, j0, N, w, lane);
+        ca.start(pa, A.rs, A.cs, i0, kbeg);
+        cb.start(pb, B.cs, B.rs, j0, kbeg);
+        int kr = kbeg;  // first k of the next request
+        auto request = [&](int t, T *at) {
+            if (SYM && t == ns) {
+                ca.start(pb, A.rs, A.cs, i0, kbeg);
+                cb.start(pa, B.cs, B.rs, j0, kbeg);
+                kr = kbeg;
+            }
+            ca.fetch(at, A.cs, kr, Kl, w, lane);
+            cb.fetch(at + SA::ELEMS, B.rs, kr, Kl, w, lane);
+            kr += BK;
+        };
+        // slabs within [klo, khi) touch neither the zero side of a triangle nor the end of the range: nothing to mask
+        const int klo = __builtin_amdgcn_readfirstlane(max(o.triA == 2 ? i0 + BM - 1 : 0, triB_o == 2 ? j0 + BN - 1 : 0));
+        const int khi = __builtin_amdgcn_readfirstlane(min(kend, min(o.triA == 1 ? i0 + 1 : kend, triB_o == 1 ? j0 + 1 : kend)));
+        constexpr int BUF = SA::ELEMS + SB::ELEMS;
+        auto slab = [&](int t, T *at, T *other) {  // other: the buffer of slab t + 1
+            wait_loads();
+            __syncthreads();
+            const int k0 = kbeg + (SYM && t >= ns ? t - ns : t) * BK;
+            const bool edge = k0 < klo || k0 + BK > khi;
+#pragma unroll
+            for (int part = 0; part < PARTS; ++part) {
+                constexpr int NS = BK / (4 * VW) / PARTS;
+                const int kp = k0 + part * NS * 4 * VW;
+                Fragments<T, BM, BKB, AKF, NS> fa;
+                Fragments<T, BN, BKB, BKF, NS> fb;
+                fa.read(at, part * NS, wm, lane);
+                fb.read(at + SA::ELEMS, part * NS, wn, lane);
+                if (part == PARTS - 1) {
+                    if constexpr (NB == 1)
+                        __syncthreads();  // everybody has read the slab
+                    if (t + 1 < total)
+                        request(t + 1, other);
+                }
+                if (edge) {
+                    if (o.triA)
+                        fa.mask_tri(i0 + wm, kp, o.triA, lane);
+                    if (triB_o)
+                        fb.mask_tri(j0 + wn, kp, triB_o, lane);
+                    if (k0 + BK > Kl) {
+                        fa.mask_end(kp, Kl, lane);
+                        fb.mask_end(kp, Kl, lane);
+                    }
+                }
+#pragma unroll
+                for (int s = 0; s < NS; ++s) {
+                    if (BM * BN < 128 * 128 && kp + 4 * VW * s >= kend)
+                        break;
+#pragma unroll
+                    for (int u = 0; u < VW; ++u)
+#pragma unroll
+                        for (int x = 0; x < TM; ++x)
+#pragma unroll
+                            for (int y = 0; y < TN; ++y)
+                                acc[x][y] = MF::run(fa.value(x, s, u), fb.value(y, s, u), acc[x][y]);
+                }
+            }
+        };
+        request(0, lds);
+        // two slabs a turn: the buffers' places are then part of the instructions
+        for (int t = 0; t < total; t += NB) {
+            slab(t, lds, lds + (NB - 1) * BUF);
+            if (NB == 2 && t + 1 < total)
+                slab(t + 1, lds + BUF, lds);
+        }
+    }
+
+    const int l16 = lane & 15;
+    if constexpr (SYM) {
+        // Every value goes to both triangles.  The wavefront lays its part out in LDS, stores the entries on and below the diagonal row by
+        // row and their mirror images column by column, so that both run along the rows of C.
+        constexpr int LD = WN + 1;
+        __syncthreads();
+        T *part = lds + w * PART;
+#pragma unroll
+        for (int x = 0; x < TM; ++x)
+#pragma unroll
+            for (int y = 0; y < TN; ++y)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    part[SA::map(x, MF::row(lane, v)) * LD + SB::map(y, l16)] = alpha * acc[x][y][v];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        const int it = i0 + wm, jt = j0 + wn;
+        if (jt > it + WM - 1 || it >= M)
+            return;
+        constexpr int RP = 64 / WN;  // rows per turn
+        {
+            const int u0 = lane / WN, c = lane % WN, rows = min(M - it, WM) - u0, first = jt + c - it - u0;  // rows q from `first` to `rows` are kept
+            T *at = Cp + (int64_t)(it + u0) * C.rs + (int64_t)(jt + c) * C.cs;
+            T *p = part + u0 * LD + c;
+#pragma unroll
+            for (int q = 0; q < WM; q += RP, at += RP * C.rs)
+                if (q < rows && q >= first) {
+                    T upd = p[q * LD];
+                    if (beta != T(0)) {
+                        upd = fma(beta, *at, upd);
+                        p[q * LD] = upd;
+                    }
+                    *at = upd;
+                }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        constexpr int CP = 64 / WM;  // columns per turn
+        const int c0 = lane / WM, u = lane % WM, cols = it + u < M ? it + u - jt - c0 : 0;  // columns q below `cols` have a mirror image
+        T *at = Cp + (int64_t)(jt + c0) * C.rs + (int64_t)(it + u) * C.cs;
+        const T *p = part + u * LD + c0;
+#pragma unroll
+        for (int q = 0; q < WN; q += CP, at += CP * C.rs)
+            if (q < cols)
+                *at = p[q];
+        return;
+    }
+    if (C.cs == 1 && (i0 >= j0 + BN || j0 >= i0 + BM || !(o.halfDiag || o.maskC == 1 || o.maskC == 2))) {
+        // Nothing is masked: addresses are a uniform part and one offset per lane, G neighbouring columns are stored at once.
+        constexpr int G = SB::G;
+        typedef T vec __attribute__((ext_vector_type(G), aligned(sizeof(T))));
+        const bool whole = i0 + BM <= M && j0 + BN <= N;
+        const int row = SA::map(0, MF::row(lane, 0)), col = SB::map(0, l16), rows = M - i0 - wm - row, cols = N - j0 - wn - col;  // what is left from here
+        const uint32_t off = (uint32_t)(row * C.rs + col) * (uint32_t)sizeof(T);
+        constexpr int VR = MF::row(0, 1) * SA::G;  // rows from one register of an accumulator to the next
+        T *Ct = Cp + (int64_t)(i0 + wm) * C.rs + (j0 + wn);
+#pragma unroll
+        for (int x = 0; x < TM; ++x) {
+            T *Cx = Ct + (int64_t)SA::map(x, 0) * C.rs;
+            auto at = [&](int v, int y) { return reinterpret_cast<T *>(reinterpret_cast<char *>(Cx + v * VR * C.rs + SB::map(y, 0)) + off); };
+            auto left = [&](int v, int y) { return whole ? G : (SA::map(x, 0) + v * VR < rows ? cols - SB::map(y, 0) : 0); };
+            vec old[4][TN / G];
+            if (beta != T(0)) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int y = 0; y < TN; y += G) {
+                        const int n = left(v, y);
+                        if (n >= G) {
+                            old[v][y / G] = *reinterpret_cast<const vec *>(at(v, y));
+                        } else {
+#pragma unroll
+                            for (int g = 0; g < G - 1; ++g)
+                                if (g < n)
+                                    old[v][y / G][g] = at(v, y)[g];
+                        }
+                    }
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int y = 0; y < TN; y += G) {
+                    vec r;
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        r[g] = alpha * acc[x][y + g][v];
+                        if (beta != T(0))
+                            r[g] = fma(beta, old[v][y / G][g], r[g]);
+                    }
+                    const int n = left(v, y);
+                    if (n >= G) {
+                        *reinterpret_cast<vec *>(at(v, y)) = r;
+                    } else {
+#pragma unroll
+                        for (int g = 0; g < G - 1; ++g)
+                            if (g < n)
+                                at(v, y)[g] = r[g];
+                    }
+                }
+        }
+        return;
+    }
+#pragma unroll
+    for (int x = 0; x < TM; ++x)
+#pragma unroll
+        for (int y = 0; y < TN; ++y)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                store_c<T>(Cp, C.rs, C.cs, i0 + wm + SA::map(x, MF::row(lane, v)), j0 + wn + SB::map(y, l16), M, N, acc[x][y][v],
+                           alpha, beta, o);
+}
+
+// ---------------------------------------------------------------------------------------
+// Ragged operands (odd sizes and leading dimensions): slabs travel global memory -> registers -> LDS, chunks loaded with the alignment of one
+// element, the ones that cross the end of the operand element by element, zeros behind it.  The kernel above with such a copier was
+// 10 % behind in the long triangular products of one matrix (n = 3001, fp64, factor + gradient 2270 -> 2550 us): it keeps more in registers.
+// LDS slab layouts (chosen so that global->LDS stores are 16-byte vectors and the fragment reads are bank-conflict free):
 //   k contiguous:     s[o][BK + VW]      (row stride 18 doubles / 20 floats)
 //   outer contiguous: s[k][OUT + 16]
 // ---------------------------------------------------------------------------------------
 template <typename T, int OUT, int BK, bool KF>
-struct Slab {
+struct StagedSlab {
     using MF = Mfma<T>;
     static constexpr int VW = MF::VW;
     static constexpr int LD = KF ? (BK + VW) : (OUT + 16);
@@ -187,14 +603,13 @@ struct Slab {
 };
 
 // One slab of an operand into registers: outer rows o0 .. o0 + OUT - 1 of `no`, k from k0 on, of `nk`.
-// RAG = false: whole aligned chunks only (nk a multiple of BK; `no` a multiple of VW when !KF).
-template <typename T, int OUT, int BK, bool KF, bool RAG, typename RV>
+template <typename T, int OUT, int BK, bool KF, typename RV>
 __device__ __forceinline__ void slab_fetch(RV &r, const T *src, int64_t so, int64_t sk, int o0, int no, int k0, int nk)
 {
-    using S = Slab<T, OUT, BK, KF>;
+    using S = StagedSlab<T, OUT, BK, KF>;
     using V = typename Mfma<T>::vec_t;
     using L = typename LooseVec<T>::type;
-    if (RAG && o0 + OUT <= no && k0 + BK <= nk) {  // (uniform) nothing crosses an end
+    if (o0 + OUT <= no && k0 + BK <= nk) {  // (uniform) nothing crosses an end
 #pragma unroll
         for (int c = 0; c < S::NCH; ++c) {
             int o, k;
@@ -214,22 +629,17 @@ __device__ __forceinline__ void slab_fetch(RV &r, const T *src, int64_t so, int6
         else
             v = V{0, 0, 0, 0};
         const T *e = src + (int64_t)(o0 + o) * so + (int64_t)(k0 + k) * sk;
-        if constexpr (RAG) {
-            // elements of the chunk that exist
-            const int left = KF ? (o0 + o < no ? nk - (k0 + k) : 0) : (k0 + k < nk ? no - (o0 + o) : 0);
-            if (left >= S::VW) {
-                const L x = *reinterpret_cast<const L *>(e);
-                v = __builtin_bit_cast(V, x);
-            } else {
-                T *q = reinterpret_cast<T *>(&v);
-#pragma unroll
-                for (int u = 0; u < S::VW - 1; ++u)
-                    if (u < left)
-                        q[u] = e[u];
-            }
+        // elements of the chunk that exist
+        const int left = KF ? (o0 + o < no ? nk - (k0 + k) : 0) : (k0 + k < nk ? no - (o0 + o) : 0);
+        if (left >= S::VW) {
+            const L x = *reinterpret_cast<const L *>(e);
+            v = __builtin_bit_cast(V, x);
         } else {
-            if (o0 + o < no)
-                v = *reinterpret_cast<const V *>(e);
+            T *q = reinterpret_cast<T *>(&v);
+#pragma unroll
+            for (int u = 0; u < S::VW - 1; ++u)
+                if (u < left)
+                    q[u] = e[u];
         }
         r[c] = v;
     }
@@ -238,7 +648,7 @@ __device__ __forceinline__ void slab_fetch(RV &r, const T *src, int64_t so, int6
 template <typename T, int OUT, int BK, bool KF, typename RV>
 __device__ __forceinline__ void slab_commit(T *s, RV &r, int o0, int k0, int tri)
 {
-    using S = Slab<T, OUT, BK, KF>;
+    using S = StagedSlab<T, OUT, BK, KF>;
     using V = typename Mfma<T>::vec_t;
     // Does this slab touch the zero side of a triangular operand at all?  Decided once per slab
     // (a scalar branch); most slabs do not and take the plain copy below.
@@ -274,15 +684,15 @@ __device__ __forceinline__ void slab_commit(T *s, RV &r, int o0, int k0, int tri
     }
 }
 
-template <typename T, int BM, int BN, int BK, int NBUF, bool AKF, bool BKF, bool RAG, bool SYM>
-__global__ __launch_bounds__(256, 2) void k_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M,
-                                                 int N, int K, T alpha, T beta, GemmOpts o, int tiles_m, int tiles_n)
+template <typename T, int BM, int BN, int BK, int NBUF, bool AKF, bool BKF, bool SYM>
+__global__ __launch_bounds__(256, 2) void k_gemm_staged(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N, int K,
+                                                        T alpha, T beta, GemmOpts o, int tiles_m, int tiles_n)
 {
     using MF = Mfma<T>;
     using acc_t = typename MF::acc_t;
     using V = typename MF::vec_t;
-    using SA = Slab<T, BM, BK, AKF>;
-    using SB = Slab<T, BN, BK, BKF>;
+    using SA = StagedSlab<T, BM, BK, AKF>;
+    using SB = StagedSlab<T, BN, BK, BKF>;
     constexpr int WM = BM / 2, WN = BN / 2;
     constexpr int TM = WM / 16, TN = WN / 16;
     __shared__ __align__(16) T sA[NBUF][SA::ELEMS];
@@ -375,13 +785,13 @@ __global__ __launch_bounds__(256, 2) void k_gemm(View<const T> A, View<const T> 
     }
     if constexpr (NBUF == 2) {
         if (kbeg < kend) {
-            slab_fetch<T, BM, BK, AKF, RAG>(ra, Ap, A.rs, A.cs, i0, M, kbeg, Kl);
-            slab_fetch<T, BN, BK, BKF, RAG>(rb, Bp, B.cs, B.rs, j0, N, kbeg, Kl);
+            slab_fetch<T, BM, BK, AKF>(ra, Ap, A.rs, A.cs, i0, M, kbeg, Kl);
+            slab_fetch<T, BN, BK, BKF>(rb, Bp, B.cs, B.rs, j0, N, kbeg, Kl);
             slab_commit<T, BM, BK, AKF>(sA[0], ra, i0, kbeg, o.triA);
             slab_commit<T, BN, BK, BKF>(sB[0], rb, j0, kbeg, triB_o);
             if (kbeg + BK < kend) {
-                slab_fetch<T, BM, BK, AKF, RAG>(ra, Ap, A.rs, A.cs, i0, M, kbeg + BK, Kl);
-                slab_fetch<T, BN, BK, BKF, RAG>(rb, Bp, B.cs, B.rs, j0, N, kbeg + BK, Kl);
+                slab_fetch<T, BM, BK, AKF>(ra, Ap, A.rs, A.cs, i0, M, kbeg + BK, Kl);
+                slab_fetch<T, BN, BK, BKF>(rb, Bp, B.cs, B.rs, j0, N, kbeg + BK, Kl);
             }
             __syncthreads();
         }
@@ -392,8 +802,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm(View<const T> A, View<const T> 
                 slab_commit<T, BN, BK, BKF>(sB[buf ^ 1], rb, j0, k0 + BK, triB_o);
             }
             if (k0 + 2 * BK < kend) {
-                slab_fetch<T, BM, BK, AKF, RAG>(ra, Ap, A.rs, A.cs, i0, M, k0 + 2 * BK, Kl);
-                slab_fetch<T, BN, BK, BKF, RAG>(rb, Bp, B.cs, B.rs, j0, N, k0 + 2 * BK, Kl);
+                slab_fetch<T, BM, BK, AKF>(ra, Ap, A.rs, A.cs, i0, M, k0 + 2 * BK, Kl);
+                slab_fetch<T, BN, BK, BKF>(rb, Bp, B.cs, B.rs, j0, N, k0 + 2 * BK, Kl);
             }
             multiply(sA[buf], sB[buf]);
             __syncthreads();
@@ -401,16 +811,16 @@ __global__ __launch_bounds__(256, 2) void k_gemm(View<const T> A, View<const T> 
         }
     } else {
         if (kbeg < kend) {
-            slab_fetch<T, BM, BK, AKF, RAG>(ra, Ap, A.rs, A.cs, i0, M, kbeg, Kl);
-            slab_fetch<T, BN, BK, BKF, RAG>(rb, Bp, B.cs, B.rs, j0, N, kbeg, Kl);
+            slab_fetch<T, BM, BK, AKF>(ra, Ap, A.rs, A.cs, i0, M, kbeg, Kl);
+            slab_fetch<T, BN, BK, BKF>(rb, Bp, B.cs, B.rs, j0, N, kbeg, Kl);
         }
         for (int k0 = kbeg; k0 < kend; k0 += BK) {
             slab_commit<T, BM, BK, AKF>(sA[0], ra, i0, k0, o.triA);
             slab_commit<T, BN, BK, BKF>(sB[0], rb, j0, k0, triB_o);
             __syncthreads();
             if (k0 + BK < kend) {
-                slab_fetch<T, BM, BK, AKF, RAG>(ra, Ap, A.rs, A.cs, i0, M, k0 + BK, Kl);
-                slab_fetch<T, BN, BK, BKF, RAG>(rb, Bp, B.cs, B.rs, j0, N, k0 + BK, Kl);
+                slab_fetch<T, BM, BK, AKF>(ra, Ap, A.rs, A.cs, i0, M, k0 + BK, Kl);
+                slab_fetch<T, BN, BK, BKF>(rb, Bp, B.cs, B.rs, j0, N, k0 + BK, Kl);
             }
             multiply(sA[0], sB[0]);
             __syncthreads();
@@ -639,37 +1049,13 @@ static inline int pick_order(const GemmOpts &o, int tiles_m, int tiles_n)
     return o.shells ? 3 : 0;
 }
 
-template <typename T, int BM, int BN, int BK, int NBUF, bool RAG>
-static void launch_form(bool akf, bool bkf, View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N,
-                        int K, T alpha, T beta, GemmOpts o, hipStream_t st)
+// Bytes of LDS: no more buffers than slabs.
+template <typename T, int BM, int BN, int BKB, int NB>
+static size_t gemm_lds(int K, bool sym)
 {
-    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    o.order = pick_order(o, tiles_m, tiles_n);
-    const int64_t per = tile_count(o.order, tiles_m, tiles_n);
-    o.xcd_batch = (batch >= 8 && per > 1) ? 1 : 0;
-    const int64_t wgs = o.xcd_batch ? 8 * ((batch + 7) / 8) * per : per * batch;
-    const dim3 grid((unsigned)wgs), block(256);
-#define LA_GO(AK, BKF_, SYM_)                                                                                          \
-    LA_LAUNCH((k_gemm<T, BM, BN, BK, NBUF, AK, BKF_, RAG, SYM_>), grid, block, 0, st, A, B, C, batch, M, N, K, alpha,  \
-              beta, o, tiles_m, tiles_n)
-    if constexpr (BM <= 64) {  // the symmetric sum exists for the small tiles only (launch_gemm picks them)
-        if (o.symsum) {         // and its operands have mirrored strides, so akf == bkf
-            if (akf)
-                LA_GO(true, true, true);
-            else
-                LA_GO(false, false, true);
-            return;
-        }
-    }
-    if (akf && bkf)
-        LA_GO(true, true, false);
-    else if (akf && !bkf)
-        LA_GO(true, false, false);
-    else if (!akf && bkf)
-        LA_GO(false, true, false);
-    else
-        LA_GO(false, false, false);
-#undef LA_GO
+    const size_t slab = (size_t)(BM + BN) * BKB;
+    const size_t slabs = ((size_t)K * sizeof(T) + BKB - 1) / BKB * (sym ? 2 : 1);
+    return std::max(std::min(slabs, (size_t)NB) * slab, sym ? 4 * (BM / 2) * (BN / 2 + 1) * sizeof(T) : 0);
 }
 
 struct GemmForm {
@@ -677,14 +1063,120 @@ struct GemmForm {
     bool rag;       // some chunk is unaligned or incomplete
 };
 
-template <typename T, int BM, int BN, int BK, int NBUF>
+// Workgroups of a launch with tiles of BM x BN; chooses the tiles' order.
+template <int BM, int BN>
+static dim3 gemm_grid(int64_t batch, int M, int N, GemmOpts &o, int &tiles_m, int &tiles_n)
+{
+    tiles_m = (M + BM - 1) / BM;
+    tiles_n = (N + BN - 1) / BN;
+    o.order = pick_order(o, tiles_m, tiles_n);
+    const int64_t per = tile_count(o.order, tiles_m, tiles_n);
+    // (an XCD takes whole items: not where that leaves some with an item more than others, 14 slices of 500 x 500 x 9568 in the sparse GP
+    // 90 -> 78 us)
+    o.xcd_batch = (batch >= 8 && per > 1 && (8 - (batch & 7)) % 8 * 8 <= batch) ? 1 : 0;
+    return dim3((unsigned)(o.xcd_batch ? 8 * ((batch + 7) / 8) * per : per * batch));
+}
+
+// (the symmetric sum exists for tiles up to 64, launch_gemm picks them, and its operands have mirrored strides, so akf == bkf)
+#define LA_FORMS(GO)                       \
+    if constexpr (BM <= 64) {              \
+        if (o.symsum) {                    \
+            if (f.akf)                     \
+                GO(true, true, true);      \
+            else                           \
+                GO(false, false, true);    \
+            return;                        \
+        }                                  \
+    }                                      \
+    if (f.akf && f.bkf)                    \
+        GO(true, true, false);             \
+    else if (f.akf)                        \
+        GO(true, false, false);            \
+    else if (f.bkf)                        \
+        GO(false, true, false);            \
+    else                                   \
+        GO(false, false, false)
+
+template <typename T, int BM, int BN, int BKB, int NB = 2>
 static void launch_tiles(GemmForm f, View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N, int K,
                          T alpha, T beta, GemmOpts o, hipStream_t st)
 {
-    if (f.rag)
-        launch_form<T, BM, BN, BK, NBUF, true>(f.akf, f.bkf, A, B, C, batch, M, N, K, alpha, beta, o, st);
-    else
-        launch_form<T, BM, BN, BK, NBUF, false>(f.akf, f.bkf, A, B, C, batch, M, N, K, alpha, beta, o, st);
+    int tiles_m, tiles_n;
+    const dim3 grid = gemm_grid<BM, BN>(batch, M, N, o, tiles_m, tiles_n);
+#define LA_GO(AK, BKF_, SYM_)                                                                                                       \
+    LA_LAUNCH((k_gemm<T, BM, BN, BKB, NB, AK, BKF_, SYM_>), grid, dim3(256), (gemm_lds<T, BM, BN, BKB, NB>(K, SYM_)), st, A, B, C, batch, M, \
+              N, K, alpha, beta, o, tiles_m, tiles_n)
+    LA_FORMS(LA_GO);
+#undef LA_GO
+}
+
+template <typename T, int BM, int BN, int BK, int NBUF>
+static void launch_staged(GemmForm f, View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N, int K,
+                          T alpha, T beta, GemmOpts o, hipStream_t st)
+{
+    int tiles_m, tiles_n;
+    const dim3 grid = gemm_grid<BM, BN>(batch, M, N, o, tiles_m, tiles_n);
+#define LA_GO(AK, BKF_, SYM_)                                                                                                               \
+    LA_LAUNCH((k_gemm_staged<T, BM, BN, BK, NBUF, AK, BKF_, SYM_>), grid, dim3(256), 0, st, A, B, C, batch, M, N, K, alpha, beta, o, tiles_m, \
+              tiles_n)
+    LA_FORMS(LA_GO);
+#undef LA_GO
+}
+#undef LA_FORMS
+
+// Time of a product in e x e tiles, in us beyond what every launch costs.  A tile takes its matrix instructions (at 2.1 GHz, the clock the chip
+// holds under them; small tiles also wait for L2) and a part that nothing overlaps with; a compute unit holds 5, 4 or 2 workgroups at a time, and
+// however few there are, a workgroup's slabs follow each other at the latency of memory.  Fitted to 2300 products of 16 to 8192 rows, columns
+// and K, uniform and triangular: the tile taken is 0.6 % slower than the best of the three on average.  us, 32 x 32 /
+// 64 x 64 / 128 x 128 tiles, fp64: 32 x 128^3 7.2 / 9.0 / 21, 32 x 256^3 26 / 23.5 / 38, 2048^2 x 128 30 / 22.8 / 25, 500 x 9568 x 500 107 / 92 / 132,
+// 32 x 512^3 171 / 138 / 132, 3001 x 1024 x 2000 238 / 205 / 256, 4096^3 2540 / 2070 / 1965.
+template <typename T>
+static double tile_cost(int e, int64_t wgs, int K, const GemmOpts &o)
+{
+    const bool f32 = sizeof(T) == 4;
+    const double g = e == 128 ? 1.0 : (e == 64 ? (f32 ? 1.13 : 1.05) : (f32 ? 1.36 : 1.44));
+    const double fixed = e == 128 ? (f32 ? 3.0 : 1.2) : (e == 64 ? (f32 ? 0.25 : 0.3) : 0.32);
+    const int held = e == 128 ? 2 : (e == 64 ? 4 : 5), bk = (e == 32 ? 256 : 128) / (int)sizeof(T), passes = o.symsum == 1 ? 2 : 1;
+    const double matrix = 2e-6 * e * e * ((K + 15) / 16 * 16) * passes / (f32 ? 0.536 : 0.268);  // a tile over the whole K range
+    const double latency = (double)((K + bk - 1) / bk) * passes * (f32 ? 0.46 : 0.63);
+    const int tri = (o.triA != 0) + (o.triB != 0);
+    if (tri == 0) {
+        const double tile = matrix * g + fixed, chain = latency + matrix + fixed;
+        const int64_t n = (wgs + 255) / 256;
+        return (double)(n / held) * std::max(held * tile, chain) + (n % held ? std::max((double)(n % held) * tile, chain) : 0.0);
+    }
+    // triangular operands: part of the K range on average, the heaviest tiles first, and part of a tile at the end that does not even out
+    const double n = (double)wgs / 256.0, share = tri == 1 ? 0.455 : 0.3, whole = f32 ? 0.74 : 0.87;
+    return std::max(n * (matrix * g * share + fixed), whole * (latency + matrix) + fixed) + (n > 1.0 ? (f32 ? 0.26 : 0.35) * (matrix * g + fixed) : 0.0);
+}
+
+// Tiles of ragged products: the largest that still fill the chip.
+template <typename F>
+static int staged_edge(F &&wgs, int64_t batch, int M, int N, int K, bool k64, const GemmOpts &o)
+{
+    const int64_t wg128 = wgs(128), wg64 = wgs(64);
+    // No 128 x 128 tiles where they stick out of C by a quarter more than tiles of 64 do: 130 products of 129 x 129 x 129 79 -> 41 us in fp64,
+    // 40 -> 22 in fp32, 300 times trmm of 131 with 131 vectors 135 -> 68 and 73 -> 35; 383 x 383 (144 tiles against 180 quarters) is the same in both.
+    const bool padded = (int64_t)((M + 127) / 128) * ((N + 127) / 128) * 16 > (int64_t)((M + 63) / 64) * ((N + 63) / 64) * 5;
+    int e;
+    if (o.triA | o.triB) {
+        // Triangular operands make the K range, hence the time, of a tile vary along the tile list (heaviest first): the 512 workgroup slots only
+        // fill evenly if there are several rounds of tiles, so take the largest tile that still gives 1024 workgroups.
+        e = wg128 >= 1024 && !padded ? 128 : ((wg64 >= 1024 || !k64 || o.min_tile64) ? 64 : 32);
+    } else {
+        // Equal tiles: big tiles once they (nearly) fill the 512 workgroup slots, quarter tiles while 64 x 64 tiles would fill them less than twice --
+        // with so few rounds the last one runs part empty.  Up to K = 32 writing C is most of the work, and more, smaller workgroups overlap it with
+        // their loads (83 items of 1033 x 251, K = 2, fp64 48 -> 39 us, K = 32 72 -> 58, fp32 28 -> 25 and 37 -> 32).
+        const int64_t t128 = o.maskC ? wg128 : (int64_t)((M + 127) / 128) * ((N + 127) / 128) * batch;
+        const bool big = K > 32 && (o.maskC ? (M >= 2048 && N >= 2048) : (M >= 128 && N >= 128));
+        // Two nearly full rounds of 64 x 64 tiles are better than quarter tiles that save no padding: the chunks' address arithmetic counts (b items
+        // of 61 x 174, K = 147, us, 32 x 32 -> 64 x 64: b = 331, 993 tiles, fp64 60 -> 44, fp32 29 -> 22; with one round and a half the products of
+        // potri's backward rule, 30 x 297 x 297, 220 -> 232; 26 x 2478 x 22, 1014 tiles that the quarters halve, fp32 36 -> 54).
+        const bool two_rounds = !o.maskC && !o.symsum && wg64 >= 960 &&
+                                (int64_t)((M + 63) / 64) * ((N + 63) / 64) * 4 == (int64_t)((M + 31) / 32) * ((N + 31) / 32);
+        e = (t128 >= (o.maskC ? 512 : 480) && big && !padded) ? 128 : ((wg64 < 1024 && k64 && !o.min_tile64 && !two_rounds) ? 32 : 64);
+    }
+    return o.symsum && e == 128 ? 64 : e;  // (the form that stores both triangles has tiles up to 64 only)
 }
 
 static inline int flip_tri(int t) { return t == 1 ? 2 : (t == 2 ? 1 : 0); }
@@ -734,7 +1226,10 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
         return LA_ERR_UNSUPPORTED;  // (no operator of the library builds such a view)
     const bool a_ok = f.akf ? aligned16<T>(A, A.rs) : (aligned16<T>(A, A.cs) && M % VW == 0);
     const bool b_ok = f.bkf ? aligned16<T>(B, B.cs) : (aligned16<T>(B, B.rs) && N % VW == 0);
-    f.rag = !(K % 16 == 0 && a_ok && b_ok);
+    f.rag = !(a_ok && b_ok && (K % VW == 0 || !(f.akf || f.bkf)));
+    const int64_t longest = std::max(std::max(std::max(A.rs, A.cs), std::max(B.rs, B.cs)), std::max(C.rs, C.cs));
+    if (longest >= (int64_t)1 << 22)  // (k_gemm's offsets inside a tile have 32 bits)
+        f.rag = true;
     {
         const int64_t t64 = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch;
         if (t64 > 0x1fffffffll)  // (quarter tiles and the batched mapping round the grid up)
@@ -745,39 +1240,7 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             const int tm = (M + e - 1) / e, tn = (N + e - 1) / e;
             return tile_count(pick_order(o, tm, tn), tm, tn) * batch;
         };
-        const int64_t wg128 = wgs(128), wg64 = wgs(64);
-        // K slabs of 64: the whole range in such slabs, or (ragged) little of the last one empty
-        const bool k64 = f.rag ? (K >= 128 || (K & 63) == 0 || (K & 63) > 32) : K % 64 == 0;
-        // Quarter tiles exist with slabs of 64 only; aligned operands with another K take them in the ragged form, whose last slab ends where K
-        // does and whose loads cost address arithmetic, instead of 64 x 64 tiles in slabs of 16.  Two things decide: how many tiles of 64 there
-        // are, `work` (a last slab counts whole), against the 512 slots, and `share`, the quarter tiles' area as a part of theirs.  Gain, mean of
-        // 2700 products of 128 <= K <= 2000, by work (300 to 420 / 420 to 520 / 520 to 640 / 640 to 720 / 720 to 820 / above):
-        //   uniform, fp64, share above 1 (K far from the end of a slab) 1.07 / 0.88 / 0.90 / 0.79 / 0.76 / 0.79, 0.88 to 1 1.16 / 0.96 / 1.04 / 0.91 / 0.96 /
-        //   0.88, 0.75 to 0.88 1.28 / 1.09 / 1.10 / 0.95 / 0.96 / 0.96, below 1.68 / 1.48 / 1.44 / 1.46 / 1.31 / 1.34;
-        //   uniform, fp32, above 1 1.23 / 1.01 / 0.99 / 0.91 / 0.88 / 0.89, 0.88 to 1 1.29 / 1.08 / 1.11 / 1.03 / 1.00 / 1.01;
-        //   triangular operands, fp64, above 1 1.35 / 1.23 / 1.09 / 1.10 / 1.01 / 0.94, 0.88 to 1 1.47 / 1.29 / 1.23 / 1.22 / 1.11 / 1.02; fp32, above 1
-        //   1.63 / 1.46 / 1.26 / 1.18 / 1.08 / 1.07;
-        //   symmetric results, fp64, above 1 1.13 / 1.05 / 1.07 / 1.03 / 0.94 / 0.92, 0.88 to 1 1.26 / 1.12 / 1.15 / 1.02 / 1.00 / 0.99, 0.75 to 0.88 1.37 /
-        //   1.13 / 1.16 / 1.13 / 1.08 / 1.02; fp32, above 1 1.15 / 1.11 / 1.13 / 1.00 / 0.99 / 0.99.
-        // Within 513 to 560 tiles the last round of 64 x 64 ones runs nearly empty (uniform, fp64, share 0.88 to 1: 1.09).  Up to K = 192 the last of two
-        // or three slabs is too much of the work: share above 0.88, fp64 0.84 to 0.97, uniform, and 0.79 to 1.07, triangular
-        // (0.83: 138 x 144^2 with 80 vectors 0.90).  Of the 2700, 47 are
-        // 4 % or more slower than with tiles of 64, ten of them 10 to 22 % (7 x (720 x 300 x 1824) and 237 x (122 x 80 x 1200), fp32).
-        const bool f32 = sizeof(T) == 4, tri = (o.triA | o.triB) != 0, uniform = !tri && !o.symsum;
-        const double slabs = (double)((K + 63) / 64 * 64) / K, work = (double)wg64 * slabs;
-        const double share = 0.25 * (double)wgs(32) / (double)wg64 * slabs;
-        double most = f32 ? 1.0 : 0.875;  // share up to which the quarter tiles are taken
-        if (work < (uniform && f32 ? 448.0 : 416.0))
-            most = 2.0;
-        else if (uniform)
-            most = f32 || (wg64 > 512 && wg64 <= 560) ? 1.0 : (work < 640.0 ? 0.875 : 0.74);
-        else if (work < 720.0)
-            most = 1.05;
-        else if (tri)
-            most = f32 ? (work < 1100.0 ? 1.1 : 1.0) : 0.93;
-        if (K <= 192 && work >= 400.0)
-            most = std::min(most, 0.8);
-        const bool quarters = k64 || (K >= 128 && share <= most);
+        const int64_t wg64 = wgs(64);
         if (!o.triA && !o.triB && !o.min_tile64 && !o.ksplit && !o.symsum && wg64 <= 128 && K >= 2048 && A.nb2 == 1 && B.nb2 == 1 &&
             C.nb2 == 1) {
             int splits = (int)std::min<int64_t>(512 / wg64, K / 256);
@@ -785,7 +1248,7 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             splits = (K + Kc - 1) / Kc;
             const size_t bytes = (size_t)batch * splits * M * N * sizeof(T);
             // (an unaligned or odd-sized product goes without the split where the caller gave no memory for it)
-            if (splits >= 2 && bytes <= SPLITK_MAX_BYTES && ((!f.rag && !o.split_if_room) || arena_room(bytes))) {
+            if (splits >= 2 && bytes <= SPLITK_MAX_BYTES && ((K % 16 == 0 && a_ok && b_ok && !o.split_if_room) || arena_room(bytes))) {
                 ArenaFrame frame;
                 void *buf = nullptr;
                 LA_TRY(arena_take(bytes, &buf));
@@ -796,7 +1259,10 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
                 ps.maskC = o.maskC;  // tiles beyond the kept triangle are not computed (nor read back)
                 ps.ksplit = splits;
                 ps.ktotal = K;
-                launch_tiles<T, 64, 64, 16, 2>(f, As, Bs, Ps, batch * splits, M, N, Kc, T(1), T(0), ps, st);
+                if (f.rag)
+                    launch_staged<T, 64, 64, 16, 2>(f, As, Bs, Ps, batch * splits, M, N, Kc, T(1), T(0), ps, st);
+                else
+                    launch_tiles<T, 64, 64, 128>(f, As, Bs, Ps, batch * splits, M, N, Kc, T(1), T(0), ps, st);
                 LA_TRY(launch_check("gemm_splitk"));
                 const int64_t total = batch * mn;
                 LA_LAUNCH((k_splitk_reduce<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
@@ -804,46 +1270,44 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
                 return launch_check("splitk_reduce");
             }
         }
-        // No 128 x 128 tiles where they stick out of C by a quarter more than tiles of 64 do: 130 products of 129 x 129 x 129
-        // 79 -> 41 us in fp64, 40 -> 22 in fp32, 64 of 320 x 320 x 320 146 -> 90 and 75 -> 47, 300 times trmm of 131 with 131
-        // vectors 135 -> 68 and 73 -> 35; 383 x 383 (144 tiles against 180 quarters) is the same in both.
-        const bool padded = (int64_t)((M + 127) / 128) * ((N + 127) / 128) * 16 > (int64_t)((M + 63) / 64) * ((N + 63) / 64) * 5;
-        int e;
-        if (o.triA | o.triB) {
-            // Triangular operands make the K range, hence the time, of a tile vary along the tile
-            // list (heaviest first): the 512 workgroup slots only fill evenly if there are several
-            // rounds of tiles, so take the largest tile that still gives 1024 workgroups.
-            e = wg128 >= 1024 && !padded ? 128 : ((wg64 >= 1024 || !quarters || o.min_tile64) ? 64 : 32);
+        // ragged: K slabs of 64, or 32, unless much of the last one would be empty
+        const bool k64 = K >= 128 || (K & 63) == 0 || (K & 63) > 32;
+        int e = o.min_tile64 ? 64 : 32;
+        if (f.rag) {
+            e = staged_edge(wgs, batch, M, N, K, k64, o);
         } else {
-            // Equal tiles: big tiles once they (nearly) fill the 512 workgroup slots (496 tiles, 3952 x 2048 x 2000, fp64 598 -> 555
-            // us and fp32 310 -> 296 against 64 x 64 tiles, 480 the same, 448 262 -> 291; a compute unit with one workgroup waits for
-            // its loads: a sparse GP with 300 tiles of 128 1497 -> 1429 us in 64 x 64 tiles, factor + gradient of
-            // n = 5500 with 432 of them 7737 -> 7511, fp64; 8192 with 192 to 256 of them in several products 16.84 -> 16.79 ms,
-            // in fp32 10.07 -> 9.81), quarter tiles while 64 x 64 tiles
-            // would fill the 512 workgroup slots less than twice -- with so few rounds the last one runs
-            // part empty (32 x 384 x 384 lower triangle, K = 128: 672 tiles of 64, 38 -> 30 us; potrf of
-            // 32 x 512 x 512 0.245 -> 0.231 ms, of 4 x 2048 x 2048 1.14 -> 1.10, 8192 x 8192 with 512
-            // vectors trsm 1.19 -> 1.12 ms).  In fp64 nearly one big tile for each of the 256 compute units is as good as many
-            // rounds, unless k is contiguous in both operands (us, 64 x 64 -> 128 x 128: 2048^3 355 -> 326 and with both k
-            // contiguous 309 -> 338, 8192 x 512 x 1024 181 -> 167, 2304 x 1792 x 512, 252 tiles, 101 -> 88; 7168 x 512 x 1024, 224
-            // tiles, 163 -> 168, 2048 x 1536 x 1024, 192 tiles, 144 -> 167; a batch of 13 x 512^3, 208 tiles, 98 -> 88).
-            const int64_t t128 = o.maskC ? wg128 : (int64_t)((M + 127) / 128) * ((N + 127) / 128) * batch;
-            // Up to K = 32 writing C is most of the work, and more, smaller workgroups overlap it with their loads (us, 128 x 128 ->
-            // 64 x 64: 83 items of 1033 x 251, K = 2, fp64 48 -> 39, K = 32 72 -> 58, fp32 28 -> 25 and 37 -> 32; 64 x 512 x 512, K = 16,
-            // 32 -> 30 and 22 -> 18; from K = 33 on it depends: 64 x 512 x 512 51 -> 64, 83 x 1033 x 251 89 -> 86).
-            const bool big = K > 32 && (o.maskC ? (M >= 2048 && N >= 2048) : (M >= 128 && N >= 128));
-            const bool one_round = sizeof(T) == 8 && !f.rag && !(f.akf && f.bkf) && !o.maskC && t128 <= 256 &&
-                                   t128 > (batch > 1 ? 192 : 224);
-            // Two nearly full rounds of 64 x 64 tiles are better than quarter tiles where the chunks are ragged, which costs address arithmetic
-            // per load, and the quarters save no padding (b items of 61 x 174, K = 147, us, 32 x 32 -> 64 x 64: b = 331, 993 tiles, fp64
-            // 60 -> 44, fp32 29 -> 22; with one round and a half the products of potri's backward rule, 30 x 297 x 297, 220 -> 232; 26 x 2478 x 22, 1014
-            // tiles that the quarters halve, fp32 36 -> 54).
-            const bool two_rounds = f.rag && !o.maskC && !o.symsum && wg64 >= 960 &&
-                                    (int64_t)((M + 63) / 64) * ((N + 63) / 64) * 4 == (int64_t)((M + 31) / 32) * ((N + 31) / 32);
-            e = ((t128 >= (o.maskC ? 512 : 480) || one_round) && big && !padded) ? 128 : ((wg64 < 1024 && quarters && !o.min_tile64 && !two_rounds) ? 32 : 64);
+            double least = 0;
+            for (int c = e, first = c; c <= (o.symsum ? 64 : 128); c *= 2) {
+                const double cost = tile_cost<T>(c, wgs(c), K, o);
+                if (c == first || cost < least) {
+                    e = c;
+                    least = cost;
+                }
+            }
         }
-        if (o.symsum && e == 128)  // (the form that stores both triangles has tiles up to 64 only)
-            e = 64;
+        auto launch = [&](View<const T> A_, View<T> C_, int m, int n, GemmOpts op) {
+            if (f.rag) {
+                if (e == 128)
+                    launch_staged<T, 128, 128, 16, 2>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
+                else if (e == 32)
+                    launch_staged<T, 32, 32, 64, 1>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
+                else if (k64)  // (slabs of 64 in one buffer hold two workgroups a compute unit, of 32 four)
+                    launch_staged<T, 64, 64, 32, 1>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
+                else
+                    launch_staged<T, 64, 64, 16, 2>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
+            } else if (e == 128) {
+                launch_tiles<T, 128, 128, 128>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
+            } else if (e == 32) {
+                launch_tiles<T, 32, 32, 256>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
+            } else if (sizeof(T) == 4 && K <= 128 && wg64 > 1024) {
+                // one LDS buffer: short products of many tiles are bound by C, more workgroups a compute unit (fp32, K <= 64, above 2048 tiles:
+                // 4 to 6 % faster on average; above K = 128 up to 5 % slower)
+                launch_tiles<T, 64, 64, 128, sizeof(T) == 4 ? 1 : 2>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
+            } else {
+                launch_tiles<T, 64, 64, 128>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
+            }
+            return launch_check("gemm");
+        };
         if (e >= 64 && o.maskC == 1 && !o.triA && !o.triB && !o.halfDiag && !o.shells && !o.min_tile64 && M == N &&
             M % e == 0 && A.nb2 == 1 && B.nb2 == 1 && C.nb2 == 1) {
             // Lower triangle in e x e tiles: T (T + 1) / 2 of them.  When that is a few tiles more than
@@ -855,31 +1319,12 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
             if (batch == 1 && per > 512 && spill > 0 && spill <= 64 && (below == 0 || below > 256)) {
                 GemmOpts lo = o;
                 lo.maskC = 3;  // tiles with tn <= tm of the view that starts e rows down, nothing masked inside
-                View<const T> A1 = A.sub(e, 0);
-                View<T> C1 = C.sub(e, 0);
-                if (e == 128)
-                    launch_tiles<T, 128, 128, 16, 2>(f, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
-                else if (k64)
-                    launch_tiles<T, 64, 64, 32, 1>(f, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
-                else
-                    launch_tiles<T, 64, 64, 16, 2>(f, A1, B, C1, batch, M - e, N - e, K, alpha, beta, lo, st);
-                LA_TRY(launch_check("gemm"));
+                LA_TRY(launch(A.sub(e, 0), C.sub(e, 0), M - e, N - e, lo));
                 return launch_gemm<T>(A.level2((int64_t)e * A.rs, (int)Tt), B.level2((int64_t)e * B.cs, (int)Tt),
                                       C.level2((int64_t)e * (C.rs + C.cs), (int)Tt), batch * Tt, e, e, K, alpha, beta, o, st);
             }
         }
-        if (e == 32 && !k64)
-            f.rag = true;
-        if (e == 128)
-            launch_tiles<T, 128, 128, 16, 2>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
-        else if (e == 32)
-            launch_tiles<T, 32, 32, 64, 1>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
-        else if (k64)  // (slabs of 64 in one buffer hold two workgroups a compute unit, of 32 four: 32 matrices of
-                       // n = 512, fp64, factor + gradient 593 -> 570 us; slabs of 16 in two buffers 590)
-            launch_tiles<T, 64, 64, 32, 1>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
-        else
-            launch_tiles<T, 64, 64, 16, 2>(f, A, B, C, batch, M, N, K, alpha, beta, o, st);
-        return launch_check("gemm");
+        return launch(A, C, M, N, o);
     }
 }
 
