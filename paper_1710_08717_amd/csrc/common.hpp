@@ -582,6 +582,7 @@ struct GemmOpts {
                          // A^T B's, so the second pass only swaps the two base pointers -- and store every entry with its
                          // mirror image.  2: C = alpha A B + beta C for an A B that is symmetric (same strides) and a C of
                          // which the lower triangle is read: one pass, stored in the same way.  maskC is not used.
+    int padA = 0, padB = 0;  // 1: rows of the operand may be read up to the next multiple of 16 bytes, whatever is there (a padded working copy)
     int split_if_room = 0;  // 1: a long inner dimension is split only where the workspace has room for the partial sums
 };
 template <typename T>

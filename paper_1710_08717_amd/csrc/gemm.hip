@@ -208,17 +208,17 @@ struct Copier {
         next = reinterpret_cast<const char *>(src + o0 * so + k0 * sk);
         step = S::BK * sk * (int64_t)sizeof(T);
     }
-    // no: rows of the operand, a multiple of VW where those are contiguous, as is every o0
+    // no: rows of the operand; where those are contiguous, up to a multiple of VW exist, or may be read (GemmOpts::padA)
     __device__ __forceinline__ void init(int64_t so, int64_t sk, int o0, int no, int w, int lane)
     {
 #pragma unroll
         for (int i = 0; i < S::NCH; ++i) {
             int o, k;
             S::coords(i, w, lane, o, k);
-            off[i] = (uint32_t)(min(o, (KF ? no - 1 : no - VW) - o0) * so + k * sk) * (uint32_t)sizeof(T);
+            off[i] = (uint32_t)(min(o, (KF ? no - 1 : (no - 1) / VW * VW) - o0) * so + k * sk) * (uint32_t)sizeof(T);
         }
     }
-    // k0, nk: the slab's first k and the operand's end, both multiples of VW where k is contiguous
+    // k0, nk: the slab's first k, a multiple of VW, and the operand's end, the same for k as above
     __device__ __forceinline__ void fetch(T *lds, int64_t sk, int k0, int nk, int w, int lane)
     {
         const char *base = next;
@@ -232,7 +232,7 @@ struct Copier {
             for (int i = 0; i < S::NCH; ++i) {
                 int o, k;
                 S::coords(i, w, lane, o, k);
-                const int back = max(k - (nk - (KF ? VW : 1) - k0), 0);
+                const int back = max(k - ((KF ? (nk - 1) / VW * VW : nk - 1) - k0), 0);
                 load_lds16(base, off[i] - (uint32_t)(back * sk) * (uint32_t)sizeof(T), lds + (i * 4 + w) * 64 * VW);
             }
         }
@@ -1071,9 +1071,9 @@ static dim3 gemm_grid(int64_t batch, int M, int N, GemmOpts &o, int &tiles_m, in
     tiles_n = (N + BN - 1) / BN;
     o.order = pick_order(o, tiles_m, tiles_n);
     const int64_t per = tile_count(o.order, tiles_m, tiles_n);
-    // (an XCD takes whole items: not where that leaves some with an item more than others, 14 slices of 500 x 500 x 9568 in the sparse GP
-    // 90 -> 78 us)
-    o.xcd_batch = (batch >= 8 && per > 1 && (8 - (batch & 7)) % 8 * 8 <= batch) ? 1 : 0;
+    // (an XCD takes whole items: not the slices of a split K range where that leaves some with a slice more than others, 14 of 500 x 500 x 9568 in
+    // the sparse GP 90 -> 78 us)
+    o.xcd_batch = (batch >= 8 && per > 1 && (o.ksplit <= 1 || (8 - (batch & 7)) % 8 * 8 <= batch)) ? 1 : 0;
     return dim3((unsigned)(o.xcd_batch ? 8 * ((batch + 7) / 8) * per : per * batch));
 }
 
@@ -1216,6 +1216,8 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
         t.shells = o.shells;
         t.min_tile64 = o.min_tile64;
         t.split_if_room = o.split_if_room;
+        t.padA = o.padB;
+        t.padB = o.padA;
         return launch_gemm<T>(B.t(), A.t(), C.t(), batch, N, M, K, alpha, beta, t, st);
     }
     constexpr int VW = Mfma<T>::VW;
@@ -1224,9 +1226,9 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
     f.bkf = (B.rs == 1);
     if ((!f.akf && A.rs != 1) || (!f.bkf && B.cs != 1))
         return LA_ERR_UNSUPPORTED;  // (no operator of the library builds such a view)
-    const bool a_ok = f.akf ? aligned16<T>(A, A.rs) : (aligned16<T>(A, A.cs) && M % VW == 0);
-    const bool b_ok = f.bkf ? aligned16<T>(B, B.cs) : (aligned16<T>(B, B.rs) && N % VW == 0);
-    f.rag = !(a_ok && b_ok && (K % VW == 0 || !(f.akf || f.bkf)));
+    const bool a_ok = aligned16<T>(A, f.akf ? A.rs : A.cs) && (o.padA || (f.akf ? K : M) % VW == 0);
+    const bool b_ok = aligned16<T>(B, f.bkf ? B.cs : B.rs) && (o.padB || (f.bkf ? K : N) % VW == 0);
+    f.rag = !(a_ok && b_ok);
     const int64_t longest = std::max(std::max(std::max(A.rs, A.cs), std::max(B.rs, B.cs)), std::max(C.rs, C.cs));
     if (longest >= (int64_t)1 << 22)  // (k_gemm's offsets inside a tile have 32 bits)
         f.rag = true;
@@ -1297,6 +1299,10 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
                     launch_staged<T, 64, 64, 16, 2>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
             } else if (e == 128) {
                 launch_tiles<T, 128, 128, 128>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
+            } else if (sizeof(T) == 4 && e == 32 && wgs(32) > 1024) {
+                // one LDS buffer: eight workgroups a compute unit instead of five (1000 to 4500 tiles, 64 < K <= 512, 4 to 9 % faster, fewer tiles 1 to
+                // 5 % slower)
+                launch_tiles<T, 32, 32, 256, sizeof(T) == 4 ? 1 : 2>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
             } else if (e == 32) {
                 launch_tiles<T, 32, 32, 256>(f, A_, B, C_, batch, m, n, K, alpha, beta, op, st);
             } else if (sizeof(T) == 4 && K <= 128 && wg64 > 1024) {

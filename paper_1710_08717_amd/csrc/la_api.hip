@@ -79,15 +79,24 @@ static la_status sizing_pass(F &&op, size_t *peak, bool needed_only = false)
 }
 
 template <typename T>
-static la_status scratch_views(int64_t batch, int n, int count, View<T> *out)
+static la_status scratch_views(int64_t batch, int n, int count, View<T> *out, int ld = 0)
 {
-    // `count` row-major n x n matrices per batch item, each batch-contiguous
-    const int64_t nn = (int64_t)n * n;
+    // `count` row-major n x n matrices per batch item, each batch-contiguous, rows ld apart (0: n)
+    ld = ld ? ld : n;
+    const int64_t nn = (int64_t)n * ld;
     void *p = nullptr;
     LA_TRY(arena_take((size_t)count * batch * nn * sizeof(T), &p));
     for (int c = 0; c < count; ++c)
-        out[c] = View<T>{(T *)p + (int64_t)c * batch * nn, nn, n, 1};
+        out[c] = View<T>{(T *)p + (int64_t)c * batch * nn, nn, ld, 1};
     return LA_OK;
+}
+
+// Rows of n elements, padded to whole 16-byte chunks.
+template <typename T>
+static inline int padded(int n)
+{
+    constexpr int VW = 16 / (int)sizeof(T);
+    return (n + VW - 1) / VW * VW;
 }
 
 // Rough time, per unit of K, of the lower-triangle update C -= P P^T on n2 rows: the product
@@ -138,23 +147,24 @@ static inline View<const T> cv(View<T> v)
 //     inv [A 0; C D] = [A^-1 0; -D^-1 C A^-1, D^-1]
 // with all pairs of one level in one batched GEMM pair.  Stops when blocks of `upto` are
 // inverted (upto >= n: the whole matrix).  Tmp: scratch of at least n*n/2 per item.
+// pad: Inv's rows are padded (GemmOpts::padA), with 2 Lam's too.
 // ---------------------------------------------------------------------------------
 template <typename T>
 static la_status inverse_merge(View<const T> Lam, View<T> Inv, View<T> Tmp, int64_t batch, int n, int upto,
-                               hipStream_t st);
+                               hipStream_t st, int pad = 0);
 
 template <typename T>
 static la_status inverse_build(View<const T> Lam, View<T> Inv, View<T> Tmp, int64_t batch, int n, int upto,
-                               hipStream_t st)
+                               hipStream_t st, int pad = 0)
 {
     LA_TRY(launch_tri_inverse128<T>(Lam, Inv, batch, n, st));
-    return inverse_merge<T>(Lam, Inv, Tmp, batch, n, upto, st);
+    return inverse_merge<T>(Lam, Inv, Tmp, batch, n, upto, st, pad);
 }
 
 // The merge levels of inverse_build alone: Inv already holds the inverses of the 128 x 128 diagonal blocks.
 template <typename T>
 static la_status inverse_merge(View<const T> Lam, View<T> Inv, View<T> Tmp, int64_t batch, int n, int upto,
-                               hipStream_t st)
+                               hipStream_t st, int pad)
 {
     for (int64_t h = 2 * NB; h < upto && h < n; h *= 2) {
         const int nfull = (int)(n / (2 * h));                       // pairs whose right block is a full h
@@ -175,6 +185,8 @@ static la_status inverse_merge(View<const T> Lam, View<T> Inv, View<T> Tmp, int6
             o1.reverse = 1;  //   so the last rows go first
             o2.triB = 1;     // A^-1 is lower triangular: the K range shrinks with the tile column
                              //   (the launcher enumerates such tiles column by column)
+            o1.padA = pad != 0;
+            o1.padB = pad == 2;
             LA_TRY(launch_gemm<T>(D, C, Tv, batch * cnt, mr, (int)h, mr, T(1), T(0), o1, st));
             LA_TRY(launch_gemm<T>(cv(Tv), A, O, batch * cnt, mr, (int)h, (int)h, T(-1), T(0), o2, st));
         }
@@ -191,7 +203,7 @@ static la_status inverse_merge(View<const T> Lam, View<T> Inv, View<T> Tmp, int6
 // ---------------------------------------------------------------------------------
 template <typename T>
 static la_status potrf_right_looking(View<T> Wk, View<T> L, int32_t *info, int off, int64_t batch, int n, View<T> Inv,
-                                     bool need_inv, hipStream_t st)
+                                     bool need_inv, bool pad, hipStream_t st)
 {
     constexpr int P = 2 * NB;
     for (int o = 0; o < n; o += P) {
@@ -202,10 +214,10 @@ static la_status potrf_right_looking(View<T> Wk, View<T> L, int32_t *info, int o
         if (r == 0)
             break;
         View<T> L21 = L.sub(o + nb, o);
-        GemmOpts op;
+        GemmOpts op, ou;
+        op.padA = op.padB = ou.padA = ou.padB = pad;
         op.triB = 2;  // Li11^T is upper triangular
         LA_TRY(launch_gemm<T>(cv(Wk).sub(o + nb, o), cv(Inv).sub(o, o).t(), L21, batch, r, nb, nb, T(1), T(0), op, st));
-        GemmOpts ou;
         ou.maskC = 1;
         LA_TRY(launch_gemm<T>(cv(L21), cv(L21).t(), Wk.sub(o + nb, o + nb), batch, r, r, nb, T(-1), T(1), ou, st));
     }
@@ -231,7 +243,7 @@ static la_status potrf_right_looking(View<T> Wk, View<T> L, int32_t *info, int o
 // ---------------------------------------------------------------------------------
 template <typename T>
 static la_status potrf_rec(View<T> Wk, View<T> L, int32_t *info, int off, int64_t batch, int n, View<T> Inv,
-                           View<T> Tmp, bool need_inv, hipStream_t st)
+                           View<T> Tmp, bool need_inv, bool pad, hipStream_t st)
 {
     if (n <= 2 * NB)  // factor and inverse in one launch
         return launch_potrf_leaf16<T>(cv(Wk), L, need_inv ? Inv : View<T>{nullptr, 0, 0, 0}, info, off, batch, n, false, st);
@@ -239,23 +251,22 @@ static la_status potrf_rec(View<T> Wk, View<T> L, int32_t *info, int off, int64_
     // of n = 2048 0.95 -> 0.77 ms, 3000 1.78 -> 1.38, 4096 2.58 -> 2.19, 8192 8.62 -> 7.89 (fp64); with many
     // matrices in the batch the short products of the panels stop paying (32 x 1024: 0.91 -> 0.93).
     if (n <= 2304 && (double)batch * n * n < 24e6) {
-        LA_TRY(potrf_right_looking<T>(Wk, L, info, off, batch, n, Inv, need_inv, st));
-        return need_inv ? inverse_merge<T>(cv(L), Inv, Tmp, batch, n, n, st) : LA_OK;
+        LA_TRY(potrf_right_looking<T>(Wk, L, info, off, batch, n, Inv, need_inv, pad, st));
+        return need_inv ? inverse_merge<T>(cv(L), Inv, Tmp, batch, n, n, st, pad ? 2 : 0) : LA_OK;
     }
     const int n1 = split_point(n), n2 = n - n1;
     View<T> L21 = L.sub(n1, 0), Wk22 = Wk.sub(n1, n1);
-    LA_TRY(potrf_rec<T>(Wk, L, info, off, batch, n1, Inv, Tmp, true, st));
-    GemmOpts op;
+    LA_TRY(potrf_rec<T>(Wk, L, info, off, batch, n1, Inv, Tmp, true, pad, st));
+    GemmOpts op, ou, o1, o2;
+    op.padA = op.padB = ou.padA = ou.padB = o1.padA = o1.padB = o2.padA = o2.padB = pad;
     op.triB = 2;  // Li11^T is upper triangular
     LA_TRY(launch_gemm<T>(cv(Wk).sub(n1, 0), cv(Inv).t(), L21, batch, n2, n1, n1, T(1), T(0), op, st));
-    GemmOpts ou;
     ou.maskC = 1;  // trailing update of the lower triangle: A22 -= L21 L21^T
     LA_TRY(launch_gemm<T>(cv(L21), cv(L21).t(), Wk22, batch, n2, n2, n1, T(-1), T(1), ou, st));
-    LA_TRY(potrf_rec<T>(Wk22, L.sub(n1, n1), info, off + n1, batch, n2, Inv.sub(n1, n1), Tmp, need_inv, st));
+    LA_TRY(potrf_rec<T>(Wk22, L.sub(n1, n1), info, off + n1, batch, n2, Inv.sub(n1, n1), Tmp, need_inv, pad, st));
     if (!need_inv)
         return LA_OK;
     View<T> T1 = Inv.sub(0, n1).t();  // n2 x n1 temporary in the upper-right block
-    GemmOpts o1, o2;
     o1.triB = 1;  // Li11 is lower triangular: the K range shrinks with the tile column
     LA_TRY(launch_gemm<T>(cv(L21), cv(Inv), T1, batch, n2, n1, n1, T(1), T(0), o1, st));
     o2.triA = 1;  // Li22 is lower triangular: the K range grows with the tile row
@@ -308,15 +319,16 @@ static int sweep_block(int64_t batch, int n, size_t elem)
 // n0 x n0 blocks, in which the merges' temporary lives before.
 static int64_t sweep_scratch(int n0, int64_t cols)
 {
-    return cols * n0 + cols + std::max(2 * (int64_t)n0 * n0, cols * n0 / 4);
+    return cols * n0 + (cols + 15) / 16 * 16 + (std::max(2 * (int64_t)n0 * n0, cols * n0 / 4) + 15) / 16 * 16;  // (every part starts a 16-byte chunk)
 }
 
 // W = 1/2 (Li^T (P + P^T) Li) for lower triangular Li and P (what lies above their diagonals is not read), both triangles
 // of W, exactly symmetric.  X: scratch; W may be P.
 template <typename T>
-static la_status congruence(View<const T> Li, View<const T> P, View<T> X, View<T> W, int64_t batch, int n, hipStream_t st)
+static la_status congruence(View<const T> Li, View<const T> P, View<T> X, View<T> W, int64_t batch, int n, hipStream_t st, bool pad = false)
 {
-    GemmOpts oz;
+    GemmOpts oz, ow;
+    oz.padA = oz.padB = ow.padA = ow.padB = pad;  // the rows of Li, P and X are padded
     oz.triA = 1;
     oz.triB = 1;
     oz.maskC = 1;
@@ -324,7 +336,6 @@ static la_status congruence(View<const T> Li, View<const T> P, View<T> X, View<T
     LA_TRY(launch_gemm<T>(P, Li, X, batch, n, n, n, T(1), T(0), oz, st));
     // 1/2 (Li^T Z + Z^T Li) in one launch: the tiles on and below the diagonal accumulate both products (K range from the
     // tile's first row on) and write every entry with its mirror image
-    GemmOpts ow;
     ow.triA = 2;
     ow.triB = 1;
     ow.symsum = 1;
@@ -349,10 +360,15 @@ static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, in
     if (n0 > 0 || (n >= SWEEP_MIN_N && !arena_room((size_t)(2 * batch * n * n) * sizeof(T))))
         return backward_sweep<T>(Lam, G, W, batch, n, n0 > 0 ? n0 : 256, aliased, st);
     ArenaFrame frame;
-    View<T> sc[2];
-    LA_TRY(scratch_views<T>(batch, n, 2, sc));
+    // (with room for a third square: all three with rows of whole 16-byte chunks, so that two of the three products run on aligned operands)
+    View<T> sc[2], P = W;
+    const int ld = padded<T>(n);
+    const bool pad = ld != n && arena_room((size_t)3 * batch * n * ld * sizeof(T));
+    LA_TRY(scratch_views<T>(batch, n, 2, sc, pad ? ld : n));
+    if (pad)
+        LA_TRY(scratch_views<T>(batch, n, 1, &P, ld));
     View<T> Li = sc[0], X = sc[1];
-    LA_TRY(inverse_build<T>(Lam, Li, X, batch, n, n, st));
+    LA_TRY(inverse_build<T>(Lam, Li, X, batch, n, n, st, pad));
     View<const T> Gs = G;
     if (aliased) {  // Abar overwrites Lbar: keep a copy of its lower triangle
         LA_TRY(launch_copy<T>(G, X, batch, n, n, T(1), 1, st));
@@ -363,8 +379,8 @@ static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, in
     o.triB = 1;
     o.maskC = 1;
     o.halfDiag = 1;
-    LA_TRY(launch_gemm<T>(Lam.t(), Gs, W, batch, n, n, n, T(1), T(0), o, st));
-    return congruence<T>(cv(Li), cv(W), X, W, batch, n, st);
+    LA_TRY(launch_gemm<T>(Lam.t(), Gs, P, batch, n, n, n, T(1), T(0), o, st));
+    return congruence<T>(cv(Li), cv(P), X, W, batch, n, st, pad);
 }
 
 template <typename T>
@@ -433,7 +449,7 @@ static la_status sweep_column(View<const T> Lam, View<const T> inv, int c0, View
         op.maskC = 1;
         op.halfDiag = 1;
         LA_TRY(launch_gemm<T>(L11.t(), G11, X, batch, w, w, w, T(1), T(0), op, st));
-        LA_TRY(congruence<T>(inv.sub(o - c0, o - c0), cv(X), Y, W11, batch, w, st));
+        LA_TRY(congruence<T>(inv.sub(o - c0, o - c0), cv(X), Y, W11, batch, w, st, true));  // (n0 columns each)
     }
     return r > 0 ? launch_copy<T>(cv(W21).t(), W12, batch, w, r, T(1), 0, st) : LA_OK;
 }
@@ -465,14 +481,14 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
     LA_TRY(arena_take((size_t)(batch * item) * sizeof(T), &p));
     if (!arena_room(0))  // (a sizing pass for the least: the products below take none they need)
         return LA_OK;
-    View<T> Li{(T *)p, item, n0, 1}, X{Li.p + (int64_t)cols * n0 + cols, item, n0, 1}, Y{X.p + (int64_t)n0 * n0, item, n0, 1};
+    View<T> Li{(T *)p, item, n0, 1}, X{Li.p + (int64_t)cols * n0 + (cols + 15) / 16 * 16, item, n0, 1}, Y{X.p + (int64_t)n0 * n0, item, n0, 1};
     const int wide = n >= SWEEP_WIDE_N && batch <= SWEEP_WIDE_BATCH && cols == n ? 2 * n0 : n0;
     for (int o = (n - 1) / wide * wide; o >= 0; o -= wide) {
         const int q = n - o < wide ? n : o + wide;
         const int c0 = o / cols * cols, cc = n - c0 < cols ? n - c0 : cols;  // the columns whose inverses are there
         if (q == c0 + cc) {
             LA_TRY(launch_tri_inverse128<T>(Lam.sub(c0, c0), Li, batch, cc, st));
-            LA_TRY(inverse_merge<T>(Lam.sub(c0, c0), Li, X, batch, cc, n0, st));
+            LA_TRY(inverse_merge<T>(Lam.sub(c0, c0), Li, X, batch, cc, n0, st, 1));
         }
         LA_TRY(sweep_column<T>(Lam, cv(Li), c0, G, W, X, Y, batch, o, q, n, n0, aliased, st));
     }
@@ -520,11 +536,23 @@ static la_status potrf_t(int lower, int64_t batch, int n, const void *A, void *L
     // (not needed where the whole matrix is factored panel by panel without merged inverses)
     const bool outer_panels = (batch == 1 && n >= 4096) || n >= 8192;
     const bool merges = outer_panels || !(n <= 2304 && (double)batch * n * n < 24e6);
-    View<T> sc[3];
-    LA_TRY(scratch_views<T>(batch, n, merges ? 3 : 2, sc));
+    View<T> sc[3], out = Lv;
+    // Rows that are no whole number of 16-byte chunks: where the workspace has room for one more square, the factor is built in one with
+    // padded rows as well, so that every product runs on aligned operands, and copied into place at the end.  One more pass over the matrix, which
+    // the products of smaller ones do not make up for (step with one matrix, us: n = 3001, fp64 2270 -> 2190, n = 7423 12500 -> 11860, n = 986, fp32 440 -> 432;
+    // 24 x 333^2, fp32 208 -> 214; several matrices, fp64 4 x 1001^2 608 -> 586, fp32 419 -> 424, 3 x 2049^2 1213 -> 1249).
+    const int ld = padded<T>(n), squares = merges ? 3 : 2;
+    const bool pad = ld != n && n >= 800 && (sizeof(T) == 8 || batch == 1) && arena_room((size_t)(squares + 1) * batch * n * ld * sizeof(T));
+    LA_TRY(scratch_views<T>(batch, n, squares, sc, pad ? ld : n));
     if (!merges)
         sc[2] = sc[1];  // never used
-    LA_TRY(launch_tril_split<T>(Av, sc[1], Lv, batch, n, st));  // zeros above the diagonal of L
+    if (pad) {
+        LA_TRY(scratch_views<T>(batch, n, 1, &Lv, ld));
+        LA_TRY(launch_copy<T>(Av, sc[1], batch, n, n, T(1), 2, st));
+    } else {
+        LA_TRY(launch_tril_split<T>(Av, sc[1], Lv, batch, n, st));  // zeros above the diagonal of L
+    }
+    auto finish = [&]() { return pad ? launch_copy<T>(cv(Lv), out, batch, n, n, T(1), 1, st) : LA_OK; };
     // Large matrices: right-looking over panels of 2048 columns -- the panel's diagonal block by the
     // recursion below (which factors it 128 columns at a time and merges its inverse), one product
     // for the rows under it, one for the trailing triangle (K = 2048).  Against halving all the way
@@ -536,20 +564,22 @@ static la_status potrf_t(int lower, int64_t batch, int n, const void *A, void *L
         View<T> Wk = sc[1], Inv = sc[0];
         for (int o = 0; o < n; o += outer) {
             const int w = n - o < outer ? n - o : outer, r = n - o - w;
-            LA_TRY(potrf_rec<T>(Wk.sub(o, o), Lv.sub(o, o), info, o, batch, w, Inv.sub(o, o), sc[2], r > 0, st));
+            LA_TRY(potrf_rec<T>(Wk.sub(o, o), Lv.sub(o, o), info, o, batch, w, Inv.sub(o, o), sc[2], r > 0, pad, st));
             if (r == 0)
                 break;
             View<T> L21 = Lv.sub(o + w, o);
-            GemmOpts op;
+            GemmOpts op, ou;
+            op.padA = op.padB = ou.padA = ou.padB = pad;
+            ou.split_if_room = pad;  // (the copies had the first pick of the workspace)
             op.triB = 2;  // Li^T is upper triangular
             LA_TRY(launch_gemm<T>(cv(Wk).sub(o + w, o), cv(Inv).sub(o, o).t(), L21, batch, r, w, w, T(1), T(0), op, st));
-            GemmOpts ou;
             ou.maskC = 1;
             LA_TRY(launch_gemm<T>(cv(L21), cv(L21).t(), Wk.sub(o + w, o + w), batch, r, r, w, T(-1), T(1), ou, st));
         }
-        return LA_OK;
+        return finish();
     }
-    return potrf_rec<T>(sc[1], Lv, info, 0, batch, n, sc[0], sc[2], false, st);
+    LA_TRY(potrf_rec<T>(sc[1], Lv, info, 0, batch, n, sc[0], sc[2], false, pad, st));
+    return finish();
 }
 
 // Edge of the diagonal blocks of a solve with m vectors that get an explicit inverse; block

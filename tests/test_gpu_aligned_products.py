@@ -65,3 +65,38 @@ def test_syrk_symmetric(dt, b, n, k):
         ref = torch.matmul(a, a.mT.contiguous())
         err = (C.double() - ref).flatten(1).norm(dim=1) / ref.flatten(1).norm(dim=1)
         assert float(err.max()) <= 8 * k ** 0.5 * _eps(dt)
+
+
+@pytest.mark.parametrize("dt,b,n", [(torch.float64, 1, 801), (torch.float64, 2, 1001), (torch.float32, 1, 1026), (torch.float32, 1, 803),
+                                    (torch.float64, 3, 333), (torch.float32, 2, 131)])
+@pytest.mark.parametrize("lower", [True, False])
+def test_padded_working_copies(dt, b, n, lower):
+    """Odd rows: factor and gradient with the whole workspace (working copies with padded rows) and without room for those."""
+    rng = np.random.default_rng(n)
+    X = _rand(rng, dt, b, n, n).double()
+    A64 = torch.matmul(X, X.mT.contiguous()) / n + torch.eye(n, device="cuda", dtype=torch.float64)
+    A = A64.to(dt).contiguous()
+    G = _rand(rng, dt, b, n, n)
+    lib = la.load()
+    code, es = (0, 4) if dt == torch.float32 else (1, 8)
+    pad = (n + 16 // es - 1) // (16 // es) * (16 // es)
+    ref = torch.linalg.cholesky(A.double())
+    Gl = (G if lower else G.mT).double().tril()
+    P = torch.matmul(ref.mT.contiguous(), Gl).tril()
+    P = P - 0.5 * torch.diag_embed(P.diagonal(dim1=1, dim2=2))
+    Z = torch.linalg.solve_triangular(ref.mT, P, upper=True)
+    W = torch.linalg.solve_triangular(ref, Z, upper=False, left=False)
+    Ab = 0.5 * (W + W.mT)
+    tol = 2e-4 if dt == torch.float32 else 1e-10
+    for short in (0, 1):
+        def ws(op):
+            full = lib.la_workspace_bytes(op, code, b, n, 0, 0)
+            less = short * b * n * pad * es if op == 1 or n >= 800 else 0  # (the factorisation of smaller ones has no such copy)
+            return torch.empty(full - less, dtype=torch.uint8, device="cuda") if full else None
+        L = la.potrf(A, lower=lower, workspace=ws(0))
+        t = L if lower else L.mT
+        assert float(t.triu(1).abs().max()) == 0.0
+        assert float(((t.double() - ref).flatten(1).norm(dim=1) / ref.flatten(1).norm(dim=1)).max()) <= tol
+        B = la.potrf_backward(L, G, lower=lower, workspace=ws(1))
+        assert torch.equal(B, B.mT)
+        assert float(((B.double() - Ab).flatten(1).norm(dim=1) / Ab.flatten(1).norm(dim=1)).max()) <= tol
