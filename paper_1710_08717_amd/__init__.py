@@ -2,8 +2,8 @@
 the potrf backward expression) of arXiv 1710.08717, section 4.2.
 
 The work is done by hand-written HIP kernels behind the C ABI declared in ``include/la.h``;
-this package is only a thin ctypes binding that marshals ``torch`` device tensors
-(pointer + stream) into those calls.  There is no CPU or PyTorch fallback: if the shared
+this package is only a thin binding (``csrc/host_call.cpp``, ctypes for the rest) that marshals
+``torch`` device tensors (pointer + stream) into those calls.  There is no CPU or PyTorch fallback: if the shared
 library is missing, importing the binding raises.
 """
 from .binding import (  # noqa: F401

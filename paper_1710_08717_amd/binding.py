@@ -1,4 +1,4 @@
-"""ctypes binding of ``libla_mi355x.so``: argument marshalling only.
+"""Binding of ``libla_mi355x.so``: argument marshalling only, by ctypes, and for plain calls by ``_la_host.so``.
 
 Each function mirrors one ``la_*`` entry point of ``include/la.h``.  Tensors must live on
 the GPU, be contiguous and be float32 or float64; all leading axes are flattened into the
@@ -14,6 +14,7 @@ import torch
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libla_mi355x.so")
 _lib = None
+_host = None  # the module of csrc/host_call.cpp, once load() has run
 
 SYMBOLS = [
     "la_potrf_batched", "la_potrf_backward", "la_trsm_batched", "la_trmm_batched", "la_syrk_batched",
@@ -41,7 +42,7 @@ def lib_path():
 
 def load():
     """Load the HIP library (built beforehand by ``paper_1710_08717_amd.build``); raises if absent."""
-    global _lib
+    global _lib, _host
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -49,6 +50,8 @@ def load():
             f"{_LIB_PATH} is missing: build it with `python -m paper_1710_08717_amd.build` "
             "(there is no fallback path)"
         )
+    from . import _la_host
+
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64, f64 = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_double
     lib.la_potrf_batched.argtypes = [i32, i32, i64, i32, vp, vp, vp, vp]
@@ -94,7 +97,9 @@ def load():
             f = getattr(lib, name)
             f.argtypes = plain.argtypes[:-1] + [vp, ctypes.c_size_t, vp]
             f.restype = i32
+    _la_host.bind(_LIB_PATH)
     _lib = lib
+    _host = _la_host
     return lib
 
 
@@ -128,9 +133,12 @@ def _chk(*ts):
             raise LaError("tensors must share dtype and device")
 
 
-# The calls on small matrices take a few microseconds of GPU time, so what the host does per call counts: pointers go to
-# ctypes as plain integers, the device is only switched where it is another one, and the stream's handle is asked for
-# without building a Stream object (16 potrf of 32 x 32: 10.5 -> 7.0 us of host time per call, 3 of them the launch).
+# The calls on small matrices take a few microseconds of GPU time, so what the host does per call counts.  A call with
+# no tensor of the caller's for results, info or scratch goes through csrc/host_call.cpp first, which makes it or answers
+# None where it is not a plain one (potrf, trsm, potrf_backward and sumlogdiag of 16 matrices of 32 x 32: 8.6, 10.5, 9.3 and
+# 8.3 us of host time through ctypes, 4.8, 5.0, 4.9 and 4.3 through it, 3 of them the launch).
+# What comes here hands pointers to ctypes as plain integers, switches the device only where it is another one, and asks
+# for the stream's handle without building a Stream object.
 _HERE = contextlib.nullcontext()
 
 
@@ -181,6 +189,10 @@ def _ws(workspace, op, t, batch, n=0, m=0, k=0):
 
 def potrf(A, lower=True, out=None, info=None, workspace=None):
     """la_potrf_batched.  ``out`` may be ``A`` itself (in place).  ``info``: int32 [batch] or None."""
+    if _host is not None and out is None and info is None and workspace is None:
+        r = _host.potrf(A, lower)
+        if r is not None:
+            return r
     _chk(A)
     n = A.shape[-1]
     assert A.shape[-2] == n
@@ -214,6 +226,10 @@ def potrf_noalloc(A, out, lower=True, info=None):
 
 def potrf_backward(L, Lbar, lower=True, out=None, workspace=None):
     """la_potrf_backward.  ``out`` may be ``Lbar`` itself."""
+    if _host is not None and out is None and workspace is None:
+        r = _host.potrf_backward(L, Lbar, lower)
+        if r is not None:
+            return r
     _chk(L, Lbar)
     n = L.shape[-1]
     assert L.shape == Lbar.shape and L.shape[-2] == n
@@ -227,6 +243,10 @@ def potrf_backward(L, Lbar, lower=True, out=None, workspace=None):
 
 
 def _tri(op, name, L, A, lower, trans, rightside, alpha, out, workspace):
+    if _host is not None and out is None and workspace is None:
+        r = _host.tri(op == OP_TRSM, L, A, lower, trans, rightside, alpha)
+        if r is not None:
+            return r
     _chk(L, A)
     n = L.shape[-1]
     assert L.shape[-2] == n
@@ -251,6 +271,10 @@ def trmm(L, A, lower=True, trans=False, rightside=False, alpha=1.0, out=None, wo
 
 
 def _tri_backward(op, name, L, X, Bbar, lower, trans, rightside, alpha, out_a, out_l, workspace):
+    if _host is not None and out_a is None and out_l is None and workspace is None:
+        r = _host.tri_backward(op == OP_TRSM_BACKWARD, L, X, Bbar, lower, trans, rightside, alpha)
+        if r is not None:
+            return r
     _chk(L, X)
     _chk(L, Bbar)
     n = L.shape[-1]
@@ -284,6 +308,10 @@ def trmm_backward(L, A, Bbar, lower=True, trans=False, rightside=False, alpha=1.
 
 def syrk_backward(A, Bbar, trans=False, alpha=1.0, out=None, workspace=None):
     """la_syrk_backward: Abar = alpha (Bbar + Bbar^T) A  or  alpha A (Bbar + Bbar^T)."""
+    if _host is not None and out is None and workspace is None:
+        r = _host.syrk_backward(A, Bbar, trans, alpha)
+        if r is not None:
+            return r
     _chk(A, Bbar)
     n, k = (A.shape[-1], A.shape[-2]) if trans else (A.shape[-2], A.shape[-1])
     assert Bbar.shape[-2:] == (n, n) and _batch(A) == _batch(Bbar)
@@ -298,6 +326,10 @@ def syrk_backward(A, Bbar, trans=False, alpha=1.0, out=None, workspace=None):
 
 def gemm2_backward(A, B, Cbar, ta=False, tb=False, alpha=1.0, workspace=None):
     """la_gemm2_backward: (Abar, Bbar) of C = alpha t_a(A) t_b(B)."""
+    if _host is not None and workspace is None:
+        r = _host.gemm2_backward(A, B, Cbar, ta, tb, alpha)
+        if r is not None:
+            return r
     _chk(A, B)
     _chk(A, Cbar)
     m, k = (A.shape[-1], A.shape[-2]) if ta else (A.shape[-2], A.shape[-1])
@@ -314,6 +346,10 @@ def gemm2_backward(A, B, Cbar, ta=False, tb=False, alpha=1.0, workspace=None):
 
 def potri(L, lower=True, out=None, workspace=None):
     """la_potri: A^-1 from the Cholesky factor of A.  ``out`` may be ``L`` itself."""
+    if _host is not None and out is None and workspace is None:
+        r = _host.potri(L, lower)
+        if r is not None:
+            return r
     _chk(L)
     n = L.shape[-1]
     assert L.shape[-2] == n
@@ -327,6 +363,10 @@ def potri(L, lower=True, out=None, workspace=None):
 
 def potri_backward(L, B, Bbar, lower=True, out=None, workspace=None):
     """la_potri_backward: gradient of the factor from B = A^-1 and Bbar."""
+    if _host is not None and out is None and workspace is None:
+        r = _host.potri_backward(L, B, Bbar, lower)
+        if r is not None:
+            return r
     _chk(L, B)
     _chk(L, Bbar)
     n = L.shape[-1]
@@ -364,6 +404,10 @@ def sgp_criterion(Kuu, Kuf, Kff_diag, y, noise_var, workspace=None):
 
 def gp_criterion(A, y, out=None, loss=None, info=None, workspace=None):
     """la_gp_criterion: (loss [batch], Abar [batch, n, n]).  ``out`` may be ``A`` itself."""
+    if _host is not None and out is None and loss is None and info is None and workspace is None:
+        r = _host.gp_criterion(A, y)
+        if r is not None:
+            return r
     _chk(A, y)
     n = A.shape[-1]
     batch = _batch(A)
@@ -409,6 +453,10 @@ def kalman_filter(A, B, Sh, Sv, mu0, S0, v, want_states=True, info=None):
 
 
 def syrk(A, trans=False, alpha=1.0, out=None, workspace=None):
+    if _host is not None and out is None and workspace is None:
+        r = _host.syrk(A, trans, alpha)
+        if r is not None:
+            return r
     _chk(A)
     n, k = (A.shape[-1], A.shape[-2]) if trans else (A.shape[-2], A.shape[-1])
     B = torch.empty(A.shape[:-2] + (n, n), dtype=A.dtype, device=A.device) if out is None else out
@@ -422,6 +470,10 @@ def syrk(A, trans=False, alpha=1.0, out=None, workspace=None):
 
 def gemm2(A, B, ta=False, tb=False, alpha=1.0, out=None, workspace=None):
     """la_gemm2_batched: C = alpha * t_a(A) t_b(B)."""
+    if _host is not None and out is None and workspace is None:
+        r = _host.gemm2(A, B, ta, tb, alpha)
+        if r is not None:
+            return r
     _chk(A, B)
     m, k = (A.shape[-1], A.shape[-2]) if ta else (A.shape[-2], A.shape[-1])
     n = B.shape[-2] if tb else B.shape[-1]
@@ -436,6 +488,10 @@ def gemm2(A, B, ta=False, tb=False, alpha=1.0, out=None, workspace=None):
 
 
 def sumlogdiag(L, out=None):
+    if _host is not None and out is None:
+        r = _host.sumlogdiag(L)
+        if r is not None:
+            return r
     _chk(L)
     n = L.shape[-1]
     o = torch.empty(L.shape[:-2], dtype=L.dtype, device=L.device) if out is None else out

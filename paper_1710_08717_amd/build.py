@@ -1,4 +1,5 @@
-"""Compiles the HIP sources under ``csrc/`` into ``libla_mi355x.so`` (gfx950 only).
+"""Compiles the HIP sources under ``csrc/`` into ``libla_mi355x.so`` (gfx950 only) and the binding's host part,
+``csrc/host_call.cpp``, into ``_la_host.so``.
 
 hipcc cross-compiles without a GPU, so this runs on the build host; the shared object
 then travels with the tree to the GPU machine.  Run as ``python -m paper_1710_08717_amd.build``.
@@ -13,6 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libla_mi355x.so")
+HOST = os.path.join(PKG, "_la_host.so")
 
 SOURCES = ["tiny.hip", "tiny_ops.hip", "tiny_rows.hip", "leaf.hip", "small_wave.hip", "trsm_stream.hip", "gemm.hip", "elem.hip", "kalman.hip", "la_api.hip"]
 FLAGS = [
@@ -52,8 +54,24 @@ def _compile(src):
     return obj
 
 
+def _build_host():
+    import sysconfig
+
+    import torch
+
+    base = os.path.dirname(torch.__file__)
+    inc = [os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    libs = ["torch_python", "torch_cpu", "torch_hip", "c10", "c10_hip"]
+    subprocess.check_call(
+        ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+         f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", *[x for d in inc for x in ("-isystem", d)],
+         "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "host_call.cpp"), "-o", HOST,
+         "-L", os.path.join(base, "lib"), *[f"-l{x}" for x in libs]])  # (found by torch's own import, which comes first)
+
+
 def build(force=True, jobs=8):
-    """Compile every HIP source and link the C-ABI library; returns its path."""
+    """Compile every HIP source and link the C-ABI library, and the binding's host part; returns the library's path."""
     os.makedirs(BUILD, exist_ok=True)
     headers = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".hpp")] + [
         os.path.join(ROOT, "include", "la.h")
@@ -62,8 +80,12 @@ def build(force=True, jobs=8):
         s for s in SOURCES
         if force or _newer(os.path.join(BUILD, os.path.splitext(s)[0] + ".o"), [os.path.join(CSRC, s)] + headers)
     ]
-    with ThreadPoolExecutor(max_workers=min(jobs, max(1, len(todo)))) as ex:
+    host = force or _newer(HOST, [os.path.join(CSRC, "host_call.cpp"), os.path.join(ROOT, "include", "la.h")])
+    with ThreadPoolExecutor(max_workers=min(jobs, len(todo) + 1)) as ex:
+        part = ex.submit(_build_host) if host else None
         list(ex.map(_compile, todo))
+        if part:
+            part.result()
     objs = [os.path.join(BUILD, os.path.splitext(s)[0] + ".o") for s in SOURCES]
     if todo or not os.path.exists(LIB):
         subprocess.check_call(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
