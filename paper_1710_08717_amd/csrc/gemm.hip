@@ -878,19 +878,20 @@ __global__ __launch_bounds__(256, 2) void k_gemm_staged(View<const T> A, View<co
 // ---------------------------------------------------------------------------------------
 // Thin products: at most GEMV_N columns (matrix times a few vectors).  They are bound by reading A
 // once, which the tile kernels above are not built for.  A may be masked (triA); B and C are plain.
-//   A with k contiguous: one wavefront per row, lanes stride over k, shuffle reduction.
+//   A with k contiguous: one wavefront per row, lanes stride over k, shuffle reduction; or the whole block on one row (SPLIT).
 //   A with i contiguous: a block takes 64 rows, its eight wavefronts an eighth of the k range each
-//   (every load is 64 consecutive elements), LDS reduction.
+//   (every load is 64 consecutive elements), LDS reduction; or 16 rows and a 32nd of the range a quarter wavefront (SPLIT).
 // ---------------------------------------------------------------------------------------
 constexpr int GEMV_N = 8;
 constexpr int GEMV_THREADS = 512;
+constexpr int GEMV_FEW = 16;
 
 // The loads of several k go out together, those of B with them: with one k at a time and a branch per column a wavefront
 // waits for memory twice per k (500 x 9568 times one vector, fp64, 27 -> 22 us; its transpose 59 -> 11).  A
 // column more than there are costs its loads (300 items 5 x 200 times 7 columns with A transposed, fp64, bound by the
 // loads of B: 31 us with eight), so every count has its own instance.
-template <typename T, int N>
-__global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int K,
+template <typename T, int N, bool SPLIT>
+__global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<const T> B, View<T> C, View<const T> Cin, int64_t batch, int M, int K,
                                               T alpha, T beta, int triA, int tiles)
 {
     constexpr int NW = GEMV_THREADS / 64;  // wavefronts: rows per block (k contiguous) or slices of k
@@ -901,6 +902,7 @@ __global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<con
     const T *Ap = A.item(b);
     const T *Bp = B.item(b);
     T *Cp = C.item(b);
+    const T *Ci = Cin.item(b);  // what beta multiplies: C itself, or a third operand of C's strides
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int64_t jo[N];
     T acc[N];
@@ -910,10 +912,12 @@ __global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<con
         acc[j] = T(0);
     }
     const bool rows = A.cs == 1;
-    const int i = rows ? tile * NW + w : tile * 64 + lane;
+    const int i = rows ? (SPLIT ? tile : tile * NW + w) : (SPLIT ? tile * GEMV_FEW + lane % GEMV_FEW : tile * 64 + lane);
     if (i < M) {
         const int kb = triA == 2 ? i : 0, ke = triA == 1 ? min(K, i + 1) : K;
-        const int first = rows ? kb + lane : w, step = rows ? 64 : NW, last = rows ? ke : K;
+        const int first = rows ? kb + (SPLIT ? (int)threadIdx.x : lane) : (SPLIT ? (int)threadIdx.x / GEMV_FEW : w);
+        const int step = rows ? (SPLIT ? GEMV_THREADS : 64) : (SPLIT ? GEMV_THREADS / GEMV_FEW : NW);
+        const int last = rows ? ke : K;
         const T *ar = Ap + (int64_t)i * A.rs;
         for (int k0 = first; k0 < last; k0 += UN * step) {
             T a[UN], x[UN][N];
@@ -934,17 +938,35 @@ __global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<con
         }
     }
     if (rows) {
-        if (i >= M)
+        if (i >= M)  // (never where the block has one row)
             return;
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
+        for (int j = 0; j < N; ++j)
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1)
                 acc[j] += __shfl_xor(acc[j], off, WAVE);
+        if constexpr (SPLIT) {
+            if (lane == 0)
+#pragma unroll
+                for (int j = 0; j < N; ++j)
+                    red[w][0][j] = acc[j];
+            __syncthreads();
+            if (w != 0)
+                return;
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                acc[j] = T(0);
+#pragma unroll
+                for (int q = 0; q < NW; ++q)
+                    acc[j] += red[q][0][j];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
             if (lane == 0) {
-                T *c = Cp + (int64_t)i * C.rs + (int64_t)j * C.cs;
+                const int64_t e = (int64_t)i * C.rs + (int64_t)j * C.cs;
                 const T upd = alpha * acc[j];
-                *c = (beta == T(0)) ? upd : fma(beta, *c, upd);
+                Cp[e] = (beta == T(0)) ? upd : fma(beta, Ci[e], upd);
             }
         }
         return;
@@ -953,32 +975,50 @@ __global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<con
     for (int j = 0; j < N; ++j)
         red[w][lane][j] = acc[j];
     __syncthreads();
-    if (w == 0 && i < M) {
+    if (w == 0 && i < M && (!SPLIT || lane < GEMV_FEW)) {
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             T sum = T(0);
 #pragma unroll
             for (int q = 0; q < NW; ++q)
                 sum += red[q][lane][j];
-            T *c = Cp + (int64_t)i * C.rs + (int64_t)j * C.cs;
+            if constexpr (SPLIT)
+#pragma unroll
+                for (int f = GEMV_FEW; f < 64; f += GEMV_FEW)
+#pragma unroll
+                    for (int q = 0; q < NW; ++q)
+                        sum += red[q][lane + f][j];
+            const int64_t e = (int64_t)i * C.rs + (int64_t)j * C.cs;
             const T upd = alpha * sum;
-            *c = (beta == T(0)) ? upd : fma(beta, *c, upd);
+            Cp[e] = (beta == T(0)) ? upd : fma(beta, Ci[e], upd);
         }
     }
 }
 
 template <typename T>
-static la_status launch_gemv(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N, int K, T alpha,
-                             T beta, int triA, hipStream_t st)
+static la_status launch_gemv(View<const T> A, View<const T> B, View<T> C, View<const T> Cin, int64_t batch, int M, int N, int K,
+                             T alpha, T beta, int triA, hipStream_t st)
 {
-    const int tiles = (A.cs == 1) ? (M + GEMV_THREADS / 64 - 1) / (GEMV_THREADS / 64) : (M + 63) / 64;
+    const bool rows = A.cs == 1;
+    const int per = rows ? GEMV_THREADS / 64 : 64, few = rows ? 1 : GEMV_FEW;
+    // Few blocks and long sums: the finer split.  With k contiguous from 12 elements of k a block of rows on (one vector, fp32 and fp64:
+    // 500 x 9568 16 -> 6 and 22 -> 9 us, 8 x 30000 43 -> 8 and 54 -> 10; but 2000 x 2048, 250 blocks, 5.9 -> 8.0 and 7.0 -> 8.6), transposed from
+    // half an element a block on (500 x 500 7.7 -> 3.9 and 9.3 -> 4.4, 9568 x 500 8.8 -> 7.8 and 11.2 -> 8.9, 4000 x 4000 57 -> 23 and 67 -> 24;
+    // but 16000 x 100, 250 blocks, 3.7 -> 5.0 and 4.0 -> 5.1).
+    const int64_t whole = (int64_t)((M + per - 1) / per) * batch;
+    const bool split = whole < 256 && (rows ? K >= 2048 && K >= 12 * whole : K >= 64 && 2 * K >= whole);
+    const int tiles = split ? (M + few - 1) / few : (M + per - 1) / per;
     const int64_t blocks = (int64_t)tiles * batch;
     if (blocks > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
 #define LA_GO(N_)                                                                                                      \
     case N_:                                                                                                           \
-        LA_LAUNCH((k_gemv<T, N_>), dim3((unsigned)blocks), dim3(GEMV_THREADS), 0, st, A, B, C, batch, M, K, alpha, beta, triA, \
-                  tiles);                                                                                              \
+        if (split)                                                                                                     \
+            LA_LAUNCH((k_gemv<T, N_, true>), dim3((unsigned)blocks), dim3(GEMV_THREADS), 0, st, A, B, C, Cin, batch, M, K, \
+                      alpha, beta, triA, tiles);                                                                       \
+        else                                                                                                           \
+            LA_LAUNCH((k_gemv<T, N_, false>), dim3((unsigned)blocks), dim3(GEMV_THREADS), 0, st, A, B, C, Cin, batch, M, K, \
+                      alpha, beta, triA, tiles);                                                                       \
         break
     switch (N) {
         LA_GO(1);
@@ -1024,6 +1064,19 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const T *partial, View<T>
         s += p[q * mn];
     store_c<T>(C.item(b), C.rs, C.cs, i, j, M, N, s, alpha, beta, o);
 }
+
+// y = beta c + alpha A x for one item (A M x K, triA as in GemmOpts; beta = 0: c is not read), y not one of the others
+template <typename T>
+la_status launch_gemv_add(View<const T> A, const T *x, const T *c, T *y, int M, int K, T alpha, T beta, int triA, hipStream_t st)
+{
+    if (M <= 0)
+        return LA_OK;
+    if (dry_run())
+        return LA_OK;
+    return launch_gemv<T>(A, View<const T>{x, K, 1, 1}, View<T>{y, M, 1, 1}, View<const T>{c, M, 1, 1}, 1, M, 1, K, alpha, beta, triA, st);
+}
+template la_status launch_gemv_add<float>(View<const float>, const float *, const float *, float *, int, int, float, float, int, hipStream_t);
+template la_status launch_gemv_add<double>(View<const double>, const double *, const double *, double *, int, int, double, double, int, hipStream_t);
 
 template <typename T>
 static bool aligned16(const View<const T> &V, int64_t lead)
@@ -1200,9 +1253,9 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
     // a few vectors on either side: one pass over the big operand
     if (!o.maskC && !o.halfDiag && !o.min_tile64 && !o.symsum && K > 0) {
         if (N <= GEMV_N && o.triB == 0)
-            return launch_gemv<T>(A, B, C, batch, M, N, K, alpha, beta, o.triA, st);
+            return launch_gemv<T>(A, B, C, View<const T>{C.p, C.bs, C.rs, C.cs, C.bs2, C.nb2}, batch, M, N, K, alpha, beta, o.triA, st);
         if (M <= GEMV_N && o.triA == 0)  // C^T = B^T A^T
-            return launch_gemv<T>(B.t(), A.t(), C.t(), batch, N, M, K, alpha, beta, flip_tri(o.triB), st);
+            return launch_gemv<T>(B.t(), A.t(), C.t(), View<const T>{C.p, C.bs, C.cs, C.rs, C.bs2, C.nb2}, batch, N, M, K, alpha, beta, flip_tri(o.triB), st);
     }
     // Keep the stores of C along its contiguous direction: if C is stored with i contiguous,
     // compute C^T = B^T A^T instead (a pure re-labelling of the views).
