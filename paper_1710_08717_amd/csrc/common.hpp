@@ -588,6 +588,8 @@ struct GemmOpts {
 template <typename T>
 la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N, int K, T alpha,
                       T beta, GemmOpts o, hipStream_t st);
+template <typename T>
+la_status launch_gemv_add(View<const T> A, const T *x, const T *c, T *y, int M, int K, T alpha, T beta, int triA, hipStream_t st);
 
 
 // Element-wise helpers.

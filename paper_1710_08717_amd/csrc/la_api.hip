@@ -1000,6 +1000,24 @@ static la_status solve_beside_inverse(bool fwd, int64_t batch, int n, int m, con
                                  View<T>{(T *)p, (int64_t)edge * m, m, 1}, st);
 }
 
+// One vector solve with an n x n lower factor L whose inverse Li is there: dst = L^-1 src or L^-T src, src kept; tmp: 2 n elements.
+// The streaming solve's chain of blocks takes 47 and 56 us at n = 500 in fp64; a product with the inverse and one step of refinement,
+// dst += Li (src - L dst), are three products of about 5 each.  The refined result is as accurate as the chain's, since L is no worse
+// conditioned than the square root of a matrix that the precision can factor: over 288 problems of U = 129 to 700 in fp32, noise 1e-3 to 10,
+// the criterion's errors and its gradients' are 0.98 to 1.01 times those with the chain (geometric means).
+template <typename T>
+static la_status solve_vector(bool fwd, int n, const T *L, View<const T> Li, const T *src, T *dst, T *tmp, hipStream_t st)
+{
+    if (n <= 2 * NB)
+        return tri_apply_t<T>(true, 1, !fwd, 0, 1.0, 1, n, 1, L, src, dst, st);
+    const View<const T> Lv{L, (int64_t)n * n, n, 1}, A = fwd ? Lv : Lv.t(), Ai = fwd ? Li : Li.t();
+    const int tri = fwd ? 1 : 2;
+    T *first = tmp + n;
+    LA_TRY(launch_gemv_add<T>(Ai, src, nullptr, first, n, n, T(1), T(0), tri, st));
+    LA_TRY(launch_gemv_add<T>(A, first, src, tmp, n, n, T(-1), T(1), tri, st));
+    return launch_gemv_add<T>(Ai, tmp, first, dst, n, n, T(1), T(1), tri, st);
+}
+
 // potri (section 4.2 "potri"): A^-1 = Lam^-T Lam^-1 for A = Lam Lam^T (Lam = L, or R^T for an upper
 // factor: the same symmetric matrix either way).
 template <typename T>
@@ -1139,16 +1157,16 @@ static la_status sgp_t(int U, int n, const void *Kuu_, const void *Kuf_, const v
     LA_TRY(launch_plus_identity<T>(E, La, U, st));
     LA_TRY(potrf_t<T>(1, 1, U, La, La, nullptr, st));                                          // La
     LA_TRY(gemm2_t<T>(0, 0, 1.0, 1, U, 1, n, B, y, v, st));                                    // v = B y
-    LA_TRY(tri_apply_t<T>(true, 1, 0, 0, 1.0, 1, U, 1, La, v, w, st));                         // w = La^-1 v
-    // ---- backward ---------------------------------------------------------------------------
-    LA_TRY(tri_apply_t<T>(true, 1, 1, 0, 1.0, 1, U, 1, La, w, v, st));                         // a = La^-T w (in v's buffer)
-    const T *a = v;
     {
         ArenaFrame frame;
         View<T> sc[2];
         LA_TRY(scratch_views<T>(1, U, 2, sc));
         LA_TRY(inverse_build<T>(cv(square(La)), sc[0], sc[1], 1, U, U, st));
         const View<const T> Lia = cv(sc[0]);
+        LA_TRY(solve_vector<T>(true, U, La, Lia, v, w, sc[1].p, st));                          // w = La^-1 v
+        // ---- backward -----------------------------------------------------------------------
+        LA_TRY(solve_vector<T>(false, U, La, Lia, w, v, sc[1].p, st));                         // a = La^-T w (in v's buffer)
+        const T *a = v;
         LA_TRY(launch_gp_glue<T>(La, w, nullptr, a, dummy, Ab, 1, U, st, T(0.5) * r1));
         LA_TRY(gram_add<T>(Lia, T(0.5), square(Ab), T(1), 1, U, st));                          // A_bar (symmetric)
         const SumList<T> all{{{0, y, nullptr, n, 0}, {0, w, nullptr, U, 0}, {0, B, nullptr, un, 0}, {1, Kff, nullptr, n, 0},
@@ -1158,7 +1176,7 @@ static la_status sgp_t(int U, int n, const void *Kuu_, const void *Kuf_, const v
         LA_TRY(launch_gemm<T>(Lia, View<const T>{E, uu, U, 1}, sc[1], 1, U, U, U, T(1), T(0), low, st));  // S = La^-1 E
         LA_TRY(launch_gemm<T>(cv(sc[1]).t(), cv(sc[1]), square(La), 1, U, U, U, T(1), T(0), below, st));  // S^T S
     }
-    LA_TRY(launch_sgp_inner<T>(La, Ab, a, r1, vb, U, st));  // La <- Phi(Q),  Ab <- A_bar - I / 2,  v_bar
+    LA_TRY(launch_sgp_inner<T>(La, Ab, v, r1, vb, U, st));  // La <- Phi(Q),  Ab <- A_bar - I / 2,  v_bar
     {
         ArenaFrame frame;
         void *p = nullptr;
@@ -1169,9 +1187,7 @@ static la_status sgp_t(int U, int n, const void *Kuu_, const void *Kuf_, const v
         LA_TRY(solve_u(false, Bb.p, Kuf_bar));                                                 // Kuf_bar = Lu^-T B_bar
     }
     // y_bar = B^T v_bar + y / lam
-    View<T> yb{y_bar, n, 1, 1};
-    LA_TRY(launch_copy<T>(View<const T>{y, n, 1, 1}, yb, 1, n, 1, (T)(1.0 / lam), 0, st));
-    LA_TRY(launch_gemm<T>(View<const T>{B, un, 1, n}, View<const T>{vb, U, 1, 1}, yb, 1, n, 1, U, T(1), T(1), plain, st));
+    LA_TRY(launch_gemv_add<T>(View<const T>{B, un, 1, n}, vb, y, y_bar, n, U, T(1), (T)(1.0 / lam), 0, st));
     return congruence<T>(cv(Liu), cv(square(La)), square(E), square(Kuu_bar), 1, U, st);
 }
 
