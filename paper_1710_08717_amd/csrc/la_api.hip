@@ -346,13 +346,11 @@ template <typename T>
 static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, int64_t batch, int n, bool aliased,
                                hipStream_t st)
 {
-    // n <= 16: 16 lanes per matrix, HBM bound.  16 < n <= 32: the register kernel has the higher
-    // throughput (11 against 16 ns per fp32 matrix), the one-workgroup kernel the shorter latency
-    // (25 against 37 us), so the batch size decides.
-    if (n <= 16 || (n <= 32 && batch > 2048))
-        return launch_backward_tiny<T>(Lam, G, W, batch, n, st);
+    // n <= 16: 16 lanes per matrix, HBM bound; so are many matrices of n = 24.
     if (small_wave_takes<T>(SmallWaveOp::backward, batch, n))  // one wavefront per matrix
         return launch_backward_wave<T>(Lam, G, W, batch, n, st);
+    if (n <= 32)
+        return launch_backward_tiny<T>(Lam, G, W, batch, n, st);
     if (n <= backward_leaf16_max_n<T>())  // one workgroup per matrix, everything in LDS, no scratch
         return launch_backward_leaf16<T>(Lam, G, W, batch, n, st);
     // (the expression takes two squares; where the workspace has no room for them the sweep does with less)
@@ -525,9 +523,9 @@ static la_status potrf_t(int lower, int64_t batch, int n, const void *A, void *L
     // equal data volume, us: n = 41 fp32 146 -> 71, 48 57 -> 42 and fp64 161 -> 73, 56 90 -> 59, 64 56 -> 38 and 123 -> 64).
     if (small_wave_takes<T>(SmallWaveOp::potrf, batch, n))
         return launch_potrf_wave<T>(Av, Lv, info, batch, n, st);
-    if (n > 32 && n <= NB && batch > 1024)
+    if (n > 32 && n <= NB)
         return launch_potrf_small16<T>(Av, Lv, info, batch, n, st);
-    if (n <= NB)
+    if (n <= 32)
         return launch_potrf_tiny<T>(Av, Lv, info, 0, batch, n, st);
     if (n <= 2 * NB)  // one leaf: it reads A and writes L directly; nobody wants the inverse
         return launch_potrf_leaf16<T>(Av, Lv, View<T>{nullptr, 0, 0, 0}, info, 0, batch, n, true, st);
@@ -649,22 +647,21 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
     if (!solve && Lam.nb2 == 1 && trmm_wave_takes<T>(batch, n, m, Xin, X))  // one wavefront per item, in place too
         return launch_trmm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
 
-    // n <= 64 with at most 16 vectors stored as whole items back to back: G lanes per matrix.  (A solve
-    // with 16 < n over a small batch is quicker in the one-workgroup kernel below: 16 matrices of n = 32,
-    // fp64: 6.5 against 10.9 us; up to n = 32 the lane-group kernel wins once there are more matrices than
-    // workgroup slots, above that the one-workgroup kernel with four wavefronts per item does: 7281
-    // solves of 48 x 48 with 16 vectors 136 -> 35 us in fp32, 285 -> 46 in fp64.)
+    if (solve && Lam.nb2 == 1 && trsm_wave_takes<T>(batch, n, m, Xin, X))  // one wavefront per item, no scratch
+        return launch_trsm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
+
+    // n <= 32 with at most 16 vectors stored as whole items back to back: G lanes per matrix.  (A solve with 16 < n comes here only
+    // for many items of 24 rows: trsm_wave_takes.)
     // A multiply on many small items: one workgroup per item, Lam's lower tiles and the vectors in LDS, no scratch.
-    // Up to n = 32 with at most 16 vectors the lane-group kernels below are faster; above that this one is
-    // (7281 x 48 x 48 times 16 vectors, fp32 / fp64: 64 lanes per matrix 91 / 183 us).
+    // Up to n = 32 with at most 16 vectors the lane-group kernels below are faster; above that this one is.
     const bool leaf_mul = !solve && trmm_leaf_takes<T>(batch, n, m) && Lam.nb2 == 1 && Xin.nb2 == 1 && X.nb2 == 1;
     if (leaf_mul && (n > 32 || m > 16))
         return launch_trmm_leaf<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
 
-    if (n <= 64 && m <= 16 && (!solve || n <= 16 || (batch > 1024 && n <= 32)) && X.bs == nm && Xin.bs == nm && Xin.rs == X.rs && Xin.cs == X.cs && X.nb2 == 1 &&
+    if (n <= 32 && m <= 16 && (!solve || n <= 16 || batch > 1024) && X.bs == nm && Xin.bs == nm && Xin.rs == X.rs && Xin.cs == X.cs && X.nb2 == 1 &&
         Xin.nb2 == 1 && Lam.nb2 == 1) {
         const bool rowmajor = (X.rs == m && X.cs == 1), colmajor = (X.rs == 1 && X.cs == n);
-        if ((rowmajor || colmajor) && n > 16 && n <= 32)  // 16 lanes per matrix, two rows per lane
+        if ((rowmajor || colmajor) && n > 16)  // 16 lanes per matrix, two rows per lane
             return launch_tri_rows<T>(solve, fwd, alpha, batch, n, m, Lam, Xin.p, X.p, !rowmajor, st);
         if (rowmajor || colmajor)
             return launch_tri_tiny<T>(solve, fwd, alpha, batch, n, m, Lam, Xin.p, X.p, !rowmajor, st);
@@ -672,9 +669,6 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
 
     if (leaf_mul)  // (operands the lane-group kernels do not take: other strides)
         return launch_trmm_leaf<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
-
-    if (solve && Lam.nb2 == 1 && trsm_wave_takes<T>(batch, n, m, Xin, X))  // one wavefront per item, no scratch
-        return launch_trsm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
 
     if (solve && n <= 128 && m <= 48)  // small: one workgroup per item does the whole substitution, no scratch
         return launch_trsm_leaf16<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
@@ -689,7 +683,7 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
     // panel, which do; those kernels take them, too, where the workspace has no room, so that one sized for many items serves a few (with
     // scratch -> without, us, fp64 / fp32: trmm, 500 of n = 64 with 300 vectors 50 -> 51 / 25 -> 40, 1000 of n = 48 with 100 31 -> 20 /
     // 18 -> 18; trsm of the same 92 -> 55 / 54 -> 42 and 72 -> 22 / 46 -> 16).
-    if (Lam.nb2 == 1 && tri_wave_can<T>(batch, n, m, Xin, X) && !arena_room((size_t)batch * (solve ? nn : nm) * sizeof(T)))
+    if (Lam.nb2 == 1 && n > 32 && tri_wave_can<T>(batch, n, m, Xin, X) && !arena_room((size_t)batch * (solve ? nn : nm) * sizeof(T)))
         return solve ? launch_trsm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st)
                      : launch_trmm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
 
@@ -1024,10 +1018,10 @@ template <typename T>
 static la_status potri_t(int lower, int64_t batch, int n, const void *L, void *B, hipStream_t st)
 {
     View<const T> Lam = tri_view<const T>((const T *)L, n, lower);
-    if (n <= 32)  // both solves on the identity in registers, G lanes per matrix (two rows per lane above 16)
-        return launch_potri_tiny<T>(Lam, View<T>{(T *)B, (int64_t)n * n, n, 1}, batch, n, st);
     if (small_wave_takes<T>(SmallWaveOp::potri, batch, n))  // one wavefront per matrix
         return launch_potri_wave<T>(Lam, View<T>{(T *)B, (int64_t)n * n, n, 1}, batch, n, st);
+    if (n <= 32)  // both solves on the identity in registers, G lanes per matrix (two rows per lane above 16)
+        return launch_potri_tiny<T>(Lam, View<T>{(T *)B, (int64_t)n * n, n, 1}, batch, n, st);
     if (n <= 2 * NB)  // one workgroup per matrix, everything in LDS, no scratch
         return launch_potri_leaf16<T>(Lam, View<T>{(T *)B, (int64_t)n * n, n, 1}, batch, n, st);
     ArenaFrame frame;

@@ -1,4 +1,4 @@
-// Many matrices of 32 < n <= 64: one wavefront per matrix, the whole operator in registers.
+// Matrices of 16 < n <= 64: one wavefront per matrix, the whole operator in registers (trmm, syrk and the rules with them from n = 33 on).
 //
 // The one-workgroup kernels of leaf.hip give such a matrix four wavefronts and keep its 16 x 16 tiles in LDS; with nine or ten
 // tiles they spend their time in barriers and in LDS round trips between products of one tile each.  Here a wavefront holds all tiles
@@ -434,16 +434,16 @@ __global__ __launch_bounds__(SW_WAVES * 64, sizeof(T) * K <= 16 ? 4 : (sizeof(T)
     for (int i = 0; i < K; ++i)
 #pragma unroll
         for (int j = 0; j <= i; ++j) {
-            Acc<T> acc = {0, 0, 0, 0};
+            Acc<T> acc = {0, 0, 0, 0}, mirror = {0, 0, 0, 0};  // (two short sums: less rounding than one, and not one after the other)
 #pragma unroll
             for (int k = i; k < K; ++k) {
                 acc = frag_mma<T>(li[tri_at(k, i)], z[tri_at(k, j)], acc);
-                acc = frag_mma<T>(z[tri_at(k, i)], li[tri_at(k, j)], acc);
+                mirror = frag_mma<T>(z[tri_at(k, i)], li[tri_at(k, j)], mirror);
             }
             T x[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                x[v] = T(0.5) * acc[v];
+                x[v] = T(0.5) * (acc[v] + mirror[v]);
             w.store_sym(out, i, j, x, i < K - 1, j < K - 1);
         }
 }
@@ -794,13 +794,17 @@ __global__ __launch_bounds__(SW_WAVES * 64, TRI != 0 ? (sizeof(T) * K <= 12 ? 3 
 }
 
 // ---------------------------------------------------------------------------------------
-// launches: 32 < n <= 64, three or four tile rows
+// launches: two, three or four tile rows
 // ---------------------------------------------------------------------------------------
-// The edge is that of the four-wavefront kernels these stand beside; it does not lie where these stop paying.  In a graph, us, 1024 matrices, fp32 /
-// fp64: potrf of n = 37 33 -> 7.3 / 42 -> 9.6, of n = 60 28 -> 11 / 38 -> 17, backward 30 -> 8.7 / 36 -> 14 and 39 -> 16 / 47 -> 27, potri 19 -> 6.1 /
-// 22 -> 8.7 and 24 -> 10 / 29 -> 16; 128 matrices of n = 37: 33 -> 6.5 / 41 -> 8.1, 12 -> 8.0 / 13 -> 12, 7.4 -> 5.3 / 8.2 -> 7.1.  Behind they are with
-// 256 and fewer of n > 48 in fp64: backward 17 -> 20, syrk's rule 6.4 -> 8.0 (n = 64 also trmm 5.0 -> 6.7, potri 9.5 -> 12).  Left where it was.
-static bool wave_range(int64_t batch, int n) { return n > 2 * LT && n <= 4 * LT && batch > 1024 && batch <= 0x7fffffffll; }
+// Products (trmm, syrk and the rules with them): one wavefront alone takes longer than the four or sixteen of the other kernels, which two rounds of
+// workgroups a compute unit make up for, one round for less than three whole tile rows and few columns.  300 / 640 / 1024 matrices from memory, time of the
+// other kernels over this one's: syrk of n = 33 with k = 24 1.19 / 1.56 / 1.91 in fp32 and 1.16 / 1.50 / 1.72 in fp64, of n = 64 with k = 64 0.99 / 1.29 /
+// 1.54 and 0.87 / 1.22 / 1.34, its rule 1.03 / 1.42 / 1.77, 1.12 / 1.46 / 1.65 and 0.93 / 1.29 / 1.43, 1.08 / 1.41 / 1.67; with 128 matrices 0.6 to 1.1.
+static bool wave_range(int64_t batch, int n, int cols)
+{
+    return n > 2 * LT && n <= 4 * LT && batch <= 0x7fffffffll &&
+           (batch > 1024 || (cols <= 4 * LT && batch > (n < 3 * LT && cols <= 3 * LT ? 256 : 512)));
+}
 // the kernels address an item by 32-bit byte offsets
 template <typename T>
 static bool offsets_fit(int64_t rows, int64_t cols, int64_t rs, int64_t cs, int nb2)
@@ -808,12 +812,22 @@ static bool offsets_fit(int64_t rows, int64_t cols, int64_t rs, int64_t cs, int 
     return nb2 == 1 && rs >= 0 && cs >= 0 && ((rows - 1) * rs + (cols - 1) * cs + 1) * (int64_t)sizeof(T) <= 0xffffffffll;
 }
 
-// Against the four-wavefront kernels (1025 matrices or more; us, fp32 / fp64):
+// Up to 1024 matrices (us from memory, other kernel -> this one, fp32 and fp64):
+//   potrf, 64 matrices of n = 20 12.8 -> 4.4 and 13.6 -> 5.3, of 32 5.8 -> 4.5 and 7.3 -> 5.3, 256 of 33 32 -> 6.7 and 40 -> 8.3, of 49 24.7 -> 9.5 and
+//     31.8 -> 12.2, 1024 of 64 20.8 -> 12.3 and 33.5 -> 17.8;
+//   backward, 64 of 20 10 -> 5.0 and 10.8 -> 6.4, 1024 of 32 16.0 -> 6.6 and 19.6 -> 9.4, 300 of 41 17.6 -> 8.3 and 20.6 -> 13.2, of 64 16.1 -> 14.3 and
+//     22.1 -> 21.9, but 128 of 64 11.0 -> 13.1 and 13.5 -> 19.5, of 48 8.6 -> 8.3 and 10.2 -> 12.0;
+//   potri alike (128 of 33 7.4 -> 5.5 and 8.2 -> 7.1, of 64 7.4 -> 8.3 and 8.7 -> 11.1), its rule always (64 of 20 11.7 -> 5.1 and 12.2 -> 6.5,
+//     256 of 49 39 -> 16 and 53 -> 21).
+// More of them, up to n = 32: the lane-group kernels are ahead where they keep just n columns and take 16-byte pieces (n = 24 and 32): 8192 potrf of
+// n = 32 in fp32 11.8 -> 16.9, of 24 8.7 -> 14.2 and 15.3 -> 22.4 (but 31.0 -> 25.5 of n = 32 in fp64), backward of 24 17.4 -> 21.0 and 31.7 -> 38.0, of 32
+// 28 -> 26 and 75 -> 43, of 28 41 -> 23 and 94 -> 42; potri of 24 10.8 -> 13.1 and 18.1 -> 20.2, of 32 16.0 -> 15.0 and 33 -> 24; its rule, of 28, 82 -> 27
+// and 98 -> 45.
+// Above n = 32, against the four-wavefront kernels:
 //   12255 of n = 37: potrf 88 -> 41 / 140 -> 69, backward 142 -> 77 / 214 -> 162, potri 73 -> 39 / 96 -> 65, its backward rule
-//   207 -> 99 / 370 -> 288, trsm of 16 vectors 59 -> 40 / 79 -> 56, of 37 85 -> 79 / 176 -> 142;
-//   5001 of n = 51: 55 -> 32 / 83 -> 56, 109 -> 68 / 205 -> 154, 52 -> 32 / 118 -> 66, 311 -> 135 / 575 -> 347.
-// A wavefront alone takes longer than four: with 1100 matrices of n = 64, fp32, potrf 16 -> 20, backward 34 -> 36 (1600: 21 -> 21, 41 -> 38;
-// 1100 of n = 37: 14 -> 10, 22 -> 15), hence the second line.  Where nothing is ragged the four-wavefront kernels move
+//   207 -> 99 / 370 -> 288; 5001 of n = 51: 55 -> 32 / 83 -> 56, 109 -> 68 / 205 -> 154, 52 -> 32 / 118 -> 66, 311 -> 135 / 575 -> 347;
+//   1100 of n = 64: 17 -> 15 / 29 -> 22, 35 -> 25 / 48 -> 39, 18 -> 15 / 29 -> 22.
+// Where nothing is ragged the four-wavefront kernels move
 // 16-byte pieces, and from memory (not the last-level cache) they are then the faster ones: 16384 of n = 64, fp32, potrf 141 -> 180,
 // 4096 37 -> 30; 20000 of n = 48 109 -> 120, 7281 42 -> 33; backward 7281 of n = 48, fp64, 121 -> 138, 2048 39 -> 34.
 // potrf in fp64 with four tile rows is equal there: 8000 of n = 60 133 -> 142, 5001 of n = 51 83 -> 56; so is potri with nearly three whole
@@ -821,12 +835,17 @@ static bool offsets_fit(int64_t rows, int64_t cols, int64_t rs, int64_t cs, int 
 template <typename T>
 bool small_wave_takes(SmallWaveOp op, int64_t batch, int n)
 {
-    if (!wave_range(batch, n))
+    if (n <= LT || n > 4 * LT || batch > 0x7fffffffll)
         return false;
     if (op == SmallWaveOp::potri_backward)
         return true;
-    if (n > 40 && batch <= 1536)
-        return false;
+    if (n <= 2 * LT) {
+        if (op == SmallWaveOp::potrf)
+            return n % 8 != 0 || batch <= 1024 || (sizeof(T) == 8 && n == 32 && batch >= 4096);
+        return n != 24 || batch <= 2048;
+    }
+    if (batch <= 1024)
+        return op == SmallWaveOp::potrf || batch > 256 || n < (sizeof(T) == 4 ? 4 : 3) * LT;
     const double mib = (double)batch * n * n * sizeof(T) / 1048576.0;
     if (n % LT == 0)
         return mib <= 64.0;
@@ -841,24 +860,42 @@ template bool small_wave_takes<double>(SmallWaveOp, int64_t, int);
 template <typename T>
 bool tri_wave_can(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out)
 {
-    return n > 2 * LT && n <= 4 * LT && batch <= 0x7fffffffll && offsets_fit<T>(n, m, in.rs, in.cs, in.nb2) &&
+    return n > LT && n <= 4 * LT && m >= 1 && batch <= 0x7fffffffll && offsets_fit<T>(n, m, in.rs, in.cs, in.nb2) &&
            offsets_fit<T>(n, m, out.rs, out.cs, out.nb2);
 }
 template bool tri_wave_can<float>(int64_t, int, int, const View<const float> &, const View<float> &);
 template bool tri_wave_can<double>(int64_t, int, int, const View<const double> &, const View<double> &);
 
-// More than 48 vectors went through the inverse and a product before: 5001 of n = 51 with 51 vectors 167 -> 81 / 317 -> 167.  Up to
-// 48 the other kernel gives every tile of vectors a wavefront of its own: 9000 of n = 45 with 45 vectors, fp32, 70 -> 79 (with 16
+// Up to n = 32 against one workgroup an item (up to 48 vectors, and 16 lanes an item for up to 16 vectors of many), the inverse and a product above
+// (time of the other over this one's, fp32 and fp64): 64 of n = 20 with 16 vectors 1.6 and 1.5, with 48 1.2 and 1.06, with 64 2.1 and 1.9, with 128 1.5 and
+// 1.3, 8192 1.8 and 2.3, 1.9 and 2.0, 5.7 and 6.3, 4.1 and 4.3; behind are 64 of n = 32 with 48 (0.97 and 0.87) and 8192 of n = 24 with one vector in fp32 (0.90).
+// Above n = 32 and up to 256 items the sixteen wavefronts of one workgroup are ahead where there is a wavefront's work for each and little padding: 128 items
+// of n = 33, 48, 56, 64 with 16 vectors 1.39, 1.14, 1.25, 1.07 and 1.25, 1.03, 1.08, 0.92, with 24 1.18, 1.02, 1.09, 0.94 and 1.03, 0.90, 0.92, 0.84, with 48
+// 1.04, 0.90, 1.01, 0.88 and 0.92, 0.82, 0.88, 0.81; so is the inverse for many vectors: with 64 1.95, 1.51, 1.44, 1.27 and 1.83, 1.43, 1.32, 1.22, with 128
+// 1.36, 1.10, 0.99, 0.88 and 1.18, 0.92, 0.89, 0.85.  300 items: 1.11 (n = 64 with 48, fp32) to 2.6; 3000 of n = 41 to 64 with up to 48 1.3 to 3.3.
+// 5001 of n = 51 with 51 vectors 167 -> 81 / 317 -> 167.  Above 3072, up to 48 vectors, the workgroup gives every tile of vectors a wavefront
+// of its own: 9000 of n = 45 with 45 vectors, fp32, 70 -> 79 (with 16
 // 46 -> 36; of n = 40 with 40 75 -> 66), 8000 of n = 60 with 16, fp64, 93 -> 133.  Many vectors of few items are left to the product, too (fp32: 1500 of
 // n = 60 with 1000 468 -> 663, 1100 of n = 64 with 200 83 -> 96; 4096 of n = 64 with 300 437 -> 336).
 template <typename T>
 bool trsm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out)
 {
-    if (!wave_range(batch, n) || !tri_wave_can<T>(batch, n, m, in, out))
+    constexpr bool f32 = sizeof(T) == 4;
+    if (!tri_wave_can<T>(batch, n, m, in, out))
         return false;
-    if (m <= 3 * LT && (n >= 3 * LT || (n > 40 && (m > LT || batch <= 1536))))
-        return false;
-    return m <= 8 * LT || batch > 3072;
+    if (m > 8 * LT)
+        return batch > 3072;
+    if (n <= 2 * LT)
+        return !(batch <= 256 && n == 2 * LT && m > 2 * LT && m <= 3 * LT) && !(f32 && batch > 4096 && n == 24 && m < 8);
+    if (batch > 3072)
+        return m > 3 * LT || !(n >= 3 * LT || (n > 40 && m > LT));
+    if (batch > 256)
+        return true;
+    if (m <= LT)
+        return f32 || n <= 60;
+    if (m <= 3 * LT)
+        return f32 ? n < (m <= 2 * LT ? 64 : 45) : (m <= 2 * LT && n < 45);
+    return m <= 5 * LT || n < 45;
 }
 template bool trsm_wave_takes<float>(int64_t, int, int, const View<const float> &, const View<float> &);
 template bool trsm_wave_takes<double>(int64_t, int, int, const View<const double> &, const View<double> &);
@@ -869,7 +906,15 @@ template bool trsm_wave_takes<double>(int64_t, int, int, const View<const double
 template <typename T>
 bool trmm_wave_takes(int64_t batch, int n, int m, const View<const T> &in, const View<T> &out)
 {
-    if (!wave_range(batch, n) || !tri_wave_can<T>(batch, n, m, in, out))
+    if (!tri_wave_can<T>(batch, n, m, in, out) || n <= 2 * LT)
+        return false;
+    // (below 64 items there is no one-workgroup kernel: 4 of n = 33 with 8 vectors, fp32, 12.1 -> 4.0, of n = 64 with 16, fp64, 15.7 -> 6.3)
+    if (batch < 64)
+        return m <= LT;
+    if (!wave_range(batch, n, m))
+        return false;
+    // (640 of n = 56 with 24, 48, 64 vectors 0.97, 0.95, 0.83 times as fast in fp64, of n = 41 1.49, 1.35, 1.74)
+    if (sizeof(T) == 8 && batch <= 1024 && n >= 3 * LT && m > LT)
         return false;
     // 33 to 47 vectors side by side, in rows of no whole 64 bytes, from memory, fp64: the one-workgroup kernel is the faster one (10463 of n = 44
     // with 47 120 -> 150, 23423 of n = 46 with 41 241 -> 317, 24411 of n = 39 with 47 246 -> 294; 3956 of n = 46 with 45, 64 MiB, 46 -> 42, 11077 of
@@ -884,7 +929,7 @@ template bool trmm_wave_takes<double>(int64_t, int, int, const View<const double
 
 // syrk and its rule, any k: 12255 of n = 37 with k = 32 syrk 51 -> 28 / 67 -> 44, its rule 66 -> 37 / 115 -> 71, with k = 64 66 -> 38 /
 // 129 -> 79 and 130 -> 81 / 188 -> 117; 5000 of n = 61 with k = 300 184 -> 128 / 377 -> 243 and 683 -> 340 / 1425 -> 524.
-bool syrk_wave_takes(int64_t batch, int n, int k) { return wave_range(batch, n) && k >= 1; }
+bool syrk_wave_takes(int64_t batch, int n, int k) { return wave_range(batch, n, k) && k >= 1; }
 
 // The gradients of triangular operands, U V^T with one triangle kept: the rule of trmm on 12255 of n = 37 with 16 vectors 97 -> 46 /
 // 128 -> 96, with 40 205 -> 100 / 345 -> 181.  With four tile rows the ten sums leave few wavefronts on a compute unit: 8000 of n = 60
@@ -892,7 +937,7 @@ bool syrk_wave_takes(int64_t batch, int n, int k) { return wave_range(batch, n) 
 template <typename T>
 bool outer_wave_takes(int64_t batch, int n, int m)
 {
-    if (!wave_range(batch, n) || m < 1)
+    if (!wave_range(batch, n, m) || m < 1)
         return false;
     if (n <= 3 * LT)
         return true;
@@ -901,14 +946,18 @@ bool outer_wave_takes(int64_t batch, int n, int m)
 template bool outer_wave_takes<float>(int64_t, int, int);
 template bool outer_wave_takes<double>(int64_t, int, int);
 
-#define LA_GO_WAVE(KERNEL, ...)                                                                                                  \
+#define LA_GO_WAVE_FROM(K0, KERNEL, ...)                                                                                          \
     do {                                                                                                                         \
         const dim3 grid((unsigned)((batch + SW_WAVES - 1) / SW_WAVES)), block(SW_WAVES * 64);                                    \
-        if (n <= 3 * LT)                                                                                                         \
+        if (n <= 2 * LT)                                                                                                         \
+            LA_LAUNCH((KERNEL(K0)), grid, block, 0, st, __VA_ARGS__);                                                            \
+        else if (n <= 3 * LT)                                                                                                    \
             LA_LAUNCH((KERNEL(3)), grid, block, 0, st, __VA_ARGS__);                                                             \
         else                                                                                                                     \
             LA_LAUNCH((KERNEL(4)), grid, block, 0, st, __VA_ARGS__);                                                             \
     } while (0)
+#define LA_GO_WAVE(KERNEL, ...) LA_GO_WAVE_FROM(2, KERNEL, __VA_ARGS__)
+#define LA_GO_WAVE_33(KERNEL, ...) LA_GO_WAVE_FROM(3, KERNEL, __VA_ARGS__)  // (n > 32)
 
 template <typename T>
 la_status launch_potrf_wave(View<const T> A, View<T> L, int32_t *info, int64_t batch, int n, hipStream_t st)
@@ -963,9 +1012,9 @@ la_status launch_trmm_wave(View<const T> Lam, View<const T> Xin, View<T> X, int6
 #define LA_K(K_) k_trmm_wave<T, K_, true>
 #define LA_K2(K_) k_trmm_wave<T, K_, false>
     if (fwd)
-        LA_GO_WAVE(LA_K, Lam, Xin, X, batch, n, m, alpha);
+        LA_GO_WAVE_33(LA_K, Lam, Xin, X, batch, n, m, alpha);
     else
-        LA_GO_WAVE(LA_K2, Lam, Xin, X, batch, n, m, alpha);
+        LA_GO_WAVE_33(LA_K2, Lam, Xin, X, batch, n, m, alpha);
 #undef LA_K
 #undef LA_K2
     return launch_check("trmm_wave");
@@ -974,7 +1023,7 @@ template <typename T>
 la_status launch_symm_wave(T alpha, int64_t batch, int n, int k, View<const T> G, View<const T> A, View<T> Out, hipStream_t st)
 {
 #define LA_K(K_) k_symm_wave<T, K_>
-    LA_GO_WAVE(LA_K, G, A, Out, batch, n, k, alpha);
+    LA_GO_WAVE_33(LA_K, G, A, Out, batch, n, k, alpha);
 #undef LA_K
     return launch_check("symm_wave");
 }
@@ -985,11 +1034,11 @@ la_status launch_outer_wave(int tri, T alpha, int64_t batch, int n, int k, View<
 #define LA_K1(K_) k_outer_wave<T, K_, 1>
 #define LA_K2(K_) k_outer_wave<T, K_, 2>
     if (tri == 0)
-        LA_GO_WAVE(LA_K0, U, V, C, batch, n, k, alpha);
+        LA_GO_WAVE_33(LA_K0, U, V, C, batch, n, k, alpha);
     else if (tri == 1)
-        LA_GO_WAVE(LA_K1, U, V, C, batch, n, k, alpha);
+        LA_GO_WAVE_33(LA_K1, U, V, C, batch, n, k, alpha);
     else
-        LA_GO_WAVE(LA_K2, U, V, C, batch, n, k, alpha);
+        LA_GO_WAVE_33(LA_K2, U, V, C, batch, n, k, alpha);
 #undef LA_K0
 #undef LA_K1
 #undef LA_K2

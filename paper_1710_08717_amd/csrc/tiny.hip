@@ -84,9 +84,7 @@ __global__ __launch_bounds__(WAVE) void k_potrf_tiny(View<const T> A, View<T> L,
 // so that every broadcast stays inside a 16-lane DPP row (one instruction with the multiply-add)
 // instead of going through the LDS crossbar or a scalar register as with 32 or 64 lanes per
 // matrix; four matrices per wavefront.  Column j = 16 jh + jl: its entries sit in register j of
-// row slot jh of lane jl.  R = 2 for n <= 32, R = 3 for n <= 48 (R N registers per lane; in fp64 R = 3 overflows
-// into accumulation registers, takes the guarded broadcast multiply-add and is still 1.1 to 1.8 times faster
-// than 64 lanes per matrix).
+// row slot jh of lane jl.  R = 2 (n <= 32).
 // ---------------------------------------------------------------------------------
 template <typename T, int R, int N = 16 * R>
 __global__ __launch_bounds__(WAVE) void k_potrf_tiny_rows(View<const T> A, View<T> L, int32_t *info, int info_off,
@@ -437,7 +435,7 @@ la_status launch_potrf_tiny(View<const T> A, View<T> L, int32_t *info, int info_
 {
     if (batch <= 0 || nb <= 0)
         return LA_OK;
-    if (nb > 64)
+    if (nb > 32)
         return LA_ERR_UNSUPPORTED;
     if (nb <= 4) {
         constexpr int MPW = Stage<T, 4>::MPW;
@@ -454,29 +452,16 @@ la_status launch_potrf_tiny(View<const T> A, View<T> L, int32_t *info, int info_
         constexpr int MPW = Stage<T, 16>::MPW;
         LA_LAUNCH((k_potrf_tiny<T, 16>), dim3((unsigned)((batch + MPW - 1) / MPW)), dim3(WAVE), 0, st, A, L,
                            info, info_off, batch, nb);
-    } else if (nb <= 48) {
-        // 16 lanes per matrix, 2 or 3 rows per lane.  (4 rows per lane for n <= 64 need all 256
-        // registers and one wavefront per SIMD: no faster than 64 lanes per matrix at n = 64,
-        // slower below.)
+    } else {
+        // 16 lanes per matrix, two rows per lane; the column count kept is 24 or 32: the eliminations cost its cube
         constexpr int MPW = 4;
         const dim3 grid((unsigned)((batch + MPW - 1) / MPW));
-        // the column count kept is the next of 24, 32, 40, 48: the eliminations cost its cube
-        if (nb <= 24) {
+        if (nb <= 24)
             LA_LAUNCH((k_potrf_tiny_rows<T, 2, 24>), grid, dim3(WAVE), (sizeof(T) * Stage<T, 24, MPW>::ELEMS), st, A, L,
                       info, info_off, batch, nb);
-        } else if (nb <= 32) {
+        else
             LA_LAUNCH((k_potrf_tiny_rows<T, 2, 32>), grid, dim3(WAVE), (sizeof(T) * Stage<T, 32, MPW>::ELEMS), st, A, L,
                       info, info_off, batch, nb);
-        } else if (nb <= 40) {
-            LA_LAUNCH((k_potrf_tiny_rows<T, 3, 40>), grid, dim3(WAVE), (sizeof(T) * Stage<T, 40, MPW>::ELEMS), st, A, L,
-                      info, info_off, batch, nb);
-        } else {
-            LA_LAUNCH((k_potrf_tiny_rows<T, 3, 48>), grid, dim3(WAVE), (sizeof(T) * Stage<T, 48, MPW>::ELEMS), st, A, L,
-                      info, info_off, batch, nb);
-        }
-    } else {
-        LA_LAUNCH((k_potrf_tiny<T, 64>), dim3((unsigned)batch), dim3(WAVE), 0, st, A, L, info, info_off,
-                           batch, nb);
     }
     return launch_check("potrf_tiny");
 }

@@ -193,17 +193,13 @@ la_status launch_tri_tiny(bool solve, bool fwd, T alpha, int64_t batch, int n, i
 {
     if (batch <= 0 || n <= 0 || m <= 0)
         return LA_OK;
-    if (n > 64 || m > TRI_MC || batch > 0x7fffffffll)
+    if (n > 16 || m > TRI_MC || batch > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
     if (n <= 4)
         return launch_tri_tiny_g<T, 4>(solve, Lam, Bin, Bout, batch, n, m, fwd, img_tr, alpha, st);
     if (n <= 8)
         return launch_tri_tiny_g<T, 8>(solve, Lam, Bin, Bout, batch, n, m, fwd, img_tr, alpha, st);
-    if (n <= 16)
-        return launch_tri_tiny_g<T, 16>(solve, Lam, Bin, Bout, batch, n, m, fwd, img_tr, alpha, st);
-    if (n <= 32)  // broadcasts through ds_bpermute
-        return launch_tri_tiny_g<T, 32>(solve, Lam, Bin, Bout, batch, n, m, fwd, img_tr, alpha, st);
-    return launch_tri_tiny_g<T, 64>(solve, Lam, Bin, Bout, batch, n, m, fwd, img_tr, alpha, st);  // v_readlane
+    return launch_tri_tiny_g<T, 16>(solve, Lam, Bin, Bout, batch, n, m, fwd, img_tr, alpha, st);
 }
 
 template la_status launch_tri_tiny<float>(bool, bool, float, int64_t, int, int, View<const float>, const float *, float *,
