@@ -407,10 +407,10 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
 // 4.90 -> 4.48, 4096 1.83 -> 1.60 / 1.02 -> 0.92, 3001 1.05 -> 0.90 / 0.71 -> 0.57, 1000 of n = 300 2.80 -> 2.06 / 1.51 -> 1.20.
 // ---------------------------------------------------------------------------------
 // Columns [o, q) of the rows [o, end); `inv` holds the inverses of the diagonal blocks of n0 from row c0 on.  A column wider than n0 has its panel
-// solved block by block, from the right, and its diagonal block swept in turn.
+// solved block by block, from the right, and its diagonal block swept in turn.  pad: the rows of Lam and W are padded (GemmOpts::padA).
 template <typename T>
 static la_status sweep_column(View<const T> Lam, View<const T> inv, int c0, View<const T> G, View<T> W, View<T> X, View<T> Y, int64_t batch,
-                              int o, int q, int end, int n0, bool aliased, hipStream_t st)
+                              int o, int q, int end, int n0, bool aliased, bool pad, hipStream_t st)
 {
     const int w = q - o, r = end - q;
     View<const T> L11 = Lam.sub(o, o), G11 = G.sub(o, o);
@@ -422,6 +422,7 @@ static la_status sweep_column(View<const T> Lam, View<const T> inv, int c0, View
             LA_TRY(launch_copy<T>(G11, W11, batch, w, w, T(1), 2, st));
         GemmOpts plain, ol, om;
         plain.split_if_room = om.split_if_room = 1;  // (the inverses had the first pick of the workspace)
+        plain.padA = plain.padB = ol.padA = ol.padB = om.padA = om.padB = pad;
         LA_TRY(launch_gemm<T>(cv(W).sub(q, q), L21, W12.t(), batch, r, w, r, T(-2), T(1), plain, st));
         ol.triB = 1;
         for (int b = (w - 1) / n0 * n0; b >= 0; b -= n0) {
@@ -439,9 +440,10 @@ static la_status sweep_column(View<const T> Lam, View<const T> inv, int c0, View
     }
     if (w > n0) {
         for (int b = (w - 1) / n0 * n0; b >= 0; b -= n0)
-            LA_TRY(sweep_column<T>(Lam, inv, c0, G, W, X, Y, batch, o + b, w - b < n0 ? q : o + b + n0, q, n0, aliased, st));
+            LA_TRY(sweep_column<T>(Lam, inv, c0, G, W, X, Y, batch, o + b, w - b < n0 ? q : o + b + n0, q, n0, aliased, pad, st));
     } else {
         GemmOpts op;
+        op.padA = op.padB = pad;
         op.triA = 2;
         op.triB = 1;
         op.maskC = 1;
@@ -464,6 +466,23 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
                                 hipStream_t st)
 {
     ArenaFrame frame;
+    // Rows that are no whole number of 16-byte chunks: with room for two more squares the sweep of one large matrix runs on copies with padded
+    // rows, and its products on aligned operands.  us, fp64 / fp32, n = 2501 648 / 426 -> 621 / 426, 3001 864 / 546 -> 820 / 532, 5003
+    // 2714 / 1536 -> 2328 / 1424, 7423 6844 / 3825 -> 6351 / 3613; several smaller matrices lose: 16 x 1001^2 584 / 355 -> 658 / 446, 100 x 401^2
+    // 473 / 284 -> 532 / 370, 4 x 2050^2 fp32 632 -> 684.
+    View<T> out = W;
+    const int ld = padded<T>(n);
+    const bool pad = ld != n && batch == 1 && n >= 2500 && arena_room((size_t)(2 * (int64_t)n * ld + sweep_scratch(n0, n)) * sizeof(T));
+    if (pad) {
+        View<T> sc[2];
+        LA_TRY(scratch_views<T>(batch, n, 2, sc, ld));
+        LA_TRY(launch_copy<T>(Lam, sc[0], batch, n, n, T(1), 2, st));
+        LA_TRY(launch_copy<T>(G, sc[1], batch, n, n, T(1), 2, st));
+        Lam = cv(sc[0]);
+        W = sc[1];
+        G = cv(W);
+        aliased = true;
+    }
     int cols = n;  // whole blocks, or all of them
     while (!arena_room((size_t)(batch * sweep_scratch(n0, cols)) * sizeof(T)) && (cols > n0 || n0 > 2 * NB)) {
         if (cols > n0) {
@@ -486,11 +505,11 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
         const int c0 = o / cols * cols, cc = n - c0 < cols ? n - c0 : cols;  // the columns whose inverses are there
         if (q == c0 + cc) {
             LA_TRY(launch_tri_inverse128<T>(Lam.sub(c0, c0), Li, batch, cc, st));
-            LA_TRY(inverse_merge<T>(Lam.sub(c0, c0), Li, X, batch, cc, n0, st, 1));
+            LA_TRY(inverse_merge<T>(Lam.sub(c0, c0), Li, X, batch, cc, n0, st, pad ? 2 : 1));
         }
-        LA_TRY(sweep_column<T>(Lam, cv(Li), c0, G, W, X, Y, batch, o, q, n, n0, aliased, st));
+        LA_TRY(sweep_column<T>(Lam, cv(Li), c0, G, W, X, Y, batch, o, q, n, n0, aliased, pad, st));
     }
-    return LA_OK;
+    return pad ? launch_copy<T>(cv(W), out.cs == 1 ? out : out.t(), batch, n, n, T(1), 0, st) : LA_OK;  // (symmetric)
 }
 
 // ---------------------------------------------------------------------------------

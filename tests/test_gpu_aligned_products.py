@@ -68,7 +68,7 @@ def test_syrk_symmetric(dt, b, n, k):
 
 
 @pytest.mark.parametrize("dt,b,n", [(torch.float64, 1, 801), (torch.float64, 2, 1001), (torch.float32, 1, 1026), (torch.float32, 1, 803),
-                                    (torch.float64, 3, 333), (torch.float32, 2, 131)])
+                                    (torch.float64, 3, 333), (torch.float32, 2, 131), (torch.float64, 1, 2501), (torch.float32, 1, 2502)])
 @pytest.mark.parametrize("lower", [True, False])
 def test_padded_working_copies(dt, b, n, lower):
     """Odd rows: factor and gradient with the whole workspace (working copies with padded rows) and without room for those."""
