@@ -1067,25 +1067,17 @@ static la_status potri_backward_t(int lower, int64_t batch, int n, const void *L
                      : launch_potri_backward_wave<T>(Lam, Bv, G, X, batch, n, st);
     }
     GemmOpts o;
-    // Both products in one launch on G + G^T (8192 matrices, the whole rule, us, fp32 and fp64: n = 17 127 -> 73 and 206 -> 89,
-    // 40 215 -> 144 and 433 -> 251; 4096 of n = 48 118 -> 90 and 198 -> 146); at n = 64 the tiles of the general product are
-    // full (298 -> 313 us).
-    const bool leaf = n <= 48 && symm_leaf_takes<T>(batch, n, n);
     bool summed;
     LA_TRY(symm_product<T>(G.p, Bv, X, batch, n, n, lower != 0, T(1), &summed, st));
     if (lower) {
-        if (leaf) {  // (B S)^T = S B^T
-            LA_TRY(launch_symm_leaf<T>(T(1), batch, n, n, G, Bv.t(), X.t(), st));
-        } else if (!summed) {
+        if (!summed) {
             LA_TRY(launch_gemm<T>(Bv, G, X, batch, n, n, n, T(1), T(0), o, st));
             LA_TRY(launch_gemm<T>(Bv, G.t(), X, batch, n, n, n, T(1), T(1), o, st));
         }
         LA_TRY(tri_apply_t<T>(true, 1, 1, 1, -1.0, batch, n, n, L, Lbar, Lbar, st));
         return launch_zero_strict_upper<T>(X, batch, n, st);
     }
-    if (leaf) {
-        LA_TRY(launch_symm_leaf<T>(T(1), batch, n, n, G, Bv, X, st));
-    } else if (!summed) {
+    if (!summed) {
         LA_TRY(launch_gemm<T>(G, Bv, X, batch, n, n, n, T(1), T(0), o, st));
         LA_TRY(launch_gemm<T>(G.t(), Bv, X, batch, n, n, n, T(1), T(1), o, st));
     }

@@ -1,7 +1,7 @@
 // Register-resident kernels for small matrices: G lanes of a wavefront own one matrix
 // (lane = row, registers = columns), so a wave64 works on 64/G matrices at once and the
 // column reductions of the factorisation are lane broadcasts (DPP row broadcast for
-// G = 16, LDS crossbar permute for G = 32, v_readlane for G = 64).
+// G = 16).
 //
 // potrf forward: section 4.2 of arXiv 1710.08717 (A = L L^T, positive diagonal).
 // potrf backward: section 4.2 / appendix "potrf":
@@ -471,7 +471,7 @@ la_status launch_backward_tiny(View<const T> L, View<const T> G, View<T> Abar, i
 {
     if (batch <= 0 || n <= 0)
         return LA_OK;
-    if (n > 32)
+    if (n > 24)
         return LA_ERR_UNSUPPORTED;
     if (n <= 4) {
         constexpr int MPW = Stage<T, 4>::MPW;
@@ -488,15 +488,9 @@ la_status launch_backward_tiny(View<const T> L, View<const T> G, View<T> Abar, i
         constexpr int MPW = Stage<T, 16>::MPW;
         LA_LAUNCH((k_backward_tiny<T, 16>), dim3((unsigned)((batch + MPW - 1) / MPW)), dim3(WAVE), 0, st, L,
                            G, Abar, batch, n);
-    } else if (n <= 24) {
+    } else {  // 16 lanes per matrix, two rows per lane
         LA_LAUNCH((k_backward_tiny2<T, 24>), dim3((unsigned)((batch + 3) / 4)), dim3(WAVE), 0, st, L, G, Abar,
                   batch, n);
-    } else {
-        // 16 lanes per matrix, two rows per lane.  In fp64 the kernel needs 294 registers; the overflow lives in
-        // accumulation registers (hence the guarded broadcast multiply-adds), which still beats 32 lanes per
-        // matrix with ds_bpermute broadcasts by 2.5 times (16384 matrices of n = 32: 357 -> 140 us).
-        LA_LAUNCH((k_backward_tiny2<T, 32>), dim3((unsigned)((batch + 3) / 4)), dim3(WAVE), 0, st, L, G, Abar,
-                           batch, n);
     }
     return launch_check("backward_tiny");
 }

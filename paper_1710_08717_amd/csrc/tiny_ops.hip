@@ -1,4 +1,4 @@
-// Operators on many small matrices in lane groups (G = 4 .. 64 lanes of a wavefront per matrix, as in
+// Operators on many small matrices in lane groups (G = 4 .. 16 lanes of a wavefront per matrix, as in
 // tiny.hip): trsm / trmm, syrk and the outer products of the trmm / trsm backward rules, gemm2, the syrk
 // backward rule and potri (section 4.2 of arXiv 1710.08717 and its appendix).  Operands that are not
 // square travel as flat memory images of whole items through LDS.  (Their forms with two rows per lane
@@ -8,7 +8,7 @@
 namespace la {
 
 // ---------------------------------------------------------------------------------
-// trsm / trmm for n <= 64 and at most 16 vectors (section 4.2 "trsm", "trmm"), G lanes per matrix:
+// trsm / trmm for n <= 16 and at most 16 vectors (section 4.2 "trsm", "trmm"), G lanes per matrix:
 // lane i holds row i of M (M = Lam or Lam^T, whichever the operator applies) and row i of the
 // n x m operand, registers = its m columns.  The operand travels as its flat memory image (n x m
 // or, for right-side operators, m x n per item, items back to back): 16-byte loads into LDS,
@@ -707,11 +707,9 @@ la_status launch_potri_tiny(View<const T> Lam, View<T> B, int64_t batch, int n, 
 {
     if (batch <= 0 || n <= 0)
         return LA_OK;
-    if (n > 32 || (batch + 3) / 4 > 0x7fffffffll)
+    if (n > 24 || (batch + 3) / 4 > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
-    if (n > 24) {
-        LA_LAUNCH((k_potri_tiny2<T, 32>), dim3((unsigned)((batch + 3) / 4)), dim3(WAVE), 0, st, Lam, B, batch, n);
-    } else if (n > 16) {
+    if (n > 16) {
         LA_LAUNCH((k_potri_tiny2<T, 24>), dim3((unsigned)((batch + 3) / 4)), dim3(WAVE), 0, st, Lam, B, batch, n);
     } else if (n <= 4) {
         constexpr int MPW = Stage<T, 4>::MPW;

@@ -564,22 +564,17 @@ la_status launch_tri_rows(bool solve, bool fwd, T alpha, int64_t batch, int n, i
 {
     if (batch <= 0 || n <= 0 || m <= 0)
         return LA_OK;
-    if (n <= 16 || n > 32 || m > TRIR_MC || (batch + 3) / 4 > 0x7fffffffll)
+    if (n <= 16 || n > (solve ? 24 : 32) || m > TRIR_MC || (batch + 3) / 4 > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)((batch + ROWS_MPW - 1) / ROWS_MPW)), blk(WAVE);
     const int f = fwd ? 1 : 0, itr = img_tr ? 1 : 0;
 #define LA_TRI_ROWS(NN, SV) LA_LAUNCH((k_tri_rows<T, NN, SV>), grid, blk, 0, st, Lam, Bin, Bout, batch, n, m, f, itr, alpha)
-    if (n <= 24) {
-        if (solve)
-            LA_TRI_ROWS(24, true);
-        else
-            LA_TRI_ROWS(24, false);
-    } else {
-        if (solve)
-            LA_TRI_ROWS(32, true);
-        else
-            LA_TRI_ROWS(32, false);
-    }
+    if (solve)
+        LA_TRI_ROWS(24, true);
+    else if (n <= 24)
+        LA_TRI_ROWS(24, false);
+    else
+        LA_TRI_ROWS(32, false);
 #undef LA_TRI_ROWS
     return launch_check("tri_rows");
 }
