@@ -54,7 +54,8 @@ def _compile(src):
     return obj
 
 
-def _build_host():
+def host_command(src, out):
+    """The compiler's call for the binding's host part."""
     import sysconfig
 
     import torch
@@ -63,11 +64,14 @@ def _build_host():
     inc = [os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
            "/opt/rocm/include", sysconfig.get_paths()["include"]]
     libs = ["torch_python", "torch_cpu", "torch_hip", "c10", "c10_hip"]
-    subprocess.check_call(
-        ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-         f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", *[x for d in inc for x in ("-isystem", d)],
-         "-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "host_call.cpp"), "-o", HOST,
-         "-L", os.path.join(base, "lib"), *[f"-l{x}" for x in libs]])  # (found by torch's own import, which comes first)
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", *[x for d in inc for x in ("-isystem", d)],
+            "-I", os.path.join(ROOT, "include"), src, "-o", out,
+            "-L", os.path.join(base, "lib"), *[f"-l{x}" for x in libs]]  # (found by torch's own import, which comes first)
+
+
+def _build_host():
+    subprocess.check_call(host_command(os.path.join(CSRC, "host_call.cpp"), HOST))
 
 
 def build(force=True, jobs=8):

@@ -17,6 +17,7 @@
 
 #include <initializer_list>
 #include <mutex>
+#include <stdexcept>
 #include <tuple>
 #include <unordered_map>
 
@@ -46,6 +47,17 @@ bool bound = false;
 const c10::DispatchKeySet plain_keys({c10::DispatchKey::CUDA, c10::DispatchKey::AutogradCUDA, c10::DispatchKey::ADInplaceOrView,
                                       c10::DispatchKey::AutocastCUDA});
 
+bool plain(const at::Tensor &t) { return (t.key_set() | plain_keys) == plain_keys; }
+
+// A result or scratch tensor: plain as well, or the call is none of this file's.
+at::Tensor fresh(at::IntArrayRef sizes, const at::TensorOptions &options)
+{
+    at::Tensor t = at::empty(sizes, options.requires_grad(false));
+    if (!plain(t))
+        throw std::runtime_error("not a plain tensor");
+    return t;
+}
+
 // One call's tensors.
 struct Call {
     const at::Tensor *first = nullptr;
@@ -62,7 +74,7 @@ struct Call {
         if (!THPVariable_CheckExact(o))
             return nullptr;
         const at::Tensor &t = THPVariable_Unpack(o);
-        if (!t.defined() || !t.is_cuda() || t.layout() != c10::kStrided || (t.key_set() | plain_keys) != plain_keys || !t.is_contiguous() ||
+        if (!t.defined() || !t.is_cuda() || t.layout() != c10::kStrided || !plain(t) || !t.is_contiguous() ||
             t.dim() > 8)
             return nullptr;
         if (!first) {
@@ -79,17 +91,19 @@ struct Call {
         }
         return &t;
     }
-    // plain circumstances: asked once the tensors are there
+    // plain circumstances: asked once the tensors are there.  (A mode or a transform -- grad, jvp, vmap, functionalisation, tracing -- wraps what is
+    // allocated inside it, whatever the arguments are: its key is among the included ones.)
     bool here() const
     {
         return bound && device == c10::hip::current_device() && !c10::impl::TorchDispatchModeTLS::any_modes_set() &&
-               !at::impl::torch_function_mode_enabled();
+               !at::impl::torch_function_mode_enabled() &&
+               (c10::impl::tls_local_dispatch_key_set().included_ | c10::default_included_set) == c10::default_included_set;
     }
     void scratch(size_t need)
     {
         if (!need)
             return;
-        workspace = at::empty({(int64_t)need}, first->options().dtype(at::kByte).requires_grad(false));
+        workspace = fresh({(int64_t)need}, first->options().dtype(at::kByte));
         wp = workspace.data_ptr();
         wb = need;
     }
@@ -151,12 +165,20 @@ bool number(PyObject *o, double &v)
     return true;
 }
 
+// Allocations and the library's call, without the GIL, as torch makes its own: an allocation may wait for the GPU, and the GPU for a callback in
+// Python.  An exception does not leave with the GIL released.  (Only std::exception is caught, here and below: a thread that meets the end of the
+// interpreter where it takes the GIL back is unwound, which must not be held up.)
 template <class F>
 la_status unlocked(F &&f)
 {
-    la_status s;
-    Py_BEGIN_ALLOW_THREADS s = f();
-    Py_END_ALLOW_THREADS return s;
+    la_status s = LA_ERR_RUNTIME;
+    PyThreadState *state = PyEval_SaveThread();
+    try {
+        s = f();
+    } catch (const std::exception &) {
+    }
+    PyEval_RestoreThread(state);
+    return s;
 }
 
 PyObject *wrap(const at::Tensor &t) { return THPVariable_Wrap(t); }
@@ -167,12 +189,12 @@ PyObject *pair(const at::Tensor &a, const at::Tensor &b)
     Py_XDECREF(y);
     return r;
 }
-at::Tensor like(const at::Tensor &t) { return at::empty(t.sizes(), t.options().requires_grad(false)); }
+at::Tensor like(const at::Tensor &t) { return fresh(t.sizes(), t.options()); }
 at::Tensor shaped(const at::Tensor &t, int drop, std::initializer_list<int64_t> last)
 {
     std::vector<int64_t> s(t.sizes().begin(), t.sizes().end() - drop);
     s.insert(s.end(), last);
-    return at::empty(s, t.options().requires_grad(false));
+    return fresh(s, t.options());
 }
 
 // A C++ exception (no memory, say) leaves the call to the Python code, which meets it again and reports it as ever.
@@ -184,7 +206,7 @@ at::Tensor shaped(const at::Tensor &t, int drop, std::initializer_list<int64_t> 
             try {                                                                      \
                 if (PyObject *r = name##_call(a))                                      \
                     return r;                                                          \
-            } catch (...) {                                                            \
+            } catch (const std::exception &) {                                         \
             }                                                                          \
             if (PyErr_Occurred())                                                      \
                 PyErr_Clear();                                                         \
@@ -211,11 +233,14 @@ LA_FUNCTION(potrf, 2)
     if (!square(A, n) || !flag(a[1], lower) || !c.here())
         return nullptr;
     c.batch = leading(*A, 2);
-    at::Tensor L = like(*A);
-    c.scratch(LA_OP_POTRF, (int)n, 0, 0);
+    at::Tensor L;
     void *st = c.stream();
-    return unlocked([&] { return lib.potrf(c.dt, lower, c.batch, (int)n, A->data_ptr(), L.data_ptr(), nullptr, c.wp, c.wb, st); }) == LA_OK ? wrap(L)
-                                                                                                                            : nullptr;
+    const la_status s = unlocked([&] {
+        L = like(*A);
+        c.scratch(LA_OP_POTRF, (int)n, 0, 0);
+        return lib.potrf(c.dt, lower, c.batch, (int)n, A->data_ptr(), L.data_ptr(), nullptr, c.wp, c.wb, st);
+    });
+    return s == LA_OK ? wrap(L) : nullptr;
 }
 
 LA_FUNCTION(potrf_backward, 3)
@@ -227,12 +252,14 @@ LA_FUNCTION(potrf_backward, 3)
     if (!square(L, n) || !G || G->sizes() != L->sizes() || !flag(a[2], lower) || !c.here())
         return nullptr;
     c.batch = leading(*L, 2);
-    at::Tensor W = like(*G);
-    c.scratch(LA_OP_POTRF_BACKWARD, (int)n, 0, 0);
+    at::Tensor W;
     void *st = c.stream();
-    return unlocked([&] { return lib.potrf_backward(c.dt, lower, c.batch, (int)n, L->data_ptr(), G->data_ptr(), W.data_ptr(), c.wp, c.wb, st); }) == LA_OK
-               ? wrap(W)
-               : nullptr;
+    const la_status s = unlocked([&] {
+        W = like(*G);
+        c.scratch(LA_OP_POTRF_BACKWARD, (int)n, 0, 0);
+        return lib.potrf_backward(c.dt, lower, c.batch, (int)n, L->data_ptr(), G->data_ptr(), W.data_ptr(), c.wp, c.wb, st);
+    });
+    return s == LA_OK ? wrap(W) : nullptr;
 }
 
 // the vectors of trsm / trmm: m of them, or -1
@@ -257,15 +284,15 @@ LA_FUNCTION(tri, 7)
     if (m < 0 || m > INT32_MAX || !c.here())
         return nullptr;
     c.batch = leading(*L, 2);
-    at::Tensor B = like(*A);
-    c.scratch(solve ? LA_OP_TRSM : LA_OP_TRMM, (int)n, (int)m, 0);
+    at::Tensor B;
     void *st = c.stream();
-    return unlocked([&] {
-               return (solve ? lib.trsm : lib.trmm)(c.dt, lower, trans, right, alpha, c.batch, (int)n, (int)m, L->data_ptr(), A->data_ptr(), B.data_ptr(),
-                                                    c.wp, c.wb, st);
-           }) == LA_OK
-               ? wrap(B)
-               : nullptr;
+    const la_status s = unlocked([&] {
+        B = like(*A);
+        c.scratch(solve ? LA_OP_TRSM : LA_OP_TRMM, (int)n, (int)m, 0);
+        return (solve ? lib.trsm : lib.trmm)(c.dt, lower, trans, right, alpha, c.batch, (int)n, (int)m, L->data_ptr(), A->data_ptr(), B.data_ptr(),
+                                             c.wp, c.wb, st);
+    });
+    return s == LA_OK ? wrap(B) : nullptr;
 }
 
 // (solve, L, X, Bbar, lower, trans, rightside, alpha)
@@ -283,15 +310,16 @@ LA_FUNCTION(tri_backward, 8)
     if (m < 0 || m > INT32_MAX || !c.here())
         return nullptr;
     c.batch = leading(*L, 2);
-    at::Tensor Ab = like(*G), Lb = like(*L);
-    c.scratch(solve ? LA_OP_TRSM_BACKWARD : LA_OP_TRMM_BACKWARD, (int)n, (int)m, 0);
+    at::Tensor Ab, Lb;
     void *st = c.stream();
-    return unlocked([&] {
-               return (solve ? lib.trsm_backward : lib.trmm_backward)(c.dt, lower, trans, right, alpha, c.batch, (int)n, (int)m, L->data_ptr(),
-                                                                      X->data_ptr(), G->data_ptr(), Ab.data_ptr(), Lb.data_ptr(), c.wp, c.wb, st);
-           }) == LA_OK
-               ? pair(Ab, Lb)
-               : nullptr;
+    const la_status s = unlocked([&] {
+        Ab = like(*G);
+        Lb = like(*L);
+        c.scratch(solve ? LA_OP_TRSM_BACKWARD : LA_OP_TRMM_BACKWARD, (int)n, (int)m, 0);
+        return (solve ? lib.trsm_backward : lib.trmm_backward)(c.dt, lower, trans, right, alpha, c.batch, (int)n, (int)m, L->data_ptr(),
+                                                               X->data_ptr(), G->data_ptr(), Ab.data_ptr(), Lb.data_ptr(), c.wp, c.wb, st);
+    });
+    return s == LA_OK ? pair(Ab, Lb) : nullptr;
 }
 
 LA_FUNCTION(syrk, 3)
@@ -306,11 +334,14 @@ LA_FUNCTION(syrk, 3)
     if (!small(n) || k > INT32_MAX || !c.here())
         return nullptr;
     c.batch = leading(*A, 2);
-    at::Tensor B = shaped(*A, 2, {n, n});
-    c.scratch(LA_OP_SYRK, (int)n, 0, (int)k);
+    at::Tensor B;
     void *st = c.stream();
-    return unlocked([&] { return lib.syrk(c.dt, trans, alpha, c.batch, (int)n, (int)k, A->data_ptr(), B.data_ptr(), c.wp, c.wb, st); }) == LA_OK ? wrap(B)
-                                                                                                                             : nullptr;
+    const la_status s = unlocked([&] {
+        B = shaped(*A, 2, {n, n});
+        c.scratch(LA_OP_SYRK, (int)n, 0, (int)k);
+        return lib.syrk(c.dt, trans, alpha, c.batch, (int)n, (int)k, A->data_ptr(), B.data_ptr(), c.wp, c.wb, st);
+    });
+    return s == LA_OK ? wrap(B) : nullptr;
 }
 
 LA_FUNCTION(syrk_backward, 4)
@@ -325,14 +356,14 @@ LA_FUNCTION(syrk_backward, 4)
     if (G->size(-1) != n || G->size(-2) != n || leading(*A, 2) != leading(*G, 2) || !small(n) || k > INT32_MAX || !c.here())
         return nullptr;
     c.batch = leading(*A, 2);
-    at::Tensor B = like(*A);
-    c.scratch(LA_OP_SYRK_BACKWARD, (int)n, 0, (int)k);
+    at::Tensor B;
     void *st = c.stream();
-    return unlocked([&] {
-               return lib.syrk_backward(c.dt, trans, alpha, c.batch, (int)n, (int)k, A->data_ptr(), G->data_ptr(), B.data_ptr(), c.wp, c.wb, st);
-           }) == LA_OK
-               ? wrap(B)
-               : nullptr;
+    const la_status s = unlocked([&] {
+        B = like(*A);
+        c.scratch(LA_OP_SYRK_BACKWARD, (int)n, 0, (int)k);
+        return lib.syrk_backward(c.dt, trans, alpha, c.batch, (int)n, (int)k, A->data_ptr(), G->data_ptr(), B.data_ptr(), c.wp, c.wb, st);
+    });
+    return s == LA_OK ? wrap(B) : nullptr;
 }
 
 // sizes of C = t_a(A) t_b(B)
@@ -356,14 +387,14 @@ LA_FUNCTION(gemm2, 5)
     if (!flag(a[2], ta) || !flag(a[3], tb) || !number(a[4], alpha) || !product(A, B, ta, tb, m, n, k) || !c.here())
         return nullptr;
     c.batch = leading(*A, 2);
-    at::Tensor C = shaped(*A, 2, {m, n});
-    c.scratch(LA_OP_GEMM2, (int)n, (int)m, (int)k);
+    at::Tensor C;
     void *st = c.stream();
-    return unlocked([&] {
-               return lib.gemm2(c.dt, ta, tb, alpha, c.batch, (int)m, (int)n, (int)k, A->data_ptr(), B->data_ptr(), C.data_ptr(), c.wp, c.wb, st);
-           }) == LA_OK
-               ? wrap(C)
-               : nullptr;
+    const la_status s = unlocked([&] {
+        C = shaped(*A, 2, {m, n});
+        c.scratch(LA_OP_GEMM2, (int)n, (int)m, (int)k);
+        return lib.gemm2(c.dt, ta, tb, alpha, c.batch, (int)m, (int)n, (int)k, A->data_ptr(), B->data_ptr(), C.data_ptr(), c.wp, c.wb, st);
+    });
+    return s == LA_OK ? wrap(C) : nullptr;
 }
 
 LA_FUNCTION(gemm2_backward, 6)
@@ -377,15 +408,16 @@ LA_FUNCTION(gemm2_backward, 6)
         G->size(-1) != n || leading(*G, 2) != leading(*A, 2) || !c.here())
         return nullptr;
     c.batch = leading(*A, 2);
-    at::Tensor Ab = like(*A), Bb = like(*B);
-    c.scratch(LA_OP_GEMM2_BACKWARD, (int)n, (int)m, (int)k);
+    at::Tensor Ab, Bb;
     void *st = c.stream();
-    return unlocked([&] {
-               return lib.gemm2_backward(c.dt, ta, tb, alpha, c.batch, (int)m, (int)n, (int)k, A->data_ptr(), B->data_ptr(), G->data_ptr(), Ab.data_ptr(),
-                                         Bb.data_ptr(), c.wp, c.wb, st);
-           }) == LA_OK
-               ? pair(Ab, Bb)
-               : nullptr;
+    const la_status s = unlocked([&] {
+        Ab = like(*A);
+        Bb = like(*B);
+        c.scratch(LA_OP_GEMM2_BACKWARD, (int)n, (int)m, (int)k);
+        return lib.gemm2_backward(c.dt, ta, tb, alpha, c.batch, (int)m, (int)n, (int)k, A->data_ptr(), B->data_ptr(), G->data_ptr(), Ab.data_ptr(),
+                                  Bb.data_ptr(), c.wp, c.wb, st);
+    });
+    return s == LA_OK ? pair(Ab, Bb) : nullptr;
 }
 
 LA_FUNCTION(potri, 2)
@@ -397,10 +429,14 @@ LA_FUNCTION(potri, 2)
     if (!square(L, n) || !flag(a[1], lower) || !c.here())
         return nullptr;
     c.batch = leading(*L, 2);
-    at::Tensor B = like(*L);
-    c.scratch(LA_OP_POTRI, (int)n, 0, 0);
+    at::Tensor B;
     void *st = c.stream();
-    return unlocked([&] { return lib.potri(c.dt, lower, c.batch, (int)n, L->data_ptr(), B.data_ptr(), c.wp, c.wb, st); }) == LA_OK ? wrap(B) : nullptr;
+    const la_status s = unlocked([&] {
+        B = like(*L);
+        c.scratch(LA_OP_POTRI, (int)n, 0, 0);
+        return lib.potri(c.dt, lower, c.batch, (int)n, L->data_ptr(), B.data_ptr(), c.wp, c.wb, st);
+    });
+    return s == LA_OK ? wrap(B) : nullptr;
 }
 
 LA_FUNCTION(potri_backward, 4)
@@ -412,14 +448,14 @@ LA_FUNCTION(potri_backward, 4)
     if (!square(L, n) || !G || B->sizes() != L->sizes() || G->sizes() != L->sizes() || !flag(a[3], lower) || !c.here())
         return nullptr;
     c.batch = leading(*L, 2);
-    at::Tensor X = like(*L);
-    c.scratch(LA_OP_POTRI_BACKWARD, (int)n, 0, 0);
+    at::Tensor X;
     void *st = c.stream();
-    return unlocked([&] {
-               return lib.potri_backward(c.dt, lower, c.batch, (int)n, L->data_ptr(), B->data_ptr(), G->data_ptr(), X.data_ptr(), c.wp, c.wb, st);
-           }) == LA_OK
-               ? wrap(X)
-               : nullptr;
+    const la_status s = unlocked([&] {
+        X = like(*L);
+        c.scratch(LA_OP_POTRI_BACKWARD, (int)n, 0, 0);
+        return lib.potri_backward(c.dt, lower, c.batch, (int)n, L->data_ptr(), B->data_ptr(), G->data_ptr(), X.data_ptr(), c.wp, c.wb, st);
+    });
+    return s == LA_OK ? wrap(X) : nullptr;
 }
 
 LA_FUNCTION(sumlogdiag, 1)
@@ -429,10 +465,14 @@ LA_FUNCTION(sumlogdiag, 1)
     int64_t n;
     if (!square(L, n) || !c.here())
         return nullptr;
-    at::Tensor o = shaped(*L, 2, {});
+    at::Tensor o;
     void *st = c.stream();
     const int64_t batch = leading(*L, 2);
-    return unlocked([&] { return lib.sumlogdiag(c.dt, batch, (int)n, L->data_ptr(), o.data_ptr(), st); }) == LA_OK ? wrap(o) : nullptr;
+    const la_status s = unlocked([&] {
+        o = shaped(*L, 2, {});
+        return lib.sumlogdiag(c.dt, batch, (int)n, L->data_ptr(), o.data_ptr(), st);
+    });
+    return s == LA_OK ? wrap(o) : nullptr;
 }
 
 LA_FUNCTION(gp_criterion, 2)
@@ -443,14 +483,15 @@ LA_FUNCTION(gp_criterion, 2)
     if (!square(A, n) || !y || y->dim() < 1 || y->size(-1) != n || leading(*y, 1) != leading(*A, 2) || !c.here())
         return nullptr;
     c.batch = leading(*A, 2);
-    at::Tensor Ab = like(*A), loss = shaped(*A, 2, {});
-    c.scratch(lib.gp_workspace_bytes(c.dt, c.batch, (int)n));
+    at::Tensor Ab, loss;
     void *st = c.stream();
-    return unlocked([&] {
-               return lib.gp_criterion(c.dt, c.batch, (int)n, A->data_ptr(), y->data_ptr(), loss.data_ptr(), Ab.data_ptr(), nullptr, c.wp, c.wb, st);
-           }) == LA_OK
-               ? pair(loss, Ab)
-               : nullptr;
+    const la_status s = unlocked([&] {
+        Ab = like(*A);
+        loss = shaped(*A, 2, {});
+        c.scratch(lib.gp_workspace_bytes(c.dt, c.batch, (int)n));
+        return lib.gp_criterion(c.dt, c.batch, (int)n, A->data_ptr(), y->data_ptr(), loss.data_ptr(), Ab.data_ptr(), nullptr, c.wp, c.wb, st);
+    });
+    return s == LA_OK ? pair(loss, Ab) : nullptr;
 }
 
 // bind(path): the library whose functions are called

@@ -1,10 +1,16 @@
 """The binding's two ways to the library: plain calls through csrc/host_call.cpp give what the ctypes calls give, bit for bit, and all other calls
 are left to these."""
+import os
+import re
+import shutil
+import subprocess
+import sys
+
 import pytest
 import torch
 
 import paper_1710_08717_amd as la
-from paper_1710_08717_amd import binding
+from paper_1710_08717_amd import binding, build
 
 
 def spd(batch, n, dt):
@@ -82,3 +88,114 @@ def test_host_call_leaves_cpu_tensors():
     assert binding._host.potrf(A, True) is None and binding._host.gp_criterion(A, A[:, 0]) is None
     with pytest.raises(la.LaError):
         la.potrf(A)
+
+
+TRANSFORMS = {
+    "grad": lambda f, x: torch.func.grad(f)(x), "jvp": lambda f, x: torch.func.jvp(f, (x,), (x,)), "jacrev": lambda f, x: torch.func.jacrev(f)(x),
+    "hessian": lambda f, x: torch.func.hessian(f)(x), "vmap": lambda f, x: torch.func.vmap(f)(x[:, None]),
+    "functionalize": lambda f, x: torch.func.functionalize(f)(x),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", TRANSFORMS)
+@pytest.mark.parametrize("n", [8, 300])  # without and with a workspace
+def test_transforms_over_a_closed_over_tensor_go_by_ctypes(name, n):
+    """grad and the like wrap what is allocated inside them: an error that names it, as ever, where the result has no storage; vmap does not"""
+    torch.manual_seed(0)
+    A, x = spd(2, n, torch.float64).cuda(), torch.ones(3, device="cuda", dtype=torch.float64)
+    L, R, y = la.potrf(A), torch.randn(2, n, 3, dtype=torch.float64).cuda(), torch.randn(2, n, dtype=torch.float64).cuda()
+    seen, raised = [], []
+
+    def f(v):
+        for k, c in table.items():
+            try:
+                seen.append((k, c()))
+            except RuntimeError as e:
+                raised.append((k, str(e)))
+        return v.sum()
+
+    table = calls(L, A, R, y)
+    want = {k: c() for k, c in table.items()}
+    TRANSFORMS[name](f, x)
+    if name == "vmap":
+        assert not raised
+        for k, got in seen:
+            for a, b in zip(*[(t if isinstance(t, tuple) else (t,)) for t in (got, want[k])]):
+                assert torch.equal(a, b), k
+    elif name != "functionalize":
+        assert {k for k, _ in raised} == set(table) and all("storage" in e for _, e in raised), raised
+    assert torch.equal(la.potrf(A), L)
+
+
+# host_call.cpp with its device checks turned to the CPU, on a library whose functions do nothing: the paths that leave a call, without a GPU
+CPU = [("t.is_cuda()", "t.is_cpu()"), ("DispatchKey::CUDA", "DispatchKey::CPU"), ("DispatchKey::AutogradCUDA", "DispatchKey::AutogradCPU"),
+       ("DispatchKey::AutocastCUDA", "DispatchKey::AutocastCPU"), ("c10::hip::current_device()", "-1"),
+       ("(void *)c10::hip::getCurrentHIPStreamMasqueradingAsCUDA(device).stream()", "nullptr"), ("_la_host", "_cpu_host")]
+WORKER = """
+import ctypes, sys, threading, torch
+sys.path.insert(0, sys.argv[1])
+import _cpu_host as h
+stub = ctypes.CDLL(sys.argv[1] + "/stub.so")
+h.bind(sys.argv[1] + "/stub.so")
+need, wait, entered = (ctypes.c_size_t.in_dll(stub, q) for q in ("stub_need", "stub_wait", "stub_entered"))
+A, y, x = torch.eye(4).repeat(2, 1, 1), torch.ones(2, 4), torch.ones(3)
+calls = [lambda: h.potrf(A, True), lambda: h.potrf_backward(A, A, True), lambda: h.tri(True, A, A, True, False, False, 1.0),
+         lambda: h.tri_backward(True, A, A, A, True, False, False, 1.0), lambda: h.syrk(A, False, 1.0), lambda: h.syrk_backward(A, A, False, 1.0),
+         lambda: h.gemm2(A, A, False, False, 1.0), lambda: h.gemm2_backward(A, A, A, False, False, 1.0), lambda: h.potri(A, True),
+         lambda: h.potri_backward(A, A, A, True), lambda: h.sumlogdiag(A), lambda: h.gp_criterion(A, y)]
+every = lambda: [c() for c in calls]
+what = sys.argv[2]
+assert None not in every()
+if what == "memory":
+    small, (A, y), need.value = (A, y), (torch.eye(5).repeat(2, 1, 1), torch.ones(2, 5)), 1 << 60
+    assert [r is None for r in every()] == [q != 10 for q in range(12)]  # (sumlogdiag takes no workspace)
+    (A, y), need.value = small, 0  # (the answers for other sizes are remembered)
+elif what == "threads":  # a thread goes on while another is in the library
+    wait.value = 1
+    t = threading.Thread(target=calls[0])
+    t.start()
+    while not entered.value:
+        pass
+    wait.value = 0
+    t.join()
+else:
+    seen = []
+    def f(v):
+        seen.extend(every())
+        return v.sum()
+    F = torch.func
+    {"grad": lambda: F.grad(f)(x), "jvp": lambda: F.jvp(f, (x,), (x,)), "jacrev": lambda: F.jacrev(f)(x), "hessian": lambda: F.hessian(f)(x),
+     "vmap": lambda: F.vmap(f)(x[:, None]), "functionalize": lambda: F.functionalize(f)(x)}[what]()
+    assert seen and set(seen) == {None}
+assert None not in every()
+print("done")
+"""
+
+
+@pytest.fixture(scope="module")
+def cpu_host(tmp_path_factory):
+    if shutil.which("g++") is None or shutil.which("gcc") is None:
+        pytest.skip("no compiler")
+    tmp = str(tmp_path_factory.mktemp("host"))
+    with open(os.path.join(build.CSRC, "host_call.cpp")) as f:
+        src = f.read()
+    for a, b in CPU:
+        assert a in src
+        src = src.replace(a, b)
+    with open(os.path.join(tmp, "host.cpp"), "w") as f:
+        f.write(src)
+    stub = "typedef unsigned long size_t;\nvolatile size_t stub_need, stub_wait, stub_entered;\n"
+    for name in re.findall(r"LA_BIND\(\w+, (la_\w+)\)", src):
+        stub += f"size_t {name}() {{ return stub_need; }}\n" if name.endswith("bytes") else f"int {name}() {{ stub_entered = 1; while (stub_wait); return 0; }}\n"
+    with open(os.path.join(tmp, "stub.c"), "w") as f:
+        f.write(stub)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-w", "-o", tmp + "/stub.so", tmp + "/stub.c"], check=True)
+    subprocess.run([x if x != "-O2" else "-O0" for x in build.host_command(tmp + "/host.cpp", tmp + "/_cpu_host.so")], check=True)
+    return tmp
+
+
+@pytest.mark.parametrize("what", ["grad", "jvp", "jacrev", "hessian", "vmap", "functionalize", "memory", "threads"])
+def test_calls_that_are_not_plain_end_in_none(cpu_host, what):
+    r = subprocess.run([sys.executable, "-c", WORKER, cpu_host, what], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and "done" in r.stdout, (r.returncode, r.stderr[-2000:])
