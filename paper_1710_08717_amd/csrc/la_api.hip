@@ -359,13 +359,11 @@ static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, in
         return backward_sweep<T>(Lam, G, W, batch, n, n0 > 0 ? n0 : 256, aliased, st);
     ArenaFrame frame;
     // (with room for a third square: all three with rows of whole 16-byte chunks, so that two of the three products run on aligned operands)
-    View<T> sc[2], P = W;
+    View<T> sc[3];
     const int ld = padded<T>(n);
     const bool pad = ld != n && arena_room((size_t)3 * batch * n * ld * sizeof(T));
-    LA_TRY(scratch_views<T>(batch, n, 2, sc, pad ? ld : n));
-    if (pad)
-        LA_TRY(scratch_views<T>(batch, n, 1, &P, ld));
-    View<T> Li = sc[0], X = sc[1];
+    LA_TRY(scratch_views<T>(batch, n, pad ? 3 : 2, sc, pad ? ld : n));
+    View<T> Li = sc[0], X = sc[1], P = pad ? sc[2] : W;
     LA_TRY(inverse_build<T>(Lam, Li, X, batch, n, n, st, pad));
     View<const T> Gs = G;
     if (aliased) {  // Abar overwrites Lbar: keep a copy of its lower triangle
@@ -553,22 +551,22 @@ static la_status potrf_t(int lower, int64_t batch, int n, const void *A, void *L
     // (not needed where the whole matrix is factored panel by panel without merged inverses)
     const bool outer_panels = (batch == 1 && n >= 4096) || n >= 8192;
     const bool merges = outer_panels || !(n <= 2304 && (double)batch * n * n < 24e6);
-    View<T> sc[3], out = Lv;
+    View<T> sc[4], out = Lv;
     // Rows that are no whole number of 16-byte chunks: where the workspace has room for one more square, the factor is built in one with
     // padded rows as well, so that every product runs on aligned operands, and copied into place at the end.  One more pass over the matrix, which
     // the products of smaller ones do not make up for (step with one matrix, us: n = 3001, fp64 2270 -> 2190, n = 7423 12500 -> 11860, n = 986, fp32 440 -> 432;
     // 24 x 333^2, fp32 208 -> 214; several matrices, fp64 4 x 1001^2 608 -> 586, fp32 419 -> 424, 3 x 2049^2 1213 -> 1249).
     const int ld = padded<T>(n), squares = merges ? 3 : 2;
     const bool pad = ld != n && n >= 800 && (sizeof(T) == 8 || batch == 1) && arena_room((size_t)(squares + 1) * batch * n * ld * sizeof(T));
-    LA_TRY(scratch_views<T>(batch, n, squares, sc, pad ? ld : n));
-    if (!merges)
-        sc[2] = sc[1];  // never used
+    LA_TRY(scratch_views<T>(batch, n, pad ? squares + 1 : squares, sc, pad ? ld : n));  // (at once: what arena_room was asked for)
     if (pad) {
-        LA_TRY(scratch_views<T>(batch, n, 1, &Lv, ld));
+        Lv = sc[squares];
         LA_TRY(launch_copy<T>(Av, sc[1], batch, n, n, T(1), 2, st));
     } else {
         LA_TRY(launch_tril_split<T>(Av, sc[1], Lv, batch, n, st));  // zeros above the diagonal of L
     }
+    if (!merges)
+        sc[2] = sc[1];  // never used
     auto finish = [&]() { return pad ? launch_copy<T>(cv(Lv), out, batch, n, n, T(1), 1, st) : LA_OK; };
     // Large matrices: right-looking over panels of 2048 columns -- the panel's diagonal block by the
     // recursion below (which factors it 128 columns at a time and merges its inverse), one product

@@ -25,11 +25,16 @@ from ctypes import c_double as d, c_int as i, c_int64 as I, c_size_t as sz, c_vo
 shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 lib = ctypes.CDLL(sys.argv[2])
 launches = ctypes.c_long.in_dll(shim, "la_launches")
-lib.la_workspace_bytes.restype = sz
-p = [vp((q + 1) << 44) for q in range(5)]  # operands, far apart and never dereferenced
+for f in (lib.la_workspace_bytes, lib.la_gp_workspace_bytes, lib.la_sgp_workspace_bytes):
+    f.restype = sz
+p = [vp((q + 1) << 44) for q in range(10)]  # operands, far apart and never dereferenced
 
 def call(op, dt, batch, n, m, k, flags, w):
     if w is None:
+        if op == 20:
+            return lib.la_gp_workspace_bytes(i(dt), I(batch), i(n))
+        if op == 21:
+            return lib.la_sgp_workspace_bytes(i(dt), i(n), i(m))
         return lib.la_workspace_bytes(i(op), i(dt), I(batch), i(n), i(m), i(k))
     lower, trans, right = map(i, flags)
     b, n, m, k, dt = I(batch), i(n), i(m), i(k), i(dt)
@@ -43,11 +48,13 @@ def call(op, dt, batch, n, m, k, flags, w):
         3: lambda: lib.la_trmm_batched_ws(*tri, p[0], p[1], p[1], *ws),
         4: lambda: lib.la_syrk_batched_ws(dt, trans, d(1), b, n, k, p[0], p[1], *ws),
         5: lambda: lib.la_gemm2_batched_ws(dt, trans, right, d(1), b, m, n, k, p[0], p[1], p[2], *ws),
-        6: lambda: lib.la_trsm_backward_ws(*tri, *p, *ws),
-        7: lambda: lib.la_trmm_backward_ws(*tri, *p, *ws),
+        6: lambda: lib.la_trsm_backward_ws(*tri, *p[:5], *ws),
+        7: lambda: lib.la_trmm_backward_ws(*tri, *p[:5], *ws),
         8: lambda: lib.la_syrk_backward_ws(dt, trans, d(1), b, n, k, p[0], p[1], p[2], *ws),
         10: lambda: lib.la_potri_ws(dt, lower, b, n, p[0], p[1], *ws),
         11: lambda: lib.la_potri_backward_ws(dt, lower, b, n, p[0], p[1], p[2], p[3], *ws),
+        20: lambda: lib.la_gp_criterion(dt, b, n, p[0], p[1], p[2], p[3], vp(0), *ws),
+        21: lambda: lib.la_sgp_criterion(dt, n, m, *p[:4], d(1), *p[4:], *ws),
     }[op]()
     return [s, launches.value - before]
 
@@ -55,6 +62,7 @@ print(json.dumps([call(*q) for q in json.load(sys.stdin)]))
 """
 
 POTRF, BACKWARD, TRSM, TRMM, SYRK, GEMM2, TRSM_B, TRMM_B, SYRK_B, POTRI, POTRI_B = 0, 1, 2, 3, 4, 5, 6, 7, 8, 10, 11
+GP, SGP = 20, 21
 OPS = (POTRF, BACKWARD, TRSM, TRMM, SYRK, GEMM2, TRSM_B, TRMM_B, SYRK_B, POTRI, POTRI_B)
 OK, WORKSPACE = 0, 4
 
@@ -122,3 +130,26 @@ def test_matrices_of_33_to_64_rows_run_smaller_batches_on_a_larger_ones_workspac
         full = ask([[op, dt, b, n, m, 0, (1, 0, 0), None] for b in batches])
         queries = [[op, dt, b, n, m, 0, fl, w] for w, big in zip(full, batches) for b in batches if b <= big for fl in ((1, 0, 0), (0, 1, 1))]
         assert [q for q, (status, _) in zip(queries, ask(queries)) if status != OK] == []
+
+
+@pytest.mark.parametrize("dt", [0, 1])
+@pytest.mark.parametrize("op,batch,n", [(POTRF, 1, 801), (POTRF, 2, 961), (POTRF, 2, 1001), (POTRF, 1, 2001), (POTRF, 30, 901), (POTRF, 1, 6301),
+                                        (BACKWARD, 1, 131), (BACKWARD, 3, 333), (BACKWARD, 1, 507), (BACKWARD, 100, 201), (BACKWARD, 1, 2501),
+                                        (BACKWARD, 1, 6301), (POTRI, 1, 801), (GP, 1, 801), (GP, 2, 1001), (SGP, 1, 801), (SGP, 1, 1001)])
+def test_odd_sizes_take_padded_copies_only_where_all_of_them_fit(ask, op, batch, n, dt):
+    """a few steps of 256 bytes on both sides of every whole number of squares, rows padded or not, beside what the call has taken in any case"""
+    es = 8 if dt else 4
+    ld = (n * es + 15) // 16 * 16 // es
+    case = [op, dt, batch, n, 2 * n if op == SGP else 0, 0, (1, 0, 0)]
+    full, = ask([[*case, None]])
+    fixed = {GP: (2 * n * n + 2 * n) * batch * es, SGP: (4 * n * n + 2 * n * n + 3 * n + 16) * es + 8}.get(op, 0)
+    sizes = {full + 256 * q for q in range(-8, 2)}
+    for squares in range(9):
+        for row in (n, ld):
+            at = (fixed + squares * batch * n * row * es) // 256 * 256
+            sizes |= {at + 256 * q for q in range(-4, 60 if op == SGP else 12)}
+    sizes = sorted(w for w in sizes if 0 <= w <= full + 256)
+    got = ask([[*case, w] for w in sizes])
+    states = [s for s, _ in got]
+    assert set(states) <= {OK, WORKSPACE} and states == sorted(states, reverse=True) and states[sizes.index(full)] == OK
+    assert [w for w, (s, launches) in zip(sizes, got) if (s == OK) != (launches > 0)] == []
