@@ -43,10 +43,10 @@
  *    inner dimension whose sizes or addresses are off the 16-byte grid is split only where the
  *    workspace has room for it, and the backward rules of syrk and potri form Bbar + Bbar^T once
  *    where it has room for that beside what the product with it takes; potrf_backward with n >= 214 keeps
- *    fewer inverses, of smaller blocks; trsm, trmm, their backward rules and potri's do without scratch
- *    for 32 < n <= 64: la_workspace_bytes() counts that room, but the call also runs without it
- *    (as a rule slower).  For potrf_backward, and for trsm, trmm, their rules and potri's with 32 < n <= 64,
- *    a workspace that la_workspace_bytes() names for a batch thus serves every smaller batch.
+ *    fewer inverses, of smaller blocks; trsm and its backward rule do without scratch for 16 < n <= 64, trmm, its
+ *    rule and potri's for 32 < n <= 64: la_workspace_bytes() counts that room, but the call also runs without it
+ *    (as a rule slower).  For potrf_backward and those operators with those n, a workspace that la_workspace_bytes()
+ *    names for a batch thus serves every smaller batch.
  *    A workspace is device memory, 256-byte aligned, disjoint from every operand; its
  *    contents are undefined after the call; it may be reused by the next call on the
  *    same stream and must not be shared by calls that may run at the same time.

@@ -696,11 +696,12 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
             return s;
     }
 
-    // Many items of 32 < n <= 64 went to the kernels of one wavefront per item, which take no scratch.  Fewer go through the inverse or a
-    // panel, which do; those kernels take them, too, where the workspace has no room, so that one sized for many items serves a few (with
+    // Many items of 32 < n <= 64, solves of 16 < n <= 64, went to the kernels of one wavefront per item, which take no scratch.  Fewer go through the
+    // inverse or a panel, which do; those kernels take them, too, where the workspace has no room, so that one sized for many items serves a few (with
     // scratch -> without, us, fp64 / fp32: trmm, 500 of n = 64 with 300 vectors 50 -> 51 / 25 -> 40, 1000 of n = 48 with 100 31 -> 20 /
-    // 18 -> 18; trsm of the same 92 -> 55 / 54 -> 42 and 72 -> 22 / 46 -> 16).
-    if (Lam.nb2 == 1 && n > 32 && tri_wave_can<T>(batch, n, m, Xin, X) && !arena_room((size_t)batch * (solve ? nn : nm) * sizeof(T)))
+    // 18 -> 18; trsm of the same 92 -> 55 / 54 -> 42 and 72 -> 22 / 46 -> 16, 1000 of n = 24 with 200 68 -> 22 / 51 -> 18, 100 of n = 17 with 4096
+    // 82 -> 297 / 58 -> 219).
+    if (Lam.nb2 == 1 && (solve || n > 32) && tri_wave_can<T>(batch, n, m, Xin, X) && !arena_room((size_t)batch * (solve ? nn : nm) * sizeof(T)))
         return solve ? launch_trsm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st)
                      : launch_trmm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
 

@@ -165,6 +165,26 @@ def test_few_matrices_without_a_workspace(batch, n, m, lower, dtype):
     assert rel(got, oracle.potri_backward(F.astype(np.float64), B.astype(np.float64), Bbar.astype(np.float64), lower=lower)) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("lower", [True, False])
+@pytest.mark.parametrize("batch,n,m", [(1, 17, 129), (5, 24, 200), (6, 31, 700), (3, 32, 130)])
+def test_few_solves_of_17_to_32_rows_without_a_workspace(batch, n, m, lower, dtype):
+    rng = np.random.default_rng(7)
+    F = factor(n, lower, dtype)[:batch]
+    X, Xbar = (rng.standard_normal((batch, n, m)).astype(NP[dtype]) for _ in range(2))
+    M = (np.tril(F) if lower else np.triu(F)).astype(np.float64)
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    Fj, buf = torch.from_numpy(junk(F, lower)).cuda(), torch.from_numpy(X).cuda()
+    ref = np.linalg.solve(M, X.astype(np.float64))
+    assert rel(la.trsm(Fj, buf, lower=lower, workspace=none), ref) <= TOL[dtype]
+    assert rel(la.trsm(Fj, buf, lower=lower, out=buf, workspace=none), ref) <= TOL[dtype]
+    Y, Lbar = la.trsm_backward(Fj, torch.from_numpy(ref.astype(NP[dtype])).cuda(), torch.from_numpy(Xbar).cuda(), lower=lower, workspace=none)
+    Yref = np.linalg.solve(M.transpose(0, 2, 1), Xbar.astype(np.float64))
+    assert rel(Y, Yref) <= TOL[dtype]
+    G = -Yref @ ref.transpose(0, 2, 1)
+    assert rel(Lbar, np.tril(G) if lower else np.triu(G)) <= TOL[dtype]
+
+
 @pytest.mark.parametrize("batch,n,m", [(11700, 47, 8), (10700, 46, 45), (10700, 46, 40)])
 def test_sizes_from_memory(batch, n, m):
     """potri of nearly whole tiles and products with rows of an odd number of vectors, beyond 128 (192) MiB in fp64"""

@@ -133,6 +133,17 @@ def test_matrices_of_33_to_64_rows_run_smaller_batches_on_a_larger_ones_workspac
 
 
 @pytest.mark.parametrize("dt", [0, 1])
+@pytest.mark.parametrize("op", [TRSM, TRSM_B])
+def test_solves_of_17_to_32_rows_run_smaller_batches_on_a_larger_ones_workspace(ask, op, dt):
+    """across the 3072 matrices from which one wavefront each takes more than 128 vectors without scratch"""
+    batches = (1, 5, 1000, 3071, 3072, 3073, 5000)
+    for n, m in ((17, 130), (20, 129), (24, 200), (31, 128), (32, 700), (24, 4096)):
+        full = ask([[op, dt, b, n, m, 0, (1, 0, 0), None] for b in batches])
+        queries = [[op, dt, b, n, m, 0, fl, w] for w, big in zip(full, batches) for b in batches if b <= big for fl in ((1, 0, 0), (0, 1, 1))]
+        assert [q for q, (status, _) in zip(queries, ask(queries)) if status != OK] == []
+
+
+@pytest.mark.parametrize("dt", [0, 1])
 @pytest.mark.parametrize("op,batch,n", [(POTRF, 1, 801), (POTRF, 2, 961), (POTRF, 2, 1001), (POTRF, 1, 2001), (POTRF, 30, 901), (POTRF, 1, 6301),
                                         (BACKWARD, 1, 131), (BACKWARD, 3, 333), (BACKWARD, 1, 507), (BACKWARD, 100, 201), (BACKWARD, 1, 2501),
                                         (BACKWARD, 1, 6301), (POTRI, 1, 801), (GP, 1, 801), (GP, 2, 1001), (SGP, 1, 801), (SGP, 1, 1001)])
