@@ -25,11 +25,15 @@ namespace la {
 
 // One 16-byte chunk per lane from memory to LDS: lane l's goes to `lds` (uniform) + 16 l.  Written as assembly because the compiler waits for all
 // of these before it reads LDS, whichever part, and adds up the addresses in vector registers; wait_loads is where a reader waits.
+// (The warning is about any clobber of m0; without it the compiler takes m0 for unchanged.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_lds16(const char *base, uint32_t off, void *lds)
 {
     const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)lds;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 // until this wavefront's loads have landed
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

@@ -1,9 +1,10 @@
-"""Host-side check of a hardware rule the hand-written DPP multiply-adds rely on.
+"""Host-side check of hardware rules that inline assembly relies on.
 
 gfx9-family hardware needs two wait states between a VALU write of a VGPR and a DPP read
 of the same VGPR.  The compiler enforces that for its own instructions but cannot look
 inside inline asm, so this test compiles the small-matrix kernels to ISA text (no GPU
-needed) and checks the spacing for every DPP instruction in it.
+needed) and checks the spacing for every DPP instruction in it.  The products' loads from
+memory to LDS have rules of their own: for m0, and for the scalar registers of their base.
 """
 import os
 import re
@@ -22,7 +23,7 @@ def _functions(text):
         m = re.match(r"(_Z\w+):", f)
         if not m:
             continue
-        body = f.split("s_endpgm")[0]
+        body = f.split("\n.Lfunc_end")[0]  # (a kernel may have several s_endpgm)
         ins = []
         for l in body.split("\n")[1:]:
             l = l.split(";")[0].split("//")[0].strip()
@@ -77,7 +78,7 @@ def find_hazards(text):
                             seen.add((b, ws))
                             walk(b - 1, ws + 1, src, dpp, seen)
                     j -= 1
-                    if j >= 0 and not _is_label(ins[j]) and ins[j].split()[0] in ("s_branch", "s_setpc_b64"):
+                    if j >= 0 and not _is_label(ins[j]) and ins[j].split()[0] in ("s_branch", "s_setpc_b64", "s_endpgm"):
                         return  # no fall-through into the label
                     continue
                 op = p.split()[0]
@@ -141,12 +142,12 @@ def _compile_isa(name):
         return open(out).read(), ""
 
 
-_ISA_FILES = ["leaf.hip", "tiny.hip", "tiny_ops.hip", "kalman.hip", "trsm_stream.hip", "tiny_rows.hip", "small_wave.hip"]
+_ISA_FILES = ["leaf.hip", "tiny.hip", "tiny_ops.hip", "kalman.hip", "trsm_stream.hip", "tiny_rows.hip", "small_wave.hip", "gemm.hip"]
 _isa_cache = {}
 
 
 def _isa_text(name):
-    """ISA text of one source; all four files with hand-written DPP are compiled side by side on first use."""
+    """ISA text of one source; all files are compiled side by side on first use."""
     if not _isa_cache:
         from concurrent.futures import ThreadPoolExecutor
 
@@ -191,6 +192,7 @@ def test_small_matrix_operator_kernels_respect_dpp_spacing():
     # trsm / trmm, syrk and outer products, gemm2, syrk backward, potri in 4, 8 and 16 lanes per matrix
     assert text.count("v_fmac_f32_dpp") >= 2000
     assert text.count("v_fmac_f64_dpp") >= 1000
+    assert n_dpp == len(re.findall(r"_dpp\s", text))
     assert hazards == []
 
 
@@ -240,3 +242,81 @@ def test_wave_barriers_stand_between_fences():
                 if lines[i - 1] != fence % "RELEASE" or lines[i + 1] != fence % "ACQUIRE":
                     wrong.append(f"{name}:{i + 1}")
     assert seen > 0 and wrong == []
+
+
+def _sregs(tok):
+    m = re.match(r"s(\d+)$", tok.strip()) or re.match(r"s\[(\d+):(\d+)\]$", tok.strip())
+    return set(range(int(m.group(1)), int(m.group(m.lastindex)) + 1)) if m else set()
+
+
+def lds_load_faults(text):
+    """Loads from memory to LDS: m0 is set two instructions before each, by the same assembly (one wait state between), and no VALU instruction
+    writes a scalar register of the base within the five wait states before (followed backwards through the control flow, as above)."""
+    faults, count = [], 0
+    for name, ins in _functions(text).items():
+        targets = {}
+        for idx, l in enumerate(ins):
+            if not _is_label(l) and l.split()[0].startswith(("s_cbranch", "s_branch")):
+                targets.setdefault(l.split()[1] + ":", []).append(idx)
+
+        def walk(j, ws, base, load, seen):
+            while j >= 0 and ws < 5:
+                p = ins[j]
+                if _is_label(p):
+                    for b in targets.get(p, []):
+                        if (b, ws) not in seen:
+                            seen.add((b, ws))
+                            walk(b - 1, ws + 1, base, load, seen)
+                    j -= 1
+                    if j >= 0 and not _is_label(ins[j]) and ins[j].split()[0] in ("s_branch", "s_setpc_b64", "s_endpgm"):
+                        return
+                    continue
+                if p.startswith("v_") and _sregs(p.split(None, 1)[1].split(",")[0]) & base:
+                    faults.append((name, p, load))
+                ws += _wait_states(p)
+                j -= 1
+
+        for idx, l in enumerate(ins):
+            if not l.startswith("global_load_lds"):
+                continue
+            count += 1
+            if not (idx >= 2 and ins[idx - 1].startswith("s_nop") and ins[idx - 2].startswith("s_mov_b32 m0,")):
+                faults.append((name, "m0", l))
+            walk(idx - 1, 0, _sregs(l.split(",")[1].split()[0]), l, set())
+    return faults, count
+
+
+def test_lds_load_checker_sees_planted_faults():
+    load = " s_mov_b32 m0, s5\n s_nop 0\n global_load_lds_dwordx4 v1, s[2:3]\n s_endpgm\n"
+    assert lds_load_faults("_Zk:\n v_readfirstlane_b32 s9, v1\n" + load) == ([], 1)
+    assert len(lds_load_faults("_Zk:\n v_readfirstlane_b32 s3, v1\n s_nop 1\n" + load)[0]) == 1
+    assert lds_load_faults("_Zk:\n v_readfirstlane_b32 s3, v1\n s_nop 2\n" + load) == ([], 1)
+    assert len(lds_load_faults("_Zk:\n s_endpgm\n.LBB0_1:\n s_nop 4\n" + load.replace(" s_nop 0\n", ""))[0]) == 1
+
+
+def test_products_loads_to_lds_respect_the_rules_for_m0_and_their_base():
+    text = _isa_text("gemm.hip")
+    faults, count = lds_load_faults(text)
+    assert count >= 1000 and count == text.count("global_load_lds_dwordx4")
+    assert faults == []
+
+
+def test_the_compiler_knows_that_a_load_to_lds_sets_m0():
+    """between two loads of the compiler's own to one LDS address, which it otherwise sets m0 for once"""
+    from paper_1710_08717_amd import build
+
+    with open(os.path.join(build.CSRC, "gemm.hip")) as f:
+        asm = re.search(r"#pragma clang diagnostic push\n.*?#pragma clang diagnostic pop\n", f.read(), re.S).group(0)
+    own = ("__builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)%s, "
+           "(__attribute__((address_space(3))) void *)l, 4, 0, 0);\n")
+    src = ("#include <hip/hip_runtime.h>\n" + asm + "__global__ void k(const char *p, uint32_t off, int *out)\n{\n__shared__ __align__(16) char l[8192];\n"
+           + own % "p" + "load_lds16(p, off, l + 4096);\n" + own % "(p + 256)" + "__syncthreads();\nout[threadIdx.x] = l[threadIdx.x];\n}\n")
+    with tempfile.TemporaryDirectory() as d:
+        with open(os.path.join(d, "k.hip"), "w") as f:
+            f.write(src)
+        r = subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", "-o", os.path.join(d, "k.s"), os.path.join(d, "k.hip")],
+                           capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-2000:]
+        with open(os.path.join(d, "k.s")) as f:
+            seq = re.findall(r"s_mov_b32 m0|global_load_lds_dword\w*", f.read())
+    assert seq == ["s_mov_b32 m0", "global_load_lds_dword", "s_mov_b32 m0", "global_load_lds_dwordx4", "s_mov_b32 m0", "global_load_lds_dword"]
