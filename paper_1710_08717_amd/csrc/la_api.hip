@@ -99,6 +99,19 @@ static inline int padded(int n)
     return (n + VW - 1) / VW * VW;
 }
 
+// Is there room for `squares` working matrices per item with padded rows, and `more` bytes?  Not above 8 GiB a matrix (one of n = 32768 in fp64): the call
+// would run in less, and la_workspace_bytes counts what is taken here, which must not keep a problem off the card that fits on it otherwise (n = 80001:
+// operands and workspace of potrf 256 GB without the copies, 307 with them; of its gradient 154 and 257).  At the limit, n = 32001, the copies gain
+// what they do below: fp64 / fp32, ms, potrf 209 -> 187 / 107 -> 102, its gradient 398 -> 366 / 215 -> 189.
+constexpr size_t PADDED_MAX_BYTES = (size_t)8 << 30;
+template <typename T>
+static bool padded_room(int64_t batch, int n, int squares, size_t more = 0)
+{
+    const int ld = padded<T>(n);
+    const size_t square = (size_t)batch * n * ld * sizeof(T);
+    return ld != n && square <= PADDED_MAX_BYTES && arena_room(squares * square + more);
+}
+
 // Rough time, per unit of K, of the lower-triangle update C -= P P^T on n2 rows: the product
 // kernel runs two workgroups per compute unit (512 slots), with 128 x 128 tiles from 2048 rows on
 // and 64 x 64 tiles below, and a launch costs whole rounds of tiles: 528 tiles take twice as long
@@ -361,7 +374,7 @@ static la_status backward_impl(View<const T> Lam, View<const T> G, View<T> W, in
     // (with room for a third square: all three with rows of whole 16-byte chunks, so that two of the three products run on aligned operands)
     View<T> sc[3];
     const int ld = padded<T>(n);
-    const bool pad = ld != n && arena_room((size_t)3 * batch * n * ld * sizeof(T));
+    const bool pad = padded_room<T>(batch, n, 3);
     LA_TRY(scratch_views<T>(batch, n, pad ? 3 : 2, sc, pad ? ld : n));
     View<T> Li = sc[0], X = sc[1], P = pad ? sc[2] : W;
     LA_TRY(inverse_build<T>(Lam, Li, X, batch, n, n, st, pad));
@@ -470,7 +483,7 @@ static la_status backward_sweep(View<const T> Lam, View<const T> G, View<T> W, i
     // 473 / 284 -> 532 / 370, 4 x 2050^2 fp32 632 -> 684.
     View<T> out = W;
     const int ld = padded<T>(n);
-    const bool pad = ld != n && batch == 1 && n >= 2500 && arena_room((size_t)(2 * (int64_t)n * ld + sweep_scratch(n0, n)) * sizeof(T));
+    const bool pad = batch == 1 && n >= 2500 && padded_room<T>(1, n, 2, (size_t)sweep_scratch(n0, n) * sizeof(T));
     if (pad) {
         View<T> sc[2];
         LA_TRY(scratch_views<T>(batch, n, 2, sc, ld));
@@ -557,7 +570,7 @@ static la_status potrf_t(int lower, int64_t batch, int n, const void *A, void *L
     // the products of smaller ones do not make up for (step with one matrix, us: n = 3001, fp64 2270 -> 2190, n = 7423 12500 -> 11860, n = 986, fp32 440 -> 432;
     // 24 x 333^2, fp32 208 -> 214; several matrices, fp64 4 x 1001^2 608 -> 586, fp32 419 -> 424, 3 x 2049^2 1213 -> 1249).
     const int ld = padded<T>(n), squares = merges ? 3 : 2;
-    const bool pad = ld != n && n >= 800 && (sizeof(T) == 8 || batch == 1) && arena_room((size_t)(squares + 1) * batch * n * ld * sizeof(T));
+    const bool pad = n >= 800 && (sizeof(T) == 8 || batch == 1) && padded_room<T>(batch, n, squares + 1);
     LA_TRY(scratch_views<T>(batch, n, pad ? squares + 1 : squares, sc, pad ? ld : n));  // (at once: what arena_room was asked for)
     if (pad) {
         Lv = sc[squares];

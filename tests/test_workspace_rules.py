@@ -164,3 +164,18 @@ def test_odd_sizes_take_padded_copies_only_where_all_of_them_fit(ask, op, batch,
     states = [s for s, _ in got]
     assert set(states) <= {OK, WORKSPACE} and states == sorted(states, reverse=True) and states[sizes.index(full)] == OK
     assert [w for w, (s, launches) in zip(sizes, got) if (s == OK) != (launches > 0)] == []
+
+
+@pytest.mark.parametrize("dt,op,batch,n,squares", [(1, POTRF, 1, 80001, 3), (1, POTRF, 1, 32769, 3), (0, POTRF, 1, 46341, 3), (1, POTRF, 40, 9001, 3),
+                                                   (1, BACKWARD, 1, 80001, 0), (0, BACKWARD, 1, 46341, 0), (1, BACKWARD, 200000, 201, 2)])
+def test_padded_copies_of_very_large_problems_are_not_counted(ask, dt, op, batch, n, squares):
+    """what fits on the card without them still fits (288 GB; potrf of 80001 rows: operands 102, workspace 154)"""
+    es = 8 if dt else 4
+    full, = ask([[op, dt, batch, n, 0, 0, (1, 0, 0), None]])
+    assert full <= squares * batch * n * n * es + (0 if squares else 1300 * n * es) + (64 << 20)
+
+
+@pytest.mark.parametrize("dt,op,batch,n,squares", [(1, POTRF, 1, 32767, 4), (0, POTRF, 1, 46337, 4), (1, BACKWARD, 1, 32767, 2), (1, BACKWARD, 20000, 201, 3)])
+def test_padded_copies_of_large_problems_are_counted(ask, dt, op, batch, n, squares):
+    full, = ask([[op, dt, batch, n, 0, 0, (1, 0, 0), None]])
+    assert full >= squares * batch * n * n * (8 if dt else 4)
