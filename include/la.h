@@ -42,7 +42,9 @@
  *    LA_ERR_WORKSPACE (and launches nothing) when the call needs one.  A product over a long
  *    inner dimension whose sizes or addresses are off the 16-byte grid is split only where the
  *    workspace has room for it, and the backward rules of syrk and potri form Bbar + Bbar^T once
- *    where it has room for that beside what the product with it takes; potrf_backward with n >= 214 keeps
+ *    where it has room for that beside what the product with it takes; potrf and potrf_backward work on copies
+ *    whose rows are padded to whole 16-byte chunks only where it has room for all of them (sizes off that grid, up to
+ *    8 GiB a matrix); potrf_backward with n >= 214 keeps
  *    fewer inverses, of smaller blocks; trsm and its backward rule do without scratch for 16 < n <= 64, trmm, its
  *    rule and potri's for 32 < n <= 64: la_workspace_bytes() counts that room, but the call also runs without it
  *    (as a rule slower).  For potrf_backward and those operators with those n, a workspace that la_workspace_bytes()
@@ -112,11 +114,11 @@ la_status la_potrf_batched_ws(la_dtype dt, int lower, int64_t batch, int n, cons
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results
  * and errors as la_potrf_batched; the scratch of the blocked path (n > 128) is a static array of
  * LA_NOALLOC_SCRATCH_BYTES in device memory that every GPU the library is loaded on holds until the
- * process ends.  No hipMalloc / hipFree, no allocating library call.  A problem whose
- * la_workspace_bytes(LA_OP_POTRF, ...) exceeds that size is refused with LA_ERR_WORKSPACE (text in
- * la_last_error()) before anything is launched: in fp64 one matrix up to n = 1672, or any batch with
- * batch * n * n <= 2.79e6; twice that in fp32 (above 23e6 elements per batch or n >= 4096 the
- * limit is a third lower).  All calls on one GPU share that array: calls that may run at the same time on
+ * process ends.  No hipMalloc / hipFree, no allocating library call.  A problem that cannot do with that
+ * much (the room for padded copies, which la_workspace_bytes counts as well, is optional) is refused with
+ * LA_ERR_WORKSPACE (text in la_last_error()) before anything is launched: two squares of the matrices have to
+ * fit, three above n = 2304, so in fp64 any batch with batch * n * n <= 4194304 runs (one matrix up to n = 2048), in fp32
+ * twice that up to n = 2304 and one matrix up to n = 2364.  All calls on one GPU share that array: calls that may run at the same time on
  * one GPU (different streams or threads) race and must be serialised by the caller; successive
  * calls on one stream are fine, the array needs no clearing between them.  The first call on a
  * device looks up the array's address and should therefore be made outside graph capture. */

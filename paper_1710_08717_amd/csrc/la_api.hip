@@ -1250,7 +1250,7 @@ static la_status with_workspace(void *ws, size_t ws_bytes, F &&op)
     LA_TRY(sizing_pass(op, &need, true));
     if (need > 0) {
         if (!ws || need > ws_bytes) {
-            snprintf(g_err, sizeof(g_err), "this call needs a workspace of %zu bytes (la_workspace_bytes), %zu given", need,
+            snprintf(g_err, sizeof(g_err), "this call needs a workspace of at least %zu bytes, %zu given", need,
                      ws ? ws_bytes : (size_t)0);
             return LA_ERR_WORKSPACE;
         }
@@ -1693,7 +1693,8 @@ la_status la_potrf_batched_noalloc(la_dtype dt, int lower, int64_t batch, int n,
     }
     const la_status s = potrf_call(dt, lower, batch, n, A, L, info, ptr, (size_t)LA_NOALLOC_SCRATCH_BYTES, stream);
     if (s == LA_ERR_WORKSPACE) {
-        const size_t need = la_workspace_bytes(LA_OP_POTRF, dt, batch, n, 0, 0);
+        size_t need = 0;  // (la_workspace_bytes counts room that is optional, too)
+        LA_TRY(sizing_pass([&] { return potrf_body(dt, lower, batch, n, A, L, info, (hipStream_t)stream); }, &need, true));
         snprintf(g_err, sizeof(g_err),
                  "la_potrf_batched_noalloc: batch %lld of n = %d needs %zu bytes of scratch, the static buffer holds %zu",
                  (long long)batch, n, need, (size_t)LA_NOALLOC_SCRATCH_BYTES);

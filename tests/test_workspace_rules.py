@@ -14,11 +14,13 @@ int hipLaunchKernel(const void *f) { ++la_launches; return 0; }
 int hipGetLastError(void) { return 0; }
 int hipGetDevice(int *d) { *d = 0; return 0; }
 int hipFuncSetAttribute(const void *f, int a, int v) { return 0; }
+int hipGetSymbolAddress(void **p, const void *s) { *p = (void *)(1ul << 50); return 0; }
 int __hipPushCallConfiguration(void) { return 0; }
 int __hipPopCallConfiguration(void *a, void *b, void *c, void *d) { return 0; }
 """
 
-# [op, dt, batch, n, m, k, flags, bytes] -> [status, launches]; bytes null: -> what la_workspace_bytes answers
+# [op, dt, batch, n, m, k, flags, bytes] -> [status, launches]; bytes null: -> what la_workspace_bytes answers; op 30, potrf on the library's own
+# scratch array: the message as well
 WORKER = """
 import ctypes, json, sys
 from ctypes import c_double as d, c_int as i, c_int64 as I, c_size_t as sz, c_void_p as vp
@@ -27,6 +29,7 @@ lib = ctypes.CDLL(sys.argv[2])
 launches = ctypes.c_long.in_dll(shim, "la_launches")
 for f in (lib.la_workspace_bytes, lib.la_gp_workspace_bytes, lib.la_sgp_workspace_bytes):
     f.restype = sz
+lib.la_last_error.restype = ctypes.c_char_p
 p = [vp((q + 1) << 44) for q in range(10)]  # operands, far apart and never dereferenced
 
 def call(op, dt, batch, n, m, k, flags, w):
@@ -55,14 +58,15 @@ def call(op, dt, batch, n, m, k, flags, w):
         11: lambda: lib.la_potri_backward_ws(dt, lower, b, n, p[0], p[1], p[2], p[3], *ws),
         20: lambda: lib.la_gp_criterion(dt, b, n, p[0], p[1], p[2], p[3], vp(0), *ws),
         21: lambda: lib.la_sgp_criterion(dt, n, m, *p[:4], d(1), *p[4:], *ws),
+        30: lambda: lib.la_potrf_batched_noalloc(dt, lower, b, n, p[0], p[1], vp(0), vp(0)),
     }[op]()
-    return [s, launches.value - before]
+    return [s, launches.value - before] + ([lib.la_last_error().decode()] if op == 30 and s else [])
 
 print(json.dumps([call(*q) for q in json.load(sys.stdin)]))
 """
 
 POTRF, BACKWARD, TRSM, TRMM, SYRK, GEMM2, TRSM_B, TRMM_B, SYRK_B, POTRI, POTRI_B = 0, 1, 2, 3, 4, 5, 6, 7, 8, 10, 11
-GP, SGP = 20, 21
+GP, SGP, NOALLOC = 20, 21, 30
 OPS = (POTRF, BACKWARD, TRSM, TRMM, SYRK, GEMM2, TRSM_B, TRMM_B, SYRK_B, POTRI, POTRI_B)
 OK, WORKSPACE = 0, 4
 
@@ -179,3 +183,17 @@ def test_padded_copies_of_very_large_problems_are_not_counted(ask, dt, op, batch
 def test_padded_copies_of_large_problems_are_counted(ask, dt, op, batch, n, squares):
     full, = ask([[op, dt, batch, n, 0, 0, (1, 0, 0), None]])
     assert full >= squares * batch * n * n * (8 if dt else 4)
+
+
+@pytest.mark.parametrize("dt,batch,n,fits", [(1, 1, 2048, True), (1, 1, 2049, False), (1, 1, 1673, True), (1, 1, 1999, True), (1, 1, 2047, True),
+                                             (1, 4, 1023, True), (1, 16, 512, True), (1, 17, 512, False), (0, 1, 2304, True), (0, 1, 2364, True),
+                                             (0, 1, 2365, False), (0, 32, 512, True), (0, 33, 512, False), (1, 1000000, 64, True)])
+def test_potrf_on_the_librarys_own_array_takes_what_fits_without_optional_room(ask, dt, batch, n, fits):
+    """the limits that include/la.h states, and the size that a refusal names: with a workspace of that size the call runs, with less it does not"""
+    for flags in ((1, 0, 0), (0, 0, 0)):
+        (status, launches, *text), = ask([[NOALLOC, dt, batch, n, 0, 0, flags, 0]])
+        assert (status, launches > 0) == ((OK, True) if fits else (WORKSPACE, False))
+        if not fits:
+            need = int(text[0].split("needs ")[1].split()[0])
+            assert need > 64 << 20
+            assert [s for s, _ in ask([[POTRF, dt, batch, n, 0, 0, flags, w] for w in (need, need - 256)])] == [OK, WORKSPACE]
