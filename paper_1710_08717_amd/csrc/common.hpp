@@ -105,10 +105,9 @@ inline la_status launch_check(const char *where)
 }
 
 // ---------------------------------------------------------------------------------
-// Broadcast of one lane's value to the G lanes of its group (G = 4, 8, 16, 32 or 64).
+// Broadcast of one lane's value to the G lanes of its group (G = 4, 8 or 16).
 // G = 16: DPP row_newbcast, folded by the compiler into the consuming VALU op.  G = 8: two such
 // moves, one per half of the 16-lane row (bank mask).  G = 4: DPP quad_perm.
-// G = 32: ds_bpermute through the LDS crossbar.  G = 64: v_readlane into an SGPR.
 // ---------------------------------------------------------------------------------
 template <int K>
 __device__ __forceinline__ int dpp_row_bcast_i(int x)
@@ -174,18 +173,13 @@ __device__ __forceinline__ int quad_bcast_i(int x, int k)
 template <int G>
 __device__ __forceinline__ int group_bcast_i(int x, int k)
 {
-    if constexpr (G == 16) {
+    static_assert(G == 4 || G == 8 || G == 16, "lane groups of a 16-lane row");
+    if constexpr (G == 16)
         return row_bcast_i(x, k);
-    } else if constexpr (G == 8) {
+    else if constexpr (G == 8)
         return half_bcast_i(x, k);
-    } else if constexpr (G == 4) {
+    else
         return quad_bcast_i(x, k);
-    } else if constexpr (G == 32) {
-        int lane = __lane_id();
-        return __builtin_amdgcn_ds_bpermute(((lane & 32) | k) << 2, x);
-    } else {
-        return __builtin_amdgcn_readlane(x, k);
-    }
 }
 
 template <int G>

@@ -655,8 +655,10 @@ static la_status block_substitution(bool fwd, int64_t batch, int n, int m, int e
 
 // trsm / trmm (section 4.2).  vectors: columns of A/B (left) or rows (right); X(e, v) = element e
 // of vector v, so that every case is "apply Lam, Lam^T or one of their inverses to vectors".
-//   trmm: one GEMM with the triangular operand masked.
-//   trsm / trmm, n <= 64 and at most 16 vectors, many items: lane groups (two rows per lane for 16 < n <= 32).
+//   trsm, 16 < n <= 64, and trmm, 32 < n <= 64: one wavefront per item, where trsm_wave_takes and trmm_wave_takes say so.
+//   trsm / trmm, n <= 32 and at most 16 vectors: lane groups (two rows per lane above n = 16; a solve there only for many items).
+//   trmm, n <= 128 and at most 128 vectors, from 64 items on: one workgroup per item (trmm_leaf_takes).
+//   trmm, otherwise: one GEMM with the triangular operand masked.
 //   trsm, n <= 128 and at most 48 vectors: one block-substitution kernel.
 //   trsm, 128 < n <= 512: one launch per call, one workgroup per item and slab of 16 vectors, the
 //     factor streamed from memory (launch_trsm_stream), unless many vectors meet few items.
@@ -680,14 +682,14 @@ static la_status tri_apply_v(bool solve, bool fwd, T alpha, int64_t batch, int n
     if (solve && Lam.nb2 == 1 && trsm_wave_takes<T>(batch, n, m, Xin, X))  // one wavefront per item, no scratch
         return launch_trsm_wave<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
 
-    // n <= 32 with at most 16 vectors stored as whole items back to back: G lanes per matrix.  (A solve with 16 < n comes here only
-    // for many items of 24 rows: trsm_wave_takes.)
     // A multiply on many small items: one workgroup per item, Lam's lower tiles and the vectors in LDS, no scratch.
     // Up to n = 32 with at most 16 vectors the lane-group kernels below are faster; above that this one is.
     const bool leaf_mul = !solve && trmm_leaf_takes<T>(batch, n, m) && Lam.nb2 == 1 && Xin.nb2 == 1 && X.nb2 == 1;
     if (leaf_mul && (n > 32 || m > 16))
         return launch_trmm_leaf<T>(Lam, Xin, X, batch, n, m, alpha, fwd, st);
 
+    // n <= 32 with at most 16 vectors stored as whole items back to back: G lanes per matrix.  (A solve with 16 < n comes here only
+    // for many items of 24 rows: trsm_wave_takes.)
     if (n <= 32 && m <= 16 && (!solve || n <= 16 || batch > 1024) && X.bs == nm && Xin.bs == nm && Xin.rs == X.rs && Xin.cs == X.cs && X.nb2 == 1 &&
         Xin.nb2 == 1 && Lam.nb2 == 1) {
         const bool rowmajor = (X.rs == m && X.cs == 1), colmajor = (X.rs == 1 && X.cs == n);
