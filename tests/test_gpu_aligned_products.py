@@ -68,10 +68,14 @@ def test_syrk_symmetric(dt, b, n, k):
 
 
 @pytest.mark.parametrize("dt,b,n", [(torch.float64, 1, 801), (torch.float64, 2, 1001), (torch.float32, 1, 1026), (torch.float32, 1, 803),
-                                    (torch.float64, 3, 333), (torch.float32, 2, 131), (torch.float64, 1, 2501), (torch.float32, 1, 2502)])
+                                    (torch.float64, 3, 333), (torch.float32, 2, 131), (torch.float64, 1, 2501), (torch.float32, 1, 2502),
+                                    (torch.float64, 30, 901), (torch.float64, 1, 4099), (torch.float32, 1, 4097)])
 @pytest.mark.parametrize("lower", [True, False])
 def test_padded_working_copies(dt, b, n, lower):
-    """Odd rows: factor and gradient with the whole workspace (working copies with padded rows) and without room for those."""
+    """Odd rows: factor and gradient with the whole workspace (working copies with padded rows) and without room for those, on a workspace full of
+    NaN: neither a pad nor a triangle that nobody wrote may reach a sum.  Bound: a rounding error is 0.29 eps of its partial sum in the mean, the partial
+    sums of n products grow to the result, together 0.17 sqrt(n) eps as a random walk; the factorisation passes that on at most times the square root of
+    the matrix's condition number (5), the three sums of the gradient at most times that number: 0.38 and 1.5 of sqrt(n) eps, plus a third."""
     rng = np.random.default_rng(n)
     X = _rand(rng, dt, b, n, n).double()
     A64 = torch.matmul(X, X.mT.contiguous()) / n + torch.eye(n, device="cuda", dtype=torch.float64)
@@ -84,19 +88,20 @@ def test_padded_working_copies(dt, b, n, lower):
     Gl = (G if lower else G.mT).double().tril()
     P = torch.matmul(ref.mT.contiguous(), Gl).tril()
     P = P - 0.5 * torch.diag_embed(P.diagonal(dim1=1, dim2=2))
-    Z = torch.linalg.solve_triangular(ref.mT, P, upper=True)
-    W = torch.linalg.solve_triangular(ref, Z, upper=False, left=False)
-    Ab = 0.5 * (W + W.mT)
-    tol = 2e-4 if dt == torch.float32 else 1e-10
+    at = "cpu" if n > 4000 else "cuda"  # (torch's solve has no memory for these on the GPU)
+    Z = torch.linalg.solve_triangular(ref.mT.to(at), P.to(at), upper=True)
+    W = torch.linalg.solve_triangular(ref.to(at), Z, upper=False, left=False)
+    Ab = (0.5 * (W + W.mT)).cuda()
+    walk = n ** 0.5 * _eps(dt)
     for short in (0, 1):
         def ws(op):
             full = lib.la_workspace_bytes(op, code, b, n, 0, 0)
             less = short * b * n * pad * es if op == 1 or n >= 800 else 0  # (the factorisation of smaller ones has no such copy)
-            return torch.empty(full - less, dtype=torch.uint8, device="cuda") if full else None
+            return torch.full((max(full - less, full // 2),), 255, dtype=torch.uint8, device="cuda") if full else None
         L = la.potrf(A, lower=lower, workspace=ws(0))
         t = L if lower else L.mT
         assert float(t.triu(1).abs().max()) == 0.0
-        assert float(((t.double() - ref).flatten(1).norm(dim=1) / ref.flatten(1).norm(dim=1)).max()) <= tol
+        assert float(((t.double() - ref).flatten(1).norm(dim=1) / ref.flatten(1).norm(dim=1)).max()) <= 0.5 * walk
         B = la.potrf_backward(L, G, lower=lower, workspace=ws(1))
         assert torch.equal(B, B.mT)
-        assert float(((B.double() - Ab).flatten(1).norm(dim=1) / Ab.flatten(1).norm(dim=1)).max()) <= tol
+        assert float(((B.double() - Ab).flatten(1).norm(dim=1) / Ab.flatten(1).norm(dim=1)).max()) <= 2 * walk
