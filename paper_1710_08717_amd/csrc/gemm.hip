@@ -895,9 +895,11 @@ constexpr int GEMV_FEW = 16;
 // waits for memory twice per k (500 x 9568 times one vector, fp64, 27 -> 22 us; its transpose 59 -> 11).  A
 // column more than there are costs its loads (300 items 5 x 200 times 7 columns with A transposed, fp64, bound by the
 // loads of B: 31 us with eight), so every count has its own instance.
-template <typename T, int N, bool SPLIT>
-__global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<const T> B, View<T> C, View<const T> Cin, int64_t batch, int M, int K,
-                                              T alpha, T beta, int triA, int tiles)
+// ADD: beta multiplies `add` (one item, C's strides), else C itself.  (An instance of its own, because many items of a row or two are bound by each workgroup's
+// first instructions: potri's rule for 52367 matrices of n = 1, fp32, 145 us, 166 with a third operand like the other two, 155 with a pointer that may be null.)
+template <typename T, int N, bool SPLIT, bool ADD>
+__global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int K,
+                                              T alpha, T beta, int triA, int tiles, const T *add)
 {
     constexpr int NW = GEMV_THREADS / 64;  // wavefronts: rows per block (k contiguous) or slices of k
     constexpr int UN = N == 1 ? 8 : (N <= 4 ? 4 : 2);
@@ -907,7 +909,7 @@ __global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<con
     const T *Ap = A.item(b);
     const T *Bp = B.item(b);
     T *Cp = C.item(b);
-    const T *Ci = Cin.item(b);  // what beta multiplies: C itself, or a third operand of C's strides
+    const T *Ci = ADD ? add : Cp;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int64_t jo[N];
     T acc[N];
@@ -1001,8 +1003,8 @@ __global__ __launch_bounds__(GEMV_THREADS) void k_gemv(View<const T> A, View<con
 }
 
 template <typename T>
-static la_status launch_gemv(View<const T> A, View<const T> B, View<T> C, View<const T> Cin, int64_t batch, int M, int N, int K,
-                             T alpha, T beta, int triA, hipStream_t st)
+static la_status launch_gemv(View<const T> A, View<const T> B, View<T> C, int64_t batch, int M, int N, int K, T alpha, T beta, int triA,
+                             hipStream_t st, const T *add = nullptr)
 {
     const bool rows = A.cs == 1;
     const int per = rows ? GEMV_THREADS / 64 : 64, few = rows ? 1 : GEMV_FEW;
@@ -1016,15 +1018,23 @@ static la_status launch_gemv(View<const T> A, View<const T> B, View<T> C, View<c
     const int64_t blocks = (int64_t)tiles * batch;
     if (blocks > 0x7fffffffll)
         return LA_ERR_UNSUPPORTED;
-#define LA_GO(N_)                                                                                                      \
-    case N_:                                                                                                           \
-        if (split)                                                                                                     \
-            LA_LAUNCH((k_gemv<T, N_, true>), dim3((unsigned)blocks), dim3(GEMV_THREADS), 0, st, A, B, C, Cin, batch, M, K, \
-                      alpha, beta, triA, tiles);                                                                       \
-        else                                                                                                           \
-            LA_LAUNCH((k_gemv<T, N_, false>), dim3((unsigned)blocks), dim3(GEMV_THREADS), 0, st, A, B, C, Cin, batch, M, K, \
-                      alpha, beta, triA, tiles);                                                                       \
+#define LA_GEMV(N_, SPLIT_, ADD_)                                                                                        \
+    LA_LAUNCH((k_gemv<T, N_, SPLIT_, ADD_>), dim3((unsigned)blocks), dim3(GEMV_THREADS), 0, st, A, B, C, batch, M, K, alpha, beta, \
+              triA, tiles, add)
+#define LA_GO(N_)                   \
+    case N_:                        \
+        if (split)                  \
+            LA_GEMV(N_, true, false);  \
+        else                        \
+            LA_GEMV(N_, false, false); \
         break
+    if (add) {  // (launch_gemv_add: one column)
+        if (split)
+            LA_GEMV(1, true, true);
+        else
+            LA_GEMV(1, false, true);
+        return launch_check("gemv");
+    }
     switch (N) {
         LA_GO(1);
         LA_GO(2);
@@ -1038,6 +1048,7 @@ static la_status launch_gemv(View<const T> A, View<const T> B, View<T> C, View<c
         return LA_ERR_UNSUPPORTED;
     }
 #undef LA_GO
+#undef LA_GEMV
     return launch_check("gemv");
 }
 
@@ -1078,7 +1089,7 @@ la_status launch_gemv_add(View<const T> A, const T *x, const T *c, T *y, int M, 
         return LA_OK;
     if (dry_run())
         return LA_OK;
-    return launch_gemv<T>(A, View<const T>{x, K, 1, 1}, View<T>{y, M, 1, 1}, View<const T>{c, M, 1, 1}, 1, M, 1, K, alpha, beta, triA, st);
+    return launch_gemv<T>(A, View<const T>{x, K, 1, 1}, View<T>{y, M, 1, 1}, 1, M, 1, K, alpha, beta, triA, st, c);
 }
 template la_status launch_gemv_add<float>(View<const float>, const float *, const float *, float *, int, int, float, float, int, hipStream_t);
 template la_status launch_gemv_add<double>(View<const double>, const double *, const double *, double *, int, int, double, double, int, hipStream_t);
@@ -1258,9 +1269,9 @@ la_status launch_gemm(View<const T> A, View<const T> B, View<T> C, int64_t batch
     // a few vectors on either side: one pass over the big operand
     if (!o.maskC && !o.halfDiag && !o.min_tile64 && !o.symsum && K > 0) {
         if (N <= GEMV_N && o.triB == 0)
-            return launch_gemv<T>(A, B, C, View<const T>{C.p, C.bs, C.rs, C.cs, C.bs2, C.nb2}, batch, M, N, K, alpha, beta, o.triA, st);
+            return launch_gemv<T>(A, B, C, batch, M, N, K, alpha, beta, o.triA, st);
         if (M <= GEMV_N && o.triA == 0)  // C^T = B^T A^T
-            return launch_gemv<T>(B.t(), A.t(), C.t(), View<const T>{C.p, C.bs, C.cs, C.rs, C.bs2, C.nb2}, batch, N, M, K, alpha, beta, flip_tri(o.triB), st);
+            return launch_gemv<T>(B.t(), A.t(), C.t(), batch, N, M, K, alpha, beta, flip_tri(o.triB), st);
     }
     // Keep the stores of C along its contiguous direction: if C is stored with i contiguous,
     // compute C^T = B^T A^T instead (a pure re-labelling of the views).

@@ -84,14 +84,12 @@ def test_padded_working_copies(dt, b, n, lower):
     lib = la.load()
     code, es = (0, 4) if dt == torch.float32 else (1, 8)
     pad = (n + 16 // es - 1) // (16 // es) * (16 // es)
-    ref = torch.linalg.cholesky(A.double())
-    Gl = (G if lower else G.mT).double().tril()
-    P = torch.matmul(ref.mT.contiguous(), Gl).tril()
+    ref = torch.linalg.cholesky(A.double().cpu())  # (the reference on the CPU: torch's own solves on the GPU have no memory for the largest of these)
+    Gl = (G if lower else G.mT).double().tril().cpu()
+    P = torch.matmul(ref.mT, Gl).tril()
     P = P - 0.5 * torch.diag_embed(P.diagonal(dim1=1, dim2=2))
-    at = "cpu" if n > 4000 else "cuda"  # (torch's solve has no memory for these on the GPU)
-    Z = torch.linalg.solve_triangular(ref.mT.to(at), P.to(at), upper=True)
-    W = torch.linalg.solve_triangular(ref.to(at), Z, upper=False, left=False)
-    Ab = (0.5 * (W + W.mT)).cuda()
+    W = torch.linalg.solve_triangular(ref, torch.linalg.solve_triangular(ref.mT, P, upper=True), upper=False, left=False)
+    ref, Ab = ref.cuda(), (0.5 * (W + W.mT)).cuda()
     walk = n ** 0.5 * _eps(dt)
     for short in (0, 1):
         def ws(op):
