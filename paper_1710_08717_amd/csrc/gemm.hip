@@ -1011,9 +1011,13 @@ static la_status launch_gemv(View<const T> A, View<const T> B, View<T> C, int64_
     // Few blocks and long sums: the finer split.  With k contiguous from 12 elements of k a block of rows on (one vector, fp32 and fp64:
     // 500 x 9568 16 -> 6 and 22 -> 9 us, 8 x 30000 43 -> 8 and 54 -> 10; but 2000 x 2048, 250 blocks, 5.9 -> 8.0 and 7.0 -> 8.6), transposed from
     // half an element a block on (500 x 500 7.7 -> 3.9 and 9.3 -> 4.4, 9568 x 500 8.8 -> 7.8 and 11.2 -> 8.9, 4000 x 4000 57 -> 23 and 67 -> 24;
-    // but 16000 x 100, 250 blocks, 3.7 -> 5.0 and 4.0 -> 5.1).
+    // but 16000 x 100, 250 blocks, 3.7 -> 5.0 and 4.0 -> 5.1).  Whole blocks are not always full, and what is there to fill the chip are the rows: not above
+    // 10240 of them transposed (11 to 13 thousand rows, one to eight columns: 4 to 49 % slower in one case out of four), with k contiguous not above 1500
+    // in fp64, 1000 where several items read columns of their own (227 items of 7 x 3460 with eight 32 -> 63).  Of 22000 products with one to eight columns
+    // and 16 to 256 whole blocks 2.2 % were 7 % or more slower split without this line, 0.6 % with it.
     const int64_t whole = (int64_t)((M + per - 1) / per) * batch;
-    const bool split = whole < 256 && (rows ? K >= 2048 && K >= 12 * whole : K >= 64 && 2 * K >= whole);
+    const int64_t all = (int64_t)M * batch, most = !rows ? 10240 : (sizeof(T) == 4 ? 2048 : (batch == 1 || N == 1 ? 1500 : 1000));
+    const bool split = whole < 256 && all <= most && (rows ? K >= 2048 && K >= 12 * whole : K >= 64 && 2 * K >= whole);
     const int tiles = split ? (M + few - 1) / few : (M + per - 1) / per;
     const int64_t blocks = (int64_t)tiles * batch;
     if (blocks > 0x7fffffffll)

@@ -17,6 +17,8 @@ import paper_1710_08717_amd as la
 @pytest.mark.parametrize("ta", [False, True])
 @pytest.mark.parametrize("b,m,k", [
     (1, 9, 2047), (1, 9, 2048), (1, 17, 4097), (3, 40, 2500), (1, 1400, 2100), (1, 1361, 2112),  # k contiguous: from 2048 and 12 a block on
+    (1, 1500, 2300), (1, 1501, 2300), (125, 8, 2048), (143, 7, 2048),  # in fp64 up to 1500 rows, of several items 1000
+    (1, 10240, 96), (1, 10241, 96), (160, 64, 96),  # transposed up to 10240
     (1, 65, 63), (1, 65, 64), (1, 1000, 65), (5, 33, 127), (1, 8200, 64), (1, 8191, 66), (1, 130, 700),  # transposed: from 64 and half a block on
 ])
 def test_gemm2_thin(dt, n, ta, b, m, k):
